@@ -122,8 +122,9 @@ const char *hps_last_error(void);
 /*
  * Declare whether insert/update calls on OTHER streams may overlap queries (Sec. 4.2 allows
  * concurrent invocation of all APIs).  enabled = 1 (the default): queries validate each row
- * they return against the set's sequence word and re-read rows that a writer touched
- * meanwhile, so a reader sees the old or the new row and never a mixture.  enabled = 0: the
+ * they return (as a group while no writer is at work, else against the set's sequence word) and
+ * re-read rows that a writer touched meanwhile, so a reader sees the old or the new row and
+ * never a mixture.  enabled = 0: the
  * caller promises that no writer overlaps a query; queries then use plain cached loads.
  * Takes effect for calls enqueued afterwards.  Rows longer than 4 KiB (dim > 1024) cannot be
  * validated in one piece: such a cache is created with enabled = 0 and enabling returns

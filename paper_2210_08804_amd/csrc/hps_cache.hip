@@ -47,6 +47,12 @@ constexpr uint32_t kMaxRounds  = 1u << 16;
 // Longest row (in fp32) that a query may read while writers run: a row is read whole (8 wave loads
 // of 8 bytes per lane at this length) before it is validated and stored.
 constexpr uint32_t kMaxCheckedDim = 1024;
+// Writer epochs of a cache (see writer_enter): pairs of counters, one 256-byte line each.  Atomics
+// on one line execute one after the other, 11 ns each; 4,096 work-groups with two atomics each
+// cost a kernel of empty work-groups 94 us on one line, 7 us on 16 lines, 3 us on 64.  A reader
+// looks at all of them with one wave load, one lane per line.
+constexpr uint32_t kEpochs      = 16;
+constexpr uint32_t kEpochStride = 64;          // uint32 words between pairs
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));   // one 16-byte chunk of a row
 
@@ -76,6 +82,8 @@ __device__ __forceinline__ uint32_t set_of(int64_t key, uint32_t S, uint32_t sma
 __device__ __forceinline__ bool is_reserved(int64_t key) { return key < kEmpty + 2; }
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
+// The wave's number in its work-group, as the scalar that it is.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
 
 __device__ __forceinline__ int64_t shfl64(int64_t v, int src) {
     int lo = __shfl((int)(uint32_t)(uint64_t)v, src, kWave);
@@ -134,9 +142,67 @@ struct alignas(64) Table {     // one cache as the kernels see it (one 64-byte l
     uint32_t *T;               // [S][W] access stamps, LRU policy only (else nullptr)
     uint32_t *gdev;            // the cache's global iteration count g of Alg. 2 (LRU policy): one device word
     uint32_t *flags;           // one word of HPS_FLAG_* bits raised by kernels
+    uint32_t *epoch;           // kEpochs pairs {started, finished} of writer work-groups, kEpochStride words apart
 };
+static_assert(sizeof(Table) == 64, "one line of the kernel arguments per table");
 
 __device__ __forceinline__ uint32_t *seq_of(const Table &tb, uint32_t set) { return tb.sc + 2ull * set; }
+
+// Writer epochs.  Every work-group of an insert or update kernel that has keys to handle counts
+// itself in before it stores a key or a row and out after its last key and row have landed, on the pair
+// blockIdx mod kEpochs.  A reader that finds started == finished in every pair, reads keys and rows,
+// and then finds every pair unchanged knows that no writer was at work in between, so it need not
+// look at the sequence words of its sets: a writer's count is at the memory side before its first
+// store is issued (writer_entered) and its stores are there before it counts itself
+// out, so a reader that saw any of those stores sees the pair changed or not yet even.
+__device__ __forceinline__ uint32_t *epoch_of(const Table &tb, uint32_t i) { return tb.epoch + (i % kEpochs) * kEpochStride; }
+
+// A wave's view of the pairs: lanes 0 .. kEpochs-1 hold {finished, started} of one pair each.
+__device__ __forceinline__ uint64_t read_epochs(const uint32_t *epoch) {
+    const uint32_t lane = (uint32_t)lane_id();
+    return lane < kEpochs ? ld_agent(reinterpret_cast<const uint64_t *>(epoch + lane * kEpochStride)) : 0ull;
+}
+
+// A writer's work-group in LDS: waves still at work, and whether the work-group's count has arrived.  Together
+// the two counts cost a call of a few keys 0.5 us and larger ones nothing (2^18 rows: 206.8 us with them,
+// 206.4 without).
+struct WriterGroup { uint32_t left, entered; };
+// Called by all threads of the work-group at the start.  Wave 0's count is on its way when it returns.
+__device__ __forceinline__ void writer_enter(const Table &tb, WriterGroup *w) {
+    if (threadIdx.x == 0) {
+        w->left = (uint32_t)kWavesPerWg;
+        w->entered = 0u;
+        __hip_atomic_fetch_add(epoch_of(tb, blockIdx.x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+}
+// Wave 0, right after a wait for its outstanding memory operations, which covers the count: tells the
+// others.  Nothing that wave 0 does before depends on another wave.
+__device__ __forceinline__ void writer_tell(WriterGroup *w, bool &told) {
+    if (!told) __hip_atomic_store(&w->entered, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    told = true;
+}
+// Every wave, before it stores a key or a row.  The count's round trip runs beside the one in which
+// the waves take their first sets (a wait for it at the start cost 0.8 us per call).
+__device__ __forceinline__ void writer_entered(WriterGroup *w) {
+    while (__hip_atomic_load(&w->entered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
+        __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");                          // no store of the wave moves up
+}
+// Called by each wave of the work-group when its own keys and rows have landed.
+__device__ __forceinline__ void writer_leave(const Table &tb, WriterGroup *w, bool told) {
+    if (!told) wait_vm0();                                  // (wave 0 had no key to look at)
+    writer_tell(w, told);
+    if (lane_id() == 0 && __hip_atomic_fetch_sub(&w->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 1u)
+        __hip_atomic_fetch_add(epoch_of(tb, blockIdx.x) + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Division of a list of rows of C chunks into wave loads of 64 chunks.
+struct ChunkStep {
+    uint32_t C;                // chunks per row
+    uint32_t inv;              // (lane * inv) >> 16 == lane / C for lane < 64
+    uint32_t rows, rest;       // 64 / C, 64 mod C
+};
 
 // Row geometry shared by all copy loops: a row is C = d/4 chunks of 16 bytes; LPR lanes
 // cooperate on one row (16 B per lane, contiguous, so a wave load covers 64/LPR whole rows).
@@ -146,8 +212,31 @@ struct RowGeom {
     uint32_t LPR;              // lanes per row: min(64, next power of two >= C)
     uint32_t lprShift;         // log2(LPR)
     uint32_t passes;           // ceil(C / LPR): > 1 only for rows longer than 1 KiB
-    // the same for 8-byte chunks (paths that move rows with 8-byte scoped accesses)
-    uint32_t C8, LPR8, lpr8Shift, passes8;
+    uint32_t LPR8, lpr8Shift;  // lanes per row of 8-byte chunks: min(64, next power of two >= d/2)
+    ChunkStep c16, c8;         // walks over the 16-byte and the 8-byte chunks (scoped accesses) of a list of rows
+};
+
+// Lane's place (row r of the list, chunk c of that row) in wave load after wave load of a list of
+// rows whose chunks are numbered through, 64 of them to a wave load: every lane has a chunk to move
+// whatever the row's length.
+struct ChunkWalk {
+    uint32_t r, c;
+    __device__ __forceinline__ ChunkWalk(const ChunkStep &s, uint32_t lane) {
+        r = (lane * s.inv) >> 16;
+        c = lane - r * s.C;
+    }
+    __device__ __forceinline__ void next(const ChunkStep &s) {
+        r += s.rows;
+        c += s.rest;
+        if (c >= s.C) {
+            c -= s.C;
+            ++r;
+        }
+    }
+    // Makes the walk opaque to the compiler, which would otherwise keep the places of a whole group of
+    // wave loads in registers from the loads to the stores, or across groups, instead of three
+    // additions each (64 registers for 16 wave loads).
+    __device__ __forceinline__ void forget() { asm volatile("" : "+v"(r), "+v"(c)); }
 };
 
 // Copy `cnt` (> 0) rows listed in LDS: row srcRow[e] of `src` to row dstRow[e] of `dst`, for
@@ -162,97 +251,172 @@ struct RowGeom {
 // here).  Lanes beyond the list load entry 0 and store nothing; lanes beyond the row (d/4 not a
 // power of two) repeat chunk 0.
 // kD = 128 fixes the row geometry at compile time (32 lanes per row, one pass, shifts instead
-// of multiplications); kD = 0 takes it from g.
+// of multiplications); kD = 0 takes it from g and walks over the chunks of the listed rows (ChunkWalk),
+// four wave loads at a time as far as there are any.
 template <int U, int kD = 0, typename SrcIdx, typename DstIdx>
 __device__ __forceinline__ void copy_rows(const RowGeom g, const float *__restrict__ src,
                                           float *__restrict__ dst, const SrcIdx *srcRow,
                                           const DstIdx *dstRow, uint32_t cnt) {
     static_assert(kD == 0 || kD == 128, "only the 128-word row is specialised");
     const uint32_t lane = (uint32_t)lane_id();
-    const uint32_t lprShift = kD ? 5u : g.lprShift;
-    const uint32_t LPR = kD ? 32u : g.LPR;
-    const uint32_t C = kD ? 32u : g.C;
-    const uint64_t d = kD ? (uint64_t)kD : (uint64_t)g.d;
-    const uint32_t passes = kD ? 1u : g.passes;
-    const uint32_t rpi = (uint32_t)kWave >> lprShift;        // rows per wave load
-    const uint32_t sub = lane >> lprShift;                   // which of those rows this lane serves
-    const uint32_t cl  = lane & (LPR - 1);                   // chunk of the row this lane moves
-    for (uint32_t pass = 0; pass < passes; ++pass) {
-        uint32_t chunk = cl + pass * LPR;
-        chunk = chunk < C ? chunk : 0u;
-        const uint32_t off = chunk * 4;
-        for (uint32_t e0 = 0; e0 < cnt; e0 += rpi * U) {
+    if constexpr (kD == 128) {
+        const uint32_t sub = lane >> 5;                          // two rows per wave load
+        const uint32_t off = (lane & 31u) * 4;
+        for (uint32_t e0 = 0; e0 < cnt; e0 += 2 * U) {
             f32x4 buf[U];
             uint32_t ent[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t e = e0 + u * rpi + sub;
+                const uint32_t e = e0 + u * 2 + sub;
                 ent[u] = e < cnt ? e : 0xFFFFFFFFu;
-                buf[u] = *reinterpret_cast<const f32x4 *>(src + (uint64_t)srcRow[e < cnt ? e : 0u] * d + off);
+                buf[u] = *reinterpret_cast<const f32x4 *>(src + (uint64_t)srcRow[e < cnt ? e : 0u] * 128 + off);
             }
             // One wait for the whole group, stated where the compiler can see it.  The stores are
             // predicated, so the compiler cannot count them among the outstanding operations and
             // would make store k wait until at most U-1-k operations are in flight: the later
             // stores of a group would wait for the earlier ones to be acknowledged.
-            __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), other counters untouched
+            __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0), other counters untouched
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (ent[u] != 0xFFFFFFFFu)
-                    __builtin_nontemporal_store(buf[u], reinterpret_cast<f32x4 *>(dst + (uint64_t)dstRow[ent[u]] * d + off));
+                    __builtin_nontemporal_store(buf[u], reinterpret_cast<f32x4 *>(dst + (uint64_t)dstRow[ent[u]] * 128 + off));
+        }
+    } else {
+        constexpr int Q = 4;                                     // wave loads per test for the end of the list
+        static_assert(U % Q == 0, "whole blocks of wave loads");
+        const uint32_t total = cnt * g.C;
+        ChunkWalk in(g.c16, lane), out = in;
+        out.forget();
+        for (uint32_t q0 = 0; q0 < total; q0 += kWave * U) {
+            f32x4 buf[U];
+#pragma unroll
+            for (int b = 0; b < U; b += Q) {
+                if (q0 + b * kWave < total) {                    // uniform
+#pragma unroll
+                    for (int u = b; u < b + Q; ++u) {
+                        const bool live = q0 + u * kWave + lane < total;
+                        buf[u] = *reinterpret_cast<const f32x4 *>(src + (uint64_t)srcRow[live ? in.r : 0u] * g.d + (live ? in.c : 0u) * 4);
+                        in.next(g.c16);
+                    }
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);                  // as above
+#pragma unroll
+            for (int b = 0; b < U; b += Q) {
+                if (q0 + b * kWave < total) {
+#pragma unroll
+                    for (int u = b; u < b + Q; ++u) {
+                        if (q0 + u * kWave + lane < total)
+                            __builtin_nontemporal_store(buf[u], reinterpret_cast<f32x4 *>(dst + (uint64_t)dstRow[out.r] * g.d + out.c * 4));
+                        out.next(g.c16);
+                    }
+                }
+            }
         }
     }
 }
 
-// copy_rows for a reader that may overlap writers (seqlock read side).  Entry e also carries
+// copy_rows for a reader that found no writer at work when it read the epochs e1 (read_epochs).
+// Rows are loaded 8 bytes per lane with shared_ld64, in groups of U wave loads, all of a group's
+// loads in flight together; once they have completed the epochs are read again, and only if no
+// writer has started meanwhile are the group's rows stored.  A row is always read whole inside one
+// group (the longest, 4 KiB, takes 8 wave loads, which is why U >= 8 and why kMaxCheckedDim is
+// 1024): a position whose key turns out to be gone when the rest is looked up again has had nothing
+// written to its `out` row.  Returns how many rows of the list are done; the caller goes through
+// the others again with copy_rows_checked.
+template <int U, int kD = 0>
+__device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float *__restrict__ src,
+                                                    float *__restrict__ dst, const uint64_t *srcRow,
+                                                    const uint32_t *dstRow, uint32_t cnt,
+                                                    uint64_t e1, const uint32_t *epoch) {
+    static_assert((kD == 0 || kD == 128) && U >= 8 && (kD || U % 4 == 0), "a 512-byte row is one wave load of 8 bytes per lane");
+    constexpr int Q = kD ? 1 : 4;                                    // wave loads per test for the end of the list
+    const uint32_t lane = (uint32_t)lane_id();
+    const uint64_t d = kD ? (uint64_t)kD : (uint64_t)g.d;
+    const uint32_t C = kD ? 64u : g.c8.C;
+    const uint32_t span = kD ? (uint32_t)U : (uint32_t)(U * kWave) / C;   // rows per group
+    const ChunkWalk start(g.c8, lane);
+    for (uint32_t e0 = 0; e0 < cnt; e0 += span) {
+        const uint32_t total = (cnt - e0 < span ? cnt - e0 : span) * C;   // chunks of the group
+        uint64_t buf[U];
+        ChunkWalk in = start, out = start;
+        if (!kD) {
+            in.forget();
+            out.forget();
+        }
+#pragma unroll
+        for (int b = 0; b < U; b += Q) {
+            if ((uint32_t)b * kWave < total) {                       // uniform: there are chunks left
+#pragma unroll
+                for (int u = b; u < b + Q; ++u) {
+                    const bool live = kD || u * kWave + lane < total;
+                    const uint32_t r = kD ? (uint32_t)u : live ? in.r : 0u;
+                    const uint32_t c = kD ? lane : live ? in.c : 0u;
+                    buf[u] = shared_ld64(reinterpret_cast<const uint64_t *>(src + srcRow[e0 + r] * d) + c);
+                    if (!kD) in.next(g.c8);
+                }
+            }
+        }
+        shared_acquire();                                            // row loads complete before the epochs are read again
+        if (__ballot(read_epochs(epoch) != e1)) return e0;
+#pragma unroll
+        for (int b = 0; b < U; b += Q) {
+            if ((uint32_t)b * kWave < total) {
+#pragma unroll
+                for (int u = b; u < b + Q; ++u) {
+                    if (kD || u * kWave + lane < total)
+                        __builtin_nontemporal_store(
+                            buf[u], reinterpret_cast<uint64_t *>(dst + (uint64_t)dstRow[e0 + (kD ? (uint32_t)u : out.r)] * d) + (kD ? lane : out.c));
+                    if (!kD) out.next(g.c8);
+                }
+            }
+        }
+    }
+    return cnt;
+}
+
+// copy_rows for a reader that overlaps writers (seqlock read side).  Entry e also carries
 // the set it came from and the value v1 of that set's sequence word read before the probe.
 // Rows are loaded into registers (8 bytes per lane, shared_ld64), then the sequence words are
 // read again once those loads have completed; a row is stored only if its word is unchanged,
 // i.e. no writer touched the set while the row was being read.  Entries to redo are flagged in
 // the LDS word pair `retry`.
-// The wave's rows go in groups of U wave loads, all of a group's loads in flight together; then
-// ONE more wave load reads the sequence words again, lane l that of the group's row l, and a
-// ballot of "changed" gives the rows to redo.  That is two dependent round trips per group, so
-// the fewer groups the better (27.5 us per 106,496-key batch with groups of 16 rows, 21.6 us with
-// one group per wave in the stand-alone test bed).  A row is always read whole inside one group
-// (rows longer than 512 bytes take several of the group's wave loads; the longest row, 4 KiB, takes
-// 8, which is why U >= 8 and why kMaxCheckedDim is 1024) and stored only after its validation:
-// a position whose key turns out to be gone on the retry (evicted by an overlapping insert) has
-// had nothing written to its `out` row.
-template <int U, int kD = 0, bool kLong = false>
+// The wave's rows go in groups of U wave loads as in copy_rows_quiet; then ONE more wave load reads
+// the sequence words again, lane l that of the group's row l, and a ballot of "changed" gives the
+// rows to redo.  That is two dependent round trips per group, so the fewer groups the better (27.5 us
+// per 106,496-key batch with groups of 16 rows, 21.6 us with one group per wave in the stand-alone
+// test bed).
+template <int U, int kD = 0>
 __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *__restrict__ src,
                                                   float *__restrict__ dst, const uint64_t *srcRow,
                                                   const uint32_t *dstRow, const uint32_t *setOf,
                                                   const uint32_t *v1Of, const uint32_t *sc,
                                                   uint32_t cnt, uint32_t *retry) {
-    static_assert(!(kD && kLong), "the compile-time geometry is a short row");
+    static_assert((kD == 0 || kD == 128) && U >= 8, "a 512-byte row is one wave load of 8 bytes per lane");
     const uint32_t lane = (uint32_t)lane_id();
-    // Geometry of one wave load of 8 bytes per lane.  Short rows (kLong false, up to 512 bytes):
-    // LPR8 lanes per row, rpi rows per wave load.  Long rows (kLong, up to kMaxCheckedDim fp32):
-    // passes8 wave loads per row.  kD = 128: a 512-byte row is exactly one wave load.
-    // A long row takes 2^pShift >= passes8 of a group's wave loads (those past the row's end are idle).
-    const uint32_t pShift = kLong ? 32u - (uint32_t)__builtin_clz(g.passes8 - 1u) : 0u;
-    const uint32_t rpiShift = (kD || kLong) ? 0u : 6u - g.lpr8Shift;
-    const uint32_t sub = (kD || kLong) ? 0u : lane >> g.lpr8Shift;
-    const uint32_t cl  = (kD || kLong) ? lane : lane & (g.LPR8 - 1);
     const uint64_t d = kD ? (uint64_t)kD : (uint64_t)g.d;
-    // rows per group: every row of a group is read whole (all its wave loads are among the group's
-    // U), and one lane per row re-reads its sequence word, so a group has at most 64 rows
-    uint32_t span = kLong ? (uint32_t)U >> pShift : (uint32_t)U << rpiShift;
+    const uint32_t C = kD ? 64u : g.c8.C;
+    // rows per group: one lane per row re-reads its sequence word, so a group has at most 64 rows
+    uint32_t span = kD ? (uint32_t)U : (uint32_t)(U * kWave) / C;
     span = span < (uint32_t)kWave ? span : (uint32_t)kWave;
+    const ChunkWalk start(g.c8, lane);
     for (uint32_t e0 = 0; e0 < cnt; e0 += span) {
         const uint32_t rows = cnt - e0 < span ? cnt - e0 : span;
+        const uint32_t total = rows * C;                             // chunks of the group
         uint64_t buf[U];
-        // wave load u of the group: rows u*rpi .. (short rows), or part u mod 2^pShift of row
-        // u >> pShift (long rows)
+        ChunkWalk in = start, out = start;
+        if (!kD) {
+            in.forget();
+            out.forget();
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t r0 = kLong ? (uint32_t)u >> pShift : (uint32_t)u << rpiShift;
-            if (r0 < rows) {                                         // uniform: this wave load has rows to fetch
-                uint32_t r = r0 + sub;
-                r = r < rows ? r : 0u;
-                uint32_t chunk = kLong ? (((uint32_t)u & ((1u << pShift) - 1u)) << 6) + lane : cl;
-                chunk = chunk < g.C8 || kD ? chunk : 0u;
-                buf[u] = shared_ld64(reinterpret_cast<const uint64_t *>(src + srcRow[e0 + r] * d) + chunk);
+            if ((uint32_t)u * kWave < total) {                       // uniform: there are chunks left
+                const bool live = kD || u * kWave + lane < total;
+                const uint32_t r = kD ? (uint32_t)u : live ? in.r : 0u;
+                const uint32_t c = kD ? lane : live ? in.c : 0u;
+                buf[u] = shared_ld64(reinterpret_cast<const uint64_t *>(src + srcRow[e0 + r] * d) + c);
+                if (!kD) in.next(g.c8);
             }
         }
         shared_acquire();                                            // row loads complete before the re-read
@@ -261,13 +425,12 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
         const uint64_t bad = __ballot(mine && v2 != v1Of[e0 + lane]);   // bit r: row e0 + r was touched by a writer
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t r0 = kLong ? (uint32_t)u >> pShift : (uint32_t)u << rpiShift;
-            if (r0 < rows) {
-                const uint32_t r = r0 + sub;
-                const uint32_t chunk = kLong ? (((uint32_t)u & ((1u << pShift) - 1u)) << 6) + lane : cl;
-                if (r < rows && (chunk < g.C8 || kD) && !((bad >> r) & 1ull))
-                    __builtin_nontemporal_store(
-                        buf[u], reinterpret_cast<uint64_t *>(dst + (uint64_t)dstRow[e0 + r] * d) + chunk);
+            if ((uint32_t)u * kWave < total) {
+                const uint32_t r = kD ? (uint32_t)u : out.r;
+                const uint32_t c = kD ? lane : out.c;
+                if ((kD || u * kWave + lane < total) && !((bad >> r) & 1ull))
+                    __builtin_nontemporal_store(buf[u], reinterpret_cast<uint64_t *>(dst + (uint64_t)dstRow[e0 + r] * d) + c);
+                if (!kD) out.next(g.c8);
             }
         }
         if (bad && lane == 0) {                                      // e0 + rows <= cnt <= 64
@@ -278,59 +441,161 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
     }
 }
 
-// Writer side: copy `cnt` (> 0) rows listed in LDS from the caller's batch into the cache with
-// shared_st64 (8 bytes per lane), so that overlapping readers observe them without cache flushes.
-// Two register buffers alternate: the loads of the next U wave loads are issued before the
-// stores of the current ones, so a write-through store's long acknowledgement never sits between
-// a wave and its next loads.  Lanes past the list repeat entry 0 (same bytes to the same place),
-// and the loads issued past the last group re-read entry 0 and are dropped.  (Groups of 16 or 32
-// wave loads all in flight before the first store, which is what the query's copy does, cost the
-// writers occupancy and time: insert 102 us against 83 us per 2^18 rows, update 118 against 81 us.)
-template <int U>
-__device__ __forceinline__ void copy_rows_shared(const RowGeom g, const float *__restrict__ src,
+// Writer side: the rows listed in LDS go from the caller's batch into the cache with shared_st64 (8 bytes
+// per lane), so that overlapping readers observe them without cache flushes.  start() requests the
+// first two groups of U wave loads; finish() stores them and moves what is left, each group's loads
+// issued before the stores of the group ahead of it, so that a write-through store's long
+// acknowledgement never sits between a wave and its next loads.  The two halves are apart because
+// which rows are read may be known long before it is known which of them are to be stored.
+// Rows of up to 512 bytes (kLong false) take LPR8 lanes each, a whole number of them per wave load; longer
+// ones go through the walk over the chunks of the list, so that no wave load is partly idle and
+// the parts of a row are in flight together (30,000 rows of 1,280 bytes inserted, updated and queried:
+// 93.6 us when each 512-byte part of the rows was a pass of its own, 71 us with the walk).  For short
+// rows the walk's arithmetic costs more than it saves (400-byte rows 41.7 against 38.7 us).
+// (Groups of 16 or 32 wave loads all in flight before the first store, which is what the query's copy
+// does, cost the writers occupancy and time: insert 102 us against 83 us per 2^18 rows, update 118
+// against 81 us.)
+constexpr uint64_t kSkipRow = ~0ull;             // dstRow of an entry that finish() is not to store
+
+template <int U, bool kLong>
+struct RowMover {
+    const RowGeom &g;
+    const float *const src;
+    float *const dst;
+    const uint32_t *const srcRow;
+    const uint64_t *const dstRow;
+    uint32_t cnt;
+    ChunkWalk in, out;
+    uint64_t bufA[U], bufB[U];
+
+    __device__ __forceinline__ RowMover(const RowGeom &g_, const float *src_, float *dst_, const uint32_t *srcRow_, const uint64_t *dstRow_)
+        : g(g_), src(src_), dst(dst_), srcRow(srcRow_), dstRow(dstRow_), cnt(0), in(g_.c8, (uint32_t)lane_id()), out(in) {}
+
+    // Wave load k of the list: does it hold rows at all (uniform), does this lane have one, which row, which chunk of it.
+    __device__ __forceinline__ bool any(uint32_t k) const {
+        return kLong ? k * kWave < cnt * g.c8.C : (k << (6u - g.lpr8Shift)) < cnt;
+    }
+    __device__ __forceinline__ bool place(uint32_t k, ChunkWalk &w, uint32_t &r, uint32_t &c) const {
+        const uint32_t lane = (uint32_t)lane_id();
+        bool live;
+        if (kLong) {
+            live = k * kWave + lane < cnt * g.c8.C;
+            r = live ? w.r : 0u;
+            c = live ? w.c : 0u;
+            w.next(g.c8);
+        } else {
+            const uint32_t e = (k << (6u - g.lpr8Shift)) + (lane >> g.lpr8Shift);
+            live = e < cnt;
+            r = live ? e : 0u;
+            c = lane & (g.LPR8 - 1u);
+            c = c < g.c8.C ? c : 0u;
+        }
+        return live;
+    }
+    __device__ __forceinline__ void load(uint32_t k, uint64_t (&buf)[U]) {       // lanes past the list read entry 0
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint32_t r, c;
+            (void)place(k + u, in, r, c);
+            buf[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (uint64_t)srcRow[r] * g.d) + c);
+        }
+    }
+    // A whole group of rows that are all to be stored goes out in one piece.  Otherwise the wait comes first: the
+    // compiler cannot count predicated stores among the outstanding operations.
+    __device__ __forceinline__ void put(uint32_t k, const uint64_t (&buf)[U], bool all) {
+        if (all && any(k + U - 1)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                uint32_t r, c;
+                (void)place(k + u, out, r, c);
+                shared_st64(reinterpret_cast<uint64_t *>(dst + dstRow[r] * g.d) + c, buf[u]);
+            }
+        } else {
+            wait_vm0();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!any(k + u)) break;
+                uint32_t r, c;
+                const bool live = place(k + u, out, r, c);
+                const uint64_t row = dstRow[r];
+                if (live && row != kSkipRow) shared_st64(reinterpret_cast<uint64_t *>(dst + row * g.d) + c, buf[u]);
+            }
+        }
+    }
+    __device__ __forceinline__ void start(uint32_t cnt_) {
+        cnt = cnt_;
+        if (kLong) {
+            in = out = ChunkWalk(g.c8, (uint32_t)lane_id());
+            out.forget();
+        }
+        load(0, bufA);
+        if (any(U)) load(U, bufB);
+    }
+    __device__ __forceinline__ void finish(bool all) {
+        for (uint32_t k = 0;;) {
+            put(k, bufA, all);
+            if (any(k + 2 * U)) load(k + 2 * U, bufA);
+            if (!any(k += U)) return;
+            put(k, bufB, all);
+            if (any(k + 2 * U)) load(k + 2 * U, bufB);
+            if (!any(k += U)) return;
+        }
+    }
+};
+
+// The same in one go, for rows that are all stored.
+template <int U, bool kLong>
+__device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *__restrict__ src,
                                                  float *dst, const uint32_t *srcRow,
                                                  const uint64_t *dstRow, uint32_t cnt) {
     const uint32_t lane = (uint32_t)lane_id();
     const uint32_t rpi = (uint32_t)kWave >> g.lpr8Shift;
     const uint32_t sub = lane >> g.lpr8Shift;
-    const uint32_t cl  = lane & (g.LPR8 - 1);
-    const uint32_t step = rpi * U;
-    for (uint32_t pass = 0; pass < g.passes8; ++pass) {
-        uint32_t chunk = cl + pass * g.LPR8;
-        chunk = chunk < g.C8 ? chunk : 0u;
-        uint64_t bufA[U], bufB[U];
-        uint32_t entA[U], entB[U];
-        auto load = [&](uint32_t e0, uint64_t (&buf)[U], uint32_t (&ent)[U]) {
+    uint32_t cl = lane & (g.LPR8 - 1);
+    cl = cl < g.c8.C ? cl : 0u;
+    const uint32_t step = kLong ? (uint32_t)(kWave * U) : rpi * U;
+    const uint32_t total = kLong ? cnt * g.c8.C : cnt;                // chunks, or rows
+    uint64_t bufA[U], bufB[U];
+    uint32_t entA[U], entB[U], offA[kLong ? U : 1], offB[kLong ? U : 1];
+    ChunkWalk in(g.c8, lane);
+    auto load = [&](uint32_t q0, uint64_t (&buf)[U], uint32_t (&ent)[U], uint32_t *off) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t e = e0 + u * rpi + sub;
-                ent[u] = e < cnt ? e : 0u;
-                buf[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (uint64_t)srcRow[ent[u]] * g.d) + chunk);
+        for (int u = 0; u < U; ++u) {
+            if (kLong) {
+                const bool live = q0 + u * kWave + lane < total;
+                ent[u] = live ? in.r : 0u;
+                off[u] = live ? in.c : 0u;
+                in.next(g.c8);
+            } else {
+                const uint32_t e = q0 + u * rpi + sub;
+                ent[u] = e < total ? e : 0u;
             }
-        };
-        auto store = [&](const uint64_t (&buf)[U], const uint32_t (&ent)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                shared_st64(reinterpret_cast<uint64_t *>(dst + dstRow[ent[u]] * g.d) + chunk, buf[u]);
-        };
-        load(0, bufA, entA);
-        for (uint32_t e0 = 0;; e0 += 2 * step) {
-            load(e0 + step, bufB, entB);
-            store(bufA, entA);
-            if (e0 + step >= cnt) break;
-            load(e0 + 2 * step, bufA, entA);
-            store(bufB, entB);
-            if (e0 + 2 * step >= cnt) break;
+            buf[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (uint64_t)srcRow[ent[u]] * g.d) + (kLong ? off[u] : cl));
         }
+    };
+    auto store = [&](const uint64_t (&buf)[U], const uint32_t (&ent)[U], const uint32_t *off) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            shared_st64(reinterpret_cast<uint64_t *>(dst + dstRow[ent[u]] * g.d) + (kLong ? off[u] : cl), buf[u]);
+    };
+    load(0, bufA, entA, offA);
+    for (uint32_t q0 = 0;; q0 += 2 * step) {
+        load(q0 + step, bufB, entB, offB);
+        store(bufA, entA, offA);
+        if (q0 + step >= total) break;
+        load(q0 + 2 * step, bufA, entA, offA);
+        store(bufB, entB, offB);
+        if (q0 + 2 * step >= total) break;
     }
 }
 
 // Set probe for the first KPW lanes' keys of a wave (Alg. 2 "warpReadOutSlab" + match): W lanes
 // read the W slot keys of one set (contiguous 8*W bytes), so one wave load covers 64/W sets; a
-// ballot over the equality test gives every key its way.  Returns the way or -1.
-template <int W, int KPW, bool kShared = false>
+// ballot over the equality test gives every key its way.  Returns the way or -1.  between() runs after
+// the loads of the (last) round have been issued: it may issue further loads behind them.
+template <int W, int KPW, bool kShared = false, typename Between>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key,
-                                          uint32_t set, bool want) {
+                                          uint32_t set, bool want, Between &&between) {
     constexpr int G = kWave / W;                       // keys per wave load
     constexpr int R = (KPW + G - 1) / G;               // wave loads needed for KPW keys
     constexpr int RC = R > 32 ? 32 : R;                // wave loads in flight together (64 for W = 64 would not fit the registers)
@@ -348,6 +613,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
             const int64_t *p = K + (uint64_t)sj * W + slot;
             sk[r] = kShared ? (int64_t)shared_ld64(reinterpret_cast<const uint64_t *>(p)) : *p;
         }
+        if (r0 + RC >= R) between();
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
             const int j = (r0 + r) * G + sub;
@@ -361,6 +627,10 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
         }
     }
     return way;
+}
+template <int W, int KPW, bool kShared = false>
+__device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want) {
+    return probe_wave<W, KPW, kShared>(K, key, set, want, [] {});
 }
 
 // ------------------------------------------------------------------ query
@@ -457,7 +727,7 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
         const uint32_t lt = tile - t * a.tiles_per_table;
         if (wave < WPB) {
             const Table   &tb   = a.tab[t];
-            HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc));
+            HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc), "s"(tb.epoch));
             // Alg. 2 "g <- g + 1": every tile of the call stamps with the count the call will leave
             // behind; the tile that finishes the call stores it (see the helper wave below).
             const uint32_t g_call = kFull && tb.T ? *tb.gdev + 1u : 0u;
@@ -466,6 +736,7 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
             const uint32_t pos  = t * a.B + b;         // position in keys/out (< 2^32 checked on host)
 
             const int64_t key  = inb ? a.keys[pos] : kEmpty;      // keys[0 .. B) is readable also when n_dev says less
+            const uint64_t e1  = kCoherent ? read_epochs(tb.epoch) : 0ull;
             const bool    live = inb && (!kFull || !a.n_dev || b < *a.n_dev);
             const bool    want = live && !is_reserved(key);
             const uint32_t set = want ? set_of(key, tb.S, tb.smask) : 0u;
@@ -475,6 +746,22 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                 hit = false;
                 way = -1;
                 bool pending = want;
+                if (!__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {   // no writer at work
+                    shared_acquire();                                // the epochs are read before any key or row
+                    way = probe_wave<W, KPW, true>(tb.K, key, set, want);
+                    const uint64_t fmask = __ballot(way >= 0);
+                    const int r = rank_in(fmask);
+                    if (way >= 0) {
+                        s_src[wave][r] = (uint64_t)set * W + (uint32_t)way;
+                        s_dst[wave][r] = pos;
+                    }
+                    wave_lds_fence();
+                    const uint32_t nf = (uint32_t)__popcll(fmask);
+                    const uint32_t done = copy_rows_quiet<U, kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], nf, e1, tb.epoch);
+                    hit = way >= 0 && (uint32_t)r < done;
+                    pending = way >= 0 && !hit;                      // a miss is final, as below
+                    wave_lds_fence();
+                }
                 uint32_t rounds = 0;
                 while (__ballot(pending)) {
                     if (++rounds > kMaxRounds) {                     // a set never came free: report a miss
@@ -497,15 +784,9 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                         s_v1[wave][r]  = v1;
                     }
                     wave_lds_fence();
-                    if (fmask) {
-                        const uint32_t nf = (uint32_t)__popcll(fmask);
-                        if (kD != 0 || g.passes8 == 1)
-                            copy_rows_checked<U, kD, false>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
-                                                            &s_v1[wave][0], tb.sc, nf, &s_retry[wave][0]);
-                        else
-                            copy_rows_checked<(U > 16 ? 16 : U), 0, true>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
-                                                          &s_v1[wave][0], tb.sc, nf, &s_retry[wave][0]);
-                    }
+                    if (fmask)
+                        copy_rows_checked<(kD ? U : 16), kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
+                                                             &s_v1[wave][0], tb.sc, (uint32_t)__popcll(fmask), &s_retry[wave][0]);
                     wave_lds_fence();
                     bool again = false;
                     if (found) {
@@ -746,23 +1027,28 @@ struct WriteArgs {
 };
 
 // Replace (Alg. 3).  The first KPW lanes of a wave own one key each; all 64 lanes copy rows.  A
-// pending lane takes its set's sequence word (the paper's slabset lock, Sec. 4.1) with one
-// fetch-or of bit 0: it owns the set if the bit was clear.  The owners' sets are then searched with the wave-wide probe and their
-// counters read in the same round trip, new keys get their slot (key, counter, stamp) and row,
-// and every owner lets go again: word + 2 if it changed the set, the old word if the key was
-// already there.  Lanes that did not get their set search it without owning it before every
-// further attempt.  No lane ever waits while the wave owns a set: each round every pending lane
-// tries once, the owners' rows are copied by the whole wave, the sets are released, and the
-// others try again.  KPW = 16: four times as many waves as keys / 64 share the row copies, and a
-// wave's chain of dependent memory round trips is two copy groups long instead of eight.
-template <int W, int KPW>
+// pending lane takes its set's sequence word (the paper's slabset lock, Sec. 4.1) with one fetch-or
+// of bit 0, which also reads the set's counter: it owns the set if the bit was clear.  The owners' sets
+// are then searched with the wave-wide probe; new keys get their slot (key, counter, stamp) and row, and
+// every owner lets go again: word + 2 if it changed the set, the old word if the key was already
+// there.  Lanes that did not get their set search it without owning it before every further attempt.
+// No lane ever waits while the wave owns a set: each round every pending lane tries once, the owners'
+// rows are copied by the whole wave, the sets are released, and the others try again.
+// Bound by the chain of dependent round trips (key, word, set, rows, acknowledgement) in which a wave
+// holds its sets; the owners' rows are therefore requested right behind their sets' keys, before it is known
+// whether they are needed (a key that is already there has usually been found by the search without
+// owning): 2^18 new rows of 512 bytes, inserted, updated and queried, 221 -> 208 us, 32,768 rows 18.5 -> 16.8 us per
+// insert.  KPW = 16: four times as many waves as keys / 64 share the row copies, and a wave's chain is two
+// copy groups long instead of eight.
+template <int W, int KPW, bool kLong>
 __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
     __shared__ uint32_t s_srcrow[kWavesPerWg][kWave];
     __shared__ uint32_t s_owner[kWavesPerWg][kWave * 2];
+    __shared__ WriterGroup s_group;
 
     const int lane = lane_id();
-    const int wave = (int)(threadIdx.x / kWave);
+    const int wave = wave_id();
     const RowGeom g = a.g;
     const Table tb = a.tab;
     uint32_t n = a.n;
@@ -774,11 +1060,19 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
     const uint32_t wave_global = blockIdx.x * kWavesPerWg + wave;
     const uint32_t n_waves = gridDim.x * kWavesPerWg;
     const uint32_t g_now = tb.T ? *tb.gdev : 0u;            // Alg. 3 stamps with the current iteration count
+    if (blockIdx.x * kWavesPerWg >= n_tiles) return;        // nothing for any wave of this work-group
+    auto key_of = [&](uint32_t tile) {
+        const uint32_t i = tile * KPW + lane;
+        return tile < n_tiles && lane < KPW && i < n ? a.keys[i] : kEmpty;
+    };
+    int64_t key = key_of(wave_global);                      // requested before the work-group's barrier
+    writer_enter(tb, &s_group);
+    bool told = wave != 0;                                  // only wave 0 has something to tell
+    RowMover<8, kLong> rows(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0]);
 
-    for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves) {
+    for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves, key = key_of(tile)) {
         const uint32_t i = tile * KPW + lane;
         const bool mine = lane < KPW && i < n;
-        const int64_t key = mine ? a.keys[i] : kEmpty;
         bool pending = mine && !is_reserved(key);
         const uint64_t h = mix64((uint64_t)key);
         const uint32_t hs = (uint32_t)(h >> 32);
@@ -817,6 +1111,8 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             if (pending)
                 word = __hip_atomic_fetch_or(reinterpret_cast<uint64_t *>(seq_of(tb, set)), 1ull, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
+            shared_acquire();                                        // the word is owned before the set is read
+            writer_tell(&s_group, told);
             const uint32_t old = (uint32_t)word;
             const uint32_t c = (uint32_t)(word >> 32);
             const bool own = pending && !(old & 1u);
@@ -824,8 +1120,12 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
                 __builtin_amdgcn_s_sleep(8);
                 continue;
             }
-            shared_acquire();                                        // the word is owned before the set is read
-            int way = probe_wave<W, KPW, true>(tb.K, key, set, own);
+            const uint64_t ownmask = __ballot(own);
+            const int r = rank_in(ownmask);
+            if (own) s_srcrow[wave][r] = i;
+            wave_lds_fence();
+            // the owners' rows are requested behind the sets' keys and travel while those are compared
+            int way = probe_wave<W, KPW, true>(tb.K, key, set, own, [&] { rows.start((uint32_t)__popcll(ownmask)); });
             bool fresh = own && way < 0;
             if (tb.T) {                                              // LRU policy (Alg. 3)
                 if (fresh) {
@@ -846,18 +1146,14 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
                 way = (int)(c & (W - 1));                            // victim counter
             }
             const uint64_t freshmask = __ballot(fresh);
-            if (fresh) {
-                st_agent(tb.K + (uint64_t)set * W + (uint32_t)way, key);
-                const int r = rank_in(freshmask);
-                s_dst[wave][r] = (uint64_t)set * W + (uint32_t)way;
-                s_srcrow[wave][r] = i;
-            }
             if (freshmask) {
+                writer_entered(&s_group);
+                if (fresh) st_agent(tb.K + (uint64_t)set * W + (uint32_t)way, key);
+                if (own) s_dst[wave][r] = fresh ? (uint64_t)set * W + (uint32_t)way : kSkipRow;
                 wave_lds_fence();
-                copy_rows_shared<8>(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0],
-                                    (uint32_t)__popcll(freshmask));
-                wave_lds_fence();
+                rows.finish(freshmask == ownmask);
             }
+            wave_lds_fence();
             shared_release();                                        // rows and keys land before the words move on
             if (own) {
                 // let go: a changed set gets seq + 2 and ctr + 1 in one store, an unchanged one its old word
@@ -867,6 +1163,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             }
         }
     }
+    writer_leave(tb, &s_group, told);                              // (every hold ended with shared_release: its stores have landed)
 }
 
 // Update (Alg. 4) with one lock acquisition per run of lanes that share a set.  Key batches that
@@ -877,13 +1174,14 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
 // Two lanes of a group that found the same slot (a key given twice) are thinned to one per round.
 // Lanes of different groups that meet on a set compete by compare-and-swap on its word; no lane
 // waits while its wave owns a set.
-template <int W, int KPW>
+template <int W, int KPW, bool kLong>
 __global__ void __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
     __shared__ uint32_t s_srcrow[kWavesPerWg][kWave];
+    __shared__ WriterGroup s_group;
 
     const int lane = lane_id();
-    const int wave = (int)(threadIdx.x / kWave);
+    const int wave = wave_id();
     const RowGeom g = a.g;
     const Table tb = a.tab;
     uint32_t n = a.n;
@@ -895,11 +1193,18 @@ __global__ void __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
     const uint32_t wave_global = blockIdx.x * kWavesPerWg + wave;
     const uint32_t n_waves = gridDim.x * kWavesPerWg;
     const uint64_t le_lane = lane == 63 ? ~0ull : ((2ull << lane) - 1);     // bits 0..lane
+    if (blockIdx.x * kWavesPerWg >= n_tiles) return;        // nothing for any wave of this work-group
+    auto key_of = [&](uint32_t tile) {
+        const uint32_t i = tile * KPW + lane;
+        return tile < n_tiles && lane < KPW && i < n ? a.keys[i] : kEmpty;
+    };
+    int64_t key = key_of(wave_global);                      // requested before the work-group's barrier
+    writer_enter(tb, &s_group);
+    bool told = wave != 0;                                  // only wave 0 has something to tell
 
-    for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves) {
+    for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves, key = key_of(tile)) {
         const uint32_t i = tile * KPW + lane;
         const bool mine = lane < KPW && i < n;
-        const int64_t key = mine ? a.keys[i] : kEmpty;
         bool pending = mine && !is_reserved(key);
         const uint32_t set = pending ? set_of(key, tb.S, tb.smask) : 0u;
 
@@ -926,6 +1231,7 @@ __global__ void __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
             v = (uint32_t)__shfl((int)v, leader, kWave);
             const bool busy = pending && (v & 1u);
             shared_acquire();                                        // the word is read before the keys
+            writer_tell(&s_group, told);
             int way = -1;
             if (pending && !busy) {
 #pragma unroll
@@ -951,14 +1257,14 @@ __global__ void __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
             const uint64_t actmask = __ballot(act);
             if (actmask) {
                 shared_acquire();
+                writer_entered(&s_group);
                 if (act) {
                     const int r = rank_in(actmask);
                     s_dst[wave][r] = (uint64_t)set * W + (uint32_t)way;
                     s_srcrow[wave][r] = i;
                 }
                 wave_lds_fence();
-                copy_rows_shared<8>(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0],
-                                    (uint32_t)__popcll(actmask));
+                copy_rows_shared<8, kLong>(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0], (uint32_t)__popcll(actmask));
                 wave_lds_fence();
                 shared_release();                                    // rows land before the word moves on
                 if (won) st_agent(seq_of(tb, set), v + 2u);
@@ -966,6 +1272,7 @@ __global__ void __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
             }
         }
     }
+    writer_leave(tb, &s_group, told);
 }
 
 // ------------------------------------------------------------------ small kernels
@@ -1200,12 +1507,15 @@ RowGeom make_geom(uint32_t d) {
     g.LPR = lpr;
     g.lprShift = sh;
     g.passes = (g.C + lpr - 1) / lpr;
-    g.C8 = d / 2;
     lpr = 1; sh = 0;
-    while (lpr < g.C8 && lpr < (uint32_t)kWave) { lpr <<= 1; ++sh; }
+    while (lpr < d / 2 && lpr < (uint32_t)kWave) { lpr <<= 1; ++sh; }
     g.LPR8 = lpr;
     g.lpr8Shift = sh;
-    g.passes8 = (g.C8 + lpr - 1) / lpr;
+    auto step = [](uint32_t C) {               // lane * (inv * C - 2^16) < 2^16 for lane, C <= 64: the quotient is exact
+        return ChunkStep{C, C > (uint32_t)kWave ? 0u : (65536u + C - 1) / C, (uint32_t)kWave / C, (uint32_t)kWave % C};
+    };
+    g.c16 = step(g.C);
+    g.c8 = step(d / 2);
     return g;
 }
 
@@ -1229,6 +1539,7 @@ struct hps_cache {
     std::atomic<int> query_dedup;
     int      policy;                      // HPS_POLICY_*
     uint32_t *T;                          // access stamps (LRU policy), else nullptr
+    uint32_t *epoch;                      // kEpochs {started, finished} pairs of writer work-groups
     uint32_t *flags;                      // device words: [0] HPS_FLAG_* bits, [1] g, the global iteration
                                           // count of Alg. 2 (one step per query call, LRU policy)
     int      n_cus;                       // compute units of the device
@@ -1257,6 +1568,7 @@ Table table_of(const hps_cache *c) {
     t.T = c->T;
     t.gdev = c->flags + 1;
     t.flags = c->flags;
+    t.epoch = c->epoch;
     return t;
 }
 
@@ -1280,95 +1592,110 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
     return c->ring + it->second;
 }
 
-// Launch shape of the query kernel: KPW keys per worker wave, row copy in groups of U wave loads,
-// WPB worker waves per work-group.  Chosen from the batch size (measured on 256 CUs with 512-byte
-// rows): small batches want many small work-groups, ~10^5 keys want 512-key tiles (half as many
-// same-address counter atomics, which cost ~11 ns each and serialise).  U is large enough for a
-// wave's whole share of 512-byte rows to be one group (26 wave loads for the 52 keys per wave of
-// the 106,496-key batch, 32 for 64 keys per wave).
-struct QueryShape { int kpw, u, wpb; };
+// Launch shape of the query kernel: wpb worker waves per work-group, kpw keys per worker wave, row
+// copy in groups of u wave loads.  All figures are us per launch on 256 CUs.
+//
+// Workers.  Small batches want many small work-groups; ~10^5 keys want 512-key tiles (half as many
+// same-address counter atomics, which cost ~11 ns each and serialise); larger batches run several
+// work-groups per CU one after the other.  Plain, rows of 512 bytes (4 / 8 workers): 1,664 keys 5.6 /
+// 6.1, 13,312 keys 8.3 / 8.3, 39,936 keys 12.5 / 11.6, 62,400 keys 16.8 / 13.5; (8 workers in groups of 26 / 7
+// in groups of 32): 425,984 keys 65.5 / 65.3, 851,968 keys 143.0 / 125.7, the 26-table launch 400 / 378.
+// Rows of up to 128 bytes leave registers for 16 waves in two work-groups per CU and are bound by the
+// counter atomics and by the number of keys in flight: 15 workers 42.9, 7 workers 44.5 at 851,968 keys of
+// 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7.
+// Checked (4 / 7 workers): 26,624 keys of 512 bytes 11.9 / 11.9, 39,936 keys 12.8 / 12.6, 26,624 keys of 2 KiB
+// 24.0 / 20.3, 106,496 keys of 128 bytes 14.2 / 11.6; small batches as above.
+//
+// Keys per wave: at most 64, trimmed so that the work-groups come out as a whole number of rounds
+// over the CUs (106,496 keys in tiles of 8 x 52 are exactly 256 work-groups; tiles of 8 x 64 would be
+// 208, leaving 48 CUs idle).  Small batches go down to 16 keys per wave (8 below 4,096 keys): more
+// work-groups, each with a shorter chain of dependent row copies (1,664 keys: 5.5 us instead of 8.3 us;
+// 13,312 keys: 8.9 instead of 11.1 us).
+//
+// Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
+// first group's stores), and not much more, because the registers of a larger group are waves that
+// the CU cannot hold: 64 keys of 128 bytes in groups of 8 / 16 / 32 wave loads take 44.5 / 50.0 / 63.7 per 851,968
+// keys, 39,999 keys of 1,280 bytes in groups of 24 / 16 with idle lanes 19.4 / 24.1, 26,624 keys of 512
+// bytes in groups of 13 / 26 9.7 / 10.6.  Checked, 8 bytes per lane: 106,496 keys of 384 bytes in groups of 64 / 32 / 16
+// 17.0 / 18.4 / 19.1, of 256 bytes in groups of 32 / 16 13.9 / 15.3; but over several rounds (425,984 keys) 51.4 /
+// 46.6: there the second work-group that fits a CU with the smaller group is worth more.
+struct QueryShape { uint32_t kpw; int u, wpb; };
 
-QueryShape query_shape(uint64_t n, bool coherent, bool dedup) {
+QueryShape query_shape(uint64_t n, uint32_t d, uint64_t cus, bool coherent, bool dedup) {
+    QueryShape q{(uint32_t)kWave, 0, 0};
+    if (coherent) q.wpb = n * d < (1u << 22) ? 4 : 7;
+    else if (n < (1u << 14)) q.wpb = 4;
+    else if (n < (1u << 18) || dedup) q.wpb = 8;
+    else q.wpb = d <= 32 ? 15 : 7;
+    const uint64_t full = (uint64_t)q.wpb * kWave * cus;       // keys per round at 64 keys per wave
+    const uint64_t rounds = (n + full - 1) / full;
+    const uint64_t floor_k = n < 4096 ? 8 : 16;
+    if (rounds > 0 && rounds <= 8) {
+        uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
+        if (k < floor_k) k = floor_k;
+        if (k < (uint64_t)kWave) q.kpw = (uint32_t)k;
+    }
+    const uint64_t bytes = (uint64_t)q.kpw * d * 4;            // a wave's rows
     if (coherent) {
-        // The checked variant reads rows 8 bytes per lane (one 512-byte row per wave load) and pays two
-        // dependent round trips per group (rows, then the sequence words again), so a wave's rows
-        // should be ONE group: 64 keys per wave need 128 data registers, which 8 waves per
-        // work-group (2 per SIMD, 256 registers each) leave room for and 9 do not.  Measured in the
-        // stand-alone test bed on the 106,496-key batch: groups of 16 rows, 9 waves 27.5 us; groups
-        // of 32, 8 waves 23.1 us; one group, 8 waves 21.6 us.
-        // (1.7 M keys against a 64 GiB cache: 0.375 ms with this shape, 0.38-0.39 ms with groups of 16 or
-        // 32 rows and 5 waves, 0.49 ms with one group and 5 waves)
-        if (n < (1u << 16)) return QueryShape{64, 64, 4};
-        return QueryShape{64, 64, 7};
+        if (d == 128 || bytes > 16384) q.u = 64;
+        else q.u = bytes <= 8192 || rounds > 1 ? 16 : 32;
+    } else if (d == 128) {
+        q.u = q.wpb == 7 ? 32 : bytes <= 13312 ? 13 : 26;
+    } else {
+        q.u = bytes <= 8192 ? 8 : bytes <= 16384 ? 16 : q.wpb == 8 ? 24 : 32;
     }
-    // Large batches run several work-groups per CU one after the other; measured (us per launch) for
-    // 425,984 / 851,968 / 1,703,936 keys of the hot cache, the 425,984-key streaming step and the
-    // 26-table launch:
-    //   4 waves, one group of 32   76.6 / 141.2 / 275.4 / 77.6 / 439
-    //   8 waves, one group of 26   65.5 / 143.0 / 278.9 / 67.2 / 400
-    //   7 waves, one group of 32   65.3 / 125.7 / 244.0 / 65.4 / 378
-    //   8 waves, groups of 16      73.8 / 140.4 / 263.0 / 72.8 / 392
-    // (a second group waits, with its own loads, for the first group's stores: one group per wave)
-    // (4 against 8 workers, us per launch: 1,664 keys 5.6 / 6.1; 6,656 keys 6.9 / 7.3; 13,312 keys 8.3 / 8.3;
-    //  39,936 keys 12.5 / 11.6; 53,248 keys 14.3 / 12.8; 62,400 keys 16.8 / 13.5)
-    if (n < (1u << 14)) return QueryShape{64, 26, 4};
-    if (n < (1u << 18)) return QueryShape{64, 26, 8};
-    if (!dedup) return QueryShape{64, 32, 7};
-    return QueryShape{64, 16, 8};                  // (the in-tile dedup needs a power-of-two tile)
+    return q;
 }
 
-template <int W, int KPW, int U, int WPB>
-void launch_query_plain(const QueryArgs &a, bool dedup, bool full, hipStream_t st) {
+template <int W, int U, int WPB, bool kCoherent, int kD>
+void launch_query_kernel(const QueryArgs &a, bool full, hipStream_t st) {
     const uint32_t grid = a.n_tiles < (1u << 20) ? a.n_tiles : (1u << 20);
     const dim3 block((WPB + 1) * kWave);
-    if constexpr ((WPB & (WPB - 1)) == 0) {      // (the shapes chosen for dedup mode have 4 or 8 worker waves)
-        if (dedup && KPW == kWave) {
-            hipLaunchKernelGGL((query_dedup_kernel<W, (WPB == 8 ? 4 : 8), WPB>), dim3(grid), block, 0, st, a);
-            return;
-        }
-    }
-    // any row width but 128: run-time row geometry needs more registers, so smaller groups under the 9-wave limit
-    constexpr int UG = WPB == 8 ? 16 : U;
-    if (a.g.d == 128) {
-        if (full) hipLaunchKernelGGL((query_kernel<W, KPW, U, WPB, false, 128, true>), dim3(grid), block, 0, st, a);
-        else     hipLaunchKernelGGL((query_kernel<W, KPW, U, WPB, false, 128, false>), dim3(grid), block, 0, st, a);
-    } else {
-        if (full) hipLaunchKernelGGL((query_kernel<W, KPW, UG, WPB, false, 0, true>), dim3(grid), block, 0, st, a);
-        else     hipLaunchKernelGGL((query_kernel<W, KPW, UG, WPB, false, 0, false>), dim3(grid), block, 0, st, a);
-    }
+    if (full) hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, true>), dim3(grid), block, 0, st, a);
+    else      hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, false>), dim3(grid), block, 0, st, a);
 }
 
-template <int W, int KPW, int U, int WPB>
-void launch_query_checked(const QueryArgs &a, bool full, hipStream_t st) {
+template <int W, int WPB>
+void launch_query_dedup(const QueryArgs &a, hipStream_t st) {
     const uint32_t grid = a.n_tiles < (1u << 20) ? a.n_tiles : (1u << 20);
-    const dim3 block((WPB + 1) * kWave);
-    // any row width but 128: run-time row geometry, groups of 16 wave loads keep the kernel inside its registers
-    if (a.g.d == 128) {
-        if (full) hipLaunchKernelGGL((query_kernel<W, KPW, U, WPB, true, 128, true>), dim3(grid), block, 0, st, a);
-        else     hipLaunchKernelGGL((query_kernel<W, KPW, U, WPB, true, 128, false>), dim3(grid), block, 0, st, a);
-    } else {
-        if (full) hipLaunchKernelGGL((query_kernel<W, KPW, 16, WPB, true, 0, true>), dim3(grid), block, 0, st, a);
-        else     hipLaunchKernelGGL((query_kernel<W, KPW, 16, WPB, true, 0, false>), dim3(grid), block, 0, st, a);
-    }
+    hipLaunchKernelGGL((query_dedup_kernel<W, (WPB == 8 ? 4 : 8), WPB>), dim3(grid), dim3((WPB + 1) * kWave), 0, st, a);
 }
 
 template <int W>
 hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, bool dedup, bool full, hipStream_t st) {
-    const int id = q.kpw * 10000 + q.u * 100 + q.wpb;
-    if (coherent) {
-        switch (id) {
-            case 646404: launch_query_checked<W, 64, 64, 4>(a, full, st); break;
-            case 646407: launch_query_checked<W, 64, 64, 7>(a, full, st); break;
+    const int id = q.u * 100 + q.wpb;
+    const bool d128 = a.g.d == 128;
+    if (dedup) {
+        if (q.wpb == 4) launch_query_dedup<W, 4>(a, st);
+        else launch_query_dedup<W, 8>(a, st);
+    } else if (coherent) {
+        switch (d128 ? 10000 + id : id) {
+            case 16404: launch_query_kernel<W, 64, 4, true, 128>(a, full, st); break;
+            case 16407: launch_query_kernel<W, 64, 7, true, 128>(a, full, st); break;
+            case 1604: launch_query_kernel<W, 16, 4, true, 0>(a, full, st); break;
+            case 3204: launch_query_kernel<W, 32, 4, true, 0>(a, full, st); break;
+            case 6404: launch_query_kernel<W, 64, 4, true, 0>(a, full, st); break;
+            case 1607: launch_query_kernel<W, 16, 7, true, 0>(a, full, st); break;
+            case 3207: launch_query_kernel<W, 32, 7, true, 0>(a, full, st); break;
+            case 6407: launch_query_kernel<W, 64, 7, true, 0>(a, full, st); break;
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
     } else {
-        switch (id) {
-            case 642604: launch_query_plain<W, 64, 26, 4>(a, dedup, full, st); break;
-            case 642608: launch_query_plain<W, 64, 26, 8>(a, dedup, full, st); break;
-            case 641304: launch_query_plain<W, 64, 13, 4>(a, dedup, full, st); break;
-            case 641308: launch_query_plain<W, 64, 13, 8>(a, dedup, full, st); break;
-            case 643207: launch_query_plain<W, 64, 32, 7>(a, dedup, full, st); break;
-            case 641608: launch_query_plain<W, 64, 16, 8>(a, dedup, full, st); break;
+        switch (d128 ? 10000 + id : id) {
+            case 11304: launch_query_kernel<W, 13, 4, false, 128>(a, full, st); break;
+            case 12604: launch_query_kernel<W, 26, 4, false, 128>(a, full, st); break;
+            case 11308: launch_query_kernel<W, 13, 8, false, 128>(a, full, st); break;
+            case 12608: launch_query_kernel<W, 26, 8, false, 128>(a, full, st); break;
+            case 13207: launch_query_kernel<W, 32, 7, false, 128>(a, full, st); break;
+            case 804: launch_query_kernel<W, 8, 4, false, 0>(a, full, st); break;
+            case 1604: launch_query_kernel<W, 16, 4, false, 0>(a, full, st); break;
+            case 3204: launch_query_kernel<W, 32, 4, false, 0>(a, full, st); break;
+            case 808: launch_query_kernel<W, 8, 8, false, 0>(a, full, st); break;
+            case 1608: launch_query_kernel<W, 16, 8, false, 0>(a, full, st); break;
+            case 2408: launch_query_kernel<W, 24, 8, false, 0>(a, full, st); break;
+            case 1607: launch_query_kernel<W, 16, 7, false, 0>(a, full, st); break;
+            case 3207: launch_query_kernel<W, 32, 7, false, 0>(a, full, st); break;
+            case 815: launch_query_kernel<W, 8, 15, false, 0>(a, full, st); break;
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
     }
@@ -1409,15 +1736,25 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
     if (blocks > (1u << 16)) blocks = 1u << 16;
     const dim3 grid((uint32_t)blocks), block(kBlock);
+    const bool lng = c->d > 128;               // rows of more than one wave load of 8 bytes per lane
     switch (c->W) {
+#define HPS_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, 0, st, a)
 #define HPS_CASE(w)                                                                         \
     case w:                                                                                 \
-        if (kInsert) hipLaunchKernelGGL((insert_kernel<w, kInsertKpw>), grid, block, 0, st, a); \
-        else if (kpw == 16) hipLaunchKernelGGL((update_kernel<w, 16>), grid, block, 0, st, a);  \
-        else hipLaunchKernelGGL((update_kernel<w, 64>), grid, block, 0, st, a);                 \
+        if (kInsert) {                                                                      \
+            if (lng) HPS_LAUNCH(insert_kernel<w, kInsertKpw, true>);                        \
+            else HPS_LAUNCH(insert_kernel<w, kInsertKpw, false>);                           \
+        } else if (kpw == 16) {                                                             \
+            if (lng) HPS_LAUNCH(update_kernel<w, 16, true>);                                \
+            else HPS_LAUNCH(update_kernel<w, 16, false>);                                   \
+        } else {                                                                            \
+            if (lng) HPS_LAUNCH(update_kernel<w, 64, true>);                                \
+            else HPS_LAUNCH(update_kernel<w, 64, false>);                                   \
+        }                                                                                   \
         break;
         HPS_CASE(1) HPS_CASE(2) HPS_CASE(4) HPS_CASE(8) HPS_CASE(16) HPS_CASE(32) HPS_CASE(64)
 #undef HPS_CASE
+#undef HPS_LAUNCH
         default: return fail(HPS_ERR_INVALID_ARG, "unsupported ways");
     }
     HIP_TRY(hipGetLastError());
@@ -1469,7 +1806,8 @@ hps_status_t hps_cache_create_policy(size_t capacity, uint32_t ways, uint32_t di
     c->S = capacity / ways;
     c->W = ways;
     c->d = dim;
-    c->K = nullptr; c->V = nullptr; c->sc = nullptr; c->ring = nullptr; c->T = nullptr; c->flags = nullptr; c->word_half = 0;
+    c->K = nullptr; c->V = nullptr; c->sc = nullptr; c->ring = nullptr; c->T = nullptr; c->flags = nullptr;
+    c->epoch = nullptr; c->word_half = 0;
     c->policy = policy;
     c->concurrent_writers.store(dim <= kMaxCheckedDim ? 1 : 0);
     c->query_dedup.store(0);
@@ -1484,6 +1822,9 @@ hps_status_t hps_cache_create_policy(size_t capacity, uint32_t ways, uint32_t di
     if (e == hipSuccess) e = hipMalloc(&c->ring, 2 * kRing * sizeof(uint64_t));
     if (e == hipSuccess) e = hipMalloc(&c->flags, 2 * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemsetAsync(c->flags, 0, 2 * sizeof(uint32_t), 0);
+    constexpr size_t kEpochBytes = kEpochs * kEpochStride * sizeof(uint32_t);
+    if (e == hipSuccess) e = hipMalloc(&c->epoch, kEpochBytes);
+    if (e == hipSuccess) e = hipMemsetAsync(c->epoch, 0, kEpochBytes, 0);
     if (e == hipSuccess && policy == HPS_POLICY_LRU) {
         e = hipMalloc(&c->T, capacity * sizeof(uint32_t));
         if (e == hipSuccess) e = hipMemsetAsync(c->T, 0, capacity * sizeof(uint32_t), 0);
@@ -1506,6 +1847,7 @@ hps_status_t hps_cache_create_policy(size_t capacity, uint32_t ways, uint32_t di
         if (c->ring) (void)hipFree(c->ring);
         if (c->T) (void)hipFree(c->T);
         if (c->flags) (void)hipFree(c->flags);
+        if (c->epoch) (void)hipFree(c->epoch);
         delete c;
         return fail(code, msg);
     }
@@ -1523,6 +1865,7 @@ hps_status_t hps_cache_destroy(hps_cache_t *c) {
     if ((e2 = hipFree(c->ring)) != hipSuccess) e = e2;
     if (c->T && (e2 = hipFree(c->T)) != hipSuccess) e = e2;
     if ((e2 = hipFree(c->flags)) != hipSuccess) e = e2;
+    if ((e2 = hipFree(c->epoch)) != hipSuccess) e = e2;
     delete c;
     if (e != hipSuccess) return fail(HPS_ERR_DEVICE, std::string("hipFree: ") + hipGetErrorString(e));
     return HPS_OK;
@@ -1556,6 +1899,14 @@ hps_status_t hps_cache_flags(hps_cache_t *c, uint32_t *flags, int clear) {
 hps_status_t hps_cache_debug_set_seq(hps_cache_t *c, uint64_t set, uint32_t value) {
     if (hps_status_t s = check_handle(c)) return s;
     if (set >= c->S) return fail(HPS_ERR_INVALID_ARG, "set index out of range");
+    // a writer that holds a set (odd word) has counted itself in and not yet out
+    uint32_t old = 0, pair[2] = {0, 0};
+    HIP_TRY(hipMemcpy(&old, c->sc + 2 * set, sizeof(uint32_t), hipMemcpyDeviceToHost));
+    if ((old ^ value) & 1u) {
+        HIP_TRY(hipMemcpy(pair, c->epoch, sizeof(pair), hipMemcpyDeviceToHost));
+        ++pair[value & 1u ? 0 : 1];
+        HIP_TRY(hipMemcpy(c->epoch, pair, sizeof(pair), hipMemcpyHostToDevice));
+    }
     HIP_TRY(hipMemcpy(c->sc + 2 * set, &value, sizeof(uint32_t), hipMemcpyHostToDevice));
     return HPS_OK;
 }
@@ -1600,27 +1951,8 @@ static hps_status_t query_call(hps_cache_t *const *caches, uint32_t n_tables, co
     bool coherent = false;                      // any table that may see concurrent writers makes the call careful
     for (uint32_t t = 0; t < n_tables; ++t) coherent = coherent || caches[t]->concurrent_writers.load() != 0;
     const bool dedup = !coherent && caches[0]->query_dedup.load() != 0;
-    QueryShape shape = query_shape(total, coherent, dedup);
-    // Keys per worker wave: at most 64, trimmed so that the work-groups come out as a whole number
-    // of rounds over the CUs (106,496 keys in tiles of 8 x 52 are exactly 256 work-groups; tiles of
-    // 8 x 64 would be 208, leaving 48 CUs idle).  Small batches go down to 16 keys per wave (8 below
-    // 4,096 keys): more work-groups, each with a shorter chain of dependent row copies (1,664 keys:
-    // 5.5 us instead of 8.3 us; 13,312 keys: 8.9 instead of 11.1 us).
-    uint32_t kpw = (uint32_t)shape.kpw;
-    {
-        const uint64_t cus = (uint64_t)caches[0]->n_cus;
-        const uint64_t full = (uint64_t)shape.wpb * shape.kpw * cus;       // keys per round at 64 keys per wave
-        const uint64_t rounds = (total + full - 1) / full;
-        const uint64_t floor_k = total < 4096 ? 8 : 16;
-        if (rounds > 0 && rounds <= 8) {
-            uint64_t k = (total + shape.wpb * cus * rounds - 1) / (shape.wpb * cus * rounds);
-            if (k < floor_k) k = floor_k;
-            if (k <= (uint64_t)shape.kpw) kpw = (uint32_t)k;
-        }
-    }
-    // At most 26 keys per wave: a group of 13 wave loads holds them all (rows of up to 512 bytes), and the 13 loads
-    // of a 26-load group that would only repeat entry 0 are not issued (26,624 keys: 10.6 -> 9.7 us).
-    if (!coherent && shape.u == 26 && kpw <= 26 && caches[0]->d <= 128) shape.u = 13;
+    const QueryShape shape = query_shape(total, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup);
+    const uint32_t kpw = shape.kpw;
     a.kpw = kpw;
     const uint32_t tile = kpw * (uint32_t)shape.wpb;
     a.tiles_per_table = (uint32_t)((batch + tile - 1) / tile);
@@ -1764,7 +2096,7 @@ hps_status_t hps_membench_gather(const float *rows, const uint32_t *slot_of, siz
         hipLaunchKernelGGL((membench_gather_kernel<26, kWpb, 128>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
                            static_cast<hipStream_t>(stream), rows, slot_of, (uint32_t)n, (uint32_t)kpw, make_geom(dim), out);
     else
-        hipLaunchKernelGGL((membench_gather_kernel<26, kWpb, 0>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
+        hipLaunchKernelGGL((membench_gather_kernel<24, kWpb, 0>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
                            static_cast<hipStream_t>(stream), rows, slot_of, (uint32_t)n, (uint32_t)kpw, make_geom(dim), out);
     HIP_TRY(hipGetLastError());
     return HPS_OK;

@@ -1,0 +1,57 @@
+"""Rows of any width through query, insert and update: row lists whose chunks fill a wave load, miss it
+by one, or split a row over two of them; batches below, at and above the query's launch shapes."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from harness import SENTINEL, DeviceCache  # noqa: E402
+from oracle import OracleCache  # noqa: E402
+from paper_2210_08804_amd import inputs  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _compare(gc, oc, keys, d):
+    exp = np.full((len(keys), d), SENTINEL, dtype=np.uint32)
+    _, omi, _ = oc.query(keys, exp)
+    out, mi, mk = gc.query(keys)
+    assert (mi == omi).all() and (mk == keys[omi]).all()
+    assert (out == exp).all()
+
+
+@pytest.mark.parametrize("checked", [False, True])
+@pytest.mark.parametrize("d", [4, 8, 12, 28, 32, 36, 64, 68, 96, 124, 132, 192, 252, 260, 320, 512, 516, 1020, 1024])
+def test_row_widths(d, checked):
+    S, W, n_keys = 2039, 8, 1200            # no set gets more than W keys
+    keys = np.arange(n_keys, dtype=np.int64) * 7 + 1
+    rows = inputs.backing_rows(keys, d)
+    with DeviceCache(S * W, W, d, concurrent_writers=checked) as gc:
+        oc = OracleCache(S * W, W, d)
+        for lo in range(0, n_keys, 401):
+            gc.insert(keys[lo:lo + 401], rows[lo:lo + 401])
+            oc.insert(keys[lo:lo + 401], rows[lo:lo + 401])
+        upd = keys[::3].copy()
+        gc.update(upd, inputs.backing_rows(upd, d, version=1))
+        oc.update(upd, inputs.backing_rows(upd, d, version=1))
+        rng = np.random.Generator(np.random.PCG64(d))
+        for n in (1, 7, 63, 65, 1000):
+            _compare(gc, oc, rng.integers(0, 9 * n_keys, size=n, dtype=np.int64), d)
+        oc.close()
+
+
+@pytest.mark.parametrize("checked", [False, True])
+@pytest.mark.parametrize("d,n", [(16, (1 << 14) - 1), (16, 1 << 14), (16, (1 << 18) + 3), (32, (1 << 17) + 1), (32, 270001), (64, (1 << 16) + 7),
+                                 (64, 270001), (96, 43691), (160, 20001), (128, 32768), (128, 32767), (256, 16384), (320, 13107), (320, 60001)])
+def test_shapes_by_batch_and_width(d, n, checked):
+    """Both sides of every line between two launch shapes."""
+    S, W, n_keys = 8191, 8, 4000
+    keys = np.arange(n_keys, dtype=np.int64) * 5
+    rows = inputs.backing_rows(keys, d)
+    with DeviceCache(S * W, W, d, concurrent_writers=checked) as gc:
+        oc = OracleCache(S * W, W, d)
+        gc.insert(keys, rows)
+        oc.insert(keys, rows)
+        rng = np.random.Generator(np.random.PCG64(n))
+        _compare(gc, oc, rng.integers(0, 6 * n_keys, size=n, dtype=np.int64), d)
+        oc.close()
