@@ -22,6 +22,7 @@
 
 #include "hps_dedup.h"
 #include "hps_mix.h"
+#include "hps_rows.h"
 
 namespace {
 
@@ -31,8 +32,6 @@ constexpr int      kTile  = 1024;                 // keys (= threads) per work-g
 constexpr int      kLds   = 2 * kTile;            // LDS table slots (load <= 0.5)
 constexpr uint64_t kMagic = 0x4850534445445550ull;
 constexpr uint32_t kNone  = 0xFFFFFFFFu;
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Scratch of hps_dedup_noalloc, the entry point for callers that cannot allocate: one hash table
 // for batches of up to kNaMaxKeys keys (2 slots per key, 8-byte key word + 4-byte number per
@@ -174,39 +173,6 @@ __global__ void __launch_bounds__(kBlock) dedup_inverse_kernel(const int64_t *__
     }
     // the slots the previous call used in the other table
     for (uint64_t i = t; i < other_dirty; i += stride) other_tkey[i] = kEmpty;
-}
-
-// out[i] = rows[inverse[i]].  LPR lanes move one row, 16 bytes per lane; four rows per lane group
-// are in flight before the first store.  Lanes past the end repeat the last row (same bytes to
-// the same place), lanes past the row's last chunk repeat chunk 0.
-__global__ void __launch_bounds__(kBlock) expand_rows_kernel(const float *__restrict__ rows,
-                                                             const uint32_t *__restrict__ inverse, uint32_t n,
-                                                             uint32_t d, uint32_t C, uint32_t LPR, uint32_t lprShift,
-                                                             uint32_t passes, float *__restrict__ out) {
-    constexpr int U = 4;
-    const uint32_t rpb = (uint32_t)kBlock >> lprShift;                // rows per block and step
-    const uint32_t sub = threadIdx.x >> lprShift;
-    const uint32_t cl  = threadIdx.x & (LPR - 1);
-    for (uint64_t r0 = (uint64_t)blockIdx.x * rpb * U; r0 < n; r0 += (uint64_t)gridDim.x * rpb * U) {
-        uint32_t src[U], dst[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint64_t r = r0 + (uint64_t)u * rpb + sub;
-            dst[u] = r < n ? (uint32_t)r : n - 1u;
-            src[u] = inverse[dst[u]];
-        }
-        for (uint32_t pass = 0; pass < passes; ++pass) {
-            uint32_t chunk = cl + pass * LPR;
-            chunk = chunk < C ? chunk : 0u;
-            f32x4 buf[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                buf[u] = *reinterpret_cast<const f32x4 *>(rows + (uint64_t)src[u] * d + chunk * 4);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                __builtin_nontemporal_store(buf[u], reinterpret_cast<f32x4 *>(out + (uint64_t)dst[u] * d + chunk * 4));
-        }
-    }
 }
 
 }  // namespace
@@ -425,19 +391,10 @@ hps_status_t hps_expand_rows(const float *rows, const uint32_t *inverse, size_t 
     if (!rows || !inverse || !out) return fail(HPS_ERR_INVALID_ARG, "rows, inverse and out must not be NULL when n > 0");
     if (!aligned(rows, 16) || !aligned(out, 16) || !aligned(inverse, 4))
         return fail(HPS_ERR_INVALID_ARG, "rows and out must be 16-byte, inverse 4-byte aligned");
-    const uint32_t C = dim / 4;
-    uint32_t LPR = 1, shift = 0;
-    while (LPR < C && LPR < 64) {
-        LPR <<= 1;
-        ++shift;
-    }
-    const uint32_t passes = (C + LPR - 1) / LPR;
-    const uint64_t rows_per_block = ((uint64_t)kBlock >> shift) * 4;
-    uint64_t blocks = (n + rows_per_block - 1) / rows_per_block;
-    if (blocks > (1u << 16)) blocks = 1u << 16;
-    hipLaunchKernelGGL(expand_rows_kernel, dim3((uint32_t)blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream),
-                       rows, inverse, (uint32_t)n, dim, C, LPR, shift, passes, out);
-    HIP_TRY(hipGetLastError());
+    int dev = -1, cus = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    HIP_TRY(hps_launch_expand_rows(rows, inverse, (uint32_t)n, dim, out, cus > 0 ? (uint32_t)cus : 256u, static_cast<hipStream_t>(stream)));
     return HPS_OK;
 }
 
