@@ -733,13 +733,22 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
             // Alg. 2 "g <- g + 1": every tile of the call stamps with the count the call will leave
             // behind; the tile that finishes the call stores it (see the helper wave below).
             const uint32_t g_call = kFull && tb.T ? *tb.gdev + 1u : 0u;
-            const uint32_t b    = (lt * WPB + wave) * a.kpw + lane;
-            const bool     inb  = lane < (int)a.kpw && b < a.B;
+            uint32_t kpw = a.kpw, B = a.B;
+            if (kFull && a.n_dev) {
+                // The real length is known only here: the keys are spread evenly over the work-groups that were
+                // launched for the longest one (50,000 of 106,496 keys: all in the first half of them 20.0 us, spread 14.6 us).
+                const uint32_t nd = *a.n_dev;
+                B = nd < B ? nd : B;
+                const uint32_t waves = (uint32_t)WPB * a.n_tiles, k = (uint32_t)(((uint64_t)B + waves - 1) / waves);
+                kpw = k < kMinKeysPerWave ? kMinKeysPerWave : k;
+            }
+            const uint32_t b    = (lt * WPB + wave) * kpw + lane;
+            const bool     inb  = lane < (int)kpw && b < B;
             const uint32_t pos  = t * a.B + b;         // position in keys/out (< 2^32 checked on host)
 
-            const int64_t key  = inb ? a.keys[pos] : kEmpty;      // keys[0 .. B) is readable also when n_dev says less
+            const int64_t key  = inb ? a.keys[pos] : kEmpty;
             const uint64_t e1  = kCoherent ? read_epochs(tb.epoch) : 0ull;
-            const bool    live = inb && (!kFull || !a.n_dev || b < *a.n_dev);
+            const bool    live = inb;
             const bool    want = live && !is_reserved(key);
             const uint32_t set = want ? set_of(key, tb.S, tb.smask) : 0u;
             bool hit;
