@@ -56,7 +56,7 @@ hps_status_t hps_dedup(hps_dedup_t *s, const int64_t *keys, size_t n, int64_t *u
  * serving loops, harnesses that forbid allocation.  Same arguments and results as hps_dedup, but
  * no session: the hash table lives in a static device array of the library (3 MiB per GPU, held
  * until the process ends), so the call allocates and frees nothing (no hipMalloc, no hipFree, no
- * allocating library routine); it only launches three kernels on `stream`.  At most
+ * allocating library routine); it only launches two kernels on `stream`.  At most
  * HPS_DEDUP_NOALLOC_MAX keys per call: a larger n returns HPS_ERR_INVALID_ARG and launches
  * nothing.  Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (on
  * different streams, or from different threads without ordering) race and must be ordered by the
