@@ -18,6 +18,7 @@
 
 #include <atomic>
 #include <climits>
+#include <cstddef>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -199,11 +200,14 @@ __device__ __forceinline__ void writer_leave(const Table &tb, WriterGroup *w, bo
         __hip_atomic_fetch_add(epoch_of(tb, blockIdx.x) + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Division of a list of rows of C chunks into wave loads of 64 chunks.
+// Division of a list of rows of C chunks into wave loads of 64 chunks.  Packed, so that a query's scalar
+// arguments stay within two 64-byte lines.
 struct ChunkStep {
     uint32_t C;                // chunks per row
-    uint32_t inv;              // (lane * inv) >> 16 == lane / C for lane < 64
-    uint32_t rows, rest;       // 64 / C, 64 mod C
+    uint32_t packed;           // bits 0-16: inv, (lane * inv) >> 16 == lane / C for lane < 64; 17-23: 64 / C; 24-30: 64 mod C
+    __host__ __device__ __forceinline__ uint32_t inv() const { return packed & 0x1FFFFu; }
+    __host__ __device__ __forceinline__ uint32_t rows() const { return (packed >> 17) & 0x7Fu; }
+    __host__ __device__ __forceinline__ uint32_t rest() const { return packed >> 24; }
 };
 
 // Row geometry shared by all copy loops: a row is C = d/4 chunks of 16 bytes; LPR lanes
@@ -224,12 +228,12 @@ struct RowGeom {
 struct ChunkWalk {
     uint32_t r, c;
     __device__ __forceinline__ ChunkWalk(const ChunkStep &s, uint32_t lane) {
-        r = (lane * s.inv) >> 16;
+        r = (lane * s.inv()) >> 16;
         c = lane - r * s.C;
     }
     __device__ __forceinline__ void next(const ChunkStep &s) {
-        r += s.rows;
-        c += s.rest;
+        r += s.rows();
+        c += s.rest();
         if (c >= s.C) {
             c -= s.C;
             ++r;
@@ -655,6 +659,7 @@ struct QueryArgs {
     RowGeom        g;
     Table          tab[HPS_MAX_TABLES];
 };
+static_assert(offsetof(QueryArgs, tab) == 128, "two lines of scalars");
 
 // Kernel arguments are read with scalar loads where they are first used, each followed by its own
 // wait; spread over several cache lines and basic blocks that put three to five dependent
@@ -1568,7 +1573,8 @@ RowGeom make_geom(uint32_t d) {
     g.LPR8 = lpr;
     g.lpr8Shift = sh;
     auto step = [](uint32_t C) {               // lane * (inv * C - 2^16) < 2^16 for lane, C <= 64: the quotient is exact
-        return ChunkStep{C, C > (uint32_t)kWave ? 0u : (65536u + C - 1) / C, (uint32_t)kWave / C, (uint32_t)kWave % C};
+        const uint32_t inv = C > (uint32_t)kWave ? 0u : (65536u + C - 1) / C;
+        return ChunkStep{C, inv | ((uint32_t)kWave / C) << 17 | ((uint32_t)kWave % C) << 24};
     };
     g.c16 = step(g.C);
     g.c8 = step(d / 2);
@@ -1666,7 +1672,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // over the CUs (106,496 keys in tiles of 8 x 52 are exactly 256 work-groups; tiles of 8 x 64 would be
 // 208, leaving 48 CUs idle).  Small batches go down to 16 keys per wave (8 below 4,096 keys): more
 // work-groups, each with a shorter chain of dependent row copies (1,664 keys: 5.5 us instead of 8.3 us;
-// 13,312 keys: 8.9 instead of 11.1 us).
+// 13,312 keys: 8.9 instead of 11.1 us).  With several tables the keys per wave go up as long as the tables'
+// last, partly empty tiles would start another round (26 x 1,024 keys checked 16.1 -> 11.2, 26 x 4,096 plain 20.9 -> 18.9).
 //
 // Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
 // first group's stores), and not much more, because the registers of a larger group are waves that
@@ -1677,7 +1684,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // 46.6: there the second work-group that fits a CU with the smaller group is worth more.
 struct QueryShape { uint32_t kpw; int u, wpb; };
 
-QueryShape query_shape(uint64_t n, uint32_t d, uint64_t cus, bool coherent, bool dedup) {
+QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup) {
+    const uint64_t n = n_tables * batch;
     QueryShape q{(uint32_t)kWave, 0, 0};
     if (coherent) q.wpb = n * d < (1u << 22) ? 4 : 7;
     else if (n < (1u << 14)) q.wpb = 4;
@@ -1689,6 +1697,9 @@ QueryShape query_shape(uint64_t n, uint32_t d, uint64_t cus, bool coherent, bool
     if (rounds > 0 && rounds <= 8) {
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
         if (k < floor_k) k = floor_k;
+        // a tile holds keys of one table: with several tables their last tiles are not full
+        auto tiles = [&] { return n_tables * ((batch + q.wpb * k - 1) / (q.wpb * k)); };
+        while (n_tables > 1 && k < (uint64_t)kWave && tiles() > rounds * cus) ++k;
         if (k < (uint64_t)kWave) q.kpw = (uint32_t)k;
     }
     const uint64_t bytes = (uint64_t)q.kpw * d * 4;            // a wave's rows
@@ -2032,7 +2043,7 @@ static hps_status_t query_call(hps_cache_t *const *caches, uint32_t n_tables, co
     bool coherent = false;                      // any table that may see concurrent writers makes the call careful
     for (uint32_t t = 0; t < n_tables; ++t) coherent = coherent || caches[t]->concurrent_writers.load() != 0;
     const bool dedup = !coherent && caches[0]->query_dedup.load() != 0;
-    const QueryShape shape = query_shape(total, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup);
+    const QueryShape shape = query_shape(n_tables, batch, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup);
     const uint32_t kpw = shape.kpw;
     a.kpw = kpw;
     const uint32_t tile = kpw * (uint32_t)shape.wpb;
