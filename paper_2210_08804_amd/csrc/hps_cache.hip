@@ -40,7 +40,6 @@ constexpr int      kBlock      = 256;          // threads per work-group: 4 wave
 constexpr int      kWave       = 64;
 constexpr int      kWavesPerWg = kBlock / kWave;
 constexpr uint32_t kMinKeysPerWave = 8;        // fewest keys that a query gives a worker wave
-constexpr int      kInsertKpw  = 16;           // keys per wave of the insert kernel
 constexpr uint32_t kRing       = 1024;         // counter words per half of the pool (see counter_word)
 constexpr uint64_t kMagic      = 0x4850534341434845ull;
 // Every loop that waits for another kernel's writer to let go of a set gives up after this many
@@ -1054,8 +1053,8 @@ struct WriteArgs {
 // holds its sets; the owners' rows are therefore requested right behind their sets' keys, before it is known
 // whether they are needed (a key that is already there has usually been found by the search without
 // owning): 2^18 new rows of 512 bytes, inserted, updated and queried, 221 -> 208 us, 32,768 rows 18.5 -> 16.8 us per
-// insert.  KPW = 16: four times as many waves as keys / 64 share the row copies, and a wave's chain is two
-// copy groups long instead of eight.
+// insert.  KPW = 16 or 8 (launch_write): four or eight times as many waves as keys / 64 share the row copies, and a
+// wave's chain is two copy groups long, or one, instead of eight.
 template <int W, int KPW, bool kLong>
 __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
@@ -1794,11 +1793,12 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     a.n_dev = n_dev;
     a.n = (uint32_t)n;
     a.g = make_geom(c->d);
-    // insert: 16 keys per wave while 64 would leave fewer than 8 waves per CU
-    // insert: 16 keys per wave (measured best from 1 K to 1 M keys: 8, 32 and 64 are 3-45 % slower)
-    // update: 64 keys per wave, 16 for batches below 32,768 keys (measured: 8,192 rows 16 us instead
-    // of 23 us, equal at 45,056, 8-18 % slower from 65,536 rows up and 9-55 % on a 40 GB refresh)
-    const uint32_t kpw = kInsert ? (uint32_t)kInsertKpw : (n < 32768 ? 16u : (uint32_t)kWave);
+    // Insert: 16 keys per wave, 8 while 4,096 waves (four per SIMD) hold the batch that way: 8,192 rows 12.1 -> 9.7 us,
+    // 32,768 rows 16.8 -> 15.7; with 8 throughout the 425,984-key streaming step takes 166 instead of 149 us.
+    // (32 and 64 are 3-45 % slower than 16 from 1 K to 1 M keys.)
+    // Update: 64 keys per wave, 8 for batches below 32,768 keys: 1,024 rows in 8s / 16s 10.6 / 11.5 us, 8,192 rows 13.4 /
+    // 14.1 (64s: 23); from 65,536 rows up 64 is 8-18 % faster than 16, on a 40 GB refresh 9-55 %.
+    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n < 32768 ? 8u : (uint32_t)kWave);
     const uint64_t tiles = (n + kpw - 1) / kpw;
     uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
     if (blocks > (1u << 16)) blocks = 1u << 16;
@@ -1809,11 +1809,13 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
 #define HPS_CASE(w)                                                                         \
     case w:                                                                                 \
         if (kInsert) {                                                                      \
-            if (lng) HPS_LAUNCH(insert_kernel<w, kInsertKpw, true>);                        \
-            else HPS_LAUNCH(insert_kernel<w, kInsertKpw, false>);                           \
-        } else if (kpw == 16) {                                                             \
-            if (lng) HPS_LAUNCH(update_kernel<w, 16, true>);                                \
-            else HPS_LAUNCH(update_kernel<w, 16, false>);                                   \
+            if (kpw == 8 && lng) HPS_LAUNCH(insert_kernel<w, 8, true>);                     \
+            else if (kpw == 8) HPS_LAUNCH(insert_kernel<w, 8, false>);                      \
+            else if (lng) HPS_LAUNCH(insert_kernel<w, 16, true>);                           \
+            else HPS_LAUNCH(insert_kernel<w, 16, false>);                                   \
+        } else if (kpw == 8) {                                                              \
+            if (lng) HPS_LAUNCH(update_kernel<w, 8, true>);                                 \
+            else HPS_LAUNCH(update_kernel<w, 8, false>);                                    \
         } else {                                                                            \
             if (lng) HPS_LAUNCH(update_kernel<w, 64, true>);                                \
             else HPS_LAUNCH(update_kernel<w, 64, false>);                                   \
