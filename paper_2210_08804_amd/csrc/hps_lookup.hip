@@ -69,17 +69,18 @@ struct hps_lookup_session {
     hps_dedup_t *dd;          // dedup of the miss list before it leaves the device (Sec. 2.2)
     hps_dedup_t *dd_bg;       // the same for the background thread (its calls run on the side stream)
     // workspace (the paper's ws): device side
-    uint32_t *d_miss_idx, *d_n_miss, *d_inv, *d_n_unique;
+    uint32_t *d_miss_idx, *d_inv;
     int64_t  *d_miss_keys, *d_ukeys;
     float    *d_rows, *d_default;
-    // pinned host side
-    uint32_t *h_n_miss, *h_n_unique;
+    // pinned host side; the counts are written there by the kernels themselves, through the words' device
+    // addresses (a copy of four bytes is a launch of its own)
+    uint32_t *h_n_miss, *h_n_unique, *d_n_miss, *d_n_unique;
     int64_t  *h_ukeys;
     float    *h_rows;
     // background insertion
     hipStream_t side;
     int64_t  *bg_d_ukeys, *bg_d_keys, *bg_h_keys;
-    uint32_t *bg_d_inv, *bg_d_n_unique, *bg_h_n_unique;
+    uint32_t *bg_d_inv, *bg_h_n_unique, *bg_d_n_unique;
     float    *bg_d_rows, *bg_h_rows;
     std::thread worker;
     std::mutex mu;
@@ -164,7 +165,6 @@ void worker_main(hps_lookup_session *L) {
         if (e == hipSuccess &&
             hps_dedup(L->dd_bg, L->bg_d_keys, total, L->bg_d_ukeys, L->bg_d_inv, L->bg_d_n_unique, L->side) != HPS_OK)
             err = std::string("background dedup: ") + hps_dedup_last_error();
-        if (e == hipSuccess) e = hipMemcpyAsync(L->bg_h_n_unique, L->bg_d_n_unique, 4, hipMemcpyDeviceToHost, L->side);
         if (e == hipSuccess)
             e = hipMemcpyAsync(L->bg_h_keys, L->bg_d_ukeys, (size_t)total * sizeof(int64_t), hipMemcpyDeviceToHost, L->side);
         if (e == hipSuccess) e = hipStreamSynchronize(L->side);
@@ -192,10 +192,10 @@ void worker_main(hps_lookup_session *L) {
 void free_all(hps_lookup_session *L) {
     (void)hps_dedup_destroy(L->dd);
     (void)hps_dedup_destroy(L->dd_bg);
-    (void)hipFree(L->d_miss_idx); (void)hipFree(L->d_n_miss); (void)hipFree(L->d_inv); (void)hipFree(L->d_n_unique);
+    (void)hipFree(L->d_miss_idx); (void)hipFree(L->d_inv);
     (void)hipFree(L->d_miss_keys); (void)hipFree(L->d_ukeys); (void)hipFree(L->d_rows); (void)hipFree(L->d_default);
     (void)hipFree(L->bg_d_ukeys); (void)hipFree(L->bg_d_rows); (void)hipFree(L->bg_d_keys);
-    (void)hipFree(L->bg_d_inv); (void)hipFree(L->bg_d_n_unique); (void)hipHostFree(L->bg_h_n_unique);
+    (void)hipFree(L->bg_d_inv); (void)hipHostFree(L->bg_h_n_unique);
     (void)hipHostFree(L->h_n_miss); (void)hipHostFree(L->h_n_unique);
     (void)hipHostFree(L->h_ukeys); (void)hipHostFree(L->h_rows); (void)hipHostFree(L->bg_h_rows);
     (void)hipHostFree(L->bg_h_keys);
@@ -232,14 +232,15 @@ hps_status_t hps_lookup_create(hps_cache_t *cache, size_t max_batch, float hit_t
     hipError_t e = hipGetDevice(&L->device);
     auto dev = [&](void **p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
     auto pin = [&](void **p, size_t bytes) { if (e == hipSuccess) e = hipHostMalloc(p, bytes, hipHostMallocDefault); };
-    dev((void **)&L->d_miss_idx, nb * 4); dev((void **)&L->d_n_miss, 4); dev((void **)&L->d_inv, nb * 4);
-    dev((void **)&L->d_n_unique, 4);
+    dev((void **)&L->d_miss_idx, nb * 4); dev((void **)&L->d_inv, nb * 4);
     dev((void **)&L->d_miss_keys, nb * 8); dev((void **)&L->d_ukeys, nb * 8); dev((void **)&L->d_rows, nb * rowb);
     dev((void **)&L->d_default, rowb); dev((void **)&L->bg_d_ukeys, nb * 8); dev((void **)&L->bg_d_rows, nb * rowb);
     pin((void **)&L->h_n_miss, 4); pin((void **)&L->h_n_unique, 4);
     pin((void **)&L->h_ukeys, nb * 8); pin((void **)&L->h_rows, nb * rowb); pin((void **)&L->bg_h_rows, nb * rowb);
     pin((void **)&L->bg_h_keys, nb * 8); pin((void **)&L->bg_h_n_unique, 4);
-    dev((void **)&L->bg_d_keys, nb * 8); dev((void **)&L->bg_d_inv, nb * 4); dev((void **)&L->bg_d_n_unique, 4);
+    dev((void **)&L->bg_d_keys, nb * 8); dev((void **)&L->bg_d_inv, nb * 4);
+    auto seen = [&](uint32_t **d, uint32_t *h) { if (e == hipSuccess) e = hipHostGetDevicePointer((void **)d, h, 0); };
+    seen(&L->d_n_miss, L->h_n_miss); seen(&L->d_n_unique, L->h_n_unique); seen(&L->bg_d_n_unique, L->bg_h_n_unique);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&L->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMemcpy(L->d_default, default_row, rowb, hipMemcpyHostToDevice);
     {
@@ -292,7 +293,6 @@ hps_status_t hps_lookup(hps_lookup_t *L, const int64_t *keys, size_t n, float *o
     // EmbCacheLookup(Q): hits land in out, misses in the workspace
     if (hps_cache_query(L->cache, keys, n, out, L->d_miss_idx, L->d_miss_keys, L->d_n_miss, st) != HPS_OK)
         return lfail(HPS_ERR_INVALID_ARG, std::string("query: ") + hps_last_error());
-    LK_TRY(hipMemcpyAsync(L->h_n_miss, L->d_n_miss, 4, hipMemcpyDeviceToHost, st));
     LK_TRY(hipStreamSynchronize(st));
     const uint32_t m = *L->h_n_miss;
     const float rate = 1.0f - (float)m / (float)n;
@@ -306,7 +306,6 @@ hps_status_t hps_lookup(hps_lookup_t *L, const int64_t *keys, size_t n, float *o
         // distinct keys travel to the host; the map from miss-list entries to them stays here
         if (hps_dedup(L->dd, L->d_miss_keys, m, L->d_ukeys, L->d_inv, L->d_n_unique, st) != HPS_OK)
             return lfail(HPS_ERR_DEVICE, std::string("dedup: ") + hps_dedup_last_error());
-        LK_TRY(hipMemcpyAsync(L->h_n_unique, L->d_n_unique, 4, hipMemcpyDeviceToHost, st));
         LK_TRY(hipMemcpyAsync(L->h_ukeys, L->d_ukeys, (size_t)m * 8, hipMemcpyDeviceToHost, st));
         LK_TRY(hipStreamSynchronize(st));
         const uint32_t u = *L->h_n_unique;
