@@ -1796,9 +1796,10 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     // Insert: 16 keys per wave, 8 while 4,096 waves (four per SIMD) hold the batch that way: 8,192 rows 12.1 -> 9.7 us,
     // 32,768 rows 16.8 -> 15.7; with 8 throughout the 425,984-key streaming step takes 166 instead of 149 us.
     // (32 and 64 are 3-45 % slower than 16 from 1 K to 1 M keys.)
-    // Update: 64 keys per wave, 8 for batches below 32,768 keys: 1,024 rows in 8s / 16s 10.6 / 11.5 us, 8,192 rows 13.4 /
-    // 14.1 (64s: 23); from 65,536 rows up 64 is 8-18 % faster than 16, on a 40 GB refresh 9-55 %.
-    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n < 32768 ? 8u : (uint32_t)kWave);
+    // Update: 64 keys per wave, 16 for batches below 32,768 keys: 8,192 rows 14.1 us (64s: 23, 8s: 13.4, but a dump's
+    // keys come eight to a set, and 8s split sets between waves: dump + update + query of 28,000 rows of 256
+    // bytes 28.6 instead of 26.0); from 65,536 rows up 64 is 8-18 % faster than 16, on a 40 GB refresh 9-55 %.
+    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n < 32768 ? 16u : (uint32_t)kWave);
     const uint64_t tiles = (n + kpw - 1) / kpw;
     uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
     if (blocks > (1u << 16)) blocks = 1u << 16;
@@ -1813,9 +1814,9 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
             else if (kpw == 8) HPS_LAUNCH(insert_kernel<w, 8, false>);                      \
             else if (lng) HPS_LAUNCH(insert_kernel<w, 16, true>);                           \
             else HPS_LAUNCH(insert_kernel<w, 16, false>);                                   \
-        } else if (kpw == 8) {                                                              \
-            if (lng) HPS_LAUNCH(update_kernel<w, 8, true>);                                 \
-            else HPS_LAUNCH(update_kernel<w, 8, false>);                                    \
+        } else if (kpw == 16) {                                                             \
+            if (lng) HPS_LAUNCH(update_kernel<w, 16, true>);                                \
+            else HPS_LAUNCH(update_kernel<w, 16, false>);                                   \
         } else {                                                                            \
             if (lng) HPS_LAUNCH(update_kernel<w, 64, true>);                                \
             else HPS_LAUNCH(update_kernel<w, 64, false>);                                   \
