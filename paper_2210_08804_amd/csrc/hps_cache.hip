@@ -733,7 +733,8 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
         const uint32_t lt = tile - t * a.tiles_per_table;
         if (wave < WPB) {
             const Table   &tb   = a.tab[t];
-            HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc), "s"(tb.epoch));
+            if (kCoherent) HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc), "s"(tb.epoch));
+            else           HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc));
             // Alg. 2 "g <- g + 1": every tile of the call stamps with the count the call will leave
             // behind; the tile that finishes the call stores it (see the helper wave below).
             const uint32_t g_call = kFull && tb.T ? *tb.gdev + 1u : 0u;
@@ -1664,8 +1665,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // Rows of up to 128 bytes leave registers for 16 waves in two work-groups per CU and are bound by the
 // counter atomics and by the number of keys in flight: 15 workers 42.9, 7 workers 44.5 at 851,968 keys of
 // 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7.
-// Checked (4 / 7 workers): 26,624 keys of 512 bytes 11.9 / 11.9, 39,936 keys 12.8 / 12.6, 26,624 keys of 2 KiB
-// 24.0 / 20.3, 106,496 keys of 128 bytes 14.2 / 11.6; small batches as above.
+// Checked (4 / 7 workers): 5,000 keys of 512 bytes 7.2 / 7.7, 8,192 keys 7.9 / 8.0, 13,312 keys 9.0 / 8.6, of 256 bytes
+// 8.8 / 8.3, 26,624 keys of 128 bytes 9.3 / 9.0, 106,496 keys of 128 bytes 14.2 / 11.6.
 //
 // Keys per wave: at most 64, trimmed so that the work-groups come out as a whole number of rounds
 // over the CUs (106,496 keys in tiles of 8 x 52 are exactly 256 work-groups; tiles of 8 x 64 would be
@@ -1675,18 +1676,20 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // last, partly empty tiles would start another round (26 x 1,024 keys checked 16.1 -> 11.2, 26 x 4,096 plain 20.9 -> 18.9).
 //
 // Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
-// first group's stores), and not much more, because the registers of a larger group are waves that
-// the CU cannot hold: 64 keys of 128 bytes in groups of 8 / 16 / 32 wave loads take 44.5 / 50.0 / 63.7 per 851,968
-// keys, 39,999 keys of 1,280 bytes in groups of 24 / 16 with idle lanes 19.4 / 24.1, 26,624 keys of 512
-// bytes in groups of 13 / 26 9.7 / 10.6.  Checked, 8 bytes per lane: 106,496 keys of 384 bytes in groups of 64 / 32 / 16
-// 17.0 / 18.4 / 19.1, of 256 bytes in groups of 32 / 16 13.9 / 15.3; but over several rounds (425,984 keys) 51.4 /
-// 46.6: there the second work-group that fits a CU with the smaller group is worth more.
+// first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
+// hold, and its code, all of it executed, lines that a short launch has to fetch.  64 keys of 128 bytes in groups
+// of 8 / 16 / 32 wave loads take 44.5 / 50.0 / 63.7 per 851,968 keys, 39,999 keys of 1,280 bytes in groups of 24 / 16
+// with idle lanes 19.4 / 24.1, 26,624 keys of 512 bytes in groups of 13 / 26 9.7 / 10.6.  Checked, 8 bytes per lane, rows
+// of 512 bytes: 832 keys in groups of 8 / 64 6.2 / 7.8, 13,312 keys 16 / 64 8.6 / 10.8, 26,624 keys 32 / 64 10.5 / 12.0,
+// 56,000 keys 32 / 64 13.0 / 13.6; 106,496 keys of 384 bytes in groups of 64 / 32 / 16 17.0 / 18.4 / 19.1, of 256
+// bytes in groups of 32 / 16 13.9 / 15.3; but over several rounds (425,984 keys) 51.4 / 46.6: there the second
+// work-group that fits a CU with the smaller group is worth more.
 struct QueryShape { uint32_t kpw; int u, wpb; };
 
 QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup) {
     const uint64_t n = n_tables * batch;
     QueryShape q{(uint32_t)kWave, 0, 0};
-    if (coherent) q.wpb = n * d < (1u << 22) ? 4 : 7;
+    if (coherent) q.wpb = n < 10240 ? 4 : 7;
     else if (n < (1u << 14)) q.wpb = 4;
     else if (n < (1u << 18) || dedup) q.wpb = 8;
     else q.wpb = d <= 32 ? 15 : 7;
@@ -1703,12 +1706,14 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     }
     const uint64_t bytes = (uint64_t)q.kpw * d * 4;            // a wave's rows
     if (coherent) {
-        if (d == 128 || bytes > 16384) q.u = 64;
+        if (d == 128 && q.wpb == 4) q.u = q.kpw <= 8 ? 8 : 16;
+        else if (d == 128) q.u = q.kpw <= 16 ? 16 : q.kpw <= 32 ? 32 : 64;
+        else if (bytes > 16384) q.u = 64;
         else q.u = bytes <= 8192 || rounds > 1 ? 16 : 32;
     } else if (d == 128) {
-        q.u = q.wpb == 7 ? 32 : bytes <= 13312 ? 13 : 26;
+        q.u = q.wpb == 7 ? 32 : q.kpw <= 16 ? 8 : q.kpw <= 26 && q.wpb == 8 ? 13 : 26;
     } else {
-        q.u = bytes <= 8192 ? 8 : bytes <= 16384 ? 16 : q.wpb == 8 ? 24 : 32;
+        q.u = bytes <= 8192 && q.wpb != 7 ? 8 : bytes <= 16384 ? 16 : q.wpb == 8 ? 24 : 32;
     }
     return q;
 }
@@ -1736,7 +1741,10 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
         else launch_query_dedup<W, 8>(a, st);
     } else if (coherent) {
         switch (d128 ? 10000 + id : id) {
-            case 16404: launch_query_kernel<W, 64, 4, true, 128>(a, full, st); break;
+            case 10804: launch_query_kernel<W, 8, 4, true, 128>(a, full, st); break;
+            case 11604: launch_query_kernel<W, 16, 4, true, 128>(a, full, st); break;
+            case 11607: launch_query_kernel<W, 16, 7, true, 128>(a, full, st); break;
+            case 13207: launch_query_kernel<W, 32, 7, true, 128>(a, full, st); break;
             case 16407: launch_query_kernel<W, 64, 7, true, 128>(a, full, st); break;
             case 1604: launch_query_kernel<W, 16, 4, true, 0>(a, full, st); break;
             case 3204: launch_query_kernel<W, 32, 4, true, 0>(a, full, st); break;
@@ -1748,8 +1756,9 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
         }
     } else {
         switch (d128 ? 10000 + id : id) {
-            case 11304: launch_query_kernel<W, 13, 4, false, 128>(a, full, st); break;
+            case 10804: launch_query_kernel<W, 8, 4, false, 128>(a, full, st); break;
             case 12604: launch_query_kernel<W, 26, 4, false, 128>(a, full, st); break;
+            case 10808: launch_query_kernel<W, 8, 8, false, 128>(a, full, st); break;
             case 11308: launch_query_kernel<W, 13, 8, false, 128>(a, full, st); break;
             case 12608: launch_query_kernel<W, 26, 8, false, 128>(a, full, st); break;
             case 13207: launch_query_kernel<W, 32, 7, false, 128>(a, full, st); break;

@@ -42,7 +42,8 @@ def test_row_widths(d, checked):
 
 @pytest.mark.parametrize("checked", [False, True])
 @pytest.mark.parametrize("d,n", [(16, (1 << 14) - 1), (16, 1 << 14), (16, (1 << 18) + 3), (32, (1 << 17) + 1), (32, 270001), (64, (1 << 16) + 7),
-                                 (64, 270001), (96, 43691), (160, 20001), (128, 32768), (128, 32767), (256, 16384), (320, 13107), (320, 60001)])
+                                 (64, 270001), (96, 43691), (160, 20001), (128, 4095), (128, 4097), (128, 10239), (128, 10240), (128, 28673),
+                                 (128, 57345), (128, 16385), (256, 16384), (320, 13107), (320, 60001)])
 def test_shapes_by_batch_and_width(d, n, checked):
     """Both sides of every line between two launch shapes."""
     S, W, n_keys = 8191, 8, 4000

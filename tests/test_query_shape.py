@@ -1,0 +1,51 @@
+"""Every launch shape that the query's rule can choose is one that the dispatch has a kernel for: the rule is
+taken from the source and compiled for the host, the shapes are compared with the dispatch's labels."""
+import os
+import re
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "paper_2210_08804_amd", "csrc", "hps_cache.hip")
+
+MAIN = """
+int main() {
+    for (uint64_t cus : {256ull, 128ull, 38ull, 32ull, 1ull})
+        for (uint32_t t : {1u, 3u, 26u, 32u})
+            for (int mode = 0; mode < 3; ++mode)                       // plain, checked, in-tile dedup
+                for (uint32_t d = 4; d <= 2048; d += d < 160 ? 4 : d / 8 / 4 * 4)
+                    for (double x = 0; x < 32; x += 0.1)
+                        for (int o = -1; o < 2; ++o) {
+                            const uint64_t batch = (uint64_t)(__builtin_exp2(x) / t) + 1 + o;
+                            if (batch * t >= (1ull << 32) || (mode == 1 && d > 1024)) continue;
+                            const QueryShape q = query_shape(t, batch, d, cus, mode == 1, mode == 2);
+                            const int id = (d == 128 ? 10000 : 0) + q.u * 100 + q.wpb;
+                            if (q.kpw < 1 || q.kpw > 64) { std::printf("kpw %u\\n", q.kpw); return 1; }
+                            if (mode == 2 ? (q.wpb != 4 && q.wpb != 8) : !kShapes[mode].count(id)) {
+                                std::printf("mode %d d %u batch %llu tables %u cus %llu: shape %d\\n", mode, d, (unsigned long long)batch, t, (unsigned long long)cus, id);
+                                return 1;
+                            }
+                            if (mode == 1 && (uint64_t)q.u * 64 < d / 2) { std::printf("a row of %u does not fit a group of %d\\n", d, q.u); return 1; }
+                        }
+    return 0;
+}
+"""
+
+
+def test_every_shape_is_compiled_in(tmp_path):
+    with open(SRC) as f:
+        s = f.read()
+    rule = s[s.index("struct QueryShape {"):s.index("template <int W, int U, int WPB, bool kCoherent, int kD>\nvoid launch_query_kernel")]
+    dispatch = s[s.index("hps_status_t launch_query_w("):s.index("hps_status_t launch_query(uint32_t W")]
+    shapes = {"false": set(), "true": set()}
+    for label, u, wpb, checked, d in re.findall(r"case (\d+): launch_query_kernel<W, (\d+), (\d+), (true|false), (\d+)>", dispatch):
+        assert int(label) == (10000 if d == "128" else 0) + int(u) * 100 + int(wpb)
+        shapes[checked].add(int(label))
+    assert shapes["false"] and shapes["true"]
+    sets = ", ".join("{" + ", ".join(map(str, sorted(shapes[k]))) + "}" for k in ("false", "true"))
+    src = tmp_path / "shapes.cpp"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <set>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
+                   + "const std::set<int> kShapes[2] = {" + sets + "};\n" + rule + MAIN)
+    exe = tmp_path / "shapes"
+    subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
