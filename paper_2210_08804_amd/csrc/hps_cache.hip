@@ -9,6 +9,7 @@
 //                          (together so that an insert gets both with its one 64-bit atomic and
 //                          lets go of both with one store; every read is a 128-byte request)
 //   T   uint32 [S][W]      access stamps, only for caches created with the LRU policy
+//   epoch uint32 [16][64]  16 lines of {started, finished}: writer work-groups counted in and out
 //
 // Paper passages: data model Sec. 4.1; Query Alg. 2; Replace Alg. 3; Update Alg. 4; Dump and
 // the asynchronous, batch-in calling convention Sec. 4.2.  The paper's per-slabset warp lock
