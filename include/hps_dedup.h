@@ -15,8 +15,10 @@
  *
  * Pointers named "device" are GPU addresses on the session's device; keys 8-byte, rows 16-byte,
  * index arrays 4-byte aligned.  Every call is asynchronous on `stream` (a hipStream_t passed as
- * void*, NULL = the null stream).  A session owns its scratch table: calls on one session must
- * not overlap (order them on one stream or with events); different sessions are independent.
+ * void*, NULL = the null stream).  A session owns its scratch tables: calls on one session must
+ * not overlap (order them on one stream or with events), and that goes for replays of graphs
+ * captured from calls on it, one with the other; different sessions are independent.  Calls that
+ * overlap all the same end, with results that are undefined and perhaps a flag (hps_dedup_flags).
  * Status codes and hps_status_t are those of hps_cache.h; the message of the last failing call
  * of this header on the calling thread is returned by hps_dedup_last_error().
  */
@@ -60,10 +62,27 @@ hps_status_t hps_dedup(hps_dedup_t *s, const int64_t *keys, size_t n, int64_t *u
  * HPS_DEDUP_NOALLOC_MAX keys per call: a larger n returns HPS_ERR_INVALID_ARG and launches
  * nothing.  Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (on
  * different streams, or from different threads without ordering) race and must be ordered by the
- * caller; calls on one stream are ordered.  The current device is the one the call works on. */
+ * caller (see hps_dedup_flags); calls on one stream are ordered.  The current device is the one the call works on. */
 #define HPS_DEDUP_NOALLOC_MAX 131072u
 hps_status_t hps_dedup_noalloc(const int64_t *keys, size_t n, int64_t *unique_keys, uint32_t *inverse,
                                uint32_t *n_unique, void *stream);
+
+/*
+ * Flag word of a session, raised by kernels; s = NULL: of hps_dedup_noalloc on the current device.
+ * HPS_DEDUP_FLAG_STUCK: a kernel waited about 0.1 s for the number of a key that another of its
+ * work-groups had listed, or found its table full, and gave up: the inverse map is 0 at that key's
+ * positions.  Only calls that overlap on one table (a caller's mistake) get there.  *flags [host]
+ * receives the bits; clear != 0 resets them.  Synchronous on the host; call it after
+ * synchronising the streams whose work is to be covered.
+ */
+#define HPS_DEDUP_FLAG_STUCK 1u
+hps_status_t hps_dedup_flags(hps_dedup_t *s, uint32_t *flags, int clear);
+
+/*
+ * Test hook (host-synchronous): in the table that the session's next call works on, if it is one
+ * of n keys, list `key` as a work-group that never gets to its number would.
+ */
+hps_status_t hps_dedup_debug_claim(hps_dedup_t *s, int64_t key, size_t n);
 
 /* out[i] = rows[inverse[i]] for i < n: the step after the lookup of Q* (Sec. 2.2).
  *   rows    device, [u][dim] 32-bit words, read only; every inverse[i] must be < u (not checked)

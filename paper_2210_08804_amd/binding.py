@@ -21,6 +21,7 @@ HPS_MAX_TABLES = 32
 HPS_POLICY_VICTIM_COUNTER = 0
 HPS_POLICY_LRU = 1
 HPS_FLAG_STUCK_SET = 1
+HPS_DEDUP_FLAG_STUCK = 1
 
 EXPORTS = (
     "hps_cache_create", "hps_cache_destroy", "hps_cache_query", "hps_cache_insert",
@@ -32,7 +33,7 @@ EXPORTS = (
     "hps_lookup_create", "hps_lookup", "hps_lookup_drain", "hps_lookup_destroy", "hps_lookup_last_error",
     "hps_cache_refresh", "hps_refresh_create", "hps_refresh_run", "hps_refresh_destroy",
     "hps_dedup_create", "hps_dedup_destroy", "hps_dedup", "hps_expand_rows", "hps_dedup_last_error",
-    "hps_dedup_noalloc",
+    "hps_dedup_noalloc", "hps_dedup_flags", "hps_dedup_debug_claim",
     "hps_hostmap_create", "hps_hostmap_destroy", "hps_hostmap_put", "hps_hostmap_get", "hps_hostmap_fetch",
     "hps_hostmap_stats",
     "hps_membench_gather", "hps_membench_gather_half", "hps_membench_copy",
@@ -86,6 +87,8 @@ def load_library():
         "hps_dedup_destroy": [vp],
         "hps_dedup": [vp, vp, sz, vp, vp, vp, vp],
         "hps_dedup_noalloc": [vp, sz, vp, vp, vp, vp],
+        "hps_dedup_flags": [vp, C.POINTER(u32), C.c_int],
+        "hps_dedup_debug_claim": [vp, C.c_int64, sz],
         "hps_expand_rows": [vp, vp, sz, u32, vp, vp],
         "hps_hostmap_create": [u32, u32, sz, C.POINTER(vp)],
         "hps_hostmap_destroy": [vp],
@@ -381,6 +384,17 @@ def hps_dedup_noalloc(keys, n, unique_keys, inverse, n_unique, stream=None) -> N
     _check_dedup(load_library().hps_dedup_noalloc(
         _ptr(keys, torch.int64), n, _ptr(unique_keys, torch.int64), _ptr(inverse, torch.int32),
         _ptr(n_unique, torch.int32), _stream(stream)))
+
+
+def hps_dedup_flags(session=None, clear: bool = False) -> int:
+    """Flag word of a session, or (None) of hps_dedup_noalloc on the current device."""
+    f = C.c_uint32()
+    _check_dedup(load_library().hps_dedup_flags(session, C.byref(f), 1 if clear else 0))
+    return f.value
+
+
+def hps_dedup_debug_claim(session, key: int, n: int) -> None:
+    _check_dedup(load_library().hps_dedup_debug_claim(session, key, n))
 
 
 def hps_expand_rows(rows, inverse, n, dim, out, stream=None) -> None:

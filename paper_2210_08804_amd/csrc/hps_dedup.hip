@@ -12,7 +12,9 @@
 //   unique_keys and their number beside the slot,
 //   reads the numbers of the keys that other work-groups claimed, and hands every position its number.
 // The last step waits for numbers that are not there yet.  Whoever claimed such a key is running, and
-// writes its numbers before it waits for anybody else's, so every wait ends.
+// writes its numbers before it waits for anybody else's, so every wait ends, provided that no other call works
+// on the table.  One that does (a caller's mistake) can take a number away again: the wait is therefore bounded
+// and ends with a flag (kMaxRounds).
 // Bound by the chain of dependent round trips (key, swap, counter, number).  Two launches, the second
 // looking every position up again, took 17.7 us for 106,496 keys (44 % distinct); this takes 12.1 us, 15.9 with a
 // load of the slot in front of each compare-and-swap (2,000 keys: 20.7, 12.0, 18.5).
@@ -35,6 +37,8 @@ constexpr int      kBlock = 256;
 constexpr uint32_t kSmallBatch = 32768;           // most keys that go in tiles of 512 (launch_dedup)
 constexpr uint64_t kMagic = 0x4850534445445550ull;
 constexpr uint32_t kNone  = 0xFFFFFFFFu;
+// Looks at a number that another work-group has to write, some 0.1 s of them; it is there after a few.
+constexpr uint32_t kMaxRounds = 1u << 16;
 
 // Scratch of hps_dedup_noalloc, the entry point for callers that cannot allocate: one hash table
 // for batches of up to kNaMaxKeys keys (2 slots per key, 8-byte key word + 4-byte number per
@@ -44,7 +48,8 @@ constexpr uint32_t kNaMaxKeys  = HPS_DEDUP_NOALLOC_MAX;
 constexpr uint32_t kNaSlots    = 2 * kNaMaxKeys;                        // a power of two
 constexpr size_t   kNaKeyBytes = (((size_t)kNaSlots + 1) * 8 + 255) / 256 * 256;
 constexpr size_t   kNaUidBytes = (((size_t)kNaSlots + 1) * 4 + 255) / 256 * 256;
-constexpr size_t   kNaBytes    = kNaKeyBytes + kNaUidBytes + 256;       // + the counter
+constexpr size_t   kNaBytes    = kNaKeyBytes + kNaUidBytes + 256;       // + the counter, + the flag word
+constexpr size_t   kFlagOffset = 64;                                    // of the flag word behind the (first) counter, in bytes
 static_assert((kNaSlots & (kNaSlots - 1)) == 0, "slot count must be a power of two");
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 
@@ -90,7 +95,7 @@ __global__ void set_u32_kernel(uint32_t *p, uint32_t v) { *p = v; }
 template <int kTile>                                                 // keys (= threads) per work-group
 __global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict__ keys, uint32_t n,
                                                       int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
-                                                      int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique,
+                                                      uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique,
                                                       int64_t *other_tkey, uint32_t *other_tuid, uint64_t other_dirty) {
     constexpr int kLds = 2 * kTile;                    // LDS table slots (load <= 0.5)
     __shared__ unsigned long long l_key[kLds];
@@ -129,13 +134,14 @@ __global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict_
             }
         }
         // the elected lane claims the key's slot of the global table, or finds that another tile has it
-        bool won = false;
+        bool won = false, listed = false;              // listed: another tile has the key's slot, its number is there or on its way
         uint32_t slot = 0u;
         if (elected) {
             if (key == kEmpty) {
                 slot = mask + 1u;
                 won = atomicCAS(reinterpret_cast<unsigned long long *>(tkey + slot),
                                 (unsigned long long)kEmpty, 0ull) == (unsigned long long)kEmpty;
+                listed = !won;
             } else {
                 slot = (uint32_t)h & mask;
                 for (uint32_t probe = 0; probe <= mask; ++probe) {      // the table is at most half full
@@ -143,7 +149,8 @@ __global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict_
                         atomicCAS(reinterpret_cast<unsigned long long *>(tkey + slot),
                                   (unsigned long long)kEmpty, (unsigned long long)key);
                     won = old == (unsigned long long)kEmpty;
-                    if (won || old == (unsigned long long)key) break;
+                    listed = old == (unsigned long long)key;
+                    if (won || listed) break;
                     slot = (slot + 1) & mask;
                 }
             }
@@ -172,9 +179,16 @@ __global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict_
         // compiler from making the two conditions the two sides of one branch, the waiting side first.)
         __syncthreads();
         if (elected && !won) {
-            uint32_t uid;
-            while ((uid = __hip_atomic_load(tuid + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kNone)
+            uint32_t uid = kNone;
+            for (uint32_t round = 0; listed && round < kMaxRounds; ++round) {
+                uid = __hip_atomic_load(tuid + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (uid != kNone) break;
                 __builtin_amdgcn_s_sleep(1);
+            }
+            if (uid == kNone) {                                       // no number came, or the table has no room: say so
+                __hip_atomic_fetch_or(flags, (uint32_t)HPS_DEDUP_FLAG_STUCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uid = 0u;                                             // a place that an expansion may read
+            }
             l_uid[ls] = uid;
         }
         __syncthreads();
@@ -198,7 +212,7 @@ struct hps_dedup_session {
     int64_t  *tkey[3];      // [slots + 1] each; a call works on tkey[cur] (0 or 1), which is all free;
                             // table 2 serves calls that are being captured into a graph (see hps_dedup)
     uint32_t *tuid[3];      // [slots + 1] each
-    uint64_t *counter;      // one word for each of the tables, zero between calls
+    uint64_t *counter;      // one word for each of the tables, zero between calls; kFlagOffset bytes on the flag word
     uint64_t  dirty[2];     // leading slots of each table that a call has written and nobody cleared yet
     int       cur;
     int       n_cus;
@@ -217,17 +231,34 @@ hps_status_t check_session(hps_dedup_session *s) {
 // Keys per work-group: 1024; 512 for batches that would leave most CUs without a work-group, whose lanes then share
 // LDS slots with half as many others (2,000 keys 7.7 -> 6.7 us, 16,000 9.1 -> 7.3, 32,000 9.3 -> 8.1, 65,000 equal).
 void launch_dedup(const int64_t *keys, uint32_t n, int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
-                  int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique, int64_t *other_tkey, uint32_t *other_tuid,
+                  uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique, int64_t *other_tkey, uint32_t *other_tuid,
                   uint64_t other_dirty, uint32_t max_blocks, hipStream_t st) {
     const uint32_t tile = n <= kSmallBatch ? 512u : 1024u;
     const uint64_t tiles = ((uint64_t)n + tile - 1) / tile;
     const dim3 grid((uint32_t)(tiles < max_blocks ? tiles : max_blocks)), block(tile);
     if (tile == 512u)
-        hipLaunchKernelGGL(dedup_kernel<512>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, unique_keys, inverse, n_unique,
+        hipLaunchKernelGGL(dedup_kernel<512>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
                            other_tkey, other_tuid, other_dirty);
     else
-        hipLaunchKernelGGL(dedup_kernel<1024>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, unique_keys, inverse, n_unique,
+        hipLaunchKernelGGL(dedup_kernel<1024>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
                            other_tkey, other_tuid, other_dirty);
+}
+
+uint32_t *flags_behind(uint64_t *counter) { return reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(counter) + kFlagOffset); }
+
+// The array of hps_dedup_noalloc on device dev.  The array's name is only a host-side stand-in: its device address is
+// asked for once per device (each GPU holds its own copy at its own address) and used from then on.
+hps_status_t noalloc_base(int dev, unsigned char **base) {
+    if (dev < 0 || dev >= kNaMaxDevices) return fail(HPS_ERR_INVALID_ARG, "device number beyond what hps_dedup_noalloc keeps track of");
+    std::lock_guard<std::mutex> lk(g_na_mu);
+    if (!g_na_ptr[dev]) {
+        void *p = nullptr;
+        HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
+        if (!p) return fail(HPS_ERR_DEVICE, "hipGetSymbolAddress returned no address for the scratch array");
+        g_na_ptr[dev] = static_cast<unsigned char *>(p);
+    }
+    *base = g_na_ptr[dev];
+    return HPS_OK;
 }
 
 uint64_t pow2_at_least(uint64_t x) {
@@ -269,6 +300,10 @@ hps_status_t hps_dedup_create(size_t max_n, hps_dedup_t **out) {
     for (int t = 0; t < 3 && e == hipSuccess; ++t) {
         hipLaunchKernelGGL(dedup_clear_kernel, dim3(4096), dim3(kBlock), 0, 0, s->tkey[t], s->tuid[t], s->slots + 1,
                            s->counter + t);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(1), 0, 0, flags_behind(s->counter), 0u);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(0);
@@ -333,13 +368,13 @@ hps_status_t hps_dedup(hps_dedup_t *s, const int64_t *keys, size_t n, int64_t *u
         const uint64_t cb = (slots + 1 + kBlock - 1) / kBlock;
         hipLaunchKernelGGL(dedup_clear_kernel, dim3((uint32_t)(cb < cap ? cb : cap)), dim3(kBlock), 0, q,
                            s->tkey[2], s->tuid[2], slots + 1, s->counter + 2);
-        launch_dedup(keys, (uint32_t)n, s->tkey[2], s->tuid[2], mask, s->counter + 2, unique_keys, inverse, n_unique,
+        launch_dedup(keys, (uint32_t)n, s->tkey[2], s->tuid[2], mask, s->counter + 2, flags_behind(s->counter), unique_keys, inverse, n_unique,
                      s->tkey[2], s->tuid[2], 0, cap, q);
         HIP_TRY(hipGetLastError());
         return HPS_OK;
     }
     const int t = s->cur, o = 1 - t;
-    launch_dedup(keys, (uint32_t)n, s->tkey[t], s->tuid[t], mask, s->counter + t, unique_keys, inverse, n_unique,
+    launch_dedup(keys, (uint32_t)n, s->tkey[t], s->tuid[t], mask, s->counter + t, flags_behind(s->counter), unique_keys, inverse, n_unique,
                  s->tkey[o], s->tuid[o], s->dirty[o], cap, q);
     HIP_TRY(hipGetLastError());
     s->dirty[t] = slots + 1;          // this call's slots, the extra one included
@@ -363,22 +398,10 @@ hps_status_t hps_dedup_noalloc(const int64_t *keys, size_t n, int64_t *unique_ke
     if (!keys || !unique_keys || !inverse) return fail(HPS_ERR_INVALID_ARG, "keys, unique_keys and inverse must not be NULL when n > 0");
     if (!aligned(keys, 8) || !aligned(unique_keys, 8) || !aligned(inverse, 4))
         return fail(HPS_ERR_INVALID_ARG, "keys and unique_keys must be 8-byte, inverse 4-byte aligned");
-    // The array's name is only a host-side stand-in: its device address is asked for once per
-    // device (each GPU holds its own copy at its own address) and used from then on.
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
-    if (dev < 0 || dev >= kNaMaxDevices) return fail(HPS_ERR_INVALID_ARG, "device number beyond what hps_dedup_noalloc keeps track of");
     unsigned char *base = nullptr;
-    {
-        std::lock_guard<std::mutex> lk(g_na_mu);
-        if (!g_na_ptr[dev]) {
-            void *p = nullptr;
-            HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-            if (!p) return fail(HPS_ERR_DEVICE, "hipGetSymbolAddress returned no address for the scratch array");
-            g_na_ptr[dev] = static_cast<unsigned char *>(p);
-        }
-        base = g_na_ptr[dev];
-    }
+    if (hps_status_t st = noalloc_base(dev, &base)) return st;
     int64_t  *tkey    = reinterpret_cast<int64_t *>(base);
     uint32_t *tuid    = reinterpret_cast<uint32_t *>(base + kNaKeyBytes);
     uint64_t *counter = reinterpret_cast<uint64_t *>(base + kNaKeyBytes + kNaUidBytes);
@@ -392,9 +415,49 @@ hps_status_t hps_dedup_noalloc(const int64_t *keys, size_t n, int64_t *unique_ke
     // are cleared first (by a kernel, so that the call can be captured into a graph).
     const uint64_t cb = (slots + 1 + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(dedup_clear_kernel, dim3((uint32_t)(cb < cap ? cb : cap)), dim3(kBlock), 0, q, tkey, tuid, slots + 1, counter);
-    launch_dedup(keys, (uint32_t)n, tkey, tuid, mask, counter, unique_keys, inverse, n_unique, tkey, tuid, 0, cap, q);
+    launch_dedup(keys, (uint32_t)n, tkey, tuid, mask, counter, flags_behind(counter), unique_keys, inverse, n_unique, tkey, tuid, 0, cap, q);
     HIP_TRY(hipGetLastError());
     return HPS_OK;
+}
+
+hps_status_t hps_dedup_flags(hps_dedup_t *s, uint32_t *flags, int clear) {
+    if (!flags) return fail(HPS_ERR_INVALID_ARG, "flags is NULL");
+    uint32_t *word = nullptr;
+    if (s) {
+        if (hps_status_t st = check_session(s)) return st;
+        word = flags_behind(s->counter);
+    } else {
+        int dev = -1;
+        HIP_TRY(hipGetDevice(&dev));
+        unsigned char *base = nullptr;
+        if (hps_status_t st = noalloc_base(dev, &base)) return st;
+        word = flags_behind(reinterpret_cast<uint64_t *>(base + kNaKeyBytes + kNaUidBytes));
+    }
+    HIP_TRY(hipMemcpy(flags, word, sizeof(uint32_t), hipMemcpyDeviceToHost));
+    const uint32_t zero = 0u;
+    if (clear) HIP_TRY(hipMemcpy(word, &zero, sizeof(uint32_t), hipMemcpyHostToDevice));
+    return HPS_OK;
+}
+
+hps_status_t hps_dedup_debug_claim(hps_dedup_t *s, int64_t key, size_t n) {
+    if (hps_status_t st = check_session(s)) return st;
+    if (n == 0 || n > s->max_n) return fail(HPS_ERR_INVALID_ARG, "n must be in 1 .. max_n");
+    const uint64_t mask = pow2_at_least(2 * (uint64_t)n) - 1;
+    int64_t *tkey = s->tkey[s->cur];
+    HIP_TRY(hipDeviceSynchronize());
+    if (key == kEmpty) {                               // its slot holds anything but the marker
+        const int64_t taken = 0;
+        HIP_TRY(hipMemcpy(tkey + mask + 1, &taken, sizeof(taken), hipMemcpyHostToDevice));
+        return HPS_OK;
+    }
+    for (uint64_t probe = 0, slot = mix64((uint64_t)key) & mask; probe <= mask; ++probe, slot = (slot + 1) & mask) {
+        int64_t there = 0;
+        HIP_TRY(hipMemcpy(&there, tkey + slot, sizeof(there), hipMemcpyDeviceToHost));
+        if (there != kEmpty) continue;
+        HIP_TRY(hipMemcpy(tkey + slot, &key, sizeof(key), hipMemcpyHostToDevice));
+        return HPS_OK;
+    }
+    return fail(HPS_ERR_INVALID_ARG, "the table has no free slot");
 }
 
 hps_status_t hps_expand_rows(const float *rows, const uint32_t *inverse, size_t n, uint32_t dim,

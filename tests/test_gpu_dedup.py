@@ -184,3 +184,38 @@ def test_bad_arguments():
         B.hps_dedup(dd.h, k, 100, uk, inv, nu)                            # still usable
         torch.cuda.synchronize()
         assert int(nu.item()) == 1
+
+
+@pytest.mark.parametrize("n", [3000, 40000])
+def test_a_number_that_never_comes_cannot_hang_a_kernel(n):
+    """A key listed in the table without its number (what a second call on the same table can leave behind): the
+    wait for it ends, the flag says so, the inverse map stays inside Q*, and later calls are right."""
+    keys = inputs.zipf_keys(n, 2000, 1.05, n)
+    keys[::50] = EMPTY_KEY                                               # the table's own marker has a slot of its own
+    stuck = int(keys[1])
+    with Dedup(n) as dd:
+        for lost in (stuck, EMPTY_KEY):
+            B.hps_dedup_debug_claim(dd.h, lost, n)
+            uk, inv, u = dd.run(keys)
+            rest = keys != lost
+            assert B.hps_dedup_flags(dd.h, clear=True) == B.HPS_DEDUP_FLAG_STUCK
+            assert (np.sort(uk[:u]) == np.unique(keys[rest])).all()
+            assert (uk[inv[rest]] == keys[rest]).all() and (inv[~rest] == 0).all()
+            for _ in range(3):                                           # both tables are clean again
+                check_against_oracle(keys, *dd.run(keys))
+            assert B.hps_dedup_flags(dd.h) == 0
+    assert B.hps_dedup_flags() == 0                                      # hps_dedup_noalloc's word is another one
+
+
+def test_a_full_table_cannot_hang_a_kernel():
+    n = 500
+    with Dedup(n) as dd:
+        for k in range(1024):                                            # every slot of the table of a 500-key call
+            B.hps_dedup_debug_claim(dd.h, 10 ** 6 + k, n)
+        with pytest.raises(B.HpsError, match="free slot"):
+            B.hps_dedup_debug_claim(dd.h, 5, n)
+        uk, inv, u = dd.run(np.arange(n))
+        assert u == 0 and (inv == 0).all() and B.hps_dedup_flags(dd.h, clear=True) == B.HPS_DEDUP_FLAG_STUCK
+        for _ in range(3):
+            check_against_oracle(np.arange(n), *dd.run(np.arange(n)))
+        assert B.hps_dedup_flags(dd.h) == 0
