@@ -230,12 +230,20 @@ hps_status_t check_session(hps_dedup_session *s) {
 
 // Keys per work-group: 1024; 512 for batches that would leave most CUs without a work-group, whose lanes then share
 // LDS slots with half as many others (2,000 keys 7.7 -> 6.7 us, 16,000 9.1 -> 7.3, 32,000 9.3 -> 8.1, 65,000 equal).
+//
+// Work-groups: one per tile, and more if those would have to wipe more than kWipe slots of the other table per
+// thread; the further ones only wipe.  Two calls of one size leave at most four slots per key, so a loop over equal
+// batches launches none; a call of 300 keys behind one of 2^20 wipes 2^21 slots: 284 us by its one tile, 12 this way.
+constexpr uint32_t kWipe = 4;
+
 void launch_dedup(const int64_t *keys, uint32_t n, int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
                   uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique, int64_t *other_tkey, uint32_t *other_tuid,
                   uint64_t other_dirty, uint32_t max_blocks, hipStream_t st) {
     const uint32_t tile = n <= kSmallBatch ? 512u : 1024u;
     const uint64_t tiles = ((uint64_t)n + tile - 1) / tile;
-    const dim3 grid((uint32_t)(tiles < max_blocks ? tiles : max_blocks)), block(tile);
+    const uint64_t wipers = other_dirty / (kWipe * tile);
+    const uint64_t blocks = tiles > wipers ? tiles : wipers;
+    const dim3 grid((uint32_t)(blocks < max_blocks ? blocks : max_blocks)), block(tile);
     if (tile == 512u)
         hipLaunchKernelGGL(dedup_kernel<512>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
                            other_tkey, other_tuid, other_dirty);

@@ -1,0 +1,42 @@
+"""What a call costs beside another one: properties that results do not show.  Each test compares two times taken
+in turn on the same device, far enough apart that noise does not decide."""
+import pytest
+import torch
+
+from paper_2210_08804_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _median_us(calls, before, rounds=15):
+    """Medians of the device time of each of `calls`, enqueued one after the other behind before()."""
+    times = [[] for _ in calls]
+    for _ in range(rounds):
+        before()                                      # keeps the device busy while the host enqueues
+        marks = [torch.cuda.Event(enable_timing=True) for _ in range(len(calls) + 1)]
+        marks[0].record()
+        for call, mark in zip(calls, marks[1:]):
+            call()
+            mark.record()
+        torch.cuda.synchronize()
+        for t, a, b in zip(times, marks, marks[1:]):
+            t.append(a.elapsed_time(b) * 1e3)
+    return [sorted(t)[rounds // 2] for t in times]
+
+
+def test_a_small_dedup_after_a_large_one_is_small():
+    """The small call wipes what the large one left in the other table."""
+    big, small = 1 << 20, 300
+    keys = torch.randint(0, big, (big,), device="cuda")
+    uk = torch.empty(big, dtype=torch.int64, device="cuda")
+    inv = torch.empty(big, dtype=torch.int32, device="cuda")
+    nu = torch.zeros(1, dtype=torch.int32, device="cuda")
+    busy = torch.empty(1 << 26, device="cuda")
+    s = B.hps_dedup_create(big)
+    try:
+        t_big, t_small = _median_us([lambda: B.hps_dedup(s, keys, big, uk, inv, nu), lambda: B.hps_dedup(s, keys, small, uk, inv, nu)],
+                                    lambda: busy.fill_(0.0))
+    finally:
+        torch.cuda.synchronize()
+        B.hps_dedup_destroy(s)
+    assert t_small < t_big, f"{small} keys {t_small:.1f} us, {big} keys {t_big:.1f} us"
