@@ -1048,14 +1048,16 @@ struct WriteArgs {
 // of bit 0, which also reads the set's counter: it owns the set if the bit was clear.  The owners' sets
 // are then searched with the wave-wide probe; new keys get their slot (key, counter, stamp) and row, and
 // every owner lets go again: word + 2 if it changed the set, the old word if the key was already
-// there.  Lanes that did not get their set search it without owning it before every further attempt.
+// there.  Every lane also looks at its set without owning it: on the first attempt beside the fetch-or, before
+// every further one in front of it, and a key that is found that way is done.
 // No lane ever waits while the wave owns a set: each round every pending lane tries once, the owners'
 // rows are copied by the whole wave, the sets are released, and the others try again.
 // Bound by the chain of dependent round trips (key, word, set, rows, acknowledgement) in which a wave
 // holds its sets; the owners' rows are therefore requested right behind their sets' keys, before it is known
-// whether they are needed (a key that is already there has usually been found by the search without
-// owning): 2^18 new rows of 512 bytes, inserted, updated and queried, 221 -> 208 us, 32,768 rows 18.5 -> 16.8 us per
-// insert.  KPW = 16 or 8 (launch_write): four or eight times as many waves as keys / 64 share the row copies, and a
+// whether they are needed: 2^18 new rows of 512 bytes, inserted, updated and queried, 221 -> 208 us, 32,768 rows 18.5 ->
+// 16.8 us per insert.  The first look keeps this from reading the rows of keys that are already there, in the round
+// trip of the fetch-or: 2^18 such keys take 27.7 us, 47 without the look (with the LRU policy 30 and 57), new
+// ones 84-88 either way.  KPW = 16 or 8 (launch_write): four or eight times as many waves as keys / 64 share the row copies, and a
 // wave's chain is two copy groups long, or one, instead of eight.
 template <int W, int KPW, bool kLong>
 __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
@@ -1113,11 +1115,12 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
                                                    __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }
+            // Look before owning: a key given many times (a miss list carries every occurrence) is found by
+            // all but the first without taking the word, instead of each occurrence owning the set in turn.
+            // On the first attempt the look travels beside the fetch-or, later in front of it.
+            int seen = -1;
             if (rounds > 1) {
-                // A lane that lost its first attempt looks before it tries again: a key given many
-                // times (a miss list carries every occurrence) is found by all but the first
-                // without taking the word, instead of each occurrence owning the set in turn.
-                const int seen = probe_wave<W, KPW, true>(tb.K, key, set, pending);
+                seen = probe_wave<W, KPW, true>(tb.K, key, set, pending);
                 if (pending && seen >= 0) {
                     if (tb.T) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);    // Alg. 3: refresh
                     pending = false;
@@ -1128,13 +1131,19 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             if (pending)
                 word = __hip_atomic_fetch_or(reinterpret_cast<uint64_t *>(seq_of(tb, set)), 1ull, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
+            if (rounds == 1) seen = probe_wave<W, KPW, true>(tb.K, key, set, pending);
             shared_acquire();                                        // the word is owned before the set is read
             writer_tell(&s_group, told);
             const uint32_t old = (uint32_t)word;
             const uint32_t c = (uint32_t)(word >> 32);
-            const bool own = pending && !(old & 1u);
+            bool own = pending && !(old & 1u);
+            if (pending && seen >= 0) {
+                if (tb.T) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);
+                if (own) st_agent(reinterpret_cast<uint64_t *>(seq_of(tb, set)), word);
+                own = pending = false;
+            }
             if (!__ballot(own)) {
-                __builtin_amdgcn_s_sleep(8);
+                if (__ballot(pending)) __builtin_amdgcn_s_sleep(8);
                 continue;
             }
             const uint64_t ownmask = __ballot(own);
@@ -1180,7 +1189,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             }
         }
     }
-    writer_leave(tb, &s_group, told);                              // (every hold ended with shared_release: its stores have landed)
+    writer_leave(tb, &s_group, told);                              // (every hold that stored a key or a row ended with shared_release: they have landed)
 }
 
 // Update (Alg. 4) with one lock acquisition per run of lanes that share a set.  Key batches that
