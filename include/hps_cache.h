@@ -155,9 +155,14 @@ hps_status_t hps_cache_flags(hps_cache_t *cache, uint32_t *flags, int clear);
 
 /*
  * Test hook: overwrite the sequence word of one set (host-synchronous).  An odd value imitates
- * a writer that died while holding the set, which is how the bounded waits are tested.
+ * a writer that died while holding the set, which is how the bounded waits are tested; while it is
+ * odd, queries take a writer to be at work.  Insert and update may run meanwhile, on other sets.
  */
 hps_status_t hps_cache_debug_set_seq(hps_cache_t *cache, uint64_t set, uint32_t value);
+
+/* Test hook: work-groups of insert and update counted in and out so far (modulo 2^32); equal when
+ * no writer is at work.  Synchronous on the host.  Both pointers [host]. */
+hps_status_t hps_cache_debug_writers(hps_cache_t *cache, uint32_t *started, uint32_t *finished);
 
 /* Geometry of a cache.  Any output pointer [host] may be NULL. */
 hps_status_t hps_cache_info(const hps_cache_t *cache, uint64_t *num_sets, uint32_t *ways,

@@ -29,7 +29,7 @@ EXPORTS = (
     "hps_cache_export", "hps_cache_import", "hps_cache_dump", "hps_cache_query_multi",
     "hps_backing_fetch", "hps_cache_insert_dn", "hps_cache_update_dn", "hps_cache_set_query_dedup",
     "hps_cache_create_policy", "hps_cache_export_lru", "hps_cache_import_lru",
-    "hps_cache_flags", "hps_cache_debug_set_seq", "hps_cache_query_dn",
+    "hps_cache_flags", "hps_cache_debug_set_seq", "hps_cache_debug_writers", "hps_cache_query_dn",
     "hps_lookup_create", "hps_lookup", "hps_lookup_drain", "hps_lookup_destroy", "hps_lookup_last_error",
     "hps_cache_refresh", "hps_refresh_create", "hps_refresh_run", "hps_refresh_destroy",
     "hps_dedup_create", "hps_dedup_destroy", "hps_dedup", "hps_expand_rows", "hps_dedup_last_error",
@@ -75,6 +75,7 @@ def load_library():
         "hps_cache_import_lru": [vp, vp, u32, vp],
         "hps_cache_flags": [vp, C.POINTER(u32), C.c_int],
         "hps_cache_debug_set_seq": [vp, C.c_uint64, u32],
+        "hps_cache_debug_writers": [vp, C.POINTER(u32), C.POINTER(u32)],
         "hps_lookup_create": [vp, sz, C.c_float, vp, FETCH_FN, vp, C.POINTER(vp)],
         "hps_lookup": [vp, vp, sz, vp, C.POINTER(C.c_float), C.POINTER(C.c_int), vp],
         "hps_lookup_drain": [vp],
@@ -181,6 +182,13 @@ def hps_cache_flags(handle, clear: bool = False) -> int:
 
 def hps_cache_debug_set_seq(handle, set_index: int, value: int) -> None:
     _check(load_library().hps_cache_debug_set_seq(handle, set_index, value))
+
+
+def hps_cache_debug_writers(handle) -> tuple:
+    """Work-groups of writers counted in and out."""
+    a, b = C.c_uint32(), C.c_uint32()
+    _check(load_library().hps_cache_debug_writers(handle, C.byref(a), C.byref(b)))
+    return a.value, b.value
 
 
 def hps_cache_destroy(handle) -> None:

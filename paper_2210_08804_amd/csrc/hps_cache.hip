@@ -1329,6 +1329,13 @@ __global__ void counters_in_kernel(uint32_t *sc, uint64_t S, const uint32_t *ctr
     }
 }
 
+// hps_cache_debug_set_seq.  A writer that holds a set (odd word) has counted itself in and not yet out; writers that
+// are at work count on the same pair.
+__global__ void set_seq_kernel(uint32_t *seq, uint32_t value, uint32_t *epoch) {
+    const uint32_t old = __hip_atomic_exchange(seq, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((old ^ value) & 1u) __hip_atomic_fetch_add(epoch + (value & 1u ? 0 : 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Dump (Sec. 4.2): compact the non-empty keys of a slot range.  A work-group takes a tile of
 // 256*KPT consecutive slots, keeps KPT keys per lane in registers, and needs one counter atomic
 // per tile (same counter-word scheme as query).  The output keeps slot order inside a tile, so the
@@ -2013,15 +2020,22 @@ hps_status_t hps_cache_flags(hps_cache_t *c, uint32_t *flags, int clear) {
 hps_status_t hps_cache_debug_set_seq(hps_cache_t *c, uint64_t set, uint32_t value) {
     if (hps_status_t s = check_handle(c)) return s;
     if (set >= c->S) return fail(HPS_ERR_INVALID_ARG, "set index out of range");
-    // a writer that holds a set (odd word) has counted itself in and not yet out
-    uint32_t old = 0, pair[2] = {0, 0};
-    HIP_TRY(hipMemcpy(&old, c->sc + 2 * set, sizeof(uint32_t), hipMemcpyDeviceToHost));
-    if ((old ^ value) & 1u) {
-        HIP_TRY(hipMemcpy(pair, c->epoch, sizeof(pair), hipMemcpyDeviceToHost));
-        ++pair[value & 1u ? 0 : 1];
-        HIP_TRY(hipMemcpy(c->epoch, pair, sizeof(pair), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(set_seq_kernel, dim3(1), dim3(1), 0, 0, c->sc + 2 * set, value, c->epoch);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(0));
+    return HPS_OK;
+}
+
+hps_status_t hps_cache_debug_writers(hps_cache_t *c, uint32_t *started, uint32_t *finished) {
+    if (hps_status_t s = check_handle(c)) return s;
+    if (!started || !finished) return fail(HPS_ERR_INVALID_ARG, "started and finished must not be NULL");
+    uint32_t pairs[kEpochs * kEpochStride];
+    HIP_TRY(hipMemcpy(pairs, c->epoch, sizeof(pairs), hipMemcpyDeviceToHost));
+    *started = *finished = 0;
+    for (uint32_t i = 0; i < kEpochs; ++i) {
+        *started += pairs[i * kEpochStride];
+        *finished += pairs[i * kEpochStride + 1];
     }
-    HIP_TRY(hipMemcpy(c->sc + 2 * set, &value, sizeof(uint32_t), hipMemcpyHostToDevice));
     return HPS_OK;
 }
 

@@ -127,3 +127,26 @@ def test_rows_too_long_to_validate_in_one_piece_cannot_overlap_writers():
         assert hit.sum() >= 30 and (out[hit] == inputs.backing_rows(keys, d).view(np.uint32)[hit]).all()
     with DeviceCache(64, 8, 1024, concurrent_writers=True):
         pass                                                 # 4 KiB rows are fine
+
+
+def test_debug_hook_beside_running_writers_loses_no_count():
+    """hps_cache_debug_set_seq counts like a writer, on the words that running writers count on: afterwards as many
+    are out as in, or every later query would take a writer to be at work."""
+    import torch
+    S, W, d = 1 << 12, 8, 64
+    with DeviceCache(S * W, W, d, concurrent_writers=True) as gc:
+        oc = OracleCache(S * W, W, d)
+        spare = 5
+        keys = np.array([k for k in range(30000) if oc.set_of(k) != spare], dtype=np.int64)
+        gc.insert(keys, inputs.backing_rows(keys, d))
+        dk = torch.from_numpy(keys).cuda()
+        dv = torch.from_numpy(inputs.backing_rows(keys, d, 1)).cuda()
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        for value in range(1, 61):
+            for _ in range(20):
+                B.hps_cache_update(gc.h, dk, dv, len(keys), stream=st)
+            B.hps_cache_debug_set_seq(gc.h, spare, value)                # odd and even in turn, even at the end
+        torch.cuda.synchronize()
+        started, finished = B.hps_cache_debug_writers(gc.h)
+        assert started == finished and started >= 60 * 20
