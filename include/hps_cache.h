@@ -172,7 +172,8 @@ hps_status_t hps_cache_info(const hps_cache_t *cache, uint64_t *num_sets, uint32
  * State export / import for tests and checkpoints (the paper's Dump API, Sec. 4.2, is the
  * precedent).  keys [device, sets*ways int64] in [set][way] order, ctr [device, sets uint32],
  * vals [device, sets*ways*dim fp32] or NULL to skip the rows.  Export copies out; import
- * overwrites the whole state (sequence words are reset).  Enqueued on `stream`.
+ * overwrites the whole state (sequence words and writers' counts are reset: no other call on the
+ * cache may overlap it).  Enqueued on `stream`.
  */
 hps_status_t hps_cache_export(hps_cache_t *cache, int64_t *keys, uint32_t *ctr, float *vals,
                               void *stream);

@@ -1321,7 +1321,9 @@ __global__ void counters_out_kernel(const uint32_t *sc, uint64_t S, uint32_t *ct
          i += (uint64_t)gridDim.x * blockDim.x)
         ctr[i] = sc[2 * i + 1];
 }
-__global__ void counters_in_kernel(uint32_t *sc, uint64_t S, const uint32_t *ctr) {
+// (an import replaces the state: no writer holds a set of it, and none has counted itself in)
+__global__ void counters_in_kernel(uint32_t *sc, uint64_t S, const uint32_t *ctr, uint32_t *epoch) {
+    if (blockIdx.x == 0 && threadIdx.x < 2 * kEpochs) epoch[threadIdx.x / 2 * kEpochStride + threadIdx.x % 2] = 0u;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < S;
          i += (uint64_t)gridDim.x * blockDim.x) {
         sc[2 * i] = 0u;
@@ -2153,7 +2155,7 @@ hps_status_t hps_cache_import(hps_cache_t *c, const int64_t *keys, const uint32_
     HIP_TRY(hipMemcpyAsync(c->K, keys, slots * sizeof(int64_t), hipMemcpyDeviceToDevice, st));
     if (vals)
         HIP_TRY(hipMemcpyAsync(c->V, vals, slots * c->d * sizeof(float), hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(counters_in_kernel, dim3(1024), dim3(256), 0, st, c->sc, (uint64_t)c->S, ctr);
+    hipLaunchKernelGGL(counters_in_kernel, dim3(1024), dim3(256), 0, st, c->sc, (uint64_t)c->S, ctr, c->epoch);
     HIP_TRY(hipGetLastError());
     return HPS_OK;
 }

@@ -150,3 +150,19 @@ def test_debug_hook_beside_running_writers_loses_no_count():
         torch.cuda.synchronize()
         started, finished = B.hps_cache_debug_writers(gc.h)
         assert started == finished and started >= 60 * 20
+
+
+def test_import_takes_back_a_writer_that_never_left():
+    """A state that is imported has no writer at work: the counts are as in a new cache, and queries serve the set."""
+    S, W, d = 64, 8, 16
+    keys = np.arange(200, dtype=np.int64)
+    rows = inputs.backing_rows(keys, d)
+    with DeviceCache(S * W, W, d, concurrent_writers=True) as gc:
+        gc.insert(keys, rows)
+        state = gc.export()
+        B.hps_cache_debug_set_seq(gc.h, 7, 1)
+        gc.load(*state)
+        assert B.hps_cache_debug_writers(gc.h) == (0, 0)
+        out, mi, _ = gc.query(keys)
+        hit = np.isin(keys, state[0])
+        assert mi.tolist() == np.nonzero(~hit)[0].tolist() and (out[hit] == rows.view(np.uint32)[hit]).all()
