@@ -41,6 +41,16 @@ def test_library_exports_every_declared_symbol(lib):
         assert hasattr(lib, name), name
 
 
+def test_library_exports_no_other_function_of_its_own(lib):
+    """The boundary is the C ABI: no C++ function of the library is visible beside it.  (Weak symbols are
+    instantiations of the standard library's templates.)"""
+    import subprocess
+    from paper_2210_08804_amd import binding
+    table = subprocess.run(["nm", "-D", "--defined-only", binding.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    strong = {line.split()[2] for line in table.splitlines() if line.split()[1] == "T"} - {"_init", "_fini"}
+    assert strong == set(declared_functions())
+
+
 def test_bad_arguments_are_rejected_on_the_host(lib):
     h = C.c_void_p()
     bad = [(0, 8, 128), (64, 3, 128), (64, 128, 128), (60, 8, 128), (64, 8, 0), (64, 8, 6),
