@@ -1878,26 +1878,33 @@ hps_status_t write_call(hps_cache *c, const int64_t *keys, const float *vals, si
 
 hipError_t hps_launch_expand_rows(const float *rows, const uint32_t *inverse, uint32_t n, uint32_t dim, float *out,
                                   uint32_t cus, hipStream_t st) {
-    // 8 waves per work-group; keys per wave and group sizes as for the query (query_shape)
-    constexpr uint32_t kWpb = 8;
-    const uint64_t rounds = ((uint64_t)n + kWpb * kWave * cus - 1) / (kWpb * kWave * cus);
-    uint64_t kpw = ((uint64_t)n + kWpb * cus * rounds - 1) / (kWpb * cus * rounds);
-    if (kpw < 16) kpw = n < 4096 ? kMinKeysPerWave : 16;
-    const uint32_t blocks = (uint32_t)(((uint64_t)n + kWpb * kpw - 1) / (kWpb * kpw));
-    const uint64_t bytes = kpw * dim * 4;
+    // 8 waves per work-group; keys per wave and group sizes as for the query (query_shape).  A launch has fewer than 2^32
+    // work-items, and there is one for each position or more: at most 2^30 positions go in one (a quarter of what a call may have).
+    constexpr uint32_t kWpb = 8, kMost = 1u << 30;
     const RowGeom g = make_geom(dim);
+    for (uint32_t done = 0; done < n;) {
+        const uint32_t m = n - done < kMost ? n - done : kMost;
+        const uint64_t rounds = ((uint64_t)m + kWpb * kWave * cus - 1) / (kWpb * kWave * cus);
+        uint64_t kpw = ((uint64_t)m + kWpb * cus * rounds - 1) / (kWpb * cus * rounds);
+        if (kpw < 16) kpw = m < 4096 ? kMinKeysPerWave : 16;
+        const uint32_t blocks = (uint32_t)(((uint64_t)m + kWpb * kpw - 1) / (kWpb * kpw));
+        const uint64_t bytes = kpw * dim * 4;
+        const uint32_t *const inv = inverse + done;
+        float *const to = out + (uint64_t)done * dim;
 #define HPS_EXPAND(U, D) \
-    hipLaunchKernelGGL((expand_rows_kernel<U, kWpb, D>), dim3(blocks), dim3(kWpb * kWave), 0, st, rows, inverse, n, (uint32_t)kpw, g, out)
-    if (dim == 128) {
-        if (bytes <= 13312) HPS_EXPAND(13, 128);
-        else if (bytes <= 26624) HPS_EXPAND(26, 128);
-        else HPS_EXPAND(32, 128);
-    } else {
-        if (bytes <= 8192) HPS_EXPAND(8, 0);
-        else if (bytes <= 16384) HPS_EXPAND(16, 0);
-        else HPS_EXPAND(32, 0);
-    }
+    hipLaunchKernelGGL((expand_rows_kernel<U, kWpb, D>), dim3(blocks), dim3(kWpb * kWave), 0, st, rows, inv, m, (uint32_t)kpw, g, to)
+        if (dim == 128) {
+            if (bytes <= 13312) HPS_EXPAND(13, 128);
+            else if (bytes <= 26624) HPS_EXPAND(26, 128);
+            else HPS_EXPAND(32, 128);
+        } else {
+            if (bytes <= 8192) HPS_EXPAND(8, 0);
+            else if (bytes <= 16384) HPS_EXPAND(16, 0);
+            else HPS_EXPAND(32, 0);
+        }
 #undef HPS_EXPAND
+        done += m;
+    }
     return hipGetLastError();
 }
 
