@@ -746,7 +746,8 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                 const uint32_t nd = *a.n_dev;
                 B = nd < B ? nd : B;
                 const uint32_t waves = (uint32_t)WPB * a.n_tiles, k = (uint32_t)(((uint64_t)B + waves - 1) / waves);
-                kpw = k < kMinKeysPerWave ? kMinKeysPerWave : k;
+                const uint32_t least = kpw < kMinKeysPerWave ? kpw : kMinKeysPerWave;
+                kpw = k < least ? least : k;
             }
             const uint32_t b    = (lt * WPB + wave) * kpw + lane;
             const bool     inb  = lane < (int)kpw && b < B;
@@ -1705,6 +1706,10 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // work-group that fits a CU with the smaller group is worth more.
 struct QueryShape { uint32_t kpw; int u, wpb; };
 
+// Most rows of d words that a wave moves with copy_rows, which counts their 16-byte chunks in 32 bits (fewer than 64
+// only for rows of 512 MiB and more).
+uint64_t most_rows(uint32_t d) { return (1ull << 31) / (d / 4); }
+
 QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup) {
     const uint64_t n = n_tables * batch;
     QueryShape q{(uint32_t)kWave, 0, 0};
@@ -1723,6 +1728,7 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
         while (n_tables > 1 && k < (uint64_t)kWave && tiles() > rounds * cus) ++k;
         if (k < (uint64_t)kWave) q.kpw = (uint32_t)k;
     }
+    if (!dedup && q.kpw > most_rows(d)) q.kpw = (uint32_t)most_rows(d);
     const uint64_t bytes = (uint64_t)q.kpw * d * 4;            // a wave's rows
     if (coherent) {
         if (d == 128 && q.wpb == 4) q.u = q.kpw <= 8 ? 8 : 16;
@@ -1887,6 +1893,7 @@ hipError_t hps_launch_expand_rows(const float *rows, const uint32_t *inverse, ui
         const uint64_t rounds = ((uint64_t)m + kWpb * kWave * cus - 1) / (kWpb * kWave * cus);
         uint64_t kpw = ((uint64_t)m + kWpb * cus * rounds - 1) / (kWpb * cus * rounds);
         if (kpw < 16) kpw = m < 4096 ? kMinKeysPerWave : 16;
+        if (kpw > most_rows(dim)) kpw = most_rows(dim);
         const uint32_t blocks = (uint32_t)(((uint64_t)m + kWpb * kpw - 1) / (kWpb * kpw));
         const uint64_t bytes = kpw * dim * 4;
         const uint32_t *const inv = inverse + done;

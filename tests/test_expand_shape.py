@@ -28,6 +28,8 @@ static void record(dim3 grid, dim3 block, int, hipStream_t, const float *, const
     const uint64_t waves = block.x / kWave;
     if (grid.x * block.x >= 1ull << 32) bad = "work-items of a launch";
     if (kpw < 1 || kpw > 64) bad = "rows per wave";
+    const uint64_t of_a_wave = kpw < n ? kpw : n;
+    if (of_a_wave * (g.d / 4) >= (1ull << 32) - 64 * 64) bad = "chunks of a wave, counted in 32 bits";
     if (grid.x * waves * kpw < n || (grid.x - 1) * waves * kpw >= n) bad = "work-groups for n";
     if ((uintptr_t)inverse - (uintptr_t)inv0 != rows_done * 4 || (uintptr_t)out - (uintptr_t)out0 != rows_done * g.d * 4) bad = "place of a part";
     rows_done += n;
@@ -46,6 +48,7 @@ int main() {
                     uint64_t n = (uint64_t)__builtin_exp2(x) + o;
                     if (n < 1) continue;
                     if (n >= 1ull << 32) n = (1ull << 32) - 1 - (uint64_t)(o + 1) * 255;
+                    if (n * d >= 1ull << 38) continue;                     // a result of 1 TiB
                     rows_done = 0;
                     bad = nullptr;
                     hps_launch_expand_rows((const float *)0x1000, inv0, (uint32_t)n, (uint32_t)d, out0, cus, nullptr);
@@ -65,7 +68,8 @@ def test_launches_cover_every_row_and_stay_within_the_limits(tmp_path):
         s = f.read()
     start = s.index("hipError_t hps_launch_expand_rows(")
     src = tmp_path / "expand.cpp"
-    src.write_text(BEFORE + s[start:s.index("\n}\n", start) + 3] + AFTER)
+    rule = s.find("uint64_t most_rows(")
+    src.write_text(BEFORE + (s[rule:s.index("\n", rule) + 1] if rule >= 0 else "") + s[start:s.index("\n}\n", start) + 3] + AFTER)
     exe = tmp_path / "expand"
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wno-unused", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)

@@ -49,3 +49,36 @@ def test_every_shape_is_compiled_in(tmp_path):
     subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+LONG_ROWS = """
+int main() {
+    for (uint64_t cus : {256ull, 38ull})
+        for (uint64_t d = 132; d < 1ull << 32; d += d / 64 * 4)
+            for (double x = 0; x < 32; x += 0.25) {
+                const uint64_t n = (uint64_t)__builtin_exp2(x);
+                if (n * d >= 1ull << 38) continue;                         // a result of 1 TiB
+                const QueryShape q = query_shape(1, n, (uint32_t)d, cus, false, false);
+                const uint64_t rows = q.kpw < n ? q.kpw : n;
+                if (q.kpw < 1 || rows * (d / 4) >= (1ull << 32) - 64 * 64) {
+                    std::printf("d %llu batch %llu: %u keys per wave\\n", (unsigned long long)d, (unsigned long long)n, q.kpw);
+                    return 1;
+                }
+            }
+    return 0;
+}
+"""
+
+
+def test_a_wave_can_count_the_chunks_of_its_rows(tmp_path):
+    """The copy of a wave's rows numbers their 16-byte chunks in 32 bits, whatever the row's length."""
+    with open(SRC) as f:
+        s = f.read()
+    rule = s[s.index("struct QueryShape {"):s.index("template <int W, int U, int WPB, bool kCoherent, int kD>\nvoid launch_query_kernel")]
+    src = tmp_path / "long.cpp"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <initializer_list>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
+                   + rule + LONG_ROWS)
+    exe = tmp_path / "long"
+    subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
