@@ -27,6 +27,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <unordered_map>
 
 #include "hps_cache.h"
@@ -479,13 +480,13 @@ struct RowMover {
 
     // Wave load k of the list: does it hold rows at all (uniform), does this lane have one, which row, which chunk of it.
     __device__ __forceinline__ bool any(uint32_t k) const {
-        return kLong ? k * kWave < cnt * g.c8.C : (k << (6u - g.lpr8Shift)) < cnt;
+        return kLong ? (uint64_t)k * kWave < (uint64_t)cnt * g.c8.C : (k << (6u - g.lpr8Shift)) < cnt;
     }
     __device__ __forceinline__ bool place(uint32_t k, ChunkWalk &w, uint32_t &r, uint32_t &c) const {
         const uint32_t lane = (uint32_t)lane_id();
         bool live;
         if (kLong) {
-            live = k * kWave + lane < cnt * g.c8.C;
+            live = w.r < cnt;
             r = live ? w.r : 0u;
             c = live ? w.c : 0u;
             w.next(g.c8);
@@ -559,22 +560,23 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
     const uint32_t sub = lane >> g.lpr8Shift;
     uint32_t cl = lane & (g.LPR8 - 1);
     cl = cl < g.c8.C ? cl : 0u;
-    const uint32_t step = kLong ? (uint32_t)(kWave * U) : rpi * U;
-    const uint32_t total = kLong ? cnt * g.c8.C : cnt;                // chunks, or rows
+    typedef typename std::conditional<kLong, uint64_t, uint32_t>::type Count;   // 16 rows of 2 GiB have 2^32 chunks
+    const Count step = kLong ? (Count)(kWave * U) : (Count)(rpi * U);
+    const Count total = kLong ? (Count)cnt * g.c8.C : (Count)cnt;     // chunks, or rows
     uint64_t bufA[U], bufB[U];
     uint32_t entA[U], entB[U], offA[kLong ? U : 1], offB[kLong ? U : 1];
     ChunkWalk in(g.c8, lane);
-    auto load = [&](uint32_t q0, uint64_t (&buf)[U], uint32_t (&ent)[U], uint32_t *off) {
+    auto load = [&](Count q0, uint64_t (&buf)[U], uint32_t (&ent)[U], uint32_t *off) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (kLong) {
-                const bool live = q0 + u * kWave + lane < total;
+                const bool live = in.r < cnt;
                 ent[u] = live ? in.r : 0u;
                 off[u] = live ? in.c : 0u;
                 in.next(g.c8);
             } else {
-                const uint32_t e = q0 + u * rpi + sub;
-                ent[u] = e < total ? e : 0u;
+                const uint32_t e = (uint32_t)q0 + u * rpi + sub;
+                ent[u] = e < cnt ? e : 0u;
             }
             buf[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (uint64_t)srcRow[ent[u]] * g.d) + (kLong ? off[u] : cl));
         }
@@ -585,7 +587,7 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
             shared_st64(reinterpret_cast<uint64_t *>(dst + dstRow[ent[u]] * g.d) + (kLong ? off[u] : cl), buf[u]);
     };
     load(0, bufA, entA, offA);
-    for (uint32_t q0 = 0;; q0 += 2 * step) {
+    for (Count q0 = 0;; q0 += 2 * step) {
         load(q0 + step, bufB, entB, offB);
         store(bufA, entA, offA);
         if (q0 + step >= total) break;
