@@ -111,6 +111,16 @@ def test_full_size_batches(n, space, alpha, seed):
             assert uk[inv[p]] == keys[p]
 
 
+def test_more_tiles_than_work_groups():
+    """A work-group that takes several tiles waits for numbers between them; most keys are in tiles of others too."""
+    n = 8 * torch.cuda.get_device_properties(0).multi_processor_count * 1024 * 5 // 4 + 77
+    keys = np.random.Generator(np.random.PCG64(8)).integers(0, n // 3, size=n, dtype=np.int64)
+    with Dedup(n) as dd:
+        for _ in range(3):
+            check_against_oracle(keys, *dd.run(keys), exact_oracle=False)
+        assert B.hps_dedup_flags(dd.h) == 0
+
+
 @pytest.mark.parametrize("d", [4, 16, 100, 128, 132, 256, 320, 516])
 def test_expand_rows_matches_oracle(d):
     rng = np.random.Generator(np.random.PCG64(d))

@@ -386,6 +386,27 @@ def test_write_batch_sizes_around_the_kernel_switches():
         compare_query(gc, oc, pool[:50000])
 
 
+@pytest.mark.parametrize("d", [128, 132, 320, 516])
+def test_write_batches_of_long_rows_around_the_kernel_switches(d):
+    """Rows of 512 bytes and of several wave loads on both sides of the switches (8 or 16 keys per wave of the insert, 16
+    or 64 of the update).  Inserts are partly cached and give a third of their keys twice, so that new keys, cached ones
+    and ones that another wave is just inserting meet in a wave."""
+    S, W = 1 << 14, 8
+    with DeviceCache(S * W, W, d) as gc:
+        oc = OracleCache(S * W, W, d)
+        pool = np.unique(inputs.uniform_keys(90000, 1 << 40, 63))
+        rng = np.random.Generator(np.random.PCG64(d))
+        for version, n in enumerate([17, 32767, 32768, 32769, 40000], 1):
+            ins = rng.choice(pool, n - n // 4, replace=False)
+            ins = rng.permutation(np.concatenate([ins, ins[:n // 4]]))
+            insert_both(gc, oc, ins, rows_u32(ins, d, 0))
+            upd = rng.choice(pool, n, replace=False)
+            gc.update(upd, rows_u32(upd, d, version))
+            oc.update(upd, rows_u32(upd, d, version))
+            assert_same_state(gc.export(), oc)
+        compare_query(gc, oc, pool[:50000])
+
+
 def test_query_with_device_side_batch_length():
     """hps_cache_query_dn looks up min(n_max, *n_dev) positions; the rest of the buffers is
     neither read as keys, nor written, nor reported."""

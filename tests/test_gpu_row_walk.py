@@ -1,5 +1,9 @@
 """Rows of any width through query, insert and update: row lists whose chunks fill a wave load, miss it
-by one, or split a row over two of them; batches below, at and above the query's launch shapes."""
+by one, or split a row over two of them; batches below, at and above the query's launch shapes.
+
+Three modes of the query: "plain"; "quiet", the default mode with no writer at work (rows validated by the writers'
+counts); "held", the default mode while a writer holds a set (here one that no key of the batch falls into), so that
+every row goes by its set's sequence word."""
 import numpy as np
 import pytest
 
@@ -7,9 +11,20 @@ torch = pytest.importorskip("torch")
 
 from harness import SENTINEL, DeviceCache  # noqa: E402
 from oracle import OracleCache  # noqa: E402
+from paper_2210_08804_amd import binding as B  # noqa: E402
 from paper_2210_08804_amd import inputs  # noqa: E402
 
 pytestmark = pytest.mark.gpu
+
+
+def _hold_a_set(gc, oc, space):
+    """Holds a set as a writer would; returns the keys below `space` that fall into the others."""
+    sets = np.array([oc.set_of(k) for k in range(space)])
+    spare = int(sets[0])
+    B.hps_cache_debug_set_seq(gc.h, spare, 1)
+    started, finished = B.hps_cache_debug_writers(gc.h)
+    assert started == finished + 1
+    return np.nonzero(sets != spare)[0].astype(np.int64)
 
 
 def _compare(gc, oc, keys, d):
@@ -20,13 +35,13 @@ def _compare(gc, oc, keys, d):
     assert (out == exp).all()
 
 
-@pytest.mark.parametrize("checked", [False, True])
+@pytest.mark.parametrize("mode", ["plain", "quiet", "held"])
 @pytest.mark.parametrize("d", [4, 8, 12, 28, 32, 36, 64, 68, 96, 124, 132, 192, 252, 260, 320, 512, 516, 1020, 1024])
-def test_row_widths(d, checked):
+def test_row_widths(d, mode):
     S, W, n_keys = 2039, 8, 1200            # no set gets more than W keys
     keys = np.arange(n_keys, dtype=np.int64) * 7 + 1
     rows = inputs.backing_rows(keys, d)
-    with DeviceCache(S * W, W, d, concurrent_writers=checked) as gc:
+    with DeviceCache(S * W, W, d, concurrent_writers=mode != "plain") as gc:
         oc = OracleCache(S * W, W, d)
         for lo in range(0, n_keys, 401):
             gc.insert(keys[lo:lo + 401], rows[lo:lo + 401])
@@ -35,24 +50,26 @@ def test_row_widths(d, checked):
         gc.update(upd, inputs.backing_rows(upd, d, version=1))
         oc.update(upd, inputs.backing_rows(upd, d, version=1))
         rng = np.random.Generator(np.random.PCG64(d))
+        others = _hold_a_set(gc, oc, 9 * n_keys) if mode == "held" else None
         for n in (1, 7, 63, 65, 1000):
-            _compare(gc, oc, rng.integers(0, 9 * n_keys, size=n, dtype=np.int64), d)
+            _compare(gc, oc, rng.integers(0, 9 * n_keys, size=n, dtype=np.int64) if others is None else rng.choice(others, n), d)
         oc.close()
 
 
-@pytest.mark.parametrize("checked", [False, True])
+@pytest.mark.parametrize("mode", ["plain", "quiet", "held"])
 @pytest.mark.parametrize("d,n", [(16, (1 << 14) - 1), (16, 1 << 14), (16, (1 << 18) + 3), (32, (1 << 17) + 1), (32, 270001), (64, (1 << 16) + 7),
                                  (64, 270001), (96, 43691), (160, 20001), (128, 4095), (128, 4097), (128, 10239), (128, 10240), (128, 28673),
                                  (128, 57345), (128, 16385), (256, 16384), (320, 13107), (320, 60001)])
-def test_shapes_by_batch_and_width(d, n, checked):
+def test_shapes_by_batch_and_width(d, n, mode):
     """Both sides of every line between two launch shapes."""
     S, W, n_keys = 8191, 8, 4000
     keys = np.arange(n_keys, dtype=np.int64) * 5
     rows = inputs.backing_rows(keys, d)
-    with DeviceCache(S * W, W, d, concurrent_writers=checked) as gc:
+    with DeviceCache(S * W, W, d, concurrent_writers=mode != "plain") as gc:
         oc = OracleCache(S * W, W, d)
         gc.insert(keys, rows)
         oc.insert(keys, rows)
         rng = np.random.Generator(np.random.PCG64(n))
-        _compare(gc, oc, rng.integers(0, 6 * n_keys, size=n, dtype=np.int64), d)
+        others = _hold_a_set(gc, oc, 6 * n_keys) if mode == "held" else None
+        _compare(gc, oc, rng.integers(0, 6 * n_keys, size=n, dtype=np.int64) if others is None else rng.choice(others, n), d)
         oc.close()
