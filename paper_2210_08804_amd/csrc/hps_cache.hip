@@ -1172,9 +1172,10 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
                             consider(w, ld_agent(tb.K + (uint64_t)set * W + w), ld_agent(tb.T + (uint64_t)set * W + w));
                     } else {
                         // More slots than that the compiler asks for one by one, waiting for each (behind it the rows hold 64
-                        // registers): 16 at a time, loads and comparisons apart.  40,000 new rows, 16 / 32 / 64 ways: 44 / 81 /
-                        // 181 us one by one, 34 / 54 / 96 this way (8 at a time 35 / 54 / 104, 32 35 / 54 / 98).
-                        constexpr int F = 16;
+                        // registers): eight at a time, loads and comparisons apart.  40,000 new rows, 16 / 32 / 64 ways: 44 / 81 /
+                        // 181 us one by one, 35 / 54 / 104 this way (16 at a time 34 / 54 / 96, but those registers cost every
+                        // insert into such sets a wave per SIMD: with the victim counter 323 instead of 263 us per 300,000).
+                        constexpr int F = 8;
 #pragma unroll
                         for (int w0 = W - F; w0 >= 0; w0 -= F) {
                             int64_t  kw[F];
