@@ -105,3 +105,25 @@ def test_lru_insert_reads_a_wide_set_at_once():
             torch.cuda.synchronize()
             B.hps_cache_destroy(h)
     assert times[64] < 4.1 * times[16], f"us of 8 calls by ways: {times}"
+
+
+def test_insert_of_a_hot_key_does_not_queue_every_wave():
+    """32,768 cached keys of which one is a quarter, against as many different ones.  (Hot over different: 2.0 with copies
+    thinned over the work-group, 4.1 with copies thinned wave by wave.)"""
+    n, d, times = 32768, 32, []
+    busy = torch.empty(1 << 26, device="cuda")
+    rows = torch.zeros(n, d, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    for keys in ((torch.rand(n, device="cuda", generator=g) ** 6 * 2000).long(), torch.randperm(n, device="cuda", generator=g)):
+        h = B.hps_cache_create(1 << 17, 8, d)
+
+        def calls():
+            for _ in range(10):
+                B.hps_cache_insert(h, keys, rows, n)
+
+        try:
+            times += _median_us([calls], lambda: [busy.fill_(0.0) for _ in range(4)])
+        finally:
+            torch.cuda.synchronize()
+            B.hps_cache_destroy(h)
+    assert times[0] < 2.8 * times[1], f"us of 10 calls, a hot key and different keys: {times}"
