@@ -766,7 +766,9 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                 hit = false;
                 way = -1;
                 bool pending = want;
-                if (!__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {   // no writer at work
+                // No writer at work.  (A wave without keys, of which a length on the device can leave most, has nothing to
+                // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not.)
+                if (__ballot(want) && !__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {
                     shared_acquire();                                // the epochs are read before any key or row
                     way = probe_wave<W, KPW, true>(tb.K, key, set, want);
                     const uint64_t fmask = __ballot(way >= 0);
