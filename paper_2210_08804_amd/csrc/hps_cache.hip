@@ -1733,7 +1733,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // in groups of 32): 425,984 keys 65.5 / 65.3, 851,968 keys 143.0 / 125.7, the 26-table launch 400 / 378.
 // Rows of up to 128 bytes leave registers for 16 waves in two work-groups per CU and are bound by the
 // counter atomics and by the number of keys in flight: 15 workers 42.9, 7 workers 44.5 at 851,968 keys of
-// 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7.
+// 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7; nor do sets of more than 16 ways, whose keys spill
+// (300,000 keys of 128 bytes, 32 / 64 ways: 15 workers 34.4 / 52.0, 7 workers 20.1 / 24.5).
 // Checked (4 / 7 workers): 5,000 keys of 512 bytes 7.2 / 7.7, 8,192 keys 7.9 / 8.0, 13,312 keys 9.0 / 8.6, of 256 bytes
 // 8.8 / 8.3, 26,624 keys of 128 bytes 9.3 / 9.0, 106,496 keys of 128 bytes 14.2 / 11.6.
 //
@@ -1759,13 +1760,13 @@ struct QueryShape { uint32_t kpw; int u, wpb; };
 // only for rows of 512 MiB and more).
 uint64_t most_rows(uint32_t d) { return (1ull << 31) / (d / 4); }
 
-QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup) {
+QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup, uint32_t ways = 8) {
     const uint64_t n = n_tables * batch;
     QueryShape q{(uint32_t)kWave, 0, 0};
     if (coherent) q.wpb = n < 10240 ? 4 : 7;
     else if (n < (1u << 14)) q.wpb = 4;
     else if (n < (1u << 18) || dedup) q.wpb = 8;
-    else q.wpb = d <= 32 ? 15 : 7;
+    else q.wpb = d <= 32 && ways <= 16 ? 15 : 7;
     const uint64_t full = (uint64_t)q.wpb * kWave * cus;       // keys per round at 64 keys per wave
     const uint64_t rounds = (n + full - 1) / full;
     const uint64_t floor_k = n < 4096 ? kMinKeysPerWave : 16;
@@ -1844,7 +1845,7 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
             case 2408: launch_query_kernel<W, 24, 8, false, 0>(a, full, st); break;
             case 1607: launch_query_kernel<W, 16, 7, false, 0>(a, full, st); break;
             case 3207: launch_query_kernel<W, 32, 7, false, 0>(a, full, st); break;
-            case 815: launch_query_kernel<W, 8, 15, false, 0>(a, full, st); break;
+            case 815: if constexpr (W <= 16) launch_query_kernel<W, 8, 15, false, 0>(a, full, st); break;   // (wider sets do not get it)
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
     }
@@ -2144,7 +2145,7 @@ static hps_status_t query_call(hps_cache_t *const *caches, uint32_t n_tables, co
     bool coherent = false;                      // any table that may see concurrent writers makes the call careful
     for (uint32_t t = 0; t < n_tables; ++t) coherent = coherent || caches[t]->concurrent_writers.load() != 0;
     const bool dedup = !coherent && caches[0]->query_dedup.load() != 0;
-    const QueryShape shape = query_shape(n_tables, batch, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup);
+    const QueryShape shape = query_shape(n_tables, batch, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup, caches[0]->W);
     const uint32_t kpw = shape.kpw;
     a.kpw = kpw;
     const uint32_t tile = kpw * (uint32_t)shape.wpb;

@@ -82,3 +82,29 @@ def test_a_wave_can_count_the_chunks_of_its_rows(tmp_path):
     subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def test_wide_sets_do_not_get_fifteen_workers(tmp_path):
+    """Sixteen waves of one work-group have 128 registers each, too few for the probe of sets of 32 ways and more."""
+    with open(SRC) as f:
+        s = f.read()
+    rule = s[s.index("struct QueryShape {"):s.index("template <int W, int U, int WPB, bool kCoherent, int kD>\nvoid launch_query_kernel")]
+    src = tmp_path / "wide.cpp"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <initializer_list>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
+                   + rule + """
+int main() {
+    int fifteen = 0;
+    for (uint32_t ways : {1u, 2u, 4u, 8u, 16u, 32u, 64u})
+        for (uint32_t d = 4; d < 256; d += 4)
+            for (uint64_t n = 1; n < 1ull << 32; n += n / 7 + 1) {
+                const int wpb = query_shape(1, n, d, 256, false, false, ways).wpb;
+                fifteen += wpb == 15;
+                if (wpb > 8 && ways > 16) { std::printf("ways %u d %u batch %llu: %d workers\\n", ways, d, (unsigned long long)n, wpb); return 1; }
+            }
+    return fifteen ? 0 : 2;
+}
+""")
+    exe = tmp_path / "wide"
+    subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
