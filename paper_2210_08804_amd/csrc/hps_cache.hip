@@ -1797,8 +1797,10 @@ template <int W, int U, int WPB, bool kCoherent, int kD>
 void launch_query_kernel(const QueryArgs &a, bool full, hipStream_t st) {
     const uint32_t grid = a.n_tiles < (1u << 20) ? a.n_tiles : (1u << 20);
     const dim3 block((WPB + 1) * kWave);
-    if (full) hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, true>), dim3(grid), block, 0, st, a);
-    else      hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, false>), dim3(grid), block, 0, st, a);
+    if constexpr (WPB <= 8 || W <= 16) {           // query_shape gives no more than 8 workers to wider sets
+        if (full) hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, true>), dim3(grid), block, 0, st, a);
+        else      hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, false>), dim3(grid), block, 0, st, a);
+    }
 }
 
 template <int W, int WPB>
@@ -1845,7 +1847,7 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
             case 2408: launch_query_kernel<W, 24, 8, false, 0>(a, full, st); break;
             case 1607: launch_query_kernel<W, 16, 7, false, 0>(a, full, st); break;
             case 3207: launch_query_kernel<W, 32, 7, false, 0>(a, full, st); break;
-            case 815: if constexpr (W <= 16) launch_query_kernel<W, 8, 15, false, 0>(a, full, st); break;   // (wider sets do not get it)
+            case 815: launch_query_kernel<W, 8, 15, false, 0>(a, full, st); break;
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
     }
