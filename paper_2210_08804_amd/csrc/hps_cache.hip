@@ -600,10 +600,12 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
 // Set probe for the first KPW lanes' keys of a wave (Alg. 2 "warpReadOutSlab" + match): W lanes
 // read the W slot keys of one set (contiguous 8*W bytes), so one wave load covers 64/W sets; a
 // ballot over the equality test gives every key its way.  Returns the way or -1.  between() runs after
-// the loads of the (last) round have been issued: it may issue further loads behind them.
+// the loads of the (last) round have been issued: it may issue further loads behind them.  Only the first `lanes`
+// lanes have keys; with sets of 32 ways and more a wave load covers two keys or one, and those of the other lanes are left out
+// (40,000 keys of 512 bytes in 64-way sets, 23 keys per wave, checked: 19.8 us with them, all on the line of set 0, 10.2 without).
 template <int W, int KPW, bool kShared = false, typename Between>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key,
-                                          uint32_t set, bool want, Between &&between) {
+                                          uint32_t set, bool want, Between &&between, uint32_t lanes = KPW) {
     constexpr int G = kWave / W;                       // keys per wave load
     constexpr int R = (KPW + G - 1) / G;               // wave loads needed for KPW keys
     constexpr int RC = R > 32 ? 32 : R;                // wave loads in flight together (64 for W = 64 would not fit the registers)
@@ -614,31 +616,40 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += RC) {
         int64_t sk[RC];
+        constexpr int RB = W >= 32 && RC >= 8 ? 8 : RC;              // wave loads per test for lanes that have keys
 #pragma unroll
-        for (int r = 0; r < RC; ++r) {
-            const int j = (r0 + r) * G + sub;
-            const uint32_t sj = (uint32_t)__shfl((int)set, j, kWave);   // 0 for lanes without a key: a valid set
-            const int64_t *p = K + (uint64_t)sj * W + slot;
-            sk[r] = kShared ? (int64_t)shared_ld64(reinterpret_cast<const uint64_t *>(p)) : *p;
+        for (int b = 0; b < RC; b += RB) {
+            if (RB < RC && (uint32_t)((r0 + b) * G) >= lanes) continue;   // uniform
+#pragma unroll
+            for (int r = b; r < b + RB; ++r) {
+                const int j = (r0 + r) * G + sub;
+                const uint32_t sj = (uint32_t)__shfl((int)set, j, kWave);   // 0 for lanes without a key: a valid set
+                const int64_t *p = K + (uint64_t)sj * W + slot;
+                sk[r] = kShared ? (int64_t)shared_ld64(reinterpret_cast<const uint64_t *>(p)) : *p;
+            }
         }
         if (r0 + RC >= R) between();
 #pragma unroll
-        for (int r = 0; r < RC; ++r) {
-            const int j = (r0 + r) * G + sub;
-            const int64_t kj = shfl64(key, j);
-            const int wj = __shfl((int)want, j, kWave);
-            const uint64_t m = __ballot(wj && sk[r] == kj);
-            if (lane / G == r0 + r) {
-                const uint64_t field = (W == 64) ? m : ((m >> ((lane % G) * W)) & ((1ull << (W & 63)) - 1));
-                if (field) way = __builtin_ctzll(field);
+        for (int b = 0; b < RC; b += RB) {
+            if (RB < RC && (uint32_t)((r0 + b) * G) >= lanes) continue;
+#pragma unroll
+            for (int r = b; r < b + RB; ++r) {
+                const int j = (r0 + r) * G + sub;
+                const int64_t kj = shfl64(key, j);
+                const int wj = __shfl((int)want, j, kWave);
+                const uint64_t m = __ballot(wj && sk[r] == kj);
+                if (lane / G == r0 + r) {
+                    const uint64_t field = (W == 64) ? m : ((m >> ((lane % G) * W)) & ((1ull << (W & 63)) - 1));
+                    if (field) way = __builtin_ctzll(field);
+                }
             }
         }
     }
     return way;
 }
 template <int W, int KPW, bool kShared = false>
-__device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want) {
-    return probe_wave<W, KPW, kShared>(K, key, set, want, [] {});
+__device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want, uint32_t lanes = KPW) {
+    return probe_wave<W, KPW, kShared>(K, key, set, want, [] {}, lanes);
 }
 
 // ------------------------------------------------------------------ query
@@ -770,7 +781,7 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                 // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not.)
                 if (__ballot(want) && !__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {
                     shared_acquire();                                // the epochs are read before any key or row
-                    way = probe_wave<W, KPW, true>(tb.K, key, set, want);
+                    way = probe_wave<W, KPW, true>(tb.K, key, set, want, kpw);
                     const uint64_t fmask = __ballot(way >= 0);
                     const int r = rank_in(fmask);
                     if (way >= 0) {
@@ -794,7 +805,7 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                     const uint32_t v1 = pending ? ld_agent(seq_of(tb, set)) : 0u;
                     const bool busy = pending && (v1 & 1u);          // a writer holds the set: look again later
                     shared_acquire();                                // the word is read before any key or row
-                    const int w = probe_wave<W, KPW, true>(tb.K, key, set, pending && !busy);
+                    const int w = probe_wave<W, KPW, true>(tb.K, key, set, pending && !busy, kpw);
                     const bool found = w >= 0;
                     const uint64_t fmask = __ballot(found);
                     if (lane < 2) s_retry[wave][lane] = 0u;
@@ -821,7 +832,7 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                     if (__ballot(pending)) __builtin_amdgcn_s_sleep(2);
                 }
             } else {
-                way = probe_wave<W, KPW>(tb.K, key, set, want);
+                way = probe_wave<W, KPW>(tb.K, key, set, want, kpw);
                 hit = way >= 0;
             }
 
