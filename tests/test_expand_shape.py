@@ -20,7 +20,7 @@ struct RowGeom { uint32_t d; };
 static RowGeom make_geom(uint32_t d) { return RowGeom{d}; }
 static hipError_t hipGetLastError() { return 0; }
 static const char *bad = nullptr;
-static uint64_t rows_done;
+static uint64_t rows_done, the_cus;
 static const uint32_t *inv0;
 static float *out0;
 static void record(dim3 grid, dim3 block, int, hipStream_t, const float *, const uint32_t *inverse, uint32_t n, uint32_t kpw,
@@ -30,6 +30,7 @@ static void record(dim3 grid, dim3 block, int, hipStream_t, const float *, const
     if (kpw < 1 || kpw > 64) bad = "rows per wave";
     const uint64_t of_a_wave = kpw < n ? kpw : n;
     if (of_a_wave * (g.d / 4) >= (1ull << 32) - 64 * 64) bad = "chunks of a wave, counted in 32 bits";
+    if (kpw > 1 && (uint64_t)kpw * g.d * 4 > 49152 && (n + kpw - 1) / kpw < 4ull * the_cus) bad = "long rows in few waves";
     if (grid.x * waves * kpw < n || (grid.x - 1) * waves * kpw >= n) bad = "work-groups for n";
     if ((uintptr_t)inverse - (uintptr_t)inv0 != rows_done * 4 || (uintptr_t)out - (uintptr_t)out0 != rows_done * g.d * 4) bad = "place of a part";
     rows_done += n;
@@ -50,6 +51,7 @@ int main() {
                     if (n >= 1ull << 32) n = (1ull << 32) - 1 - (uint64_t)(o + 1) * 255;
                     if (n * d >= 1ull << 38) continue;                     // a result of 1 TiB
                     rows_done = 0;
+                    the_cus = cus;
                     bad = nullptr;
                     hps_launch_expand_rows((const float *)0x1000, inv0, (uint32_t)n, (uint32_t)d, out0, cus, nullptr);
                     if (rows_done != n) bad = "rows of all launches";
