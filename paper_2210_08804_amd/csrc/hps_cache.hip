@@ -1471,10 +1471,10 @@ __global__ void __launch_bounds__(kBlock) dump_kernel(const int64_t *__restrict_
     }
 }
 
-// Lower-tier stand-in.  A wave makes up to 32 rows at a time, LPR lanes to a row, four consecutive
+// Lower-tier stand-in.  A wave makes up to 32 rows at a time (rows of 16 bytes: 64), LPR lanes to a row, four consecutive
 // elements per lane and pass: the inner mix, which depends on the element and not on the key, is made
 // once per lane and pass instead of once per element.  Bound by the 64-bit products of the mixes (four
-// per element before, two now) and by the rows written: 31.7 -> 21.7 us for the 90,000 missing rows of a
+// per element before, two now) and by the rows written: 31.7 -> 20.7 us for the 90,000 missing rows of a
 // 425,984-key batch, written twice.  Few rows are spread over all waves (7,400 rows in 32s: 6.5 us, spread 4.1 us).
 constexpr uint32_t kBackingRows  = 32;
 constexpr uint32_t kBackingWaves = 8192;         // as many as 256 CUs hold
@@ -1491,32 +1491,32 @@ __global__ void __launch_bounds__(kBlock) backing_kernel(const int64_t *__restri
     const uint32_t rpi = (uint32_t)kWave >> g.lprShift;
     uint32_t per = n / kBackingWaves + 1u;
     per = per < rpi ? rpi : per < kBackingRows ? per : kBackingRows;
-    const uint64_t step = (uint64_t)gridDim.x * kWavesPerWg * per;
-    for (uint64_t i0 = ((uint64_t)blockIdx.x * kWavesPerWg + wave_id()) * per; i0 < n; i0 += step) {
+    // a wave takes one pass of a tile at a time: few long rows are shared by many waves (100 rows of 16 KiB 9.4 -> 5.5 us)
+    const uint64_t units = ((uint64_t)n + per - 1) / per * g.passes, step = (uint64_t)gridDim.x * kWavesPerWg;
+    for (uint64_t u = (uint64_t)blockIdx.x * kWavesPerWg + wave_id(); u < units; u += step) {
+        const uint64_t i0 = u / g.passes * per;
         const uint32_t cnt = n - i0 < per ? (uint32_t)(n - i0) : per;
         const int64_t key = lane < cnt ? keys[i0 + lane] : 0;
         const uint32_t to = scatter_idx && lane < cnt ? scatter_idx[i0 + lane] : 0u;
-        for (uint32_t pass = 0; pass < g.passes; ++pass) {   // all lanes stay: each holds a key that others ask it for
-            const uint32_t c = (lane & (g.LPR - 1u)) + pass * g.LPR;
-            uint64_t inner[4];
+        const uint32_t c = (lane & (g.LPR - 1u)) + (uint32_t)(u % g.passes) * g.LPR;   // all lanes stay: each holds a key that others ask it for
+        uint64_t inner[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                inner[e] = mix64((((uint64_t)version << 32) | (c * 4u + (uint32_t)e)) + 0x9E3779B97F4A7C15ull);
-            for (uint32_t r0 = 0; r0 < cnt; r0 += rpi) {
-                const uint32_t r = r0 + sub;
-                const uint64_t k = (uint64_t)shfl64(key, (int)r);            // r < 64; lanes past cnt store nothing
-                const uint32_t w = (uint32_t)__shfl((int)to, (int)r, kWave);
-                float x[4];
+        for (int e = 0; e < 4; ++e)
+            inner[e] = mix64((((uint64_t)version << 32) | (c * 4u + (uint32_t)e)) + 0x9E3779B97F4A7C15ull);
+        for (uint32_t r0 = 0; r0 < cnt; r0 += rpi) {
+            const uint32_t r = r0 + sub;
+            const uint64_t k = (uint64_t)shfl64(key, (int)r);            // r < 64; lanes past cnt store nothing
+            const uint32_t w = (uint32_t)__shfl((int)to, (int)r, kWave);
+            float x[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint64_t z = mix64(k ^ inner[e]);
-                    x[e] = (float)((int32_t)(z >> 40) - (1 << 23)) * 0x1.0p-23f;   // exact: 24-bit integer * 2^-23
-                }
-                if (r < cnt && c < g.C) {
-                    const f32x4 v4 = {x[0], x[1], x[2], x[3]};
-                    if (rows) *reinterpret_cast<f32x4 *>(rows + (i0 + r) * g.d + c * 4) = v4;
-                    if (scatter_idx) *reinterpret_cast<f32x4 *>(scatter_out + (uint64_t)w * g.d + c * 4) = v4;
-                }
+            for (int e = 0; e < 4; ++e) {
+                const uint64_t z = mix64(k ^ inner[e]);
+                x[e] = (float)((int32_t)(z >> 40) - (1 << 23)) * 0x1.0p-23f;   // exact: 24-bit integer * 2^-23
+            }
+            if (r < cnt && c < g.C) {
+                const f32x4 v4 = {x[0], x[1], x[2], x[3]};
+                if (rows) *reinterpret_cast<f32x4 *>(rows + (i0 + r) * g.d + c * 4) = v4;
+                if (scatter_idx) *reinterpret_cast<f32x4 *>(scatter_out + (uint64_t)w * g.d + c * 4) = v4;
             }
         }
     }
@@ -2374,7 +2374,7 @@ hps_status_t hps_backing_fetch(const int64_t *keys, size_t n, const uint32_t *n_
         return fail(HPS_ERR_INVALID_ARG, "misaligned buffer");
     const RowGeom g = make_geom(dim);
     const uint64_t per_block = (uint64_t)kWavesPerWg * ((uint32_t)kWave >> g.lprShift);
-    uint64_t blocks = (n + per_block - 1) / per_block;
+    uint64_t blocks = (n + per_block - 1) / per_block * g.passes;
     if (blocks > kBackingWaves / kWavesPerWg) blocks = kBackingWaves / kWavesPerWg;
     hipLaunchKernelGGL(backing_kernel, dim3((uint32_t)blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream),
                        keys, (uint32_t)n, n_dev, version, g, rows, scatter_idx, scatter_out);

@@ -178,3 +178,19 @@ def test_a_wide_set_is_read_for_the_keys_of_a_wave_only():
             torch.cuda.synchronize()
             B.hps_cache_destroy(h)
     assert times[64] < 1.8 * times[8], f"us of 20 calls by ways: {times}"
+
+
+def test_few_long_rows_are_made_by_many_waves():
+    """hps_backing_fetch: 100 rows of 16 KiB against 1,600 of 1 KiB.  (The long ones over the
+    short ones: 1.0; 3.0 with a row to a wave.)"""
+    times = {}
+    busy = torch.empty(1 << 26, device="cuda")
+    for n, d in ((100, 4096), (1600, 256)):
+        keys, rows = torch.arange(n, device="cuda"), torch.empty(n, d, device="cuda")
+
+        def calls():
+            for _ in range(20):
+                B.hps_backing_fetch(keys, n, d, rows=rows)
+
+        times[d], = _median_us([calls], lambda: [busy.fill_(0.0) for _ in range(4)])
+    assert times[4096] < 1.4 * times[256], f"us of 20 calls by row length: {times}"
