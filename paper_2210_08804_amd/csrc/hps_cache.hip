@@ -171,14 +171,14 @@ __device__ __forceinline__ uint64_t read_epochs(const uint32_t *epoch) {
 // the two counts cost a call of a few keys 0.5 us and larger ones nothing (2^18 rows: 206.8 us with them,
 // 206.4 without).
 struct WriterGroup { uint32_t left, entered; };
-// Called by all threads of the work-group at the start.  Wave 0's count is on its way when it returns.
+// Called by all threads of the work-group at the start, with a barrier of the work-group to follow.  Wave 0's count is
+// on its way when it returns.
 __device__ __forceinline__ void writer_enter(const Table &tb, WriterGroup *w) {
     if (threadIdx.x == 0) {
         w->left = (uint32_t)kWavesPerWg;
         w->entered = 0u;
         __hip_atomic_fetch_add(epoch_of(tb, blockIdx.x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
 }
 // Wave 0, right after a wait for its outstanding memory operations, which covers the count: tells the
 // others.  Nothing that wave 0 does before depends on another wave.
@@ -1103,6 +1103,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
         return tile < n_tiles && lane < KPW && i < n ? a.keys[i] : kEmpty;
     };
     int64_t key = key_of(wave_global);
+    writer_enter(tb, &s_group);                             // its round trip runs beside that of the keys
     // Copies of a key among the first keys of the work-group: all of them write their number into the key's hash slot,
     // the one whose number stays carries the key, the others drop out (Alg. 3 ignores a key that is already there,
     // so only one copy can ever take effect).  A slot shared by different keys thins nothing.  Attempts on one set go one
@@ -1115,7 +1116,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
         s_first[place] = me;
         s_key[me] = key;
     }
-    writer_enter(tb, &s_group);
+    __syncthreads();
     if (!is_reserved(key)) {
         const uint32_t o = s_first[place];
         if (o != me && s_key[o] == key) key = kEmpty;
@@ -1132,12 +1133,14 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
         const uint32_t set = pending ? (tb.smask ? (hs & tb.smask) : (hs % tb.S)) : 0u;
 
         // Further tiles, which the waves reach at different times, are thinned wave by wave.
-        if (pending) s_owner[wave][h & (kWave * 2 - 1)] = (uint32_t)lane;
-        wave_lds_fence();
-        const int o = pending ? (int)s_owner[wave][h & (kWave * 2 - 1)] : lane;
-        const int64_t ko = shfl64(key, o);
-        if (pending && o != lane && ko == key) pending = false;
-        wave_lds_fence();
+        if (tile != wave_global) {
+            if (pending) s_owner[wave][h & (kWave * 2 - 1)] = (uint32_t)lane;
+            wave_lds_fence();
+            const int o = pending ? (int)s_owner[wave][h & (kWave * 2 - 1)] : lane;
+            const int64_t ko = shfl64(key, o);
+            if (pending && o != lane && ko == key) pending = false;
+            wave_lds_fence();
+        }
 
         uint32_t rounds = 0;
         while (__ballot(pending)) {
@@ -1281,6 +1284,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBl
     };
     int64_t key = key_of(wave_global);                      // requested before the work-group's barrier
     writer_enter(tb, &s_group);
+    __syncthreads();
     bool told = wave != 0;                                  // only wave 0 has something to tell
 
     for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves, key = key_of(tile)) {
