@@ -1256,8 +1256,8 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
 // Lanes of different groups that meet on a set compete by compare-and-swap on its word; no lane
 // waits while its wave owns a set.
 // Bound by memory: 1 GiB of cached rows refreshed in dump order at 4.6 TB/s of rows read and written.  Four waves per
-// SIMD (one GiB 445, 448 us with the five that the registers would allow; groups of 16 wave loads
-// instead of 8: 444 there, but 6 us more on 2^18 scattered rows).
+// SIMD (one GiB with its dump and query 444.5 us, 449.7 with the five that the registers would allow, on one device in turn;
+// groups of 16 wave loads instead of 8: equal there, but 6 us more on 2^18 scattered rows).
 template <int W, int KPW, bool kLong>
 __global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];

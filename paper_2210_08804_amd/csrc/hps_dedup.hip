@@ -16,8 +16,8 @@
 // on the table.  One that does (a caller's mistake) can take a number away again: the wait is therefore bounded
 // and ends with a flag (kMaxRounds).
 // Bound by the chain of dependent round trips (key, swap, counter, number).  Two launches, the second
-// looking every position up again, took 17.7 us for 106,496 keys (44 % distinct); this takes 12.1 us, 15.9 with a
-// load of the slot in front of each compare-and-swap (2,000 keys: 20.7, 12.0, 18.5).
+// looking every position up again, took 17.7 us of kernel time for 106,496 keys (44 % distinct); this takes 12.1 us, 15.9
+// with a load of the slot in front of each compare-and-swap.
 // The order of unique_keys is the order in which tiles reach the counter: unspecified.
 #include <hip/hip_runtime.h>
 
@@ -229,7 +229,7 @@ hps_status_t check_session(hps_dedup_session *s) {
 }
 
 // Keys per work-group: 1024; 512 for batches that would leave most CUs without a work-group, whose lanes then share
-// LDS slots with half as many others (2,000 keys 7.7 -> 6.7 us, 16,000 9.1 -> 7.3, 32,000 9.3 -> 8.1, 65,000 equal).
+// LDS slots with half as many others (kernel times: 2,000 keys 7.7 -> 6.7 us, 16,000 9.1 -> 7.3, 32,000 9.3 -> 8.1, 65,000 equal).
 //
 // Work-groups: one per tile, and more if those would have to wipe more than kWipe slots of the other table per
 // thread; the further ones only wipe.  Two calls of one size leave at most four slots per key, so a loop over equal
