@@ -48,8 +48,8 @@ constexpr uint64_t kMagic      = 0x4850534341434845ull;
 // rounds (a held set is released within microseconds; this many rounds take about a second) and
 // raises HPS_FLAG_STUCK_SET in the cache's flag word, so that no wave can spin forever.
 constexpr uint32_t kMaxRounds  = 1u << 16;
-// Longest row (in fp32) that a query may read while writers run: a row is read whole (8 wave loads
-// of 8 bytes per lane at this length) before it is validated and stored.
+// Longest row (in fp32) that a query may read while writers run: a row is read whole (4 wave loads
+// of 16 bytes per lane at this length) before it is validated and stored.
 constexpr uint32_t kMaxCheckedDim = 1024;
 // Writer epochs of a cache (see writer_enter): pairs of counters, one 256-byte line each.  Atomics
 // on one line execute one after the other, 11 ns each; 4,096 work-groups with two atomics each
@@ -115,8 +115,8 @@ template <typename T> __device__ __forceinline__ void st_agent(T *p, T v) {
 }
 
 // Data that kernels overlapping on different streams share (keys, rows, counters of the cache):
-// every such load/store is itself an agent-scope relaxed atomic of 4 or 8 bytes (global_load /
-// global_store with sc1: the access is performed at the memory side of the non-coherent per-XCD
+// every such load/store is itself an agent-scope relaxed atomic of 4 or 8 bytes, or for the rows that a query
+// reads a load of that scope of 16 (global_load / global_store with sc1: the access is performed at the memory side of the non-coherent per-XCD
 // L2s, so it sees and is seen by every other agent-scope access of the device), and the order
 // "sequence word, then data, then sequence word" is kept by waiting until the wave's outstanding
 // vector memory operations have completed (s_waitcnt vmcnt(0)) between the steps: a wave's vector
@@ -136,6 +136,12 @@ __device__ __forceinline__ void shared_acquire() { wait_vm0(); }
 __device__ __forceinline__ void shared_release() { wait_vm0(); }
 __device__ __forceinline__ uint64_t shared_ld64(const uint64_t *p) { return ld_agent(p); }
 __device__ __forceinline__ void shared_st64(uint64_t *p, uint64_t v) { st_agent(p, v); }
+// A 16-byte chunk of a row with the same scope, in one instruction that the compiler counts among the outstanding
+// operations like any other load.  It is no atomic and need not be: what a reader loaded of a row is used only
+// if no writer was at work on it (copy_rows_quiet, copy_rows_checked).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+__device__ __forceinline__ u32x4 shared_ld128(const u32x4 *p) { return __builtin_amdgcn_global_load_b128((global_u32x4 *)p, "agent"); }
 
 struct alignas(64) Table {     // one cache as the kernels see it (one 64-byte line of the kernel arguments)
     int64_t  *K;
@@ -324,28 +330,32 @@ __device__ __forceinline__ void copy_rows(const RowGeom g, const float *__restri
 }
 
 // copy_rows for a reader that found no writer at work when it read the epochs e1 (read_epochs).
-// Rows are loaded 8 bytes per lane with shared_ld64, in groups of U wave loads, all of a group's
+// Rows are loaded 16 bytes per lane with shared_ld128, in groups of U wave loads, all of a group's
 // loads in flight together; once they have completed the epochs are read again, and only if no
 // writer has started meanwhile are the group's rows stored.  A row is always read whole inside one
-// group (the longest, 4 KiB, takes 8 wave loads, which is why U >= 8 and why kMaxCheckedDim is
+// group (the longest, 4 KiB, takes 4 wave loads, which is why U >= 4 and why kMaxCheckedDim is
 // 1024): a position whose key turns out to be gone when the rest is looked up again has had nothing
-// written to its `out` row.  Returns how many rows of the list are done; the caller goes through
+// written to its `out` row.  With kD = 128 two rows go in a wave load; behind a list of an odd number of rows its
+// last entry stands once more (written by the caller), so that no lane needs a condition.
+// Bound by memory, and before that by the loads' issue: half as many of them as with 8 bytes per lane take 106,496
+// keys of 512 bytes from 19.7 to 18.0 us, 425,984 from 73 to 65, 851,968 of 128 bytes from 54 to 50, 20,000 of 4 KiB from 32.7 to 28.  Returns how many rows of the list are done; the caller goes through
 // the others again with copy_rows_checked.
 template <int U, int kD = 0>
 __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float *__restrict__ src,
                                                     float *__restrict__ dst, const uint64_t *srcRow,
                                                     const uint32_t *dstRow, uint32_t cnt,
                                                     uint64_t e1, const uint32_t *epoch) {
-    static_assert((kD == 0 || kD == 128) && U >= 8 && (kD || U % 4 == 0), "a 512-byte row is one wave load of 8 bytes per lane");
+    static_assert((kD == 0 || kD == 128) && U >= 4 && (kD || U % 4 == 0), "a 512-byte row is half a wave load");
     constexpr int Q = kD ? 1 : 4;                                    // wave loads per test for the end of the list
     const uint32_t lane = (uint32_t)lane_id();
     const uint64_t d = kD ? (uint64_t)kD : (uint64_t)g.d;
-    const uint32_t C = kD ? 64u : g.c8.C;
-    const uint32_t span = kD ? (uint32_t)U : (uint32_t)(U * kWave) / C;   // rows per group
-    const ChunkWalk start(g.c8, lane);
+    const uint32_t C = kD ? 32u : g.c16.C;
+    const uint32_t span = kD ? (uint32_t)(2 * U) : (uint32_t)(U * kWave) / C;   // rows per group
+    const ChunkWalk start(g.c16, lane);
     for (uint32_t e0 = 0; e0 < cnt; e0 += span) {
-        const uint32_t total = (cnt - e0 < span ? cnt - e0 : span) * C;   // chunks of the group
-        uint64_t buf[U];
+        const uint32_t rows = cnt - e0 < span ? cnt - e0 : span;
+        const uint32_t total = rows * C;                             // chunks of the group
+        u32x4 buf[U];
         ChunkWalk in = start, out = start;
         if (!kD) {
             in.forget();
@@ -357,10 +367,10 @@ __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float
 #pragma unroll
                 for (int u = b; u < b + Q; ++u) {
                     const bool live = kD || u * kWave + lane < total;
-                    const uint32_t r = kD ? (uint32_t)u : live ? in.r : 0u;
-                    const uint32_t c = kD ? lane : live ? in.c : 0u;
-                    buf[u] = shared_ld64(reinterpret_cast<const uint64_t *>(src + srcRow[e0 + r] * d) + c);
-                    if (!kD) in.next(g.c8);
+                    const uint32_t r = kD ? 2 * u + (lane >> 5) : live ? in.r : 0u;
+                    const uint32_t c = kD ? lane & 31u : live ? in.c : 0u;
+                    buf[u] = shared_ld128(reinterpret_cast<const u32x4 *>(src + srcRow[e0 + r] * d) + c);
+                    if (!kD) in.next(g.c16);
                 }
             }
         }
@@ -373,8 +383,8 @@ __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float
                 for (int u = b; u < b + Q; ++u) {
                     if (kD || u * kWave + lane < total)
                         __builtin_nontemporal_store(
-                            buf[u], reinterpret_cast<uint64_t *>(dst + (uint64_t)dstRow[e0 + (kD ? (uint32_t)u : out.r)] * d) + (kD ? lane : out.c));
-                    if (!kD) out.next(g.c8);
+                            buf[u], reinterpret_cast<u32x4 *>(dst + (uint64_t)dstRow[e0 + (kD ? 2 * u + (lane >> 5) : out.r)] * d) + (kD ? lane & 31u : out.c));
+                    if (!kD) out.next(g.c16);
                 }
             }
         }
@@ -384,7 +394,7 @@ __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float
 
 // copy_rows for a reader that overlaps writers (seqlock read side).  Entry e also carries
 // the set it came from and the value v1 of that set's sequence word read before the probe.
-// Rows are loaded into registers (8 bytes per lane, shared_ld64), then the sequence words are
+// Rows are loaded into registers (16 bytes per lane, shared_ld128), then the sequence words are
 // read again once those loads have completed; a row is stored only if its word is unchanged,
 // i.e. no writer touched the set while the row was being read.  Entries to redo are flagged in
 // the LDS word pair `retry`.
@@ -399,18 +409,18 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
                                                   const uint32_t *dstRow, const uint32_t *setOf,
                                                   const uint32_t *v1Of, const uint32_t *sc,
                                                   uint32_t cnt, uint32_t *retry) {
-    static_assert((kD == 0 || kD == 128) && U >= 8, "a 512-byte row is one wave load of 8 bytes per lane");
+    static_assert((kD == 0 || kD == 128) && U >= 4, "a 512-byte row is half a wave load");
     const uint32_t lane = (uint32_t)lane_id();
     const uint64_t d = kD ? (uint64_t)kD : (uint64_t)g.d;
-    const uint32_t C = kD ? 64u : g.c8.C;
+    const uint32_t C = kD ? 32u : g.c16.C;
     // rows per group: one lane per row re-reads its sequence word, so a group has at most 64 rows
-    uint32_t span = kD ? (uint32_t)U : (uint32_t)(U * kWave) / C;
+    uint32_t span = kD ? (uint32_t)(2 * U) : (uint32_t)(U * kWave) / C;
     span = span < (uint32_t)kWave ? span : (uint32_t)kWave;
-    const ChunkWalk start(g.c8, lane);
+    const ChunkWalk start(g.c16, lane);
     for (uint32_t e0 = 0; e0 < cnt; e0 += span) {
         const uint32_t rows = cnt - e0 < span ? cnt - e0 : span;
         const uint32_t total = rows * C;                             // chunks of the group
-        uint64_t buf[U];
+        u32x4 buf[U];
         ChunkWalk in = start, out = start;
         if (!kD) {
             in.forget();
@@ -420,24 +430,24 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
         for (int u = 0; u < U; ++u) {
             if ((uint32_t)u * kWave < total) {                       // uniform: there are chunks left
                 const bool live = kD || u * kWave + lane < total;
-                const uint32_t r = kD ? (uint32_t)u : live ? in.r : 0u;
-                const uint32_t c = kD ? lane : live ? in.c : 0u;
-                buf[u] = shared_ld64(reinterpret_cast<const uint64_t *>(src + srcRow[e0 + r] * d) + c);
-                if (!kD) in.next(g.c8);
+                const uint32_t r = kD ? 2 * u + (lane >> 5) : live ? in.r : 0u;
+                const uint32_t c = kD ? lane & 31u : live ? in.c : 0u;
+                buf[u] = shared_ld128(reinterpret_cast<const u32x4 *>(src + srcRow[e0 + r] * d) + c);
+                if (!kD) in.next(g.c16);
             }
         }
         shared_acquire();                                            // row loads complete before the re-read
-        const bool mine = lane < rows;
+        const bool mine = lane < rows + (kD ? rows & 1u : 0u);       // (the entry behind an odd list is a copy of its last)
         const uint32_t v2 = mine ? ld_agent(sc + 2ull * setOf[e0 + lane]) : 0u;
         const uint64_t bad = __ballot(mine && v2 != v1Of[e0 + lane]);   // bit r: row e0 + r was touched by a writer
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if ((uint32_t)u * kWave < total) {
-                const uint32_t r = kD ? (uint32_t)u : out.r;
-                const uint32_t c = kD ? lane : out.c;
+                const uint32_t r = kD ? 2 * u + (lane >> 5) : out.r;
+                const uint32_t c = kD ? lane & 31u : out.c;
                 if ((kD || u * kWave + lane < total) && !((bad >> r) & 1ull))
-                    __builtin_nontemporal_store(buf[u], reinterpret_cast<uint64_t *>(dst + (uint64_t)dstRow[e0 + r] * d) + c);
-                if (!kD) out.next(g.c8);
+                    __builtin_nontemporal_store(buf[u], reinterpret_cast<u32x4 *>(dst + (uint64_t)dstRow[e0 + r] * d) + c);
+                if (!kD) out.next(g.c16);
             }
         }
         if (bad && lane == 0) {                                      // e0 + rows <= cnt <= 64
@@ -717,7 +727,7 @@ __device__ __forceinline__ void finish_call(const QueryArgs &a, uint32_t n_miss,
 // in every kernel the three cost 0.4 us of a 19 us launch.)
 template <int W, int KPW, int U, int WPB, bool kCoherent, int kD = 0, bool kFull = false>
 __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArgs a) {
-    __shared__ uint64_t s_src[WPB][KPW];
+    __shared__ uint64_t s_src[WPB][KPW];                // (an odd number of rows is less than KPW: room for its copied last entry)
     __shared__ uint32_t s_dst[WPB][KPW];
     __shared__ int64_t  s_mkey[WPB][KPW];
     __shared__ uint32_t s_mpos[WPB][KPW];
@@ -784,12 +794,16 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                     way = probe_wave<W, KPW, true>(tb.K, key, set, want, kpw);
                     const uint64_t fmask = __ballot(way >= 0);
                     const int r = rank_in(fmask);
+                    const uint32_t nf = (uint32_t)__popcll(fmask);
                     if (way >= 0) {
                         s_src[wave][r] = (uint64_t)set * W + (uint32_t)way;
                         s_dst[wave][r] = pos;
+                        if (kD && (nf & 1u) && r + 1 == (int)nf) {
+                            s_src[wave][nf] = (uint64_t)set * W + (uint32_t)way;
+                            s_dst[wave][nf] = pos;
+                        }
                     }
                     wave_lds_fence();
-                    const uint32_t nf = (uint32_t)__popcll(fmask);
                     const uint32_t done = copy_rows_quiet<U, kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], nf, e1, tb.epoch);
                     hit = way >= 0 && (uint32_t)r < done;
                     pending = way >= 0 && !hit;                      // a miss is final, as below
@@ -815,10 +829,17 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                         s_dst[wave][r] = pos;
                         s_set[wave][r] = set;
                         s_v1[wave][r]  = v1;
+                        const uint32_t nf = (uint32_t)__popcll(fmask);
+                        if (kD && (nf & 1u) && r + 1 == (int)nf) {
+                            s_src[wave][nf] = (uint64_t)set * W + (uint32_t)w;
+                            s_dst[wave][nf] = pos;
+                            s_set[wave][nf] = set;
+                            s_v1[wave][nf]  = v1;
+                        }
                     }
                     wave_lds_fence();
                     if (fmask)
-                        copy_rows_checked<(kD ? U : 16), kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
+                        copy_rows_checked<(kD ? U : 8), kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
                                                              &s_v1[wave][0], tb.sc, (uint32_t)__popcll(fmask), &s_retry[wave][0]);
                     wave_lds_fence();
                     bool again = false;
@@ -1750,7 +1771,7 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // counter atomics and by the number of keys in flight: 15 workers 42.9, 7 workers 44.5 at 851,968 keys of
 // 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7; nor do sets of more than 16 ways, whose keys spill
 // (300,000 keys of 128 bytes, 32 / 64 ways: 15 workers 34.4 / 52.0, 7 workers 20.1 / 24.5).
-// Checked (4 / 7 workers): 5,000 keys of 512 bytes 7.2 / 7.7, 8,192 keys 7.9 / 8.0, 13,312 keys 9.0 / 8.6, of 256 bytes
+// Checked (4 / 7 workers): 5,000 keys of 512 bytes 6.6 / 7.0, 8,192 keys 7.9 / 8.0, 13,312 keys 9.0 / 8.6, of 256 bytes
 // 8.8 / 8.3, 26,624 keys of 128 bytes 9.3 / 9.0, 106,496 keys of 128 bytes 14.2 / 11.6.
 //
 // Keys per wave: at most 64, trimmed so that the work-groups come out as a whole number of rounds
@@ -1764,11 +1785,11 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
 // hold, and its code, all of it executed, lines that a short launch has to fetch.  64 keys of 128 bytes in groups
 // of 8 / 16 / 32 wave loads take 44.5 / 50.0 / 63.7 per 851,968 keys, 39,999 keys of 1,280 bytes in groups of 24 / 16
-// with idle lanes 19.4 / 24.1, 26,624 keys of 512 bytes in groups of 13 / 26 9.7 / 10.6.  Checked, 8 bytes per lane, rows
-// of 512 bytes: 832 keys in groups of 8 / 64 6.2 / 7.8, 13,312 keys 16 / 64 8.6 / 10.8, 26,624 keys 32 / 64 10.5 / 12.0,
-// 56,000 keys 32 / 64 13.0 / 13.6; 106,496 keys of 384 bytes in groups of 64 / 32 / 16 17.0 / 18.4 / 19.1, of 256
-// bytes in groups of 32 / 16 13.9 / 15.3; but over several rounds (425,984 keys) 51.4 / 46.6: there the second
-// work-group that fits a CU with the smaller group is worth more.
+// with idle lanes 19.4 / 24.1, 26,624 keys of 512 bytes in groups of 13 / 26 9.7 / 10.6.  Checked, rows
+// of 512 bytes: 13,312 keys in groups of 8 / 32 7.9 / 8.4, 26,624 keys 16 / 32 9.8 / 10.2, 106,496 keys 32 / 16 18.0 / 20.4,
+// 425,984 keys 32 / 16 67 / 75; 106,496 keys of 384 bytes 32 / 16 15.3 / 17.3, of 256 bytes 16 / 8 12.4 / 14.1; 39,999 keys of
+// 1,280 bytes 32 / 16 17.2 / 18.4; but 851,968 keys of 128 bytes 8 / 16 50 / 60: over several rounds the second
+// work-group that fits a CU with the smaller group is worth more, as long as a wave's rows are one group or two.
 struct QueryShape { uint32_t kpw; int u, wpb; };
 
 // Most rows of d words that a wave moves with copy_rows, which counts their 16-byte chunks in 32 bits (fewer than 64
@@ -1796,10 +1817,10 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     if (!dedup && q.kpw > most_rows(d)) q.kpw = (uint32_t)most_rows(d);
     const uint64_t bytes = (uint64_t)q.kpw * d * 4;            // a wave's rows
     if (coherent) {
-        if (d == 128 && q.wpb == 4) q.u = q.kpw <= 8 ? 8 : 16;
-        else if (d == 128) q.u = q.kpw <= 16 ? 16 : q.kpw <= 32 ? 32 : 64;
-        else if (bytes > 16384) q.u = 64;
-        else q.u = bytes <= 8192 || rounds > 1 ? 16 : 32;
+        if (d == 128 && q.wpb == 4) q.u = q.kpw <= 8 ? 4 : 8;
+        else if (d == 128) q.u = q.kpw <= 16 ? 8 : q.kpw <= 32 ? 16 : 32;
+        else if (bytes > 16384) q.u = 32;
+        else q.u = bytes <= 8192 || rounds > 1 ? 8 : 16;
     } else if (d == 128) {
         q.u = q.wpb == 7 ? 32 : q.kpw <= 16 ? 8 : q.kpw <= 26 && q.wpb == 8 ? 13 : 26;
     } else {
@@ -1833,17 +1854,17 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
         else launch_query_dedup<W, 8>(a, st);
     } else if (coherent) {
         switch (d128 ? 10000 + id : id) {
+            case 10404: launch_query_kernel<W, 4, 4, true, 128>(a, full, st); break;
             case 10804: launch_query_kernel<W, 8, 4, true, 128>(a, full, st); break;
-            case 11604: launch_query_kernel<W, 16, 4, true, 128>(a, full, st); break;
+            case 10807: launch_query_kernel<W, 8, 7, true, 128>(a, full, st); break;
             case 11607: launch_query_kernel<W, 16, 7, true, 128>(a, full, st); break;
             case 13207: launch_query_kernel<W, 32, 7, true, 128>(a, full, st); break;
-            case 16407: launch_query_kernel<W, 64, 7, true, 128>(a, full, st); break;
+            case 804: launch_query_kernel<W, 8, 4, true, 0>(a, full, st); break;
             case 1604: launch_query_kernel<W, 16, 4, true, 0>(a, full, st); break;
             case 3204: launch_query_kernel<W, 32, 4, true, 0>(a, full, st); break;
-            case 6404: launch_query_kernel<W, 64, 4, true, 0>(a, full, st); break;
+            case 807: launch_query_kernel<W, 8, 7, true, 0>(a, full, st); break;
             case 1607: launch_query_kernel<W, 16, 7, true, 0>(a, full, st); break;
             case 3207: launch_query_kernel<W, 32, 7, true, 0>(a, full, st); break;
-            case 6407: launch_query_kernel<W, 64, 7, true, 0>(a, full, st); break;
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
     } else {
