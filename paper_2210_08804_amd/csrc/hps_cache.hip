@@ -115,8 +115,8 @@ template <typename T> __device__ __forceinline__ void st_agent(T *p, T v) {
 }
 
 // Data that kernels overlapping on different streams share (keys, rows, counters of the cache):
-// every such load/store is itself an agent-scope relaxed atomic of 4 or 8 bytes, or for the rows that a query
-// reads a load of that scope of 16 (global_load / global_store with sc1: the access is performed at the memory side of the non-coherent per-XCD
+// every such load/store is itself an agent-scope relaxed atomic of 4 or 8 bytes, or for rows an
+// access of that scope of 16 (global_load / global_store with sc1: the access is performed at the memory side of the non-coherent per-XCD
 // L2s, so it sees and is seen by every other agent-scope access of the device), and the order
 // "sequence word, then data, then sequence word" is kept by waiting until the wave's outstanding
 // vector memory operations have completed (s_waitcnt vmcnt(0)) between the steps: a wave's vector
@@ -137,11 +137,12 @@ __device__ __forceinline__ void shared_release() { wait_vm0(); }
 __device__ __forceinline__ uint64_t shared_ld64(const uint64_t *p) { return ld_agent(p); }
 __device__ __forceinline__ void shared_st64(uint64_t *p, uint64_t v) { st_agent(p, v); }
 // A 16-byte chunk of a row with the same scope, in one instruction that the compiler counts among the outstanding
-// operations like any other load.  It is no atomic and need not be: what a reader loaded of a row is used only
-// if no writer was at work on it (copy_rows_quiet, copy_rows_checked).
+// operations like any other.  It is no atomic and need not be: a row is only stored by the one that holds its set, and what
+// a reader loaded of it is used only if no writer was at work on it (copy_rows_quiet, copy_rows_checked).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 __device__ __forceinline__ u32x4 shared_ld128(const u32x4 *p) { return __builtin_amdgcn_global_load_b128((global_u32x4 *)p, "agent"); }
+__device__ __forceinline__ void shared_st128(u32x4 *p, u32x4 v) { __builtin_amdgcn_global_store_b128((global_u32x4 *)p, v, "agent"); }
 
 struct alignas(64) Table {     // one cache as the kernels see it (one 64-byte line of the kernel arguments)
     int64_t  *K;
@@ -225,7 +226,7 @@ struct RowGeom {
     uint32_t LPR;              // lanes per row: min(64, next power of two >= C)
     uint32_t lprShift;         // log2(LPR)
     uint32_t passes;           // ceil(C / LPR): > 1 only for rows longer than 1 KiB
-    uint32_t LPR8, lpr8Shift;  // lanes per row of 8-byte chunks: min(64, next power of two >= d/2)
+    uint32_t LPR8, lpr8Shift;  // the same with 8-byte chunks (the writers' long rows): min(64, next power of two >= d/2)
     ChunkStep c16, c8;         // walks over the 16-byte and the 8-byte chunks (scoped accesses) of a list of rows
 };
 
@@ -458,24 +459,41 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
     }
 }
 
-// Writer side: the rows listed in LDS go from the caller's batch into the cache with shared_st64 (8 bytes
-// per lane), so that overlapping readers observe them without cache flushes.  start() requests the
+// Writer side: the rows listed in LDS go from the caller's batch into the cache with agent-scope stores, so that
+// overlapping readers observe them without cache flushes.  start() requests the
 // first two groups of U wave loads; finish() stores them and moves what is left, each group's loads
 // issued before the stores of the group ahead of it, so that a write-through store's long
 // acknowledgement never sits between a wave and its next loads.  The two halves are apart because
 // which rows are read may be known long before it is known which of them are to be stored.
-// Rows of up to 512 bytes (kLong false) take LPR8 lanes each, a whole number of them per wave load; longer
-// ones go through the walk over the chunks of the list, so that no wave load is partly idle and
+// Rows of up to 1 KiB (kLong false) take LPR lanes of 16 bytes each, a whole number of them per wave load; longer
+// ones go, 8 bytes per lane, through the walk over the chunks of the list, so that no wave load is partly idle and
 // the parts of a row are in flight together (30,000 rows of 1,280 bytes inserted, updated and queried:
-// 93.6 us when each 512-byte part of the rows was a pass of its own, 71 us with the walk).  For short
-// rows the walk's arithmetic costs more than it saves (400-byte rows 41.7 against 38.7 us).
-// (Groups of 16 or 32 wave loads all in flight before the first store, which is what the query's copy
-// does, cost the writers occupancy and time: insert 102 us against 83 us per 2^18 rows, update 118
+// 93.6 us when each 512-byte part of the rows was a pass of its own, 71 us with the walk).  For shorter
+// rows the walk's arithmetic costs more than it saves (400-byte rows 41.7 against 38.7 us, 30,000 rows of 768 / 1,024 bytes inserted,
+// updated and queried 55.9 / 61.9 against 54.4 / 60.4).
+// Bound by memory and by the chain around the copy.  16 bytes per lane instead of 8, half as many loads and stores: 2^18 rows of 512
+// bytes inserted, updated and queried 206.3 -> 197.2 us, 200,000 rows of 400 bytes 172 -> 159, 1 GiB of rows refreshed 446 -> 438.
+// (Twice as many wave loads in flight, U = 8: 200.4 and 441 us.  Plain write-back stores 198.1 and 455, non-temporal ones 213 and 424, and
+// neither could be seen by a reader in time.  Groups of 16 or 32 wave loads all in flight before the first store, which is
+// what the query's copy does, cost the writers occupancy and time, measured with 8 bytes per lane: insert 102 us against 83 us per 2^18 rows, update 118
 // against 81 us.)
 constexpr uint64_t kSkipRow = ~0ull;             // dstRow of an entry that finish() is not to store
 
+// What a lane moves of a row at a time: 8 bytes of a long row, 16 of a shorter one (below).
+template <bool kLong>
+struct RowPiece {
+    typedef uint64_t type;
+    static __device__ __forceinline__ type load(const float *row, uint32_t c) { return __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(row) + c); }
+    static __device__ __forceinline__ void store(float *row, uint32_t c, type v) { shared_st64(reinterpret_cast<uint64_t *>(row) + c, v); }
+    static __device__ __forceinline__ const ChunkStep &step(const RowGeom &g) { return g.c8; }
+    static __device__ __forceinline__ uint32_t lanes(const RowGeom &g) { return g.LPR8; }
+    static __device__ __forceinline__ uint32_t shift(const RowGeom &g) { return g.lpr8Shift; }
+};
+
 template <int U, bool kLong>
 struct RowMover {
+    typedef RowPiece<kLong> P;
+    typedef typename P::type Chunk;
     const RowGeom &g;
     const float *const src;
     float *const dst;
@@ -483,14 +501,14 @@ struct RowMover {
     const uint64_t *const dstRow;
     uint32_t cnt;
     ChunkWalk in, out;
-    uint64_t bufA[U], bufB[U];
+    Chunk bufA[U], bufB[U];
 
     __device__ __forceinline__ RowMover(const RowGeom &g_, const float *src_, float *dst_, const uint32_t *srcRow_, const uint64_t *dstRow_)
-        : g(g_), src(src_), dst(dst_), srcRow(srcRow_), dstRow(dstRow_), cnt(0), in(g_.c8, (uint32_t)lane_id()), out(in) {}
+        : g(g_), src(src_), dst(dst_), srcRow(srcRow_), dstRow(dstRow_), cnt(0), in(P::step(g_), (uint32_t)lane_id()), out(in) {}
 
     // Wave load k of the list: does it hold rows at all (uniform), does this lane have one, which row, which chunk of it.
     __device__ __forceinline__ bool any(uint32_t k) const {
-        return kLong ? (uint64_t)k * kWave < (uint64_t)cnt * g.c8.C : (k << (6u - g.lpr8Shift)) < cnt;
+        return kLong ? (uint64_t)k * kWave < (uint64_t)cnt * P::step(g).C : (k << (6u - P::shift(g))) < cnt;
     }
     __device__ __forceinline__ bool place(uint32_t k, ChunkWalk &w, uint32_t &r, uint32_t &c) const {
         const uint32_t lane = (uint32_t)lane_id();
@@ -499,33 +517,33 @@ struct RowMover {
             live = w.r < cnt;
             r = live ? w.r : 0u;
             c = live ? w.c : 0u;
-            w.next(g.c8);
+            w.next(P::step(g));
         } else {
-            const uint32_t e = (k << (6u - g.lpr8Shift)) + (lane >> g.lpr8Shift);
+            const uint32_t e = (k << (6u - P::shift(g))) + (lane >> P::shift(g));
             live = e < cnt;
             r = live ? e : 0u;
-            c = lane & (g.LPR8 - 1u);
-            c = c < g.c8.C ? c : 0u;
+            c = lane & (P::lanes(g) - 1u);
+            c = c < P::step(g).C ? c : 0u;
         }
         return live;
     }
-    __device__ __forceinline__ void load(uint32_t k, uint64_t (&buf)[U]) {       // lanes past the list read entry 0
+    __device__ __forceinline__ void load(uint32_t k, Chunk (&buf)[U]) {       // lanes past the list read entry 0
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             uint32_t r, c;
             (void)place(k + u, in, r, c);
-            buf[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (uint64_t)srcRow[r] * g.d) + c);
+            buf[u] = P::load(src + (uint64_t)srcRow[r] * g.d, c);
         }
     }
     // A whole group of rows that are all to be stored goes out in one piece.  Otherwise the wait comes first: the
     // compiler cannot count predicated stores among the outstanding operations.
-    __device__ __forceinline__ void put(uint32_t k, const uint64_t (&buf)[U], bool all) {
+    __device__ __forceinline__ void put(uint32_t k, const Chunk (&buf)[U], bool all) {
         if (all && any(k + U - 1)) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 uint32_t r, c;
                 (void)place(k + u, out, r, c);
-                shared_st64(reinterpret_cast<uint64_t *>(dst + dstRow[r] * g.d) + c, buf[u]);
+                P::store(dst + dstRow[r] * g.d, c, buf[u]);
             }
         } else {
             wait_vm0();
@@ -535,14 +553,14 @@ struct RowMover {
                 uint32_t r, c;
                 const bool live = place(k + u, out, r, c);
                 const uint64_t row = dstRow[r];
-                if (live && row != kSkipRow) shared_st64(reinterpret_cast<uint64_t *>(dst + row * g.d) + c, buf[u]);
+                if (live && row != kSkipRow) P::store(dst + row * g.d, c, buf[u]);
             }
         }
     }
     __device__ __forceinline__ void start(uint32_t cnt_) {
         cnt = cnt_;
         if (kLong) {
-            in = out = ChunkWalk(g.c8, (uint32_t)lane_id());
+            in = out = ChunkWalk(P::step(g), (uint32_t)lane_id());
             out.forget();
         }
         load(0, bufA);
@@ -565,36 +583,38 @@ template <int U, bool kLong>
 __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *__restrict__ src,
                                                  float *dst, const uint32_t *srcRow,
                                                  const uint64_t *dstRow, uint32_t cnt) {
+    typedef RowPiece<kLong> P;
+    typedef typename P::type Chunk;
     const uint32_t lane = (uint32_t)lane_id();
-    const uint32_t rpi = (uint32_t)kWave >> g.lpr8Shift;
-    const uint32_t sub = lane >> g.lpr8Shift;
-    uint32_t cl = lane & (g.LPR8 - 1);
-    cl = cl < g.c8.C ? cl : 0u;
+    const uint32_t rpi = (uint32_t)kWave >> P::shift(g);
+    const uint32_t sub = lane >> P::shift(g);
+    uint32_t cl = lane & (P::lanes(g) - 1);
+    cl = cl < P::step(g).C ? cl : 0u;
     typedef typename std::conditional<kLong, uint64_t, uint32_t>::type Count;   // 16 rows of 2 GiB have 2^32 chunks
     const Count step = kLong ? (Count)(kWave * U) : (Count)(rpi * U);
-    const Count total = kLong ? (Count)cnt * g.c8.C : (Count)cnt;     // chunks, or rows
-    uint64_t bufA[U], bufB[U];
+    const Count total = kLong ? (Count)cnt * P::step(g).C : (Count)cnt;     // chunks, or rows
+    Chunk bufA[U], bufB[U];
     uint32_t entA[U], entB[U], offA[kLong ? U : 1], offB[kLong ? U : 1];
-    ChunkWalk in(g.c8, lane);
-    auto load = [&](Count q0, uint64_t (&buf)[U], uint32_t (&ent)[U], uint32_t *off) {
+    ChunkWalk in(P::step(g), lane);
+    auto load = [&](Count q0, Chunk (&buf)[U], uint32_t (&ent)[U], uint32_t *off) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (kLong) {
                 const bool live = in.r < cnt;
                 ent[u] = live ? in.r : 0u;
                 off[u] = live ? in.c : 0u;
-                in.next(g.c8);
+                in.next(P::step(g));
             } else {
                 const uint32_t e = (uint32_t)q0 + u * rpi + sub;
                 ent[u] = e < cnt ? e : 0u;
             }
-            buf[u] = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (uint64_t)srcRow[ent[u]] * g.d) + (kLong ? off[u] : cl));
+            buf[u] = P::load(src + (uint64_t)srcRow[ent[u]] * g.d, kLong ? off[u] : cl);
         }
     };
-    auto store = [&](const uint64_t (&buf)[U], const uint32_t (&ent)[U], const uint32_t *off) {
+    auto store = [&](const Chunk (&buf)[U], const uint32_t (&ent)[U], const uint32_t *off) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            shared_st64(reinterpret_cast<uint64_t *>(dst + dstRow[ent[u]] * g.d) + (kLong ? off[u] : cl), buf[u]);
+            P::store(dst + dstRow[ent[u]] * g.d, kLong ? off[u] : cl, buf[u]);
     };
     load(0, bufA, entA, offA);
     for (Count q0 = 0;; q0 += 2 * step) {
@@ -661,6 +681,17 @@ template <int W, int KPW, bool kShared = false>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want, uint32_t lanes = KPW) {
     return probe_wave<W, KPW, kShared>(K, key, set, want, [] {}, lanes);
 }
+
+// A shorter row's piece.
+template <>
+struct RowPiece<false> {
+    typedef u32x4 type;
+    static __device__ __forceinline__ type load(const float *row, uint32_t c) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row) + c); }
+    static __device__ __forceinline__ void store(float *row, uint32_t c, type v) { shared_st128(reinterpret_cast<u32x4 *>(row) + c, v); }
+    static __device__ __forceinline__ const ChunkStep &step(const RowGeom &g) { return g.c16; }
+    static __device__ __forceinline__ uint32_t lanes(const RowGeom &g) { return g.LPR; }
+    static __device__ __forceinline__ uint32_t shift(const RowGeom &g) { return g.lprShift; }
+};
 
 // ------------------------------------------------------------------ query
 
@@ -1143,7 +1174,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
         if (o != me && s_key[o] == key) key = kEmpty;
     }
     bool told = wave != 0;                                  // only wave 0 has something to tell
-    RowMover<8, kLong> rows(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0]);
+    RowMover<(kLong ? 8 : 4), kLong> rows(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0]);
 
     for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves, key = key_of(tile)) {
         const uint32_t i = tile * KPW + lane;
@@ -1277,8 +1308,8 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
 // Lanes of different groups that meet on a set compete by compare-and-swap on its word; no lane
 // waits while its wave owns a set.
 // Bound by memory: 1 GiB of cached rows refreshed in dump order at 4.6 TB/s of rows read and written.  Four waves per
-// SIMD (one GiB with its dump and query 444.5 us, 449.7 with the five that the registers would allow, on one device in turn;
-// groups of 16 wave loads instead of 8: equal there, but 6 us more on 2^18 scattered rows).
+// SIMD (one GiB with its dump and query 438 us, 446 with the six that the registers would allow, on one device in turn;
+// twice as many wave loads in flight: 2 us more there, 3 us more on 2^18 scattered rows).
 template <int W, int KPW, bool kLong>
 __global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
@@ -1379,7 +1410,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBl
                     s_srcrow[wave][r] = i;
                 }
                 wave_lds_fence();
-                copy_rows_shared<8, kLong>(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0], (uint32_t)__popcll(actmask));
+                copy_rows_shared<(kLong ? 8 : 4), kLong>(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0], (uint32_t)__popcll(actmask));
                 wave_lds_fence();
                 shared_release();                                    // rows land before the word moves on
                 if (won) st_agent(seq_of(tb, set), v + 2u);
@@ -1926,7 +1957,7 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
     if (blocks > (1u << 16)) blocks = 1u << 16;
     const dim3 grid((uint32_t)blocks), block(kBlock);
-    const bool lng = c->d > 128;               // rows of more than one wave load of 8 bytes per lane
+    const bool lng = c->d > 256;               // rows of more than one wave load
     switch (c->W) {
 #define HPS_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, 0, st, a)
 #define HPS_CASE(w)                                                                         \

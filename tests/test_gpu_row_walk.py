@@ -73,3 +73,21 @@ def test_shapes_by_batch_and_width(d, n, mode):
         others = _hold_a_set(gc, oc, 6 * n_keys) if mode == "held" else None
         _compare(gc, oc, rng.integers(0, 6 * n_keys, size=n, dtype=np.int64) if others is None else rng.choice(others, n), d)
         oc.close()
+
+
+@pytest.mark.parametrize("n", [5000, 33000])
+@pytest.mark.parametrize("d", [4, 60, 64, 124, 192, 256, 260])
+def test_writers_by_width(d, n):
+    """Rows that divide a wave's lanes and rows that do not, up to and above one wave load, in batches on both sides of the
+    writers' shapes."""
+    S, W = 131071, 8                         # no set gets more than W keys
+    keys = np.arange(n, dtype=np.int64) * 3 + 1
+    with DeviceCache(S * W, W, d) as gc:
+        oc = OracleCache(S * W, W, d)
+        for version, write in ((0, "insert"), (1, "update")):
+            batch = keys[version::2].copy() if version else keys
+            rows = inputs.backing_rows(batch, d, version=version)
+            getattr(gc, write)(batch, rows)
+            getattr(oc, write)(batch, rows)
+        _compare(gc, oc, keys, d)
+        oc.close()
