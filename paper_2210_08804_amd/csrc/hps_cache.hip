@@ -682,6 +682,57 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
     return probe_wave<W, KPW, kShared>(K, key, set, want, [] {}, lanes);
 }
 
+// probe_wave for an insert with the LRU policy: the stamps of the sets travel with their keys, and `victim` becomes the way that
+// a new key takes (Alg. 3): the lowest empty one, else that of the oldest stamp, the lowest of them.  W lanes work on a set, so
+// the choice costs no round trip; a lane that asked for its W keys and stamps by itself, behind the search, waited for most of them
+// one by one (8 ways, 512-byte rows, new keys: 262,144 over 2^20 sets 113.9 -> 82.4 us, 70,000 over 2^16 48.9 -> 38.8, 8,192 over 2^11 41.5 -> 28.7).
+template <int W, int KPW, typename Between>
+__device__ __forceinline__ int probe_lru_wave(const int64_t *K, const uint32_t *T, int64_t key, uint32_t set, bool want, uint32_t g_now,
+                                              int &victim, Between &&between) {
+    constexpr int G = kWave / W;                       // keys per wave load
+    constexpr int R = (KPW + G - 1) / G;               // wave loads needed for KPW keys
+    constexpr int RC = R > 4 ? 4 : R;                  // wave loads in flight together
+    const int lane = lane_id();
+    const int slot = lane & (W - 1);
+    const int sub  = lane / W;
+    int way = -1;
+#pragma unroll
+    for (int r0 = 0; r0 < R; r0 += RC) {
+        int64_t  sk[RC];
+        uint32_t stamp[RC];
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+            const uint32_t sj = (uint32_t)__shfl((int)set, (r0 + r) * G + sub, kWave);   // 0 for lanes without a key: a valid set
+            const uint64_t at = (uint64_t)sj * W + slot;
+            sk[r] = (int64_t)shared_ld64(reinterpret_cast<const uint64_t *>(K + at));
+            stamp[r] = ld_agent(T + at);
+        }
+        if (r0 + RC >= R) between();
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+            const int j = (r0 + r) * G + sub;
+            const int64_t kj = shfl64(key, j);
+            const int wj = __shfl((int)want, j, kWave);
+            const uint32_t age = g_now - stamp[r];
+            uint32_t oldest = age;
+#pragma unroll
+            for (int o = 1; o < W; o <<= 1) {
+                const uint32_t other = (uint32_t)__shfl_xor((int)oldest, o, kWave);
+                oldest = other > oldest ? other : oldest;
+            }
+            const uint64_t same = __ballot(wj && sk[r] == kj), empty = __ballot(sk[r] == kEmpty), old = __ballot(age == oldest);
+            if (lane / G == r0 + r) {
+                const int at = W == 64 ? 0 : (lane % G) * W;
+                constexpr uint64_t all = W == 64 ? ~0ull : (1ull << (W & 63)) - 1;
+                const uint64_t f = (same >> at) & all, e = (empty >> at) & all;
+                if (f) way = __builtin_ctzll(f);
+                victim = __builtin_ctzll(e ? e : (old >> at) & all);     // (some lane has the largest age)
+            }
+        }
+    }
+    return way;
+}
+
 // A shorter row's piece.
 template <>
 struct RowPiece<false> {
@@ -1194,8 +1245,12 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             wave_lds_fence();
         }
 
+        // A search reads a set for every lane: the sets of those in m, for the others that of the first of them, which
+        // costs no request.  (Lanes that are done reading their own sets once more, which others write to, took 262,144 new keys over
+        // 2^14 sets from 130 to 148 us, over 2^16 from 88 to 97, and 70,000 under LRU of which a third are 64 keys from 38 to 58.)
+        auto set_in = [&](bool in, uint64_t m) { return in ? set : (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(m)); };
         uint32_t rounds = 0;
-        while (__ballot(pending)) {
+        while (const uint64_t pendmask = __ballot(pending)) {
             if (++rounds > kMaxRounds) {                             // a set never came free: skip these keys
                 if (pending) __hip_atomic_fetch_or(tb.flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -1206,7 +1261,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             // On the first attempt the look travels beside the fetch-or, later in front of it.
             int seen = -1;
             if (rounds > 1) {
-                seen = probe_wave<W, KPW, true>(tb.K, key, set, pending);
+                seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending);
                 if (pending && seen >= 0) {
                     if (tb.T) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);    // Alg. 3: refresh
                     pending = false;
@@ -1217,7 +1272,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             if (pending)
                 word = __hip_atomic_fetch_or(reinterpret_cast<uint64_t *>(seq_of(tb, set)), 1ull, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
-            if (rounds == 1) seen = probe_wave<W, KPW, true>(tb.K, key, set, pending);
+            if (rounds == 1) seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending);
             shared_acquire();                                        // the word is owned before the set is read
             writer_tell(&s_group, told);
             const uint32_t old = (uint32_t)word;
@@ -1236,48 +1291,16 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             const int r = rank_in(ownmask);
             if (own) s_srcrow[wave][r] = i;
             wave_lds_fence();
-            // the owners' rows are requested behind the sets' keys and travel while those are compared
-            int way = probe_wave<W, KPW, true>(tb.K, key, set, own, [&] { rows.start((uint32_t)__popcll(ownmask)); });
-            bool fresh = own && way < 0;
-            if (tb.T) {                                              // LRU policy (Alg. 3)
-                if (fresh) {
-                    int empty_way = -1;
-                    uint32_t best = 0;
-                    int oldest = 0;
-                    auto consider = [&](int w, int64_t kw, uint32_t stamp) {         // called from the highest way to the lowest
-                        const uint32_t age = g_now - stamp;
-                        if (kw == kEmpty) empty_way = w;             // ends as the lowest empty way
-                        if (w == W - 1 || age >= best) { best = age; oldest = w; }   // largest age, lowest way on ties
-                    };
-                    if constexpr (W <= 8) {
-#pragma unroll
-                        for (int w = W - 1; w >= 0; --w)
-                            consider(w, ld_agent(tb.K + (uint64_t)set * W + w), ld_agent(tb.T + (uint64_t)set * W + w));
-                    } else {
-                        // More slots than that the compiler asks for one by one, waiting for each (behind it the rows hold 64
-                        // registers): eight at a time, loads and comparisons apart.  40,000 new rows, 16 / 32 / 64 ways: 44 / 81 /
-                        // 181 us one by one, 35 / 54 / 104 this way (16 at a time 34 / 54 / 96, but those registers cost every
-                        // insert into such sets a wave per SIMD: with the victim counter 323 instead of 263 us per 300,000).
-                        constexpr int F = 8;
-#pragma unroll
-                        for (int w0 = W - F; w0 >= 0; w0 -= F) {
-                            int64_t  kw[F];
-                            uint32_t stamp[F];
-#pragma unroll
-                            for (int w = 0; w < F; ++w) {
-                                kw[w] = ld_agent(tb.K + (uint64_t)set * W + w0 + w);
-                                stamp[w] = ld_agent(tb.T + (uint64_t)set * W + w0 + w);
-                            }
-#pragma unroll
-                            for (int w = F - 1; w >= 0; --w) consider(w0 + w, kw[w], stamp[w]);
-                        }
-                    }
-                    way = empty_way >= 0 ? empty_way : oldest;
-                }
-                if (own) st_agent(tb.T + (uint64_t)set * W + (uint32_t)way, g_now);
-            } else if (fresh) {
-                way = (int)(c & (W - 1));                            // victim counter
-            }
+            // the owners' rows are requested behind the sets' keys (LRU policy: and stamps) and travel while those are compared
+            auto rows_too = [&] { rows.start((uint32_t)__popcll(ownmask)); };
+            int victim = (int)(c & (W - 1));                         // victim counter
+            int way;
+            const uint32_t from = set_in(own, ownmask);
+            if (tb.T) way = probe_lru_wave<W, KPW>(tb.K, tb.T, key, from, own, g_now, victim, rows_too);
+            else      way = probe_wave<W, KPW, true>(tb.K, key, from, own, rows_too);
+            const bool fresh = own && way < 0;
+            if (fresh) way = victim;
+            if (tb.T && own) st_agent(tb.T + (uint64_t)set * W + (uint32_t)way, g_now);
             const uint64_t freshmask = __ballot(fresh);
             if (freshmask) {
                 writer_entered(&s_group);

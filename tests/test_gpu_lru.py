@@ -252,3 +252,43 @@ def test_one_launch_over_lru_and_counter_tables():
     finally:
         for c in caches:
             c.close()
+
+
+@pytest.mark.parametrize("d", [4, 128, 260])
+@pytest.mark.parametrize("W", [1, 2, 4, 8, 16, 32, 64])
+def test_lru_insert_takes_the_oldest_way_of_any_set(W, d):
+    """One new key per set and call, so every placement is determined: sets without an empty way, with some at any place
+    and of nothing else; stamps that tie, that are newer than the iteration count (ages wrap) and that are zero.  Calls of 1, 7 and
+    300 keys, and one of more than 32,768 positions (16 keys to a wave), most of which are not keys."""
+    S = 331
+    rng = np.random.Generator(np.random.PCG64(100 * W + d))
+    with DeviceCache(S * W, W, d, policy=LRU) as gc:
+        oc = OracleCache(S * W, W, d, policy=LRU)
+        pool = np.arange(1, 40 * S * W, dtype=np.int64)
+        where = oc.sets_of(pool)
+        by_set = [pool[where == s] for s in range(S)]
+        for n in (1, 7, 300, 40000):
+            keys = np.full((S, W), EMPTY_KEY, dtype=np.int64)
+            for s in range(S):
+                keys[s] = rng.choice(by_set[s][:2 * W], W, replace=False)
+            keys[rng.random((S, W)) < rng.choice([0.0, 0.1, 1.0], size=(S, 1))] = EMPTY_KEY
+            stamps = rng.integers(0, 1 << 32, size=(S, W), dtype=np.uint32)
+            few = rng.random(S) < 0.5
+            stamps[few] = rng.integers(3, 7, size=(int(few.sum()), W), dtype=np.uint32)
+            ctr = np.full(S, W, dtype=np.uint32)
+            vals = rng.integers(0, 1 << 30, size=(S, W, d), dtype=np.uint32)
+            gc.load(keys, ctr, vals)
+            gc.load_lru(stamps, 5)
+            oc.load_state(keys, ctr, vals, stamps=stamps)
+            oc.g = 5
+            new = np.full(n, EMPTY_KEY, dtype=np.int64)
+            at = rng.choice(n, min(n, S), replace=False)
+            new[at] = [by_set[s][2 * W + 1 + int(rng.integers(0, 5))] for s in rng.permutation(S)[:len(at)]]
+            rows = rng.integers(0, 1 << 30, size=(n, d), dtype=np.uint32)
+            gc.insert(new, rows)
+            oc.insert(new, rows)
+            gk, gctr, gv = gc.export()
+            gt, _ = gc.export_lru()
+            assert (gk == np.array(oc.keys)).all() and (gctr == np.array(oc.ctr)).all()
+            assert (gv == np.array(oc.vals)).all() and (gt == np.array(oc.stamps)).all()
+        oc.close()
