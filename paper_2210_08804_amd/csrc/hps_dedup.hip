@@ -27,6 +27,7 @@
 #include <string>
 
 #include "hps_dedup.h"
+#include "hps_dedup_missed.h"
 #include "hps_mix.h"
 #include "hps_rows.h"
 
@@ -91,9 +92,23 @@ __global__ void dedup_clear_kernel(int64_t *tkey, uint32_t *tuid, uint64_t n_slo
 
 __global__ void set_u32_kernel(uint32_t *p, uint32_t v) { *p = v; }
 
+// What hps_dedup_missed adds to a call.
+struct Missed {
+    const uint32_t *n_dev;       // the batch's length (<= n)
+    uint32_t *n_host;            // it goes here too
+    int64_t  *keys_host;         // and unique_keys here
+};
+
+// A call's slots for n keys: a power of two, at least 2 * n.
+__host__ __device__ __forceinline__ uint64_t slots_for(uint64_t n) {
+    uint64_t p = 1024;
+    while (p < 2 * n) p <<= 1;
+    return p;
+}
+
 // counter: low half = distinct keys so far, high half = tiles that have added theirs; zero between calls.
-template <int kTile>                                                 // keys (= threads) per work-group
-__global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict__ keys, uint32_t n,
+template <int kTile, bool kMissed>                                   // keys (= threads) per work-group
+__global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict__ keys, uint32_t n, const Missed more,
                                                       int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
                                                       uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique,
                                                       int64_t *other_tkey, uint32_t *other_tuid, uint64_t other_dirty) {
@@ -103,6 +118,15 @@ __global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict_
     __shared__ uint32_t l_marker_seen, l_cnt, l_base;
 
     const int lane = (int)(threadIdx.x & 63u);
+    if (kMissed) {
+        const uint32_t nd = *more.n_dev;
+        n = nd < n ? nd : n;
+        mask = (uint32_t)(slots_for(n) - 1);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *more.n_host = n;
+            if (n == 0) *n_unique = 0u;                // no tile does
+        }
+    }
     const uint32_t n_tiles = (n + kTile - 1) / kTile;
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const uint32_t i = tile * kTile + threadIdx.x;
@@ -173,6 +197,7 @@ __global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict_
             const uint32_t uid = l_base + rank;
             __hip_atomic_store(tuid + slot, uid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             unique_keys[uid] = key;
+            if (kMissed) more.keys_host[uid] = key;
             l_uid[ls] = uid;
         }
         // Every number of this work-group is on its way: only now wait for the others'.  (The barrier also keeps the
@@ -236,19 +261,20 @@ hps_status_t check_session(hps_dedup_session *s) {
 // batches launches none; a call of 300 keys behind one of 2^20 wipes 2^21 slots: 284 us by its one tile, 12 this way.
 constexpr uint32_t kWipe = 4;
 
+template <bool kMissed = false>
 void launch_dedup(const int64_t *keys, uint32_t n, int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
                   uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique, int64_t *other_tkey, uint32_t *other_tuid,
-                  uint64_t other_dirty, uint32_t max_blocks, hipStream_t st) {
+                  uint64_t other_dirty, uint32_t max_blocks, hipStream_t st, const Missed &more = Missed{nullptr, nullptr, nullptr}) {
     const uint32_t tile = n <= kSmallBatch ? 512u : 1024u;
     const uint64_t tiles = ((uint64_t)n + tile - 1) / tile;
     const uint64_t wipers = other_dirty / (kWipe * tile);
     const uint64_t blocks = tiles > wipers ? tiles : wipers;
     const dim3 grid((uint32_t)(blocks < max_blocks ? blocks : max_blocks)), block(tile);
     if (tile == 512u)
-        hipLaunchKernelGGL(dedup_kernel<512>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
+        hipLaunchKernelGGL((dedup_kernel<512, kMissed>), grid, block, 0, st, keys, n, more, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
                            other_tkey, other_tuid, other_dirty);
     else
-        hipLaunchKernelGGL(dedup_kernel<1024>, grid, block, 0, st, keys, n, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
+        hipLaunchKernelGGL((dedup_kernel<1024, kMissed>), grid, block, 0, st, keys, n, more, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
                            other_tkey, other_tuid, other_dirty);
 }
 
@@ -269,13 +295,23 @@ hps_status_t noalloc_base(int dev, unsigned char **base) {
     return HPS_OK;
 }
 
-uint64_t pow2_at_least(uint64_t x) {
-    uint64_t p = 1024;
-    while (p < x) p <<= 1;
-    return p;
+}  // namespace
+
+hps_status_t hps_dedup_missed(hps_dedup_session *s, const int64_t *keys, size_t n_max, const uint32_t *n_dev, int64_t *unique_keys,
+                              int64_t *keys_host, uint32_t *inverse, uint32_t *n_host, uint32_t *n_unique, hipStream_t st) {
+    if (hps_status_t e = check_session(s)) return e;
+    if (n_max == 0 || n_max > s->max_n) return fail(HPS_ERR_INVALID_ARG, "n_max must be in 1 .. the session's max_n");
+    const int t = s->cur, o = 1 - t;
+    launch_dedup<true>(keys, (uint32_t)n_max, s->tkey[t], s->tuid[t], 0u, s->counter + t, flags_behind(s->counter), unique_keys, inverse, n_unique,
+                       s->tkey[o], s->tuid[o], s->dirty[o], (uint32_t)s->n_cus * 8u, st, Missed{n_dev, n_host, keys_host});
+    HIP_TRY(hipGetLastError());
+    s->dirty[t] = slots_for(n_max) + 1;
+    s->dirty[o] = 0;
+    s->cur = o;
+    return HPS_OK;
 }
 
-}  // namespace
+void hps_dedup_missed_were(hps_dedup_session *s, size_t n) { s->dirty[1 - s->cur] = n ? slots_for(n) + 1 : 0; }
 
 extern "C" {
 
@@ -290,7 +326,7 @@ hps_status_t hps_dedup_create(size_t max_n, hps_dedup_t **out) {
     if (!s) return fail(HPS_ERR_OOM, "host allocation failed");
     s->magic = 0;
     s->max_n = max_n;
-    s->slots = pow2_at_least(2 * (uint64_t)max_n);
+    s->slots = slots_for(max_n);
     s->tkey[0] = s->tkey[1] = s->tkey[2] = nullptr;
     s->tuid[0] = s->tuid[1] = s->tuid[2] = nullptr;
     s->counter = nullptr;
@@ -364,7 +400,7 @@ hps_status_t hps_dedup(hps_dedup_t *s, const int64_t *keys, size_t n, int64_t *u
     if (!keys || !unique_keys || !inverse) return fail(HPS_ERR_INVALID_ARG, "keys, unique_keys and inverse must not be NULL when n > 0");
     if (!aligned(keys, 8) || !aligned(unique_keys, 8) || !aligned(inverse, 4))
         return fail(HPS_ERR_INVALID_ARG, "keys and unique_keys must be 8-byte, inverse 4-byte aligned");
-    const uint64_t slots = pow2_at_least(2 * (uint64_t)n);            // <= s->slots because n <= max_n
+    const uint64_t slots = slots_for(n);            // <= s->slots because n <= max_n
     const uint32_t mask = (uint32_t)(slots - 1);
     const uint32_t cap = (uint32_t)s->n_cus * 8u;
     // A call that is being captured into a graph must be complete in itself, because the graph may
@@ -416,7 +452,7 @@ hps_status_t hps_dedup_noalloc(const int64_t *keys, size_t n, int64_t *unique_ke
     int n_cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (n_cus <= 0) n_cus = 256;
-    const uint64_t slots = pow2_at_least(2 * (uint64_t)n);            // <= kNaSlots because n <= kNaMaxKeys
+    const uint64_t slots = slots_for(n);            // <= kNaSlots because n <= kNaMaxKeys
     const uint32_t mask = (uint32_t)(slots - 1);
     const uint32_t cap = (uint32_t)n_cus * 8u;
     // The array keeps what the last call left in it: the slots this call may touch and its counter
@@ -450,7 +486,7 @@ hps_status_t hps_dedup_flags(hps_dedup_t *s, uint32_t *flags, int clear) {
 hps_status_t hps_dedup_debug_claim(hps_dedup_t *s, int64_t key, size_t n) {
     if (hps_status_t st = check_session(s)) return st;
     if (n == 0 || n > s->max_n) return fail(HPS_ERR_INVALID_ARG, "n must be in 1 .. max_n");
-    const uint64_t mask = pow2_at_least(2 * (uint64_t)n) - 1;
+    const uint64_t mask = slots_for(n) - 1;
     int64_t *tkey = s->tkey[s->cur];
     HIP_TRY(hipDeviceSynchronize());
     if (key == kEmpty) {                               // its slot holds anything but the marker

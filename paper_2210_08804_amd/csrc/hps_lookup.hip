@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "hps_dedup.h"
+#include "hps_dedup_missed.h"
 #include "hps_lookup.h"
 
 namespace {
@@ -46,6 +47,12 @@ __global__ void place_rows_kernel(float *out, const uint32_t *__restrict__ idx,
 constexpr size_t kMaxQueued = 64;
 constexpr size_t kMaxSlotBytes = 256ull << 20;
 
+// Longest batch whose miss list is made distinct ahead of the host's wait for its length (hps_lookup).  The kernel then writes the
+// distinct keys into host memory, 8 bytes per lane, which for very many takes longer than the copy it saves: us per lookup, most
+// keys missing, after the wait / ahead of it: 2,000 keys 110 / 99, 26,624 (a tenth missing) 169 / 147, 50,000 401 / 377, 100,000 1,012 / 998,
+// 400,000 4,490 / 4,770.
+constexpr size_t kMostAhead = 65536;
+
 struct Slot {
     int64_t   *d_keys;        // device copy of a batch's miss list (every occurrence)
     hipEvent_t ready;         // that copy has finished
@@ -75,7 +82,9 @@ struct hps_lookup_session {
     // pinned host side; the counts are written there by the kernels themselves, through the words' device
     // addresses (a copy of four bytes is a launch of its own)
     uint32_t *h_n_miss, *h_n_unique, *d_n_miss, *d_n_unique;
-    int64_t  *h_ukeys;
+    int64_t  *h_ukeys, *d_h_ukeys;
+    uint32_t *d_count;                    // the miss count, on the device
+    bool      had_misses;                 // the last lookup's batch
     float    *h_rows;
     // background insertion
     hipStream_t side;
@@ -195,7 +204,7 @@ void free_all(hps_lookup_session *L) {
     (void)hipFree(L->d_miss_idx); (void)hipFree(L->d_inv);
     (void)hipFree(L->d_miss_keys); (void)hipFree(L->d_ukeys); (void)hipFree(L->d_rows); (void)hipFree(L->d_default);
     (void)hipFree(L->bg_d_ukeys); (void)hipFree(L->bg_d_rows); (void)hipFree(L->bg_d_keys);
-    (void)hipFree(L->bg_d_inv); (void)hipHostFree(L->bg_h_n_unique);
+    (void)hipFree(L->bg_d_inv); (void)hipFree(L->d_count); (void)hipHostFree(L->bg_h_n_unique);
     (void)hipHostFree(L->h_n_miss); (void)hipHostFree(L->h_n_unique);
     (void)hipHostFree(L->h_ukeys); (void)hipHostFree(L->h_rows); (void)hipHostFree(L->bg_h_rows);
     (void)hipHostFree(L->bg_h_keys);
@@ -225,7 +234,8 @@ hps_status_t hps_lookup_create(hps_cache_t *cache, size_t max_batch, float hit_t
     L->fetch = fetch; L->user = user;
     L->dd = nullptr; L->dd_bg = nullptr;
     L->d_miss_idx = L->d_n_miss = L->d_inv = L->d_n_unique = nullptr; L->d_miss_keys = L->d_ukeys = nullptr;
-    L->d_rows = L->d_default = nullptr; L->h_n_miss = L->h_n_unique = nullptr; L->h_ukeys = nullptr;
+    L->d_rows = L->d_default = nullptr; L->h_n_miss = L->h_n_unique = nullptr; L->h_ukeys = L->d_h_ukeys = nullptr;
+    L->d_count = nullptr; L->had_misses = true;
     L->h_rows = nullptr; L->side = nullptr; L->bg_d_ukeys = nullptr; L->bg_d_rows = L->bg_h_rows = nullptr;
     L->bg_h_keys = nullptr; L->bg_d_keys = nullptr; L->bg_d_inv = L->bg_d_n_unique = L->bg_h_n_unique = nullptr;
     const size_t nb = max_batch, rowb = (size_t)dim * sizeof(float);
@@ -238,9 +248,10 @@ hps_status_t hps_lookup_create(hps_cache_t *cache, size_t max_batch, float hit_t
     pin((void **)&L->h_n_miss, 4); pin((void **)&L->h_n_unique, 4);
     pin((void **)&L->h_ukeys, nb * 8); pin((void **)&L->h_rows, nb * rowb); pin((void **)&L->bg_h_rows, nb * rowb);
     pin((void **)&L->bg_h_keys, nb * 8); pin((void **)&L->bg_h_n_unique, 4);
-    dev((void **)&L->bg_d_keys, nb * 8); dev((void **)&L->bg_d_inv, nb * 4);
-    auto seen = [&](uint32_t **d, uint32_t *h) { if (e == hipSuccess) e = hipHostGetDevicePointer((void **)d, h, 0); };
+    dev((void **)&L->bg_d_keys, nb * 8); dev((void **)&L->bg_d_inv, nb * 4); dev((void **)&L->d_count, 4);
+    auto seen = [&](auto **d, auto *h) { if (e == hipSuccess) e = hipHostGetDevicePointer((void **)d, h, 0); };
     seen(&L->d_n_miss, L->h_n_miss); seen(&L->d_n_unique, L->h_n_unique); seen(&L->bg_d_n_unique, L->bg_h_n_unique);
+    seen(&L->d_h_ukeys, L->h_ukeys);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&L->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMemcpy(L->d_default, default_row, rowb, hipMemcpyHostToDevice);
     {
@@ -290,11 +301,18 @@ hps_status_t hps_lookup(hps_lookup_t *L, const int64_t *keys, size_t n, float *o
     if (hit_rate) *hit_rate = 1.0f;
     if (was_synchronous) *was_synchronous = 0;
     if (n == 0) return HPS_OK;
-    // EmbCacheLookup(Q): hits land in out, misses in the workspace
-    if (hps_cache_query(L->cache, keys, n, out, L->d_miss_idx, L->d_miss_keys, L->d_n_miss, st) != HPS_OK)
+    // EmbCacheLookup(Q): hits land in out, misses in the workspace.  Where a miss means a synchronous insertion whatever the hit
+    // rate, the miss list's dedup goes out behind the query, without the host's wait for its length in between (and not if the
+    // last batch had no misses: the dedup of an empty list costs a lookup that only hits 4 us).
+    const bool ahead = L->threshold > 1.0f && L->had_misses && n <= kMostAhead;
+    if (hps_cache_query(L->cache, keys, n, out, L->d_miss_idx, L->d_miss_keys, ahead ? L->d_count : L->d_n_miss, st) != HPS_OK)
         return lfail(HPS_ERR_INVALID_ARG, std::string("query: ") + hps_last_error());
+    if (ahead && hps_dedup_missed(L->dd, L->d_miss_keys, n, L->d_count, L->d_ukeys, L->d_h_ukeys, L->d_inv, L->d_n_miss, L->d_n_unique, st) != HPS_OK)
+        return lfail(HPS_ERR_DEVICE, std::string("dedup: ") + hps_dedup_last_error());
     LK_TRY(hipStreamSynchronize(st));
     const uint32_t m = *L->h_n_miss;
+    L->had_misses = m != 0;
+    if (ahead) hps_dedup_missed_were(L->dd, m);
     const float rate = 1.0f - (float)m / (float)n;
     if (hit_rate) *hit_rate = rate;
     if (m == 0) return HPS_OK;
@@ -304,10 +322,12 @@ hps_status_t hps_lookup(hps_lookup_t *L, const int64_t *keys, size_t n, float *o
         if (was_synchronous) *was_synchronous = 1;
         // the lower tiers see each missing key once (Sec. 2.2): dedup on the device, only the
         // distinct keys travel to the host; the map from miss-list entries to them stays here
-        if (hps_dedup(L->dd, L->d_miss_keys, m, L->d_ukeys, L->d_inv, L->d_n_unique, st) != HPS_OK)
-            return lfail(HPS_ERR_DEVICE, std::string("dedup: ") + hps_dedup_last_error());
-        LK_TRY(hipMemcpyAsync(L->h_ukeys, L->d_ukeys, (size_t)m * 8, hipMemcpyDeviceToHost, st));
-        LK_TRY(hipStreamSynchronize(st));
+        if (!ahead) {
+            if (hps_dedup(L->dd, L->d_miss_keys, m, L->d_ukeys, L->d_inv, L->d_n_unique, st) != HPS_OK)
+                return lfail(HPS_ERR_DEVICE, std::string("dedup: ") + hps_dedup_last_error());
+            LK_TRY(hipMemcpyAsync(L->h_ukeys, L->d_ukeys, (size_t)m * 8, hipMemcpyDeviceToHost, st));
+            LK_TRY(hipStreamSynchronize(st));
+        }
         const uint32_t u = *L->h_n_unique;
         L->fetch(L->user, L->h_ukeys, u, L->h_rows);
         LK_TRY(hipMemcpyAsync(L->d_rows, L->h_rows, (size_t)u * L->dim * sizeof(float), hipMemcpyHostToDevice, st));

@@ -355,3 +355,44 @@ def test_three_lookup_objects_on_three_threads_share_one_cache(threshold):
             for lk in lks:
                 B.hps_lookup_destroy(lk)
             B.hps_hostmap_destroy(hm)
+
+
+@pytest.mark.parametrize("max_batch", [512, 20000, 40000, 70000])
+def test_always_synchronous_lookup_whatever_the_last_batch_missed(max_batch):
+    """Threshold above 1: the miss list is made distinct behind the query, its length known on the device only, unless the last batch
+    had no misses.  Batches that miss everywhere, nowhere (also twice in a row), in one place, on one key given often, on the key
+    that marks a free slot of the dedup's table (never cached, so always missing), long behind short and short behind long
+    ones (the slots the last call used are wiped), of one key and of max_batch."""
+    S, W, d = 4099, 16, 16
+    seen = []
+
+    def fetch(user, keys_p, n, rows_p):
+        keys = np.ctypeslib.as_array(keys_p, shape=(n,)).copy()
+        seen.append(keys)
+        np.ctypeslib.as_array(rows_p, shape=(n, d))[...] = inputs.backing_rows(keys, d, 0)
+
+    cb = B.FETCH_FN(fetch)
+    marker = -(1 << 63)
+    a = np.arange(1, max_batch + 1, dtype=np.int64) % 20000
+    fresh = lambda k, n: 10 ** 6 * k + np.arange(n, dtype=np.int64)
+    few = max_batch // 40
+    batches = [fresh(1, few), fresh(1, few), fresh(1, few), np.concatenate([fresh(1, few), fresh(2, 1)]), a, a, a[:1], fresh(3, 1), fresh(3, 1),
+               np.full(max_batch, 7 * 10 ** 6, dtype=np.int64), np.full(max_batch, 7 * 10 ** 6, dtype=np.int64),
+               np.concatenate([a[:few], np.full(3, marker), fresh(4, few)]), np.full(few, marker), fresh(5, few)]
+    with DeviceCache(S * W, W, d, concurrent_writers=True) as gc:
+        lk = B.hps_lookup_create(gc.h, max_batch, 2.0, np.zeros(d, np.float32), cb)
+        try:
+            cached = set()
+            for keys in batches:
+                out = torch.full((len(keys), d), 7.0, dtype=torch.float32, device="cuda")
+                del seen[:]
+                rate, sync = B.hps_lookup(lk, torch.from_numpy(keys).cuda(), len(keys), out)
+                missing = [k for k in keys.tolist() if k not in cached]
+                assert np.float32(rate) == np.float32(1.0) - np.float32(len(missing)) / np.float32(len(keys))
+                assert sync == bool(missing) and len(seen) == (1 if missing else 0)
+                if missing:
+                    assert sorted(seen[0].tolist()) == sorted(set(missing))
+                    cached |= set(missing) - {marker}
+                assert (out.cpu().numpy() == inputs.backing_rows(keys, d, 0)).all()
+        finally:
+            B.hps_lookup_destroy(lk)
