@@ -658,6 +658,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
     const int slot = lane & (W - 1);
     const int sub  = lane / W;
     int way = -1;
+    const int64_t sought = want ? key : kEmpty + 1;    // what no slot holds: the lanes' keys travel alone, without their `want`
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += RC) {
         int64_t sk[RC];
@@ -680,9 +681,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
 #pragma unroll
             for (int r = b; r < b + RB; ++r) {
                 const int j = (r0 + r) * G + sub;
-                const int64_t kj = shfl64(key, j);
-                const int wj = __shfl((int)want, j, kWave);
-                const uint64_t m = __ballot(wj && sk[r] == kj);
+                const uint64_t m = __ballot(sk[r] == shfl64(sought, j));
                 if (lane / G == r0 + r) {
                     const uint64_t field = (W == 64) ? m : ((m >> ((lane % G) * W)) & ((1ull << (W & 63)) - 1));
                     if (field) way = __builtin_ctzll(field);
@@ -690,7 +689,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
             }
         }
     }
-    return way;
+    return want ? way : -1;
 }
 template <int W, int KPW, bool kShared = false>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want, uint32_t lanes = KPW) {
@@ -1407,23 +1406,18 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBl
             const bool busy = pending && (v & 1u);
             shared_acquire();                                        // the word is read before the keys
             writer_tell(&s_group, told);
+            // W lanes read a set's line, as in the other kernels; lanes without one to search read that of the first that has one, which
+            // is read anyway.  (Each lane reading its own set, 8 bytes at a time, made W requests of a line: 262,144 rows in random order
+            // 79.9 us, this way 75.6; as many absent keys 16.1 and 11.4.)
+            const bool search = pending && !busy;
+            const uint64_t smask = __ballot(search);
             int way = -1;
-            if (pending && !busy) {
-                // Loads and comparisons apart: with 64 ways in one loop the compiler waits for each key before
-                // it asks for the next (5,000 absent keys 12.3 us, this way 8.7).
-                constexpr int F = W > 32 ? 32 : W;                   // keys in flight together
-#pragma unroll
-                for (int w0 = 0; w0 < W; w0 += F) {
-                    int64_t sk[F];
-#pragma unroll
-                    for (int w = 0; w < F; ++w) sk[w] = ld_agent(tb.K + (uint64_t)set * W + w0 + w);
-#pragma unroll
-                    for (int w = 0; w < F; ++w)
-                        if (sk[w] == key) way = w0 + w;
-                }
-                if (way < 0) pending = false;                        // not cached: ignored
+            if (smask) {
+                const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(smask));
+                way = probe_wave<W, KPW, true>(tb.K, key, search ? set : some, search);
             }
-            bool winner = pending && !busy && way >= 0;
+            if (search && way < 0) pending = false;                  // not cached: ignored
+            bool winner = search && way >= 0;
 #pragma unroll
             for (int w = 0; w < W; ++w) {                            // one lane per slot and round
                 const uint64_t m = __ballot(winner && way == w) & gmask;
@@ -1988,10 +1982,11 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     // Insert: 16 keys per wave, 8 while 4,096 waves (four per SIMD) hold the batch that way: 8,192 rows 12.1 -> 9.7 us,
     // 32,768 rows 16.8 -> 15.7; with 8 throughout the 425,984-key streaming step takes 166 instead of 149 us.
     // (32 and 64 are 3-45 % slower than 16 from 1 K to 1 M keys.)
-    // Update: 64 keys per wave, 16 for batches below 32,768 keys: 8,192 rows 14.1 us (64s: 23, 8s: 13.4, but a dump's
+    // Update: 64 keys per wave, 16 for batches of up to 49,152 keys: 8,192 rows 14.1 us (64s: 23, 8s: 13.4, but a dump's
     // keys come eight to a set, and 8s split sets between waves: dump + update + query of 28,000 rows of 256
-    // bytes 28.6 instead of 26.0); from 65,536 rows up 64 is 8-18 % faster than 16, on a 40 GB refresh 9-55 %.
-    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n < 32768 ? 16u : (uint32_t)kWave);
+    // bytes 28.6 instead of 26.0); 16s / 64s, in random order and in a dump's: 32,768 rows 17.5 / 21.8 and 13.5 / 17.0, 50,000 22.9 / 24.5 and
+    // 18.5 / 18.1, 65,536 27.2 / 28.2 and 21.3 / 18.5; on a 40 GB refresh 64s are 9-55 % faster.
+    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n <= 49152 ? 16u : (uint32_t)kWave);
     const uint64_t tiles = (n + kpw - 1) / kpw;
     uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
     if (blocks > (1u << 16)) blocks = 1u << 16;

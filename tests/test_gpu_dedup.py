@@ -229,3 +229,15 @@ def test_a_full_table_cannot_hang_a_kernel():
         for _ in range(3):
             check_against_oracle(np.arange(n), *dd.run(np.arange(n)))
         assert B.hps_dedup_flags(dd.h) == 0
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 2048 * 17, 2048 * 17 + 1, 2048 * 51, 2048 * 53 - 1, 2048 * 63, 2048 * 64 + 63])
+def test_expand_rows_of_512_bytes_with_odd_and_even_lists(n):
+    """Lists of an odd number of rows, of one row, full and not (2,048 waves on a whole chip), in every group size."""
+    d, u = 128, 999
+    rng = np.random.Generator(np.random.PCG64(n))
+    rows = torch.from_numpy(rng.integers(0, 1 << 31, size=(u, d), dtype=np.int64).astype(np.int32)).cuda()
+    inv = torch.from_numpy(rng.integers(0, u, size=n).astype(np.int32)).cuda()
+    out = torch.full((n + 3, d), SENTINEL, dtype=torch.int32, device="cuda")
+    B.hps_expand_rows(rows.view(torch.float32), inv, n, d, out.view(torch.float32))
+    assert torch.equal(out[:n], rows[inv.long()]) and bool((out[n:] == SENTINEL).all())

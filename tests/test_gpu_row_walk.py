@@ -91,3 +91,29 @@ def test_writers_by_width(d, n):
             getattr(oc, write)(batch, rows)
         _compare(gc, oc, keys, d)
         oc.close()
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 49152, 49153])
+@pytest.mark.parametrize("W", [1, 2, 8, 32, 64])
+def test_update_finds_its_keys_in_any_set(W, n):
+    """16 and 64 keys to a wave on both sides of the switch between them: cached keys in random order, next to each other in slot
+    order, given twice (with the same row), absent ones and the reserved values."""
+    S, d = 1021, 8
+    rng = np.random.Generator(np.random.PCG64(n + W))
+    pool = np.arange(1, S * W, dtype=np.int64)
+    rows = inputs.backing_rows(pool, d)
+    with DeviceCache(S * W, W, d) as gc:
+        oc = OracleCache(S * W, W, d)
+        gc.insert(pool, rows)
+        gk, gctr, gv = gc.export()
+        oc.load_state(gk, gctr, gv)
+        cached = gk[gk != -(1 << 63)]
+        keys = np.concatenate([cached, rng.choice(cached, 30000), pool + 10 ** 7, np.array([-(1 << 63), -(1 << 63) + 1] * 20, dtype=np.int64)])
+        for order in ("slots", "random"):
+            k = np.resize(keys, n) if order == "slots" else rng.choice(keys, n)
+            r = inputs.backing_rows(k, d, version=1 + (order == "random"))
+            gc.update(k, r)
+            oc.update(k, r)
+            gk2, gctr2, gv2 = gc.export()
+            assert (gk2 == gk).all() and (gctr2 == gctr).all() and (gv2 == np.array(oc.vals)).all()
+        oc.close()
