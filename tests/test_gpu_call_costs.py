@@ -42,10 +42,12 @@ def test_a_small_dedup_after_a_large_one_is_small():
     assert t_small < t_big, f"{small} keys {t_small:.1f} us, {big} keys {t_big:.1f} us"
 
 
-@pytest.mark.parametrize("policy,limit", [(B.HPS_POLICY_VICTIM_COUNTER, 0.35), (B.HPS_POLICY_LRU, 0.24)])
+@pytest.mark.parametrize("policy,limit", [(B.HPS_POLICY_VICTIM_COUNTER, 0.35), (B.HPS_POLICY_LRU, 0.35)])
 def test_inserting_cached_keys_does_not_move_rows(policy, limit):
     """Alg. 3 ignores a key that is already there: its row of the batch need not be read.  (Present keys over new
-    ones, counter / LRU: 0.24 / 0.17 with the rows left alone, 0.49 / 0.33 with all of them read.)"""
+    ones, counter / LRU: 0.26 / 0.25 with the rows left alone, 0.50 / 0.53 with all of them read.  Under LRU present keys take the 22 us
+    that they always took; new ones took 120 and now take 90, so the bound of 0.24 for their quotient, which stood between 0.17
+    and 0.33 then, stands between 0.25 and 0.53 now.)"""
     n, d, W, S, rounds = 1 << 18, 128, 8, 1 << 20, 9
     batches = iter(torch.randperm(n * rounds, device="cuda").view(rounds, n))
     rows = torch.zeros(n, d, device="cuda")
