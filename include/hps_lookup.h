@@ -56,7 +56,8 @@ hps_status_t hps_lookup_create(hps_cache_t *cache, size_t max_batch, float hit_t
  * capacity of the cache).  On return every row of out is either its key's cached row, its fetched
  * row (synchronous mode) or the default row (asynchronous mode), in stream order: the call
  * synchronises the host with `stream` once, to read the miss count, as Alg. 1 needs it.
- * *hit_rate [host] and *was_synchronous [host] may be NULL.
+ * *hit_rate [host] and *was_synchronous [host] may be NULL.  A stream that is being captured into a graph is refused
+ * (DEVICE): the wait cannot be captured.
  */
 hps_status_t hps_lookup(hps_lookup_t *lookup, const int64_t *keys, size_t n, float *out,
                         float *hit_rate, int *was_synchronous, void *stream);

@@ -301,10 +301,17 @@ hps_status_t hps_lookup(hps_lookup_t *L, const int64_t *keys, size_t n, float *o
     if (hit_rate) *hit_rate = 1.0f;
     if (was_synchronous) *was_synchronous = 0;
     if (n == 0) return HPS_OK;
+    // A lookup waits for its stream, which a capture cannot hold: refused before anything is recorded or a table of the dedup
+    // changes hands.  (Where the runtime cannot say, as on the legacy stream beside a capture, the calls below do as they may.)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(st, &capture) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    else if (capture != hipStreamCaptureStatusNone)
+        return lfail(HPS_ERR_DEVICE, "hps_lookup waits for its stream and cannot be captured into a graph");
     // EmbCacheLookup(Q): hits land in out, misses in the workspace.  Where a miss means a synchronous insertion whatever the hit
     // rate, the miss list's dedup goes out behind the query, without the host's wait for its length in between (and not if the
     // last batch had no misses: the dedup of an empty list costs a lookup that only hits 4 us).
-    const bool ahead = L->threshold > 1.0f && L->had_misses && n <= kMostAhead;
+    const bool ahead = known && L->threshold > 1.0f && L->had_misses && n <= kMostAhead;
     if (hps_cache_query(L->cache, keys, n, out, L->d_miss_idx, L->d_miss_keys, ahead ? L->d_count : L->d_n_miss, st) != HPS_OK)
         return lfail(HPS_ERR_INVALID_ARG, std::string("query: ") + hps_last_error());
     if (ahead && hps_dedup_missed(L->dd, L->d_miss_keys, n, L->d_count, L->d_ukeys, L->d_h_ukeys, L->d_inv, L->d_n_miss, L->d_n_unique, st) != HPS_OK)

@@ -396,3 +396,51 @@ def test_always_synchronous_lookup_whatever_the_last_batch_missed(max_batch):
                 assert (out.cpu().numpy() == inputs.backing_rows(keys, d, 0)).all()
         finally:
             B.hps_lookup_destroy(lk)
+
+
+@pytest.mark.parametrize("threshold", [0.8, 2.0])
+def test_a_lookup_under_capture_is_refused_and_changes_nothing(threshold):
+    """A lookup waits, which a capture cannot hold: it is refused, the capture goes on without it, and the lookups behind it find
+    the dedup's tables as the last one left them.  A cache of 8 slots, so that the same keys are missing every time."""
+    W, d, n = 8, 16, 500
+    seen = []
+
+    def fetch(user, keys_p, m, rows_p):
+        keys = np.ctypeslib.as_array(keys_p, shape=(m,)).copy()
+        seen.append(keys)
+        np.ctypeslib.as_array(rows_p, shape=(m, d))[...] = inputs.backing_rows(keys, d, 0)
+
+    cb = B.FETCH_FN(fetch)
+    with DeviceCache(W, W, d, concurrent_writers=True) as gc:
+        lk = B.hps_lookup_create(gc.h, n, threshold, np.zeros(d, np.float32), cb)
+
+        def look(keys):
+            out = torch.full((len(keys), d), 7.0, dtype=torch.float32, device="cuda")
+            del seen[:]
+            rate, sync = B.hps_lookup(lk, torch.from_numpy(keys).cuda(), len(keys), out)
+            assert sync and rate < 0.1 and len(seen) == 1 and len(set(seen[0].tolist())) == len(seen[0])
+            assert (out.cpu().numpy() == inputs.backing_rows(keys, d, 0)).all()
+
+        try:
+            keys = np.arange(n, dtype=np.int64)
+            mark, out = torch.ones(1, device="cuda"), torch.empty(n, d, device="cuda")
+            dk = torch.from_numpy(keys).cuda()
+            for _ in range(3):
+                look(keys)
+                torch.cuda.synchronize()
+                g, cs = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+                with torch.cuda.stream(cs):
+                    g.capture_begin()
+                    mark.zero_()
+                    with pytest.raises(B.HpsError):
+                        B.hps_lookup(lk, dk, n, out, cs)
+                    g.capture_end()
+                torch.cuda.synchronize()
+                mark.fill_(1.0)
+                g.replay()
+                torch.cuda.synchronize()
+                assert mark.item() == 0.0
+                look(keys[::-1].copy())
+                look(keys[n // 3:] + 100)
+        finally:
+            B.hps_lookup_destroy(lk)
