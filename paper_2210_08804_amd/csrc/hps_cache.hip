@@ -650,11 +650,10 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
 // (40,000 keys of 512 bytes in 64-way sets, 23 keys per wave, checked: 19.8 us with them, all on the line of set 0, 10.2 without).
 template <int W, int KPW, bool kShared = false, typename Between>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key,
-                                          uint32_t set, bool want, Between &&between, uint32_t lanes = KPW) {
+                                          uint32_t set, bool want, Between &&between, uint32_t lanes = KPW, int lane = lane_id()) {
     constexpr int G = kWave / W;                       // keys per wave load
     constexpr int R = (KPW + G - 1) / G;               // wave loads needed for KPW keys
     constexpr int RC = R > 32 ? 32 : R;                // wave loads in flight together (64 for W = 64 would not fit the registers)
-    const int lane = lane_id();
     const int slot = lane & (W - 1);
     const int sub  = lane / W;
     int way = -1;
@@ -700,13 +699,12 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
 // a new key takes (Alg. 3): the lowest empty one, else that of the oldest stamp, the lowest of them.  W lanes work on a set, so
 // the choice costs no round trip; a lane that asked for its W keys and stamps by itself, behind the search, waited for most of them
 // one by one (8 ways, 512-byte rows, new keys: 262,144 over 2^20 sets 113.9 -> 82.4 us, 70,000 over 2^16 48.9 -> 38.8, 8,192 over 2^11 41.5 -> 28.7).
-template <int W, int KPW, typename Between>
+template <int W, int KPW, int kMost, typename Between>
 __device__ __forceinline__ int probe_lru_wave(const int64_t *K, const uint32_t *T, int64_t key, uint32_t set, bool want, uint32_t g_now,
-                                              int &victim, Between &&between) {
+                                              int &victim, int lane, Between &&between) {
     constexpr int G = kWave / W;                       // keys per wave load
     constexpr int R = (KPW + G - 1) / G;               // wave loads needed for KPW keys
-    constexpr int RC = R > 4 ? 4 : R;                  // wave loads in flight together
-    const int lane = lane_id();
+    constexpr int RC = R > kMost ? kMost : R;          // wave loads in flight together
     const int slot = lane & (W - 1);
     const int sub  = lane / W;
     int way = -1;
@@ -1192,8 +1190,16 @@ struct WriteArgs {
 // trip of the fetch-or: 2^18 such keys take 27.7 us, 47 without the look (with the LRU policy 30 and 57), new
 // ones 84-88 either way.  KPW = 16 or 8 (launch_write): four or eight times as many waves as keys / 64 share the row copies, and a
 // wave's chain is two copy groups long, or one, instead of eight.
-template <int W, int KPW, bool kLong>
-__global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
+//
+// Each policy has its own kernels, so that the victim counter's do not hold the LRU search's keys and stamps: in one kernel they took
+// long rows from four waves per SIMD to three.  The LRU kernels of long rows keep four with kTight (up to 8 ways; it does not reach so far
+// with more).  200,000 new rows of 1,280 / 2,048 bytes, 8 ways: counter 127 / 181 -> 117 / 174 us, LRU 125 / 163 -> 112 / 152.
+// More than four waves fit short rows, but wait for each other's sets: 262,144 new keys over 2^11 sets of 8 ways 432 us with
+// four, 505 with five; 64-way sets under LRU, where a search reads 768 bytes per key, 200,000 over 2^9 / 2^15 sets 3,750 / 150
+// with three, 6,750 / 179 with four.
+template <int W, int KPW, bool kLong, bool kLru>
+__global__ void __attribute__((amdgpu_waves_per_eu(1, (W == 64 && kLru ? 3 : 4)))) __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
+    constexpr bool kTight = kLong && kLru && W <= 8;
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
     __shared__ uint32_t s_srcrow[kWavesPerWg][kWave];
     __shared__ uint32_t s_owner[kWavesPerWg][kWave * 2];
@@ -1213,7 +1219,7 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
     const uint32_t n_tiles = (n + KPW - 1) / KPW;
     const uint32_t wave_global = blockIdx.x * kWavesPerWg + wave;
     const uint32_t n_waves = gridDim.x * kWavesPerWg;
-    const uint32_t g_now = tb.T ? *tb.gdev : 0u;            // Alg. 3 stamps with the current iteration count
+    const uint32_t g_now = kLru ? *tb.gdev : 0u;            // Alg. 3 stamps with the current iteration count
     if (blockIdx.x * kWavesPerWg >= n_tiles) return;        // nothing for any wave of this work-group
     auto key_of = [&](uint32_t tile) {
         const uint32_t i = tile * KPW + lane;
@@ -1274,10 +1280,12 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             // all but the first without taking the word, instead of each occurrence owning the set in turn.
             // On the first attempt the look travels beside the fetch-or, later in front of it.
             int seen = -1;
+            int here = lane;
+            if constexpr (kTight) asm volatile("" : "+v"(here));     // the searches' lane arithmetic is done again, not kept in registers
             if (rounds > 1) {
-                seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending);
+                seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending, [] {}, KPW, here);
                 if (pending && seen >= 0) {
-                    if (tb.T) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);    // Alg. 3: refresh
+                    if (kLru) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);    // Alg. 3: refresh
                     pending = false;
                 }
             }
@@ -1286,14 +1294,14 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             if (pending)
                 word = __hip_atomic_fetch_or(reinterpret_cast<uint64_t *>(seq_of(tb, set)), 1ull, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
-            if (rounds == 1) seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending);
+            if (rounds == 1) seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending, [] {}, KPW, here);
             shared_acquire();                                        // the word is owned before the set is read
             writer_tell(&s_group, told);
             const uint32_t old = (uint32_t)word;
             const uint32_t c = (uint32_t)(word >> 32);
             bool own = pending && !(old & 1u);
             if (pending && seen >= 0) {
-                if (tb.T) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);
+                if (kLru) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);
                 if (own) st_agent(reinterpret_cast<uint64_t *>(seq_of(tb, set)), word);
                 own = pending = false;
             }
@@ -1310,11 +1318,11 @@ __global__ void __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
             int victim = (int)(c & (W - 1));                         // victim counter
             int way;
             const uint32_t from = set_in(own, ownmask);
-            if (tb.T) way = probe_lru_wave<W, KPW>(tb.K, tb.T, key, from, own, g_now, victim, rows_too);
-            else      way = probe_wave<W, KPW, true>(tb.K, key, from, own, rows_too);
+            if constexpr (kLru) way = probe_lru_wave<W, KPW, (kTight ? 1 : 4)>(tb.K, tb.T, key, from, own, g_now, victim, here, rows_too);
+            else way = probe_wave<W, KPW, true>(tb.K, key, from, own, rows_too, KPW, here);
             const bool fresh = own && way < 0;
             if (fresh) way = victim;
-            if (tb.T && own) st_agent(tb.T + (uint64_t)set * W + (uint32_t)way, g_now);
+            if (kLru && own) st_agent(tb.T + (uint64_t)set * W + (uint32_t)way, g_now);
             const uint64_t freshmask = __ballot(fresh);
             if (freshmask) {
                 writer_entered(&s_group);
@@ -1994,13 +2002,18 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     const bool lng = c->d > 256;               // rows of more than one wave load
     switch (c->W) {
 #define HPS_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, 0, st, a)
+#define HPS_INSERT(w, lru)                                                                  \
+    do {                                                                                    \
+        if (kpw == 8 && lng) HPS_LAUNCH(insert_kernel<w, 8, true, lru>);                    \
+        else if (kpw == 8) HPS_LAUNCH(insert_kernel<w, 8, false, lru>);                     \
+        else if (lng) HPS_LAUNCH(insert_kernel<w, 16, true, lru>);                          \
+        else HPS_LAUNCH(insert_kernel<w, 16, false, lru>);                                  \
+    } while (0)
 #define HPS_CASE(w)                                                                         \
     case w:                                                                                 \
         if (kInsert) {                                                                      \
-            if (kpw == 8 && lng) HPS_LAUNCH(insert_kernel<w, 8, true>);                     \
-            else if (kpw == 8) HPS_LAUNCH(insert_kernel<w, 8, false>);                      \
-            else if (lng) HPS_LAUNCH(insert_kernel<w, 16, true>);                           \
-            else HPS_LAUNCH(insert_kernel<w, 16, false>);                                   \
+            if (a.tab.T) HPS_INSERT(w, true);                                               \
+            else HPS_INSERT(w, false);                                                      \
         } else if (kpw == 16) {                                                             \
             if (lng) HPS_LAUNCH(update_kernel<w, 16, true>);                                \
             else HPS_LAUNCH(update_kernel<w, 16, false>);                                   \
@@ -2011,6 +2024,7 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
         break;
         HPS_CASE(1) HPS_CASE(2) HPS_CASE(4) HPS_CASE(8) HPS_CASE(16) HPS_CASE(32) HPS_CASE(64)
 #undef HPS_CASE
+#undef HPS_INSERT
 #undef HPS_LAUNCH
         default: return fail(HPS_ERR_INVALID_ARG, "unsupported ways");
     }

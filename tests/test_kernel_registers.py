@@ -1,0 +1,36 @@
+"""Vector registers of the built library's own kernels, where a few more cost a wave per SIMD and no result shows it."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2210_08804_amd import binding
+
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def vgprs(tmp_path_factory):
+    """Registers by kernel name, as the code objects' metadata give them."""
+    d = tmp_path_factory.mktemp("objects")
+    lib = shutil.copy(binding.LIB_PATH, d)
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", lib], check=True, capture_output=True)
+    found = {}
+    for f in sorted(os.listdir(d)):
+        if "gfx950" in f:
+            notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", os.path.join(d, f)], check=True, capture_output=True, text=True).stdout
+            for kernel in notes.split(".agpr_count:")[1:]:
+                found[re.search(r"\.name:\s*(\S+)", kernel)[1]] = int(re.search(r"\.vgpr_count:\s*(\d+)", kernel)[1])
+    return found
+
+
+@pytest.mark.parametrize("lru", [0, 1])
+@pytest.mark.parametrize("kpw", [8, 16])
+@pytest.mark.parametrize("W", [1, 2, 4, 8])
+def test_inserts_of_long_rows_keep_four_waves(vgprs, W, kpw, lru):
+    """512 registers per SIMD lane, 128 for each of four waves."""
+    name = f"insert_kernelILi{W}ELi{kpw}ELb1ELb{lru}E"
+    mine = [v for k, v in vgprs.items() if name in k]
+    assert len(mine) == 1 and mine[0] <= 128
