@@ -648,7 +648,9 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
 // the loads of the (last) round have been issued: it may issue further loads behind them.  Only the first `lanes`
 // lanes have keys; with sets of 32 ways and more a wave load covers two keys or one, and those of the other lanes are left out
 // (40,000 keys of 512 bytes in 64-way sets, 23 keys per wave, checked: 19.8 us with them, all on the line of set 0, 10.2 without).
-template <int W, int KPW, bool kShared = false, typename Between>
+// kAlone: a lane that wants nothing seeks a value that no slot holds, and the lanes' keys travel alone; without it their `want` travels
+// beside them, one shuffle in four more (query_kernel says where that is the faster one).
+template <int W, int KPW, bool kShared = false, bool kAlone = true, typename Between>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key,
                                           uint32_t set, bool want, Between &&between, uint32_t lanes = KPW, int lane = lane_id()) {
     constexpr int G = kWave / W;                       // keys per wave load
@@ -657,7 +659,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
     const int slot = lane & (W - 1);
     const int sub  = lane / W;
     int way = -1;
-    const int64_t sought = want ? key : kEmpty + 1;    // what no slot holds: the lanes' keys travel alone, without their `want`
+    const int64_t sought = !kAlone || want ? key : kEmpty + 1;
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += RC) {
         int64_t sk[RC];
@@ -680,7 +682,9 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
 #pragma unroll
             for (int r = b; r < b + RB; ++r) {
                 const int j = (r0 + r) * G + sub;
-                const uint64_t m = __ballot(sk[r] == shfl64(sought, j));
+                const int64_t kj = shfl64(sought, j);
+                const int wj = kAlone ? 1 : __shfl((int)want, j, kWave);
+                const uint64_t m = __ballot(wj && sk[r] == kj);
                 if (lane / G == r0 + r) {
                     const uint64_t field = (W == 64) ? m : ((m >> ((lane % G) * W)) & ((1ull << (W & 63)) - 1));
                     if (field) way = __builtin_ctzll(field);
@@ -688,11 +692,11 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
             }
         }
     }
-    return want ? way : -1;
+    return !kAlone || want ? way : -1;
 }
-template <int W, int KPW, bool kShared = false>
+template <int W, int KPW, bool kShared = false, bool kAlone = true>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want, uint32_t lanes = KPW) {
-    return probe_wave<W, KPW, kShared>(K, key, set, want, [] {}, lanes);
+    return probe_wave<W, KPW, kShared, kAlone>(K, key, set, want, [] {}, lanes);
 }
 
 // probe_wave for an insert with the LRU policy: the stamps of the sets travel with their keys, and `victim` becomes the way that
@@ -819,8 +823,14 @@ __device__ __forceinline__ void finish_call(const QueryArgs &a, uint32_t n_miss,
 // kFull = true is launched for calls that name an LRU table or take their length from the device
 // (n_dev): only those kernels read g, stamp their hits and read *n_dev.  (As never-taken branches
 // in every kernel the three cost 0.4 us of a 19 us launch.)
+// The probe's keys travel alone (probe_wave), but not in plain work-groups of 8 workers with groups of 16 wave loads and more and sets
+// of 2 to 8 ways: 39,999 keys, 8 ways, with `want` / alone, rows of 768 bytes 13.1 / 13.6 us, 1,280 bytes 19.0 / 19.4, 2,048 bytes 27.1 / 27.6;
+// 20,000 of 1,280 bytes 13.4 / 13.9, 100,000 of 1 KiB 33.1 / 33.4.  Elsewhere alone is as fast or faster: 64 bytes 7.9 / 7.7, 512 bytes
+// 10.5 / 10.4, 106,496 keys of 512 bytes 16.8 / 16.6, 5,000 of 1,280 bytes 7.6 / 7.5, sets of 1 / 16 / 64 ways, 768 bytes 11.5 / 11.3, 14.1 / 13.8 and
+// 16.7 / 16.3; in work-groups of 7 workers within 1 % either way.  Registers and loads are the same but for two registers.
 template <int W, int KPW, int U, int WPB, bool kCoherent, int kD = 0, bool kFull = false>
 __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArgs a) {
+    constexpr bool kAlone = kD || WPB != 8 || U < 16 || W < 2 || W > 8;
     __shared__ uint64_t s_src[WPB][KPW];                // (an odd number of rows is less than KPW: room for its copied last entry)
     __shared__ uint32_t s_dst[WPB][KPW];
     __shared__ int64_t  s_mkey[WPB][KPW];
@@ -947,7 +957,7 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArg
                     if (__ballot(pending)) __builtin_amdgcn_s_sleep(2);
                 }
             } else {
-                way = probe_wave<W, KPW>(tb.K, key, set, want, kpw);
+                way = probe_wave<W, KPW, false, kAlone>(tb.K, key, set, want, kpw);
                 hit = way >= 0;
             }
 
