@@ -1366,9 +1366,10 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, (W == 64 && kLru ? 3 : 4))
 // waits while its wave owns a set.
 // Bound by memory: 1 GiB of cached rows refreshed in dump order at 4.6 TB/s of rows read and written.  Four waves per
 // SIMD (one GiB with its dump and query 438 us, 446 with the six that the registers would allow, on one device in turn;
-// twice as many wave loads in flight: 2 us more there, 3 us more on 2^18 scattered rows).
+// twice as many wave loads in flight: 2 us more there, 3 us more on 2^18 scattered rows).  Long rows of 16 and 32 ways need the limit from
+// below too: with 129 registers 262,144 rows of 1,280 bytes, 32 ways, in a dump's order 145 us, 131 this way.
 template <int W, int KPW, bool kLong>
-__global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
+__global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
     __shared__ uint32_t s_srcrow[kWavesPerWg][kWave];
     __shared__ WriterGroup s_group;
@@ -1427,12 +1428,31 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, 4))) __launch_bounds__(kBl
             shared_acquire();                                        // the word is read before the keys
             writer_tell(&s_group, told);
             // W lanes read a set's line, as in the other kernels; lanes without one to search read that of the first that has one, which
-            // is read anyway.  (Each lane reading its own set, 8 bytes at a time, made W requests of a line: 262,144 rows in random order
-            // 79.9 us, this way 75.6; as many absent keys 16.1 and 11.4.)
+            // is read anyway.  With 64 keys to a wave each lane reads its own set instead where that is less work: in a dump's order, where
+            // a run's lanes read the same line, and in wide sets when few lanes search, as behind a lost attempt.  (us, each lane its own / W lanes each /
+            // this way.  Rows of 512 bytes, random order, 8 ways: 262,144 95 / 85 / 85, absent 15.5 / 9.5 / 9.5; 100,000 rows, 16 ways 88 / 75 / 72,
+            // 64 ways 343 / 481 / 331, absent 37 / 21 / 22.  In a dump's order, 8 ways: 262,144 51.6 / 50.0 / 49.1; 100,000, 16 ways 29.0 / 29.1 / 27.1, 64 ways
+            // 39 / 62 / 39.  Both searches in the kernels of long rows and 8 ways cost 0.3-1 us in every order: 65,536 of 1,280 bytes in a dump's
+            // 34.7 / 34.9 / 35.1, random 53.6 / 53.5 / 54.4; fewer than four ways gain nothing.  With 16 keys to a wave W lanes each throughout.)
             const bool search = pending && !busy;
             const uint64_t smask = __ballot(search);
+            constexpr bool kBoth = KPW == kWave && W >= (kLong ? 16 : 4);
+            constexpr int kFew = W == 64 ? 32 : W >= 16 ? 8 : 0;
             int way = -1;
-            if (smask) {
+            if (kBoth && (2 * __popcll(startmask) <= __popcll(pendmask) || __popcll(smask) <= kFew)) {
+                if (search) {
+                    constexpr int F = W > 32 ? 32 : W;               // keys in flight together
+#pragma unroll 1
+                    for (int w0 = 0; w0 < W; w0 += F) {
+                        int64_t sk[F];
+#pragma unroll
+                        for (int w = 0; w < F; ++w) sk[w] = ld_agent(tb.K + (uint64_t)set * W + w0 + w);
+#pragma unroll
+                        for (int w = 0; w < F; ++w)
+                            if (sk[w] == key) way = w0 + w;
+                    }
+                }
+            } else if (smask) {
                 const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(smask));
                 way = probe_wave<W, KPW, true>(tb.K, key, search ? set : some, search);
             }
@@ -2002,11 +2022,16 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     // Insert: 16 keys per wave, 8 while 4,096 waves (four per SIMD) hold the batch that way: 8,192 rows 12.1 -> 9.7 us,
     // 32,768 rows 16.8 -> 15.7; with 8 throughout the 425,984-key streaming step takes 166 instead of 149 us.
     // (32 and 64 are 3-45 % slower than 16 from 1 K to 1 M keys.)
-    // Update: 64 keys per wave, 16 for batches of up to 49,152 keys: 8,192 rows 14.1 us (64s: 23, 8s: 13.4, but a dump's
+    // Update: 64 keys per wave, 16 for batches below 32,768 keys: 8,192 rows 14.1 us (64s: 23, 8s: 13.4, but a dump's
     // keys come eight to a set, and 8s split sets between waves: dump + update + query of 28,000 rows of 256
-    // bytes 28.6 instead of 26.0); 16s / 64s, in random order and in a dump's: 32,768 rows 17.5 / 21.8 and 13.5 / 17.0, 50,000 22.9 / 24.5 and
-    // 18.5 / 18.1, 65,536 27.2 / 28.2 and 21.3 / 18.5; on a 40 GB refresh 64s are 9-55 % faster.
-    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n <= 49152 ? 16u : (uint32_t)kWave);
+    // bytes 28.6 instead of 26.0); on a 40 GB refresh 64s are 9-55 % faster.
+    // Up to 49,152 keys 16 where the rows are long enough to outweigh that in a dump's order the waves wait for each other's sets.  16s / 64s,
+    // random order and a dump's: 40,000 rows of 512 bytes, 8 ways 25.1 / 29.5 and 15.2 / 17.2, 256 bytes 20.2 / 24.3 and 11.8 / 11.4, but 128 bytes
+    // 19.1 / 20.9 and 11.0 / 9.7; 33,000 rows, 16 ways, 256 bytes 25 / 33 and 12.1 / 13.7, 128 bytes 24 / 26 and 12.3 / 11.0; 32 ways, 512 bytes 46 / 60 and
+    // 20 / 22, 256 bytes 42 / 55 and 19.4 / 16.8; 64 ways, 512 bytes 90 / 132 and 44 / 29.  49,152 rows of 512 bytes, 8 ways 28.2 / 31.1 and 17.2 / 18.1,
+    // 60,000 33.6 / 35.2 and 20.2 / 18.7.
+    const uint32_t least = c->W <= 4 ? 16 * c->W : c->W <= 16 ? 64u : c->W <= 32 ? 128u : ~0u;
+    const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n < 32768 || (n <= 49152 && c->d >= least) ? 16u : (uint32_t)kWave);
     const uint64_t tiles = (n + kpw - 1) / kpw;
     uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
     if (blocks > (1u << 16)) blocks = 1u << 16;

@@ -88,6 +88,34 @@ def test_update_reads_a_wide_set_at_once():
     assert times[64] < 2.15 * times[16], f"us of 20 calls by ways: {times}"
 
 
+def test_update_in_slot_order_does_not_search_a_wide_set_again_for_every_lane():
+    """A dump's keys: the lanes of a set ask for its line together, once.  (64 ways over 8: 2.1; one search for every lane, and again
+    behind every lost attempt, 3.7.)"""
+    n, d, times = 100000, 32, {}
+    rows = torch.zeros(n, d, device="cuda")
+    busy = torch.empty(1 << 26, device="cuda")
+    for W in (8, 64):
+        slots = 1 << 19
+        h = B.hps_cache_create(slots, W, d)
+        dumped = torch.empty(slots, dtype=torch.int64, device="cuda")
+        n_dumped = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+        def calls():
+            for _ in range(10):
+                B.hps_cache_update(h, dumped, rows, n)
+
+        try:
+            for keys in torch.arange(slots // 2, device="cuda").split(1 << 16):
+                B.hps_cache_insert(h, keys, rows, len(keys))
+            B.hps_cache_dump(h, 0, slots, dumped, n_dumped)
+            assert n_dumped.item() > n
+            times[W], = _median_us([calls], lambda: [busy.fill_(0.0) for _ in range(4)])
+        finally:
+            torch.cuda.synchronize()
+            B.hps_cache_destroy(h)
+    assert times[64] < 2.8 * times[8], f"us of 10 calls by ways: {times}"
+
+
 def test_lru_insert_reads_a_wide_set_at_once():
     """Alg. 3's search for the oldest slot asks for keys and stamps together.  (New keys, 64 ways over 16: 3.5; one by one 4.7.)"""
     n, d, times = 40000, 32, {}

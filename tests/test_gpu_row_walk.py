@@ -75,11 +75,38 @@ def test_shapes_by_batch_and_width(d, n, mode):
         oc.close()
 
 
+@pytest.mark.parametrize("W,d", [(1, 12), (1, 16), (4, 60), (4, 64), (8, 60), (8, 64), (8, 124), (8, 192), (8, 256), (8, 260), (8, 320), (8, 516), (16, 60),
+                                 (16, 64), (16, 260), (32, 124), (32, 128), (32, 260), (64, 128), (64, 260)])
+def test_updates_on_both_sides_of_their_switches(W, d):
+    """16 keys to a wave below 32,768 of them and, for rows long enough, up to 49,152, else 64; there each lane searches its own set in a
+    dump's order and where few lanes search, W lanes search it otherwise.  Cached keys, absent ones and keys given twice (with the same
+    row); rows of less than a wave load, of one and of several."""
+    S = (1 << 16) // W
+    rng = np.random.Generator(np.random.PCG64(1000 * W + d))
+    with DeviceCache(S * W, W, d) as gc:
+        oc = OracleCache(S * W, W, d)
+        pool = np.arange(1, S * W, dtype=np.int64)
+        gc.insert(pool, inputs.backing_rows(pool, d))
+        gk, gctr, gv = gc.export()
+        oc.load_state(gk, gctr, gv)
+        cached = gk[gk != -(1 << 63)]
+        slots = np.resize(cached, 70001)
+        mixed = rng.permutation(np.concatenate([cached, cached[:3000], pool[:20000] + 10 ** 7]))
+        for version, keys in enumerate([slots[:32767], slots[:32768], slots[:49152], slots[:49153], slots,
+                                        mixed[:32768], np.resize(mixed, 49152), np.resize(mixed, 49153)], 1):
+            rows = inputs.backing_rows(keys, d, version=version)
+            gc.update(keys, rows)
+            oc.update(keys, rows)
+            gk2, gctr2, gv2 = gc.export()
+            assert (gk2 == gk).all() and (gctr2 == gctr).all() and (gv2 == np.array(oc.vals)).all()
+        oc.close()
+
+
 @pytest.mark.parametrize("n", [5000, 33000])
 @pytest.mark.parametrize("d", [4, 60, 64, 124, 192, 256, 260])
 def test_writers_by_width(d, n):
-    """Rows that divide a wave's lanes and rows that do not, up to and above one wave load, in batches on both sides of the
-    writers' shapes."""
+    """Rows that divide a wave's lanes and rows that do not, up to and above one wave load, in inserts on both sides of their
+    switch and updates of half as many rows, 16 keys to a wave."""
     S, W = 131071, 8                         # no set gets more than W keys
     keys = np.arange(n, dtype=np.int64) * 3 + 1
     with DeviceCache(S * W, W, d) as gc:

@@ -34,3 +34,12 @@ def test_inserts_of_long_rows_keep_four_waves(vgprs, W, kpw, lru):
     name = f"insert_kernelILi{W}ELi{kpw}ELb1ELb{lru}E"
     mine = [v for k, v in vgprs.items() if name in k]
     assert len(mine) == 1 and mine[0] <= 128
+
+
+@pytest.mark.parametrize("lng", [0, 1])
+@pytest.mark.parametrize("kpw", [16, 64])
+@pytest.mark.parametrize("W", [1, 2, 4, 8, 16, 32, 64])
+def test_updates_keep_four_waves(vgprs, W, kpw, lng):
+    name = f"update_kernelILi{W}ELi{kpw}ELb{lng}E"
+    mine = [v for k, v in vgprs.items() if name in k]
+    assert len(mine) == 1 and mine[0] <= 128
