@@ -226,7 +226,6 @@ struct RowGeom {
     uint32_t LPR;              // lanes per row: min(64, next power of two >= C)
     uint32_t lprShift;         // log2(LPR)
     uint32_t passes;           // ceil(C / LPR): > 1 only for rows longer than 1 KiB
-    uint32_t LPR8, lpr8Shift;  // the same with 8-byte chunks (the writers' long rows): min(64, next power of two >= d/2)
     ChunkStep c16, c8;         // walks over the 16-byte and the 8-byte chunks (scoped accesses) of a list of rows
 };
 
@@ -494,15 +493,20 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
 // against 81 us.)
 constexpr uint64_t kSkipRow = ~0ull;             // dstRow of an entry that finish() is not to store
 
-// What a lane moves of a row at a time: 8 bytes of a long row, 16 of a shorter one (below).
+// What a lane moves of a row at a time: 8 bytes of a long row, 16 of a shorter one.
 template <bool kLong>
 struct RowPiece {
     typedef uint64_t type;
     static __device__ __forceinline__ type load(const float *row, uint32_t c) { return __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(row) + c); }
     static __device__ __forceinline__ void store(float *row, uint32_t c, type v) { shared_st64(reinterpret_cast<uint64_t *>(row) + c, v); }
     static __device__ __forceinline__ const ChunkStep &step(const RowGeom &g) { return g.c8; }
-    static __device__ __forceinline__ uint32_t lanes(const RowGeom &g) { return g.LPR8; }
-    static __device__ __forceinline__ uint32_t shift(const RowGeom &g) { return g.lpr8Shift; }
+};
+template <>
+struct RowPiece<false> {
+    typedef u32x4 type;
+    static __device__ __forceinline__ type load(const float *row, uint32_t c) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row) + c); }
+    static __device__ __forceinline__ void store(float *row, uint32_t c, type v) { shared_st128(reinterpret_cast<u32x4 *>(row) + c, v); }
+    static __device__ __forceinline__ const ChunkStep &step(const RowGeom &g) { return g.c16; }
 };
 
 template <int U, bool kLong>
@@ -523,7 +527,7 @@ struct RowMover {
 
     // Wave load k of the list: does it hold rows at all (uniform), does this lane have one, which row, which chunk of it.
     __device__ __forceinline__ bool any(uint32_t k) const {
-        return kLong ? (uint64_t)k * kWave < (uint64_t)cnt * P::step(g).C : (k << (6u - P::shift(g))) < cnt;
+        return kLong ? (uint64_t)k * kWave < (uint64_t)cnt * P::step(g).C : (k << (6u - g.lprShift)) < cnt;
     }
     __device__ __forceinline__ bool place(uint32_t k, ChunkWalk &w, uint32_t &r, uint32_t &c) const {
         const uint32_t lane = (uint32_t)lane_id();
@@ -534,10 +538,10 @@ struct RowMover {
             c = live ? w.c : 0u;
             w.next(P::step(g));
         } else {
-            const uint32_t e = (k << (6u - P::shift(g))) + (lane >> P::shift(g));
+            const uint32_t e = (k << (6u - g.lprShift)) + (lane >> g.lprShift);
             live = e < cnt;
             r = live ? e : 0u;
-            c = lane & (P::lanes(g) - 1u);
+            c = lane & (g.LPR - 1u);
             c = c < P::step(g).C ? c : 0u;
         }
         return live;
@@ -601,9 +605,9 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
     typedef RowPiece<kLong> P;
     typedef typename P::type Chunk;
     const uint32_t lane = (uint32_t)lane_id();
-    const uint32_t rpi = (uint32_t)kWave >> P::shift(g);
-    const uint32_t sub = lane >> P::shift(g);
-    uint32_t cl = lane & (P::lanes(g) - 1);
+    const uint32_t rpi = (uint32_t)kWave >> g.lprShift;
+    const uint32_t sub = lane >> g.lprShift;
+    uint32_t cl = lane & (g.LPR - 1);
     cl = cl < P::step(g).C ? cl : 0u;
     typedef typename std::conditional<kLong, uint64_t, uint32_t>::type Count;   // 16 rows of 2 GiB have 2^32 chunks
     const Count step = kLong ? (Count)(kWave * U) : (Count)(rpi * U);
@@ -748,17 +752,6 @@ __device__ __forceinline__ int probe_lru_wave(const int64_t *K, const uint32_t *
     }
     return way;
 }
-
-// A shorter row's piece.
-template <>
-struct RowPiece<false> {
-    typedef u32x4 type;
-    static __device__ __forceinline__ type load(const float *row, uint32_t c) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row) + c); }
-    static __device__ __forceinline__ void store(float *row, uint32_t c, type v) { shared_st128(reinterpret_cast<u32x4 *>(row) + c, v); }
-    static __device__ __forceinline__ const ChunkStep &step(const RowGeom &g) { return g.c16; }
-    static __device__ __forceinline__ uint32_t lanes(const RowGeom &g) { return g.LPR; }
-    static __device__ __forceinline__ uint32_t shift(const RowGeom &g) { return g.lprShift; }
-};
 
 // ------------------------------------------------------------------ query
 
@@ -1777,10 +1770,6 @@ RowGeom make_geom(uint32_t d) {
     g.LPR = lpr;
     g.lprShift = sh;
     g.passes = (g.C + lpr - 1) / lpr;
-    lpr = 1; sh = 0;
-    while (lpr < d / 2 && lpr < (uint32_t)kWave) { lpr <<= 1; ++sh; }
-    g.LPR8 = lpr;
-    g.lpr8Shift = sh;
     auto step = [](uint32_t C) {               // lane * (inv * C - 2^16) < 2^16 for lane, C <= 64: the quotient is exact
         const uint32_t inv = C > (uint32_t)kWave ? 0u : (65536u + C - 1) / C;
         return ChunkStep{C, inv | ((uint32_t)kWave / C) << 17 | ((uint32_t)kWave % C) << 24};
