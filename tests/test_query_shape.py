@@ -24,7 +24,7 @@ int main() {
                                 std::printf("mode %d d %u batch %llu tables %u cus %llu: shape %d\\n", mode, d, (unsigned long long)batch, t, (unsigned long long)cus, id);
                                 return 1;
                             }
-                            if (mode == 1 && (uint64_t)q.u * 64 < d / 2) { std::printf("a row of %u does not fit a group of %d\\n", d, q.u); return 1; }
+                            if (mode == 1 && (uint64_t)q.u * 64 < d / 4) { std::printf("a row of %u does not fit a group of %d\\n", d, q.u); return 1; }
                         }
     return 0;
 }
