@@ -45,9 +45,9 @@ def test_a_small_dedup_after_a_large_one_is_small():
 @pytest.mark.parametrize("policy,limit", [(B.HPS_POLICY_VICTIM_COUNTER, 0.35), (B.HPS_POLICY_LRU, 0.35)])
 def test_inserting_cached_keys_does_not_move_rows(policy, limit):
     """Alg. 3 ignores a key that is already there: its row of the batch need not be read.  (Present keys over new
-    ones, counter / LRU: 0.26 / 0.25 with the rows left alone, 0.50 / 0.53 with all of them read.  Under LRU present keys take the 22 us
-    that they always took; new ones took 120 and now take 90, so the bound of 0.24 for their quotient, which stood between 0.17
-    and 0.33 then, stands between 0.25 and 0.53 now.)"""
+    ones, counter / LRU: 0.26 / 0.25 with the rows left alone, 0.50 / 0.53 with all of them read.  Under LRU the quotient was 0.18 and the
+    bound 0.24 while the search for a victim was longer: both builds on one device, present keys 23.1 then and 22.6 us now, new ones
+    129 and 90.  A bound of 0.24 would be 21.6 us now, less than present keys ever took; 0.35 stands between 0.25 and 0.53.)"""
     n, d, W, S, rounds = 1 << 18, 128, 8, 1 << 20, 9
     batches = iter(torch.randperm(n * rounds, device="cuda").view(rounds, n))
     rows = torch.zeros(n, d, device="cuda")
