@@ -484,7 +484,7 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
 // the parts of a row are in flight together (30,000 rows of 1,280 bytes inserted, updated and queried:
 // 93.6 us when each 512-byte part of the rows was a pass of its own, 71 us with the walk).  For shorter
 // rows the walk's arithmetic costs more than it saves (400-byte rows 41.7 against 38.7 us, 30,000 rows of 768 / 1,024 bytes inserted,
-// updated and queried 55.9 / 61.9 against 54.4 / 60.4).
+// updated and queried 55.9 / 61.9 against 54.4 / 60.4).  A walk in pieces of 16 bytes has not been measured.
 // Bound by memory and by the chain around the copy.  16 bytes per lane instead of 8, half as many loads and stores: 2^18 rows of 512
 // bytes inserted, updated and queried 206.3 -> 197.2 us, 200,000 rows of 400 bytes 172 -> 159, 1 GiB of rows refreshed 446 -> 438.
 // (Twice as many wave loads in flight, U = 8: 200.4 and 441 us.  Plain write-back stores 198.1 and 455, non-temporal ones 213 and 424, and
@@ -1190,8 +1190,8 @@ struct WriteArgs {
 // holds its sets; the owners' rows are therefore requested right behind their sets' keys, before it is known
 // whether they are needed: 2^18 new rows of 512 bytes, inserted, updated and queried, 221 -> 208 us, 32,768 rows 18.5 ->
 // 16.8 us per insert.  The first look keeps this from reading the rows of keys that are already there, in the round
-// trip of the fetch-or: 2^18 such keys take 27.7 us, 47 without the look (with the LRU policy 30 and 57), new
-// ones 84-88 either way.  KPW = 16 or 8 (launch_write): four or eight times as many waves as keys / 64 share the row copies, and a
+// trip of the fetch-or: when it came in 2^18 such keys took 27.7 us, 47 without it (with the LRU policy 30 and 57), new
+// ones 84-88 either way; now present ones take 19.7 (22.6), new ones 77 (90).  KPW = 16 or 8 (launch_write): four or eight times as many waves as keys / 64 share the row copies, and a
 // wave's chain is two copy groups long, or one, instead of eight.
 //
 // Each policy has its own kernels, so that the victim counter's do not hold the LRU search's keys and stamps: in one kernel they took
@@ -1864,8 +1864,9 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // counter atomics and by the number of keys in flight: 15 workers 42.9, 7 workers 44.5 at 851,968 keys of
 // 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7; nor do sets of more than 16 ways, whose keys spill
 // (300,000 keys of 128 bytes, 32 / 64 ways: 15 workers 34.4 / 52.0, 7 workers 20.1 / 24.5).
-// Checked (4 / 7 workers): 5,000 keys of 512 bytes 6.6 / 7.0, 8,192 keys 7.9 / 8.0, 13,312 keys 9.0 / 8.6, of 256 bytes
-// 8.8 / 8.3, 26,624 keys of 128 bytes 9.3 / 9.0, 106,496 keys of 128 bytes 14.2 / 11.6.
+// Checked (4 / 7 workers): 832 keys of 512 bytes 5.8 / 6.1, 5,000 keys 6.6 / 7.2, 8,192 keys 7.2 / 7.5, 10,240 keys 7.65 / 7.7, 13,312 keys 8.3 / 8.1,
+// 26,624 keys 10.8 / 9.7; of 256 bytes 8,192 keys 6.8 / 6.7, 13,312 keys 7.9 / 7.3; of 128 bytes 8,192 keys 6.6 / 6.5, 106,496 keys 12.8 / 10.1; of 1,280 bytes
+// 5,000 keys 8.9 / 10.1, 13,312 keys 10.8 / 11.6.
 //
 // Keys per wave: at most 64, trimmed so that the work-groups come out as a whole number of rounds
 // over the CUs (106,496 keys in tiles of 8 x 52 are exactly 256 work-groups; tiles of 8 x 64 would be
