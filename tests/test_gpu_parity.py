@@ -396,7 +396,7 @@ def test_write_batches_of_long_rows_around_the_kernel_switches(d):
         oc = OracleCache(S * W, W, d)
         pool = np.unique(inputs.uniform_keys(90000, 1 << 40, 63))
         rng = np.random.Generator(np.random.PCG64(d))
-        for version, n in enumerate([17, 32767, 32768, 32769, 40000], 1):
+        for version, n in enumerate([17, 32767, 32768, 32769, 40000, 49153], 1):
             ins = rng.choice(pool, n - n // 4, replace=False)
             ins = rng.permutation(np.concatenate([ins, ins[:n // 4]]))
             insert_both(gc, oc, ins, rows_u32(ins, d, 0))
