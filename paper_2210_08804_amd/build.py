@@ -15,6 +15,8 @@ FLAGS = [
     # keep single-lane atomics as written: the wave-aggregating rewrite reads the result back at
     # once (readfirstlane), which puts the atomic's latency on the critical path
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+    # the leading words of a kernel's arguments arrive in registers (query_kernel)
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wextra", "-Wno-unused-parameter",
     "-I", os.path.join(ROOT, "include"),
 ]

@@ -253,61 +253,40 @@ struct ChunkWalk {
 };
 
 // Copy `cnt` (> 0) rows listed in LDS: row srcRow[e] of `src` to row dstRow[e] of `dst`, for
-// e < cnt.  LPR lanes move one row, 16 B per lane, so a wave load/store covers 64/LPR whole
-// rows.  The rows go in groups of U wave loads: a group's loads are ALL issued, one wait for
-// them follows, then the group's stores go out back to back.  With U = 26 the 52 rows of a wave
-// of the 106,496-key batch (two 512-byte rows per wave load) are one group, every worker wave has
-// its whole share of the batch in flight at once, and the launch takes 18.4 us in the stand-alone
-// test bed against 21.5 us with two alternating buffers of 2 wave loads and 22.9 us with one
-// buffer of 4 (two groups of 15: 20.3 us).  Non-temporal loads here cost 6 us (repeated keys live
-// on L2 hits), non-temporal stores save 2 us (rows of `out` are written once and not read again
-// here).  Lanes beyond the list load entry 0 and store nothing; lanes beyond the row (d/4 not a
-// power of two) repeat chunk 0.
-// kPadded (kD = 128 only): behind a list of an odd number of rows its last entry stands once more (written by the caller), and
-// no lane needs a condition.  For a full list, an expansion's, that is the faster form (106,496 positions of 47,000 rows 16.9 -> 16.0 us); a
-// query's, where a part of the entries misses, is not full (18.1 us per 106,496 keys as it is, 19.8 this way).
-// kD = 128 fixes the row geometry at compile time (32 lanes per row, one pass, shifts instead
-// of multiplications); kD = 0 takes it from g and walks over the chunks of the listed rows (ChunkWalk),
-// four wave loads at a time as far as there are any.
-template <int U, int kD = 0, bool kPadded = false, typename SrcIdx, typename DstIdx>
+// e < cnt.  A wave load/store moves 64 chunks of 16 bytes, of as many rows as that is.  The rows go in groups of U wave
+// loads: a group's loads are ALL issued, one wait for them follows, then the group's stores go out back to back.  With
+// U = 26 the 52 rows of a wave of the 106,496-key batch (two 512-byte rows per wave load) are one group, and every worker wave has
+// its whole share of the batch in flight at once (stand-alone test bed: 18.3 us per launch; two alternating buffers of 2 wave
+// loads 21.5, one buffer of 4 22.9, two groups of 15 20.3).  Non-temporal loads here cost 6 us (repeated keys live
+// on L2 hits), non-temporal stores save 2 us (rows of `out` are written once and not read again here).
+// arrived() is called once, when the last group's rows are in registers.
+// kD = 128 fixes the row geometry at compile time (32 lanes per row, one pass, shifts instead of multiplications); behind a list of an
+// odd number of rows its last entry stands once more (written by the caller), and no lane needs a condition.
+// kD = 0 takes the geometry from g and walks over the chunks of the listed rows (ChunkWalk), four wave loads at a time as far as
+// there are any; lanes beyond the list load entry 0 and store nothing.
+template <int U, int kD = 0, typename SrcIdx, typename DstIdx, typename Arrived>
 __device__ __forceinline__ void copy_rows(const RowGeom g, const float *__restrict__ src,
                                           float *__restrict__ dst, const SrcIdx *srcRow,
-                                          const DstIdx *dstRow, uint32_t cnt) {
+                                          const DstIdx *dstRow, uint32_t cnt, Arrived &&arrived) {
     static_assert(kD == 0 || kD == 128, "only the 128-word row is specialised");
     const uint32_t lane = (uint32_t)lane_id();
     if constexpr (kD == 128) {
         const uint32_t sub = lane >> 5;                          // two rows per wave load
         const uint32_t off = (lane & 31u) * 4;
-        for (uint32_t e0 = 0; kPadded && e0 < cnt; e0 += 2 * U) {
+        for (uint32_t e0 = 0; e0 < cnt; e0 += 2 * U) {
             f32x4 buf[U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (e0 + 2 * u < cnt)                                // uniform
                     buf[u] = *reinterpret_cast<const f32x4 *>(src + (uint64_t)srcRow[e0 + 2 * u + sub] * 128 + off);
-            __builtin_amdgcn_s_waitcnt(0x0F70);                      // as below
+            // One wait for the whole group, stated where the compiler can see it: it cannot count loads and stores under a
+            // condition among the outstanding operations, and would make the later stores of a group wait for the earlier ones.
+            __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), other counters untouched
+            if (e0 + 2 * U >= cnt) arrived();
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (e0 + 2 * u < cnt)
                     __builtin_nontemporal_store(buf[u], reinterpret_cast<f32x4 *>(dst + (uint64_t)dstRow[e0 + 2 * u + sub] * 128 + off));
-        }
-        for (uint32_t e0 = 0; !kPadded && e0 < cnt; e0 += 2 * U) {
-            f32x4 buf[U];
-            uint32_t ent[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t e = e0 + u * 2 + sub;
-                ent[u] = e < cnt ? e : 0xFFFFFFFFu;
-                buf[u] = *reinterpret_cast<const f32x4 *>(src + (uint64_t)srcRow[e < cnt ? e : 0u] * 128 + off);
-            }
-            // One wait for the whole group, stated where the compiler can see it.  The stores are
-            // predicated, so the compiler cannot count them among the outstanding operations and
-            // would make store k wait until at most U-1-k operations are in flight: the later
-            // stores of a group would wait for the earlier ones to be acknowledged.
-            __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0), other counters untouched
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (ent[u] != 0xFFFFFFFFu)
-                    __builtin_nontemporal_store(buf[u], reinterpret_cast<f32x4 *>(dst + (uint64_t)dstRow[ent[u]] * 128 + off));
         }
     } else {
         constexpr int Q = 4;                                     // wave loads per test for the end of the list
@@ -329,6 +308,7 @@ __device__ __forceinline__ void copy_rows(const RowGeom g, const float *__restri
                 }
             }
             __builtin_amdgcn_s_waitcnt(0x0F70);                  // as above
+            if (q0 + kWave * U >= total) arrived();
 #pragma unroll
             for (int b = 0; b < U; b += Q) {
                 if (q0 + b * kWave < total) {
@@ -355,11 +335,11 @@ __device__ __forceinline__ void copy_rows(const RowGeom g, const float *__restri
 // Bound by memory, and before that by the loads' issue: half as many of them as with 8 bytes per lane take 106,496
 // keys of 512 bytes from 19.7 to 18.0 us, 425,984 from 73 to 65, 851,968 of 128 bytes from 54 to 50, 20,000 of 4 KiB from 32.7 to 28.  Returns how many rows of the list are done; the caller goes through
 // the others again with copy_rows_checked.
-template <int U, int kD = 0>
+template <int U, int kD = 0, typename Tell>
 __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float *__restrict__ src,
                                                     float *__restrict__ dst, const uint64_t *srcRow,
                                                     const uint32_t *dstRow, uint32_t cnt,
-                                                    uint64_t e1, const uint32_t *epoch) {
+                                                    uint64_t e1, const uint32_t *epoch, Tell &&tell) {
     static_assert((kD == 0 || kD == 128) && U >= 4 && (kD || U % 4 == 0), "a 512-byte row is half a wave load");
     constexpr int Q = kD ? 1 : 4;                                    // wave loads per test for the end of the list
     const uint32_t lane = (uint32_t)lane_id();
@@ -391,6 +371,7 @@ __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float
         }
         shared_acquire();                                            // row loads complete before the epochs are read again
         if (__ballot(read_epochs(epoch) != e1)) return e0;
+        if (e0 + span >= cnt) tell();
 #pragma unroll
         for (int b = 0; b < U; b += Q) {
             if ((uint32_t)b * kWave < total) {
@@ -404,6 +385,7 @@ __device__ __forceinline__ uint32_t copy_rows_quiet(const RowGeom g, const float
             }
         }
     }
+    if (cnt == 0) tell();
     return cnt;
 }
 
@@ -423,9 +405,8 @@ __device__ __forceinline__ void copy_rows_checked(const RowGeom g, const float *
                                                   float *__restrict__ dst, const uint64_t *srcRow,
                                                   const uint32_t *dstRow, const uint32_t *setOf,
                                                   const uint32_t *v1Of, const uint32_t *sc,
-                                                  uint32_t cnt, uint32_t *retry) {
+                                                  uint32_t cnt, uint32_t *retry, uint32_t lane) {
     static_assert((kD == 0 || kD == 128) && U >= 4, "a 512-byte row is half a wave load");
-    const uint32_t lane = (uint32_t)lane_id();
     const uint64_t d = kD ? (uint64_t)kD : (uint64_t)g.d;
     const uint32_t C = kD ? 32u : g.c16.C;
     // rows per group: one lane per row re-reads its sequence word, so a group has at most 64 rows
@@ -756,7 +737,7 @@ __device__ __forceinline__ int probe_lru_wave(const int64_t *K, const uint32_t *
 // ------------------------------------------------------------------ query
 
 // The scalars come first, in two 64-byte lines, then one line per table: a kernel's first reads of
-// its arguments miss in the scalar cache line by line.
+// its arguments miss in the scalar cache line by line.  (What query_kernel needs for its first loads it is given in registers.)
 struct QueryArgs {
     const int64_t *keys;        // [T][B]
     float         *out;         // [T][B][d]
@@ -774,6 +755,12 @@ struct QueryArgs {
     Table          tab[HPS_MAX_TABLES];
 };
 static_assert(offsetof(QueryArgs, tab) == 128, "two lines of scalars");
+// Where query_kernel's QueryArgs stand in its argument block: behind 14 words of its own, at the next multiple of their alignment.
+constexpr uint32_t kQueryArgsAt = 64;
+static_assert(alignof(QueryArgs) == 64, "kQueryArgsAt");
+typedef const __attribute__((address_space(4))) QueryArgs *QueryArgsIn;
+constexpr uint32_t kGridX = 1u << 20;          // work-groups in a row of a query's grid
+constexpr uint32_t kDealt = 8;                 // neighbouring keys that a wave takes of a batch whose length is read on the device
 
 // Kernel arguments are read with scalar loads where they are first used, each followed by its own
 // wait; spread over several cache lines and basic blocks that put three to five dependent
@@ -786,27 +773,35 @@ static_assert(offsetof(QueryArgs, tab) == 128, "two lines of scalars");
 // publish the miss count, clear the call's counter word for the next call on the stream, and
 // advance the iteration count g of every LRU table of the call (Alg. 2 has thread 0 do the
 // atomic add; every tile has read g by then, because a tile reads it before it adds its count).
-__device__ __forceinline__ void finish_call(const QueryArgs &a, uint32_t n_miss, int lane) {
+// gdev: lane t's word of table t, nullptr for a table without stamps.
+__device__ __forceinline__ void finish_call(uint32_t *n_miss, uint64_t *slot, uint32_t *gdev, uint32_t misses, int lane) {
     if (lane == 0) {
-        *a.n_miss = n_miss;
-        __hip_atomic_store(a.slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *n_miss = misses;
+        __hip_atomic_store(slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if ((uint32_t)lane < a.n_tables && a.tab[lane].T)
-        __hip_atomic_fetch_add(a.tab[lane].gdev, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (gdev) __hip_atomic_fetch_add(gdev, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Query (Alg. 2).  A work-group is WPB worker waves plus one helper wave and handles tiles of
-// WPB*KPW positions; the first KPW lanes of each worker wave own one key each.
+// Query (Alg. 2).  A work-group is WPB worker waves plus one helper wave and handles one tile of
+// WPB*kpw positions; the first kpw lanes of each worker wave own one key each.
 //   workers  load key, hash, probe the set (probe_wave); misses are compacted per wave into LDS
 //            (ballot + mbcnt prefix), hits into the wave's <source slot, destination position>
-//            list; the wave then copies its rows (copy_rows) without waiting for the others.
-//   helper   once every worker wave has listed its misses (an LDS counter in the plain variant,
-//            a barrier in the checked one) it adds the tile's miss count to the call's counter
+//            list; the wave then copies its rows without waiting for the others.
+//   helper   once every worker wave has its rows (an LDS counter) it adds the tile's miss count to the call's counter
 //            word with one 64-bit atomic (low half: misses so far, high half: tiles done), then
 //            writes the tile's miss entries from LDS to the global list.  The tile that finds
 //            every other tile done publishes *n_miss and clears the word for the next call.
 // The helper exists so that no worker has the atomic's round trip in front of its row loads
-// (vector memory results return in issue order).
+// (vector memory results return in issue order).  It is told between a wave's loads and its stores: the tiles' atomics go to one
+// address, one after the other, and hold up what else goes to that channel, which a wave waits for while it reads rows and
+// nobody does while they are written (told as soon as the misses were known: 39,999 keys of 1,280 bytes plain 18.6 us, this way 15.7; 106,496 of
+// 512 bytes 17.3, 16.3; 26 tables 214, 208).
+// One tile to a work-group, and no loop over tiles around it: what a loop keeps in registers from one tile to the next took up to 100 more of
+// them, and as long before the first load (registers plain / checked, 512-byte rows in groups of 32: 221 / 237 with the loop, 138 / 151 without,
+// 128-byte rows checked 103, 62).  The first 14 words of the arguments arrive in registers (-amdgpu-kernarg-preload-count), so that a
+// wave's keys are requested ahead of the scalar loads for the rest, on which they waited before.  Both together with the above, us: 26,624 keys under LRU
+// 10.6 -> 9.2, 106,496 keys plain 17.9 -> 17.0 and checked 18.0 -> 16.7, 851,968 of 128 bytes checked 49.8 -> 44.5, 47,000 distinct keys
+// through a length on the device 12.6 -> 11.
 //
 // kCoherent = true is the variant for queries that may overlap insert/update kernels on other
 // streams: each worker reads its sets' sequence words before probing, skips sets a writer holds
@@ -822,196 +817,239 @@ __device__ __forceinline__ void finish_call(const QueryArgs &a, uint32_t n_miss,
 // 10.5 / 10.4, 106,496 keys of 512 bytes 16.8 / 16.6, 5,000 of 1,280 bytes 7.6 / 7.5, sets of 1 / 16 / 64 ways, 768 bytes 11.5 / 11.3, 14.1 / 13.8 and
 // 16.7 / 16.3; in work-groups of 7 workers within 1 % either way.  Registers and loads are the same but for two registers.
 template <int W, int KPW, int U, int WPB, bool kCoherent, int kD = 0, bool kFull = false>
-__global__ void __launch_bounds__((WPB + 1) * kWave) query_kernel(const QueryArgs a) {
+__global__ void __launch_bounds__((WPB + 1) * kWave)
+query_kernel(const int64_t *__restrict__ keys, const int64_t *K0, const uint32_t *epoch0, const uint32_t *n_dev, uint32_t batch, uint32_t kpw,
+             uint32_t tiles_per_table, uint32_t n_tiles, uint32_t S0, uint32_t smask0, const QueryArgs) {
     constexpr bool kAlone = kD || WPB != 8 || U < 16 || W < 2 || W > 8;
     __shared__ uint64_t s_src[WPB][KPW];                // (an odd number of rows is less than KPW: room for its copied last entry)
     __shared__ uint32_t s_dst[WPB][KPW];
     __shared__ int64_t  s_mkey[WPB][KPW];
     __shared__ uint32_t s_mpos[WPB][KPW];
     __shared__ uint32_t s_wcnt[WPB];
-    __shared__ uint32_t s_ready;                   // worker waves that have listed their misses (plain variant)
+    __shared__ uint32_t s_ready;                   // worker waves that have listed their misses
     __shared__ uint32_t s_set[kCoherent ? WPB : 1][kCoherent ? KPW : 1];
     __shared__ uint32_t s_v1[kCoherent ? WPB : 1][kCoherent ? KPW : 1];
     __shared__ uint32_t s_retry[kCoherent ? WPB : 1][2];
 
     const int lane = lane_id();
-    const int wave = (int)(threadIdx.x / kWave);
-    HPS_ARGS_NOW("s"(a.keys), "s"(a.out), "s"(a.n_dev), "s"(a.B), "s"(a.kpw), "s"(a.tiles_per_table), "s"(a.n_tiles),
-                 "s"(a.tab[0].K), "s"(a.tab[0].V), "s"(a.tab[0].T), "s"(a.tab[0].S), "s"(a.tab[0].smask));
-    const RowGeom g = a.g;
-    const bool many_tiles = a.n_tiles > gridDim.x;     // this work-group may take several tiles
-
-    if (!kCoherent) {
-        // The plain variant has no work-group barrier between probe and row copy: each worker
-        // wave goes on to its rows as soon as its own probe is done and only tells the helper,
-        // through s_ready, that its misses are listed.  (The barrier made every wave wait for the
-        // slowest probe of the work-group: 22.9 -> 22.1 us per 106,496-key batch without it.)
-        if (threadIdx.x == 0) s_ready = 0u;
-        __syncthreads();
+    const int wave = wave_id();
+    const uint32_t tile = blockIdx.y * kGridX + blockIdx.x;
+    if (tile >= n_tiles) return;                       // the grid's last row need not be full
+    const bool one = tiles_per_table == n_tiles;       // a call on one table
+    uint32_t t = 0u, lt = tile;
+    if (!one) {
+        t  = tile / tiles_per_table;
+        lt = tile - t * tiles_per_table;
     }
-    for (uint32_t tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-        const uint32_t t  = tile / a.tiles_per_table;
-        const uint32_t lt = tile - t * a.tiles_per_table;
-        if (wave < WPB) {
-            const Table   &tb   = a.tab[t];
-            if (kCoherent) HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc), "s"(tb.epoch));
-            else           HPS_ARGS_NOW("s"(tb.K), "s"(tb.V), "s"(tb.T), "s"(tb.gdev), "s"(tb.S), "s"(tb.smask), "s"(tb.sc));
-            // Alg. 2 "g <- g + 1": every tile of the call stamps with the count the call will leave
-            // behind; the tile that finishes the call stores it (see the helper wave below).
-            const uint32_t g_call = kFull && tb.T ? *tb.gdev + 1u : 0u;
-            uint32_t kpw = a.kpw, B = a.B;
-            if (kFull && a.n_dev) {
-                // The real length is known only here: the keys are spread evenly over the work-groups that were
-                // launched for the longest one (50,000 of 106,496 keys: all in the first half of them 20.0 us, spread 14.6 us).
-                const uint32_t nd = *a.n_dev;
-                B = nd < B ? nd : B;
-                const uint32_t waves = (uint32_t)WPB * a.n_tiles, k = (uint32_t)(((uint64_t)B + waves - 1) / waves);
-                const uint32_t least = kpw < kMinKeysPerWave ? kpw : kMinKeysPerWave;
-                kpw = k < least ? least : k;
-            }
-            const uint32_t b    = (lt * WPB + wave) * kpw + lane;
-            const bool     inb  = lane < (int)kpw && b < B;
-            const uint32_t pos  = t * a.B + b;         // position in keys/out (< 2^32 checked on host)
+    QueryArgsIn in = (QueryArgsIn)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + kQueryArgsAt);
+    if (threadIdx.x == 0) s_ready = 0u;
+    // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, eight at a
+    // time, so that a wave's keys can be requested beside it (50,000 of 106,496 keys: all in the first half of the waves 20.0 us, spread 14.6).
+    // At most kpw, rounded up to eights, fall to a wave.  In the default mode tiles to which none fall leave, and are not counted (3,000 of 300,000 keys 13.3 -> 6.8; a test
+    // holds it to be no slower than the plain one there, which would gain as much).
+    const bool dealt = kFull && n_dev && kpw >= kDealt;
+    auto tiles_of = [&](uint32_t nd) {
+        const uint32_t m = (nd + kDealt * WPB - 1) / (kDealt * WPB);
+        return !kCoherent || !dealt ? n_tiles : m == 0 ? 1u : m < n_tiles ? m : n_tiles;
+    };
 
-            const int64_t key  = inb ? a.keys[pos] : kEmpty;
-            const uint64_t e1  = kCoherent ? read_epochs(tb.epoch) : 0ull;
-            const bool    live = inb;
-            const bool    want = live && !is_reserved(key);
-            const uint32_t set = want ? set_of(key, tb.S, tb.smask) : 0u;
-            bool hit;
-            int  way;
-            if (kCoherent) {
-                hit = false;
-                way = -1;
-                bool pending = want;
-                // No writer at work.  (A wave without keys, of which a length on the device can leave most, has nothing to
-                // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not.)
-                if (__ballot(want) && !__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {
-                    shared_acquire();                                // the epochs are read before any key or row
-                    way = probe_wave<W, KPW, true>(tb.K, key, set, want, kpw);
-                    const uint64_t fmask = __ballot(way >= 0);
-                    const int r = rank_in(fmask);
-                    const uint32_t nf = (uint32_t)__popcll(fmask);
-                    if (way >= 0) {
-                        s_src[wave][r] = (uint64_t)set * W + (uint32_t)way;
-                        s_dst[wave][r] = pos;
-                        if (kD && (nf & 1u) && r + 1 == (int)nf) {
-                            s_src[wave][nf] = (uint64_t)set * W + (uint32_t)way;
-                            s_dst[wave][nf] = pos;
-                        }
-                    }
-                    wave_lds_fence();
-                    const uint32_t done = copy_rows_quiet<U, kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], nf, e1, tb.epoch);
-                    hit = way >= 0 && (uint32_t)r < done;
-                    pending = way >= 0 && !hit;                      // a miss is final, as below
-                    wave_lds_fence();
-                }
-                uint32_t rounds = 0;
-                while (__ballot(pending)) {
-                    if (++rounds > kMaxRounds) {                     // a set never came free: report a miss
-                        if (pending) __hip_atomic_fetch_or(tb.flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT);
-                        break;
-                    }
-                    const uint32_t v1 = pending ? ld_agent(seq_of(tb, set)) : 0u;
-                    const bool busy = pending && (v1 & 1u);          // a writer holds the set: look again later
-                    shared_acquire();                                // the word is read before any key or row
-                    const int w = probe_wave<W, KPW, true>(tb.K, key, set, pending && !busy, kpw);
-                    const bool found = w >= 0;
-                    const uint64_t fmask = __ballot(found);
-                    if (lane < 2) s_retry[wave][lane] = 0u;
-                    if (found) {
-                        const int r = rank_in(fmask);
-                        s_src[wave][r] = (uint64_t)set * W + (uint32_t)w;
-                        s_dst[wave][r] = pos;
-                        s_set[wave][r] = set;
-                        s_v1[wave][r]  = v1;
-                        const uint32_t nf = (uint32_t)__popcll(fmask);
-                        if (kD && (nf & 1u) && r + 1 == (int)nf) {
-                            s_src[wave][nf] = (uint64_t)set * W + (uint32_t)w;
-                            s_dst[wave][nf] = pos;
-                            s_set[wave][nf] = set;
-                            s_v1[wave][nf]  = v1;
-                        }
-                    }
-                    wave_lds_fence();
-                    if (fmask)
-                        copy_rows_checked<(kD ? U : 8), kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
-                                                             &s_v1[wave][0], tb.sc, (uint32_t)__popcll(fmask), &s_retry[wave][0]);
-                    wave_lds_fence();
-                    bool again = false;
-                    if (found) {
-                        const int r = rank_in(fmask);
-                        again = (s_retry[wave][r >> 5] >> (r & 31)) & 1u;
-                        if (!again) { hit = true; way = w; }
-                    }
-                    pending = busy || again;                         // a clean miss is final
-                    wave_lds_fence();
-                    if (__ballot(pending)) __builtin_amdgcn_s_sleep(2);
-                }
-            } else {
-                way = probe_wave<W, KPW, false, kAlone>(tb.K, key, set, want, kpw);
-                hit = way >= 0;
-            }
-
-            const uint64_t missmask = __ballot(live && !hit);
-            if (live && !hit) {
-                const int r = rank_in(missmask);
-                s_mpos[wave][r] = pos;
-                s_mkey[wave][r] = key;
-            }
-            if (lane == 0) s_wcnt[wave] = (uint32_t)__popcll(missmask);
-            // Alg. 2: refresh the counter.  A plain store: the XCD's write-back L2 merges the many stores
-            // a hot key draws (an agent-scope store per hit serialises them at the memory side and
-            // triples the kernel time); they reach memory at the latest when the kernel ends.
-            if (kFull && tb.T && hit) tb.T[(uint64_t)set * W + (uint32_t)way] = g_call;
-
-            if (kCoherent) {
-                __syncthreads();                           // rows were copied inside the retry loop
-            } else {
-                const uint64_t hitmask = __ballot(hit);
-                const uint32_t nh      = (uint32_t)__popcll(hitmask);
-                if (hit) {
-                    const int r = rank_in(hitmask);
-                    s_src[wave][r] = (uint64_t)set * W + (uint32_t)way;
-                    s_dst[wave][r] = pos;
-                }
-                wave_lds_fence();
-                if (lane == 0) __hip_atomic_fetch_add(&s_ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (nh) copy_rows<U, kD>(g, tb.V, a.out, &s_src[wave][0], &s_dst[wave][0], nh);
-            }
-        } else {
-            if (kCoherent) {
-                __syncthreads();
-            } else {
-                // every worker wave of the work-group reaches its increment (none leaves early), so this ends
-                while (__hip_atomic_load(&s_ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < (uint32_t)WPB)
-                    __builtin_amdgcn_s_sleep(2);
-            }
-            uint32_t total = 0;
-#pragma unroll
-            for (int w = 0; w < WPB; ++w) total += s_wcnt[w];
-            uint64_t old = 0;
-            if (lane == 0)
-                old = __hip_atomic_fetch_add(a.slot, (1ull << 32) | (uint64_t)total, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-            old = (uint64_t)shfl64((int64_t)old, 0);
-            uint32_t o = (uint32_t)old;
-#pragma unroll
-            for (int w = 0; w < WPB; ++w) {
-                const uint32_t c = s_wcnt[w];
-                for (uint32_t j = (uint32_t)lane; j < c; j += kWave) {
-                    a.miss_idx[o + j]  = s_mpos[w][j];
-                    a.miss_keys[o + j] = s_mkey[w][j];
-                }
-                o += c;
-            }
-            if ((uint32_t)(old >> 32) + 1u == a.n_tiles) {   // every tile has added its count (and read g)
-                finish_call(a, (uint32_t)old + total, lane);
-            }
-            if (!kCoherent && many_tiles && lane == 0) s_ready = 0u;
+    if (wave >= WPB) {
+        // ---- helper
+        uint32_t counted = n_tiles;
+        if (kFull && n_dev) {
+            const uint32_t nd = *n_dev;
+            counted = tiles_of(nd < batch ? nd : batch);
+            if (tile >= counted) return;
         }
-        if (kCoherent || many_tiles) __syncthreads();   // LDS lists are reused by the next tile
+        __syncthreads();
+        uint32_t *const miss_idx = in->miss_idx, *const n_miss = in->n_miss;
+        int64_t *const miss_keys = in->miss_keys;
+        uint64_t *const slot = in->slot;
+        HPS_ARGS_NOW("s"(miss_idx), "s"(miss_keys), "s"(slot), "s"(n_miss));
+        // (looked up now: behind the last tile's atomic the call would wait for it)
+        uint32_t *const gdev = kFull && (uint32_t)lane < in->n_tables && in->tab[lane].T ? in->tab[lane].gdev : nullptr;
+        // every worker wave of the work-group reaches its increment (none leaves early), so this ends
+        while (__hip_atomic_load(&s_ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < (uint32_t)WPB)
+            __builtin_amdgcn_s_sleep(kCoherent ? 1 : 2);
+        uint32_t total = 0;
+#pragma unroll
+        for (int w = 0; w < WPB; ++w) total += s_wcnt[w];
+        uint64_t old = 0;
+        if (lane == 0)
+            old = __hip_atomic_fetch_add(slot, (1ull << 32) | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        old = (uint64_t)shfl64((int64_t)old, 0);
+        uint32_t o = (uint32_t)old;
+#pragma unroll
+        for (int w = 0; w < WPB; ++w) {
+            const uint32_t c = s_wcnt[w];
+            for (uint32_t j = (uint32_t)lane; j < c; j += kWave) {
+                miss_idx[o + j]  = s_mpos[w][j];
+                miss_keys[o + j] = s_mkey[w][j];
+            }
+            o += c;
+        }
+        if ((uint32_t)(old >> 32) + 1u == counted)     // every tile has added its count (and read g)
+            finish_call(n_miss, slot, gdev, (uint32_t)old + total, lane);
+        return;
+    }
+
+    // ---- worker
+    const int64_t *K = K0;
+    const uint32_t *epoch = epoch0;
+    uint32_t S = S0, smask = smask0;
+    if (!one) {
+        K = in->tab[t].K;
+        epoch = in->tab[t].epoch;
+        S = in->tab[t].S;
+        smask = in->tab[t].smask;
+        if (kCoherent) HPS_ARGS_NOW("s"(K), "s"(epoch), "s"(S), "s"(smask));
+        else           HPS_ARGS_NOW("s"(K), "s"(S), "s"(smask));
+    }
+    uint32_t b = (lt * WPB + wave) * kpw + lane;
+    if (dealt) b = ((uint32_t)lane / kDealt * (n_tiles * WPB) + lt * WPB + wave) * kDealt + (uint32_t)lane % kDealt;
+    bool          live = (lane < (int)kpw || dealt) && b < batch;
+    const uint32_t pos = t * batch + b;                // position in keys/out (< 2^32 checked on host)
+
+    const int64_t  key = live ? keys[pos] : kEmpty;
+    const uint64_t e1  = kCoherent ? read_epochs(epoch) : 0ull;
+    if (kFull && n_dev) {
+        const uint32_t nd = *n_dev;
+        if (tile >= tiles_of(nd < batch ? nd : batch)) return;
+        live = live && b < nd;
+    }
+    __syncthreads();                                   // s_ready is zero
+    __builtin_amdgcn_sched_barrier(0);                 // (nobody waits here for keys)
+    // All that is needed from here on, while the keys travel.
+    asm volatile("" : "+s"(in));
+    float *const V = in->tab[t].V, *const out = in->out;
+    uint32_t *const T = in->tab[t].T, *const sc = in->tab[t].sc;
+    const RowGeom g = {in->g.d, in->g.C, in->g.LPR, in->g.lprShift, in->g.passes, {in->g.c16.C, in->g.c16.packed}, {in->g.c8.C, in->g.c8.packed}};
+    HPS_ARGS_NOW("s"(V), "s"(out), "s"(T), "s"(sc), "s"(g.d), "s"(g.c16.C), "s"(g.c16.packed));
+    // Alg. 2 "g <- g + 1": every tile of the call stamps with the count the call will leave
+    // behind; the tile that finishes the call stores it (finish_call).
+    const uint32_t g_call = kFull && T ? *in->tab[t].gdev + 1u : 0u;
+    const bool     want = live && !is_reserved(key);
+    const uint32_t set = want ? set_of(key, S, smask) : 0u;
+
+    // A wave's misses go to LDS, the helper is told.
+    uint32_t n_missed = 0;
+    auto list_misses = [&](bool missed) {
+        const uint64_t m = __ballot(missed);
+        if (missed) {
+            const uint32_t r = n_missed + (uint32_t)rank_in(m);
+            s_mpos[wave][r] = pos;
+            s_mkey[wave][r] = key;
+        }
+        n_missed += (uint32_t)__popcll(m);
+    };
+    auto tell = [&] {
+        if (lane == 0) {
+            s_wcnt[wave] = n_missed;
+            __hip_atomic_fetch_add(&s_ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+    // Alg. 2: refresh the counter.  A plain store: the XCD's write-back L2 merges the many stores
+    // a hot key draws (an agent-scope store per hit serialises them at the memory side and
+    // triples the kernel time); they reach memory at the latest when the kernel ends.
+    auto stamp = [&](bool hit, int way) {
+        if (kFull && T && hit) T[(uint64_t)set * W + (uint32_t)way] = g_call;
+    };
+
+    if constexpr (!kCoherent) {
+        const int  way = probe_wave<W, KPW, false, kAlone>(K, key, set, want, kpw);
+        const bool hit = way >= 0;
+        list_misses(live && !hit);
+        const uint64_t hitmask = __ballot(hit);
+        const uint32_t nh      = (uint32_t)__popcll(hitmask);
+        if (hit) {
+            const int r = rank_in(hitmask);
+            s_src[wave][r] = (uint64_t)set * W + (uint32_t)way;
+            s_dst[wave][r] = pos;
+            if (kD && (nh & 1u) && r + 1 == (int)nh) {
+                s_src[wave][nh] = (uint64_t)set * W + (uint32_t)way;
+                s_dst[wave][nh] = pos;
+            }
+        }
+        stamp(hit, way);
+        wave_lds_fence();
+        if (nh) copy_rows<U, kD>(g, V, out, &s_src[wave][0], &s_dst[wave][0], nh, tell);
+        else    tell();
+    } else {
+        bool pending = want;
+        list_misses(live && !want);
+        // No writer at work.  (A wave without keys, of which a length on the device can leave most, has nothing to
+        // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not.)
+        if (__ballot(want) && !__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {
+            shared_acquire();                          // the epochs are read before any key or row
+            const int way = probe_wave<W, KPW, true>(K, key, set, want, kpw);
+            const uint64_t fmask = __ballot(way >= 0);
+            const int r = rank_in(fmask);
+            const uint32_t nf = (uint32_t)__popcll(fmask);
+            if (way >= 0) {
+                s_src[wave][r] = (uint64_t)set * W + (uint32_t)way;
+                s_dst[wave][r] = pos;
+                if (kD && (nf & 1u) && r + 1 == (int)nf) {
+                    s_src[wave][nf] = (uint64_t)set * W + (uint32_t)way;
+                    s_dst[wave][nf] = pos;
+                }
+            }
+            list_misses(want && way < 0);              // a miss is final
+            wave_lds_fence();
+            const uint32_t done = copy_rows_quiet<U, kD>(g, V, out, &s_src[wave][0], &s_dst[wave][0], nf, e1, epoch, tell);
+            const bool hit = way >= 0 && (uint32_t)r < done;
+            stamp(hit, way);
+            pending = way >= 0 && !hit;
+            if (!__ballot(pending)) return;            // the helper has been told
+            wave_lds_fence();
+        }
+        uint32_t rounds = 0;
+        while (__ballot(pending)) {
+            if (++rounds > kMaxRounds) {               // a set never came free: report a miss
+                if (pending) __hip_atomic_fetch_or(in->tab[t].flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                list_misses(pending);
+                break;
+            }
+            int here = lane;
+            asm volatile("" : "+v"(here));             // this loop's lane arithmetic is not kept in registers from the start of the kernel
+            const uint32_t v1 = pending ? ld_agent(sc + 2ull * set) : 0u;
+            const bool busy = pending && (v1 & 1u);    // a writer holds the set: look again later
+            shared_acquire();                          // the word is read before any key or row
+            const int w = probe_wave<W, KPW, true>(K, key, set, pending && !busy, [] {}, kpw, here);
+            const bool found = w >= 0;
+            const uint64_t fmask = __ballot(found);
+            if (here < 2) s_retry[wave][here] = 0u;
+            if (found) {
+                const int r = rank_in(fmask);
+                s_src[wave][r] = (uint64_t)set * W + (uint32_t)w;
+                s_dst[wave][r] = pos;
+                s_set[wave][r] = set;
+                s_v1[wave][r]  = v1;
+                const uint32_t nf = (uint32_t)__popcll(fmask);
+                if (kD && (nf & 1u) && r + 1 == (int)nf) {
+                    s_src[wave][nf] = (uint64_t)set * W + (uint32_t)w;
+                    s_dst[wave][nf] = pos;
+                    s_set[wave][nf] = set;
+                    s_v1[wave][nf]  = v1;
+                }
+            }
+            wave_lds_fence();
+            if (fmask)
+                copy_rows_checked<(kD ? U : 8), kD>(g, V, out, &s_src[wave][0], &s_dst[wave][0], &s_set[wave][0],
+                                                     &s_v1[wave][0], sc, (uint32_t)__popcll(fmask), &s_retry[wave][0], (uint32_t)here);
+            wave_lds_fence();
+            bool again = false;
+            if (found) {
+                const int r = rank_in(fmask);
+                again = (s_retry[wave][r >> 5] >> (r & 31)) & 1u;
+            }
+            stamp(found && !again, w);
+            list_misses(pending && !busy && !found);   // a clean miss is final
+            pending = busy || again;
+            wave_lds_fence();
+            if (__ballot(pending)) __builtin_amdgcn_s_sleep(2);
+        }
+        wave_lds_fence();
+        tell();
     }
 }
 
@@ -1160,7 +1198,8 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_dedup_kernel(const Qu
                 }
                 o += c;
             }
-            if ((uint32_t)(old >> 32) + 1u == a.n_tiles) finish_call(a, (uint32_t)old + total, lane);
+            if ((uint32_t)(old >> 32) + 1u == a.n_tiles)
+                finish_call(a.n_miss, a.slot, (uint32_t)lane < a.n_tables && a.tab[lane].T ? a.tab[lane].gdev : nullptr, (uint32_t)old + total, lane);
         }
         __syncthreads();                                        // #5 LDS is reused by the next tile
     }
@@ -1662,7 +1701,7 @@ __global__ void __launch_bounds__(WPB * kWave) expand_rows_kernel(const float *_
         s_dst[wave][lane] = p;
     }
     wave_lds_fence();
-    copy_rows<U, kD, true>(g, rows, out, &s_src[wave][0], &s_dst[wave][0], cnt);
+    copy_rows<U, kD>(g, rows, out, &s_src[wave][0], &s_dst[wave][0], cnt, [] {});
 }
 
 // ------------------------------------------------------------------ measurement kernels (hps_membench.h)
@@ -1687,9 +1726,13 @@ __global__ void __launch_bounds__(WPB * kWave) membench_gather_kernel(const floa
         const int r = rank_in(hitmask);
         s_src[wave][r] = sl;
         s_dst[wave][r] = pos;
+        if (kD && (nh & 1u) && r + 1 == (int)nh) {          // (an odd number is less than 64)
+            s_src[wave][nh] = sl;
+            s_dst[wave][nh] = pos;
+        }
     }
     wave_lds_fence();
-    if (nh) copy_rows<U, kD>(g, rows, out, &s_src[wave][0], &s_dst[wave][0], nh);
+    if (nh) copy_rows<U, kD>(g, rows, out, &s_src[wave][0], &s_dst[wave][0], nh, [] {});
 }
 
 // Half of that row movement: kReads = true issues the group's row loads and stores nothing (the
@@ -1925,11 +1968,15 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
 
 template <int W, int U, int WPB, bool kCoherent, int kD>
 void launch_query_kernel(const QueryArgs &a, bool full, hipStream_t st) {
-    const uint32_t grid = a.n_tiles < (1u << 20) ? a.n_tiles : (1u << 20);
-    const dim3 block((WPB + 1) * kWave);
+    const dim3 grid(a.n_tiles < kGridX ? a.n_tiles : kGridX, (a.n_tiles + kGridX - 1) / kGridX), block((WPB + 1) * kWave);
+    const Table &t = a.tab[0];
     if constexpr (WPB <= 8 || W <= 16) {           // query_shape gives no more than 8 workers to wider sets
-        if (full) hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, true>), dim3(grid), block, 0, st, a);
-        else      hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, false>), dim3(grid), block, 0, st, a);
+#define HPS_QUERY(full) \
+    hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, full>), grid, block, 0, st, a.keys, t.K, t.epoch, a.n_dev, a.B, a.kpw, \
+                       a.tiles_per_table, a.n_tiles, t.S, t.smask, a)
+        if (full) HPS_QUERY(true);
+        else      HPS_QUERY(false);
+#undef HPS_QUERY
     }
 }
 
