@@ -633,9 +633,8 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
 // the loads of the (last) round have been issued: it may issue further loads behind them.  Only the first `lanes`
 // lanes have keys; with sets of 32 ways and more a wave load covers two keys or one, and those of the other lanes are left out
 // (40,000 keys of 512 bytes in 64-way sets, 23 keys per wave, checked: 19.8 us with them, all on the line of set 0, 10.2 without).
-// kAlone: a lane that wants nothing seeks a value that no slot holds, and the lanes' keys travel alone; without it their `want` travels
-// beside them, one shuffle in four more (query_kernel says where that is the faster one).
-template <int W, int KPW, bool kShared = false, bool kAlone = true, typename Between>
+// A lane that wants nothing seeks a value that no slot holds: its key travels alone, one shuffle in four less than with its `want` beside it.
+template <int W, int KPW, bool kShared = false, typename Between>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key,
                                           uint32_t set, bool want, Between &&between, uint32_t lanes = KPW, int lane = lane_id()) {
     constexpr int G = kWave / W;                       // keys per wave load
@@ -644,7 +643,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
     const int slot = lane & (W - 1);
     const int sub  = lane / W;
     int way = -1;
-    const int64_t sought = !kAlone || want ? key : kEmpty + 1;
+    const int64_t sought = want ? key : kEmpty + 1;
 #pragma unroll
     for (int r0 = 0; r0 < R; r0 += RC) {
         int64_t sk[RC];
@@ -668,8 +667,7 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
             for (int r = b; r < b + RB; ++r) {
                 const int j = (r0 + r) * G + sub;
                 const int64_t kj = shfl64(sought, j);
-                const int wj = kAlone ? 1 : __shfl((int)want, j, kWave);
-                const uint64_t m = __ballot(wj && sk[r] == kj);
+                const uint64_t m = __ballot(sk[r] == kj);
                 if (lane / G == r0 + r) {
                     const uint64_t field = (W == 64) ? m : ((m >> ((lane % G) * W)) & ((1ull << (W & 63)) - 1));
                     if (field) way = __builtin_ctzll(field);
@@ -677,11 +675,11 @@ __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t
             }
         }
     }
-    return !kAlone || want ? way : -1;
+    return want ? way : -1;
 }
-template <int W, int KPW, bool kShared = false, bool kAlone = true>
+template <int W, int KPW, bool kShared = false>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key, uint32_t set, bool want, uint32_t lanes = KPW) {
-    return probe_wave<W, KPW, kShared, kAlone>(K, key, set, want, [] {}, lanes);
+    return probe_wave<W, KPW, kShared>(K, key, set, want, [] {}, lanes);
 }
 
 // probe_wave for an insert with the LRU policy: the stamps of the sets travel with their keys, and `victim` becomes the way that
@@ -760,7 +758,7 @@ constexpr uint32_t kQueryArgsAt = 64;
 static_assert(alignof(QueryArgs) == 64, "kQueryArgsAt");
 typedef const __attribute__((address_space(4))) QueryArgs *QueryArgsIn;
 constexpr uint32_t kGridX = 1u << 20;          // work-groups in a row of a query's grid
-constexpr uint32_t kDealt = 8;                 // neighbouring keys that a wave takes of a batch whose length is read on the device
+constexpr uint32_t kDealt = 16;                // neighbouring keys that a wave takes of a batch whose length is read on the device
 
 // Kernel arguments are read with scalar loads where they are first used, each followed by its own
 // wait; spread over several cache lines and basic blocks that put three to five dependent
@@ -811,16 +809,10 @@ __device__ __forceinline__ void finish_call(uint32_t *n_miss, uint64_t *slot, ui
 // kFull = true is launched for calls that name an LRU table or take their length from the device
 // (n_dev): only those kernels read g, stamp their hits and read *n_dev.  (As never-taken branches
 // in every kernel the three cost 0.4 us of a 19 us launch.)
-// The probe's keys travel alone (probe_wave), but not in plain work-groups of 8 workers with groups of 16 wave loads and more and sets
-// of 2 to 8 ways: 39,999 keys, 8 ways, with `want` / alone, rows of 768 bytes 13.1 / 13.6 us, 1,280 bytes 19.0 / 19.4, 2,048 bytes 27.1 / 27.6;
-// 20,000 of 1,280 bytes 13.4 / 13.9, 100,000 of 1 KiB 33.1 / 33.4.  Elsewhere alone is as fast or faster: 64 bytes 7.9 / 7.7, 512 bytes
-// 10.5 / 10.4, 106,496 keys of 512 bytes 16.8 / 16.6, 5,000 of 1,280 bytes 7.6 / 7.5, sets of 1 / 16 / 64 ways, 768 bytes 11.5 / 11.3, 14.1 / 13.8 and
-// 16.7 / 16.3; in work-groups of 7 workers within 1 % either way.  Registers and loads are the same but for two registers.
 template <int W, int KPW, int U, int WPB, bool kCoherent, int kD = 0, bool kFull = false>
 __global__ void __launch_bounds__((WPB + 1) * kWave)
 query_kernel(const int64_t *__restrict__ keys, const int64_t *K0, const uint32_t *epoch0, const uint32_t *n_dev, uint32_t batch, uint32_t kpw,
              uint32_t tiles_per_table, uint32_t n_tiles, uint32_t S0, uint32_t smask0, const QueryArgs) {
-    constexpr bool kAlone = kD || WPB != 8 || U < 16 || W < 2 || W > 8;
     __shared__ uint64_t s_src[WPB][KPW];                // (an odd number of rows is less than KPW: room for its copied last entry)
     __shared__ uint32_t s_dst[WPB][KPW];
     __shared__ int64_t  s_mkey[WPB][KPW];
@@ -843,10 +835,11 @@ query_kernel(const int64_t *__restrict__ keys, const int64_t *K0, const uint32_t
     }
     QueryArgsIn in = (QueryArgsIn)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + kQueryArgsAt);
     if (threadIdx.x == 0) s_ready = 0u;
-    // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, eight at a
+    // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, sixteen at a
     // time, so that a wave's keys can be requested beside it (50,000 of 106,496 keys: all in the first half of the waves 20.0 us, spread 14.6).
-    // At most kpw, rounded up to eights, fall to a wave.  In the default mode tiles to which none fall leave, and are not counted (3,000 of 300,000 keys 13.3 -> 6.8; a test
-    // holds it to be no slower than the plain one there, which would gain as much).
+    // At most kpw, rounded up to sixteens, fall to a wave.  In the default mode tiles to which none fall leave, and are not counted (3,000 of 300,000 keys 13.3 -> 6.8; a test
+    // holds it to be no slower than the plain one there, which would gain as much; 50,000 of them dealt in
+    // fours / sixteens 16.2 / 12.3, 47,000 of 106,496 9.3 / 8.9).
     const bool dealt = kFull && n_dev && kpw >= kDealt;
     auto tiles_of = [&](uint32_t nd) {
         const uint32_t m = (nd + kDealt * WPB - 1) / (kDealt * WPB);
@@ -956,7 +949,7 @@ query_kernel(const int64_t *__restrict__ keys, const int64_t *K0, const uint32_t
     };
 
     if constexpr (!kCoherent) {
-        const int  way = probe_wave<W, KPW, false, kAlone>(K, key, set, want, kpw);
+        const int  way = probe_wave<W, KPW, false>(K, key, set, want, kpw);
         const bool hit = way >= 0;
         list_misses(live && !hit);
         const uint64_t hitmask = __ballot(hit);
@@ -1896,73 +1889,64 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 }
 
 // Launch shape of the query kernel: wpb worker waves per work-group, kpw keys per worker wave, row
-// copy in groups of u wave loads.  All figures are us per launch on 256 CUs.
+// copy in groups of u wave loads.  All figures are us per launch on 256 CUs (checked / plain where both are given).
 //
-// Workers.  Small batches want many small work-groups; ~10^5 keys want 512-key tiles (half as many
-// same-address counter atomics, which cost ~11 ns each and serialise); larger batches run several
-// work-groups per CU one after the other.  Plain, rows of 512 bytes (4 / 8 workers): 1,664 keys 5.6 /
-// 6.1, 13,312 keys 8.3 / 8.3, 39,936 keys 12.5 / 11.6, 62,400 keys 16.8 / 13.5; (8 workers in groups of 26 / 7
-// in groups of 32): 425,984 keys 65.5 / 65.3, 851,968 keys 143.0 / 125.7, the 26-table launch 400 / 378.
-// Rows of up to 128 bytes leave registers for 16 waves in two work-groups per CU and are bound by the
-// counter atomics and by the number of keys in flight: 15 workers 42.9, 7 workers 44.5 at 851,968 keys of
-// 128 bytes (32.7 / 36.8 at 64 bytes); rows of 256 bytes do not: 78.5 / 72.7; nor do sets of more than 16 ways, whose keys spill
-// (300,000 keys of 128 bytes, 32 / 64 ways: 15 workers 34.4 / 52.0, 7 workers 20.1 / 24.5).
-// Checked (4 / 7 workers): 832 keys of 512 bytes 5.8 / 6.1, 5,000 keys 6.6 / 7.2, 8,192 keys 7.2 / 7.5, 10,240 keys 7.65 / 7.7, 13,312 keys 8.3 / 8.1,
-// 26,624 keys 10.8 / 9.7; of 256 bytes 8,192 keys 6.8 / 6.7, 13,312 keys 7.9 / 7.3; of 128 bytes 8,192 keys 6.6 / 6.5, 106,496 keys 12.8 / 10.1; of 1,280 bytes
-// 5,000 keys 8.9 / 10.1, 13,312 keys 10.8 / 11.6.
+// Keys per wave: 16 KiB of rows (64 rows of up to 256 bytes) while the batch fits the CUs that way, else up to 32 KiB, which is the
+// longest group.  Fewer and larger waves than would fill the chip: every tile adds to one counter word, ~11 ns each
+// one after the other (26,624 keys of 512 bytes 15 / 32 keys to a wave 8.4 / 7.5, of 256 bytes 15 / 64 8.1 / 6.9; 106,496 keys 60 / 64
+// 16.1 / 15.6).  Small batches are bound by the chain of round trips of a wave, to which its own rows add, and go down to 8 keys, for about 100 tiles.
+// Beyond one round of tiles over the CUs the waves are trimmed such that the last round is full (106,496 keys of 1 KiB 64 / 32 to a wave 34.8 / 30);
+// with several tables the keys per wave go up as long as the tables' last, partly empty tiles would start another round (26 x 1,024 keys checked
+// 16.1 -> 11.2, 26 x 4,096 plain 20.9 -> 18.9).
 //
-// Keys per wave: at most 64, trimmed so that the work-groups come out as a whole number of rounds
-// over the CUs (106,496 keys in tiles of 8 x 52 are exactly 256 work-groups; tiles of 8 x 64 would be
-// 208, leaving 48 CUs idle).  Small batches go down to 16 keys per wave (8 below 4,096 keys): more
-// work-groups, each with a shorter chain of dependent row copies (1,664 keys: 5.5 us instead of 8.3 us;
-// 13,312 keys: 8.9 instead of 11.1 us).  With several tables the keys per wave go up as long as the tables'
-// last, partly empty tiles would start another round (26 x 1,024 keys checked 16.1 -> 11.2, 26 x 4,096 plain 20.9 -> 18.9).
+// Workers.  4 while that makes few tiles, 5 up to three quarters of the CUs, then 7 (5 / 7 / 8, 26,624 keys of 512 bytes 7.5 / 7.8 / 7.9;
+// 7 / 8, 106,496 keys 15.6 / 15.8, 425,984 keys 58.2 / 60.2, 106,496 of 1 KiB 29.9 / 30.7).  From 2^19 rows of up to 256 bytes on 11, one work-group per CU
+// (7 / 11, checked: 851,968 rows of 256 bytes 72 / 67.5, of 128 bytes 44.5 / 43.1, of 64 bytes 32.8 / 32.2; at 425,984 rows of 128 bytes 23.3 / 23.5), plain of up to 32
+// bytes 15 (11 / 15, 3,407,872 of 16 bytes 74.6 / 68.0); sets of more than 16 ways not, whose keys spill there.
 //
 // Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
 // first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
-// hold, and its code, all of it executed, lines that a short launch has to fetch.  64 keys of 128 bytes in groups
-// of 8 / 16 / 32 wave loads take 44.5 / 50.0 / 63.7 per 851,968 keys, 39,999 keys of 1,280 bytes in groups of 24 / 16
-// with idle lanes 19.4 / 24.1, 26,624 keys of 512 bytes in groups of 13 / 26 9.7 / 10.6.  Checked, rows
-// of 512 bytes: 13,312 keys in groups of 8 / 32 7.9 / 8.4, 26,624 keys 16 / 32 9.8 / 10.2, 106,496 keys 32 / 16 18.0 / 20.4,
-// 425,984 keys 32 / 16 67 / 75; 106,496 keys of 384 bytes 32 / 16 15.3 / 17.3, of 256 bytes 16 / 8 12.4 / 14.1; 39,999 keys of
-// 1,280 bytes 32 / 16 17.2 / 18.4; but 851,968 keys of 128 bytes 8 / 16 50 / 60: over several rounds the second
-// work-group that fits a CU with the smaller group is worth more, as long as a wave's rows are one group or two.
+// hold, and its code, all of it executed, lines that a short launch has to fetch (13,312 keys of 512 bytes in groups of 16 / 32
+// 6.35 / 6.30, 5,000 keys in groups of 8 / 16 6.1 / 6.2; 425,984 keys in groups of 32 / 16 58 / 70).  11 workers with rows of 128 bytes: 16 / 8 43.1 / 44.2.
 struct QueryShape { uint32_t kpw; int u, wpb; };
 
 // Most rows of d words that a wave moves with copy_rows, which counts their 16-byte chunks in 32 bits (fewer than 64
 // only for rows of 512 MiB and more).
 uint64_t most_rows(uint32_t d) { return (1ull << 31) / (d / 4); }
 
-QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup, uint32_t ways = 8) {
-    const uint64_t n = n_tables * batch;
-    QueryShape q{(uint32_t)kWave, 0, 0};
-    if (coherent) q.wpb = n < 10240 ? 4 : 7;
-    else if (n < (1u << 14)) q.wpb = 4;
-    else if (n < (1u << 18) || dedup) q.wpb = 8;
-    else q.wpb = d <= 32 && ways <= 16 ? 15 : 7;
-    const uint64_t full = (uint64_t)q.wpb * kWave * cus;       // keys per round at 64 keys per wave
-    const uint64_t rounds = (n + full - 1) / full;
-    const uint64_t floor_k = n < 4096 ? kMinKeysPerWave : 16;
-    if (rounds > 0 && rounds <= 8) {
+QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup, uint32_t ways = 8, bool n_dev = false) {
+    const uint64_t n = n_tables * batch, row = (uint64_t)d * 4;
+    auto rows_of = [&](uint64_t bytes) {                       // rows of a wave
+        const uint64_t k = bytes / row;
+        return k < kMinKeysPerWave ? (uint64_t)kMinKeysPerWave : k < (uint64_t)kWave ? k : (uint64_t)kWave;
+    };
+    const uint64_t some = rows_of(16384), most = dedup || n_dev ? (uint64_t)kWave : rows_of(32768);
+    QueryShape q{(uint32_t)most, 0, 0};
+    if (dedup) q.wpb = n < (1u << 14) ? 4 : 8;
+    else if (n >= (n_dev ? 1u << 18 : 1u << 19) && d <= 64 && ways <= 16) q.wpb = d <= 8 && !coherent ? 15 : 11;
+    else q.wpb = n <= 2 * some * cus ? 4 : 4 * n <= 15 * some * cus ? 5 : 7;      // up to cus / 2 and 3 / 4 cus tiles of that many keys per wave
+    const uint64_t full = (uint64_t)q.wpb * most * cus;        // keys per round
+    const uint64_t rounds = n ? (n + full - 1) / full : 1;
+    if (rounds <= 8) {
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
-        if (k < floor_k) k = floor_k;
+        if (coherent) k += k / 15;                             // (a few CUs without a tile are less than the tiles more; 425,984 keys plain 60 / 64 56.1 / 57.4)
+        if (rounds == 1) {
+            uint64_t least = n < 4096 ? kMinKeysPerWave : 16;
+            if (!dedup) least = (5 * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);    // 2 / 5 cus tiles
+            if (least > some) least = some;
+            if (least < kMinKeysPerWave) least = kMinKeysPerWave;
+            if (k < least) k = least;
+        }
         // a tile holds keys of one table: with several tables their last tiles are not full
         auto tiles = [&] { return n_tables * ((batch + q.wpb * k - 1) / (q.wpb * k)); };
-        while (n_tables > 1 && k < (uint64_t)kWave && tiles() > rounds * cus) ++k;
-        if (k < (uint64_t)kWave) q.kpw = (uint32_t)k;
+        while (n_tables > 1 && k < (q.wpb < 7 ? some : most) && tiles() > rounds * cus) ++k;
+        if (k < most) q.kpw = (uint32_t)k;
     }
     if (!dedup && q.kpw > most_rows(d)) q.kpw = (uint32_t)most_rows(d);
-    const uint64_t bytes = (uint64_t)q.kpw * d * 4;            // a wave's rows
-    if (coherent) {
-        if (d == 128 && q.wpb == 4) q.u = q.kpw <= 8 ? 4 : 8;
-        else if (d == 128) q.u = q.kpw <= 16 ? 8 : q.kpw <= 32 ? 16 : 32;
-        else if (bytes > 16384) q.u = 32;
-        else q.u = bytes <= 8192 || rounds > 1 ? 8 : 16;
-    } else if (d == 128) {
-        q.u = q.wpb == 7 ? 32 : q.kpw <= 16 ? 8 : q.kpw <= 26 && q.wpb == 8 ? 13 : 26;
-    } else {
-        q.u = bytes <= 8192 && q.wpb != 7 ? 8 : bytes <= 16384 ? 16 : q.wpb == 8 ? 24 : 32;
-    }
+    const uint64_t bytes = q.kpw * row;                        // a wave's rows
+    if (d == 128 && q.wpb == 4 && q.kpw <= 8) q.u = 4;
+    else if (q.wpb == 11) q.u = d <= 16 ? 8 : 16;
+    else q.u = bytes <= 8192 && (d != 128 || q.wpb == 4) ? 8 : bytes <= 16384 ? 16 : 32;
     return q;
 }
 
@@ -1997,33 +1981,42 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
         switch (d128 ? 10000 + id : id) {
             case 10404: launch_query_kernel<W, 4, 4, true, 128>(a, full, st); break;
             case 10804: launch_query_kernel<W, 8, 4, true, 128>(a, full, st); break;
-            case 10807: launch_query_kernel<W, 8, 7, true, 128>(a, full, st); break;
+            case 11604: launch_query_kernel<W, 16, 4, true, 128>(a, full, st); break;
+            case 11605: launch_query_kernel<W, 16, 5, true, 128>(a, full, st); break;
             case 11607: launch_query_kernel<W, 16, 7, true, 128>(a, full, st); break;
             case 13207: launch_query_kernel<W, 32, 7, true, 128>(a, full, st); break;
             case 804: launch_query_kernel<W, 8, 4, true, 0>(a, full, st); break;
             case 1604: launch_query_kernel<W, 16, 4, true, 0>(a, full, st); break;
             case 3204: launch_query_kernel<W, 32, 4, true, 0>(a, full, st); break;
+            case 805: launch_query_kernel<W, 8, 5, true, 0>(a, full, st); break;
+            case 1605: launch_query_kernel<W, 16, 5, true, 0>(a, full, st); break;
+            case 3205: launch_query_kernel<W, 32, 5, true, 0>(a, full, st); break;
             case 807: launch_query_kernel<W, 8, 7, true, 0>(a, full, st); break;
             case 1607: launch_query_kernel<W, 16, 7, true, 0>(a, full, st); break;
             case 3207: launch_query_kernel<W, 32, 7, true, 0>(a, full, st); break;
+            case 811: launch_query_kernel<W, 8, 11, true, 0>(a, full, st); break;
+            case 1611: launch_query_kernel<W, 16, 11, true, 0>(a, full, st); break;
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
     } else {
         switch (d128 ? 10000 + id : id) {
+            case 10404: launch_query_kernel<W, 4, 4, false, 128>(a, full, st); break;
             case 10804: launch_query_kernel<W, 8, 4, false, 128>(a, full, st); break;
-            case 12604: launch_query_kernel<W, 26, 4, false, 128>(a, full, st); break;
-            case 10808: launch_query_kernel<W, 8, 8, false, 128>(a, full, st); break;
-            case 11308: launch_query_kernel<W, 13, 8, false, 128>(a, full, st); break;
-            case 12608: launch_query_kernel<W, 26, 8, false, 128>(a, full, st); break;
+            case 11604: launch_query_kernel<W, 16, 4, false, 128>(a, full, st); break;
+            case 11605: launch_query_kernel<W, 16, 5, false, 128>(a, full, st); break;
+            case 11607: launch_query_kernel<W, 16, 7, false, 128>(a, full, st); break;
             case 13207: launch_query_kernel<W, 32, 7, false, 128>(a, full, st); break;
             case 804: launch_query_kernel<W, 8, 4, false, 0>(a, full, st); break;
             case 1604: launch_query_kernel<W, 16, 4, false, 0>(a, full, st); break;
             case 3204: launch_query_kernel<W, 32, 4, false, 0>(a, full, st); break;
-            case 808: launch_query_kernel<W, 8, 8, false, 0>(a, full, st); break;
-            case 1608: launch_query_kernel<W, 16, 8, false, 0>(a, full, st); break;
-            case 2408: launch_query_kernel<W, 24, 8, false, 0>(a, full, st); break;
+            case 805: launch_query_kernel<W, 8, 5, false, 0>(a, full, st); break;
+            case 1605: launch_query_kernel<W, 16, 5, false, 0>(a, full, st); break;
+            case 3205: launch_query_kernel<W, 32, 5, false, 0>(a, full, st); break;
+            case 807: launch_query_kernel<W, 8, 7, false, 0>(a, full, st); break;
             case 1607: launch_query_kernel<W, 16, 7, false, 0>(a, full, st); break;
             case 3207: launch_query_kernel<W, 32, 7, false, 0>(a, full, st); break;
+            case 811: launch_query_kernel<W, 8, 11, false, 0>(a, full, st); break;
+            case 1611: launch_query_kernel<W, 16, 11, false, 0>(a, full, st); break;
             case 815: launch_query_kernel<W, 8, 15, false, 0>(a, full, st); break;
             default: return fail(HPS_ERR_INVALID_ARG, "query shape not compiled in");
         }
@@ -2340,7 +2333,7 @@ static hps_status_t query_call(hps_cache_t *const *caches, uint32_t n_tables, co
     bool coherent = false;                      // any table that may see concurrent writers makes the call careful
     for (uint32_t t = 0; t < n_tables; ++t) coherent = coherent || caches[t]->concurrent_writers.load() != 0;
     const bool dedup = !coherent && caches[0]->query_dedup.load() != 0;
-    const QueryShape shape = query_shape(n_tables, batch, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup, caches[0]->W);
+    const QueryShape shape = query_shape(n_tables, batch, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup, caches[0]->W, n_dev != nullptr);
     const uint32_t kpw = shape.kpw;
     a.kpw = kpw;
     const uint32_t tile = kpw * (uint32_t)shape.wpb;

@@ -1,0 +1,78 @@
+"""Edges of a query's tiles: lengths that are read on the device, whose keys are dealt to the waves sixteen at a time, and
+launch shapes at the batch sizes where the rule changes them.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import OracleCache
+from paper_2210_08804_amd import binding as B
+from paper_2210_08804_amd import inputs
+from harness import DeviceCache, SENTINEL
+
+pytestmark = pytest.mark.gpu
+
+
+def filled(d, policy=0, ways=8):
+    """A cache and its oracle with 6,000 keys in 8,192 sets, none of which overflows; a batch over twice as many."""
+    keys = np.arange(6000, dtype=np.int64)
+    rows = inputs.backing_rows(keys, d)
+    gc, oc = DeviceCache(8192 * ways, ways, d, policy=policy), OracleCache(8192 * ways, ways, d)
+    for k, r in zip(np.array_split(keys, 12), np.array_split(rows, 12)):
+        B.hps_cache_insert(gc.h, torch.from_numpy(k).cuda(), torch.from_numpy(r).cuda(), len(k))
+        torch.cuda.synchronize()
+        oc.insert(k, r)
+    return gc, oc
+
+
+def expected(oc, keys, d):
+    out = np.full((len(keys), d), SENTINEL, dtype=np.uint32)
+    _, mi, mk = oc.query(keys, out)
+    return out, mi, mk
+
+
+@pytest.mark.parametrize("checked", [True, False])
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("d,n_max", [(128, 26624), (128, 5000), (32, 7000), (320, 9000)])
+def test_length_on_the_device_at_the_edges_of_the_deal(d, n_max, policy, checked):
+    gc, oc = filled(d, policy)
+    with gc:
+        B.hps_cache_set_concurrent_writers(gc.h, checked)
+        keys = np.random.default_rng(5).integers(0, 12000, n_max)
+        dk = torch.from_numpy(keys).cuda()
+        # one deal, one wave's and one tile's worth of keys with 4, 5 and 7 workers, and the whole batch; each with its neighbours
+        for m in sorted({max(0, min(n_max, e + o)) for e in (0, 16, 32, 64, 80, 112, 128, 1024, n_max) for o in (-1, 0, 1)}):
+            out = torch.full((n_max, d), 0, dtype=torch.int32, device="cuda")
+            out.fill_(SENTINEL)
+            mi = torch.full((n_max,), -1, dtype=torch.int32, device="cuda")
+            mk = torch.full((n_max,), -1, dtype=torch.int64, device="cuda")
+            nm = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+            nd = torch.tensor([m], dtype=torch.int32, device="cuda")
+            B.hps_cache_query_dn(gc.h, dk, n_max, nd, out.view(torch.float32), mi, mk, nm)
+            torch.cuda.synchronize()
+            want, wi, wk = expected(oc, keys[:m], d)
+            got = out.cpu().numpy().view(np.uint32)
+            assert int(nm.item()) == len(wi), m
+            assert (got[:m] == want).all() and (got[m:] == np.uint32(SENTINEL)).all(), m
+            order = np.argsort(mi.cpu().numpy()[:len(wi)])
+            assert (mi.cpu().numpy()[:len(wi)][order] == wi).all() and (mk.cpu().numpy()[:len(wi)][order] == wk).all(), m
+            assert (mi.cpu().numpy()[len(wi):] == -1).all(), m
+
+
+@pytest.mark.parametrize("checked", [True, False])
+@pytest.mark.parametrize("d,n", [
+    (128, 1), (128, 3264), (128, 3265), (128, 16384), (128, 16385), (128, 30720), (128, 30721), (128, 57344), (128, 57345),
+    (512, 4096), (512, 4097), (512, 7681), (512, 28673), (4, 1 << 19), (16, (1 << 19) - 1), (16, (1 << 19) + 705), (32, (1 << 19) + 1), (64, 1 << 19),
+    (68, 1 << 19), (1024, 2049)])
+def test_batches_where_the_launch_shape_changes(d, n, checked):
+    gc, oc = filled(d)
+    with gc:
+        B.hps_cache_set_concurrent_writers(gc.h, checked)
+        keys = np.random.default_rng(n).integers(0, 12000, n)
+        out, mi, mk = gc.query(keys)
+        # the oracle looks at every key once
+        uniq, inv = np.unique(keys, return_inverse=True)
+        want, wi, _ = expected(oc, uniq, d)
+        missed = np.zeros(len(uniq), dtype=bool)
+        missed[wi] = True
+        assert (out == want[inv]).all()
+        assert (mi == np.flatnonzero(missed[inv])).all() and (mk == keys[missed[inv]]).all()
