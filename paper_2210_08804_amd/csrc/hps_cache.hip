@@ -144,6 +144,13 @@ typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 __device__ __forceinline__ u32x4 shared_ld128(const u32x4 *p) { return __builtin_amdgcn_global_load_b128((global_u32x4 *)p, "agent"); }
 __device__ __forceinline__ void shared_st128(u32x4 *p, u32x4 v) { __builtin_amdgcn_global_store_b128((global_u32x4 *)p, v, "agent"); }
 
+// Arguments that arrive in registers.  They go in vectors: the runtime takes a while for each argument of a launch (eight of
+// them more 0.3 us of the host's time).
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <typename T> __device__ __forceinline__ T *global_at(uint64_t word) { return (T *)(__attribute__((address_space(1))) T *)word; }
+inline uint64_t word_of(const void *p) { return (uint64_t)reinterpret_cast<uintptr_t>(p); }
+
 struct alignas(64) Table {     // one cache as the kernels see it (one 64-byte line of the kernel arguments)
     int64_t  *K;
     float    *V;
@@ -811,8 +818,12 @@ __device__ __forceinline__ void finish_call(uint32_t *n_miss, uint64_t *slot, ui
 // in every kernel the three cost 0.4 us of a 19 us launch.)
 template <int W, int KPW, int U, int WPB, bool kCoherent, int kD = 0, bool kFull = false>
 __global__ void __launch_bounds__((WPB + 1) * kWave)
-query_kernel(const int64_t *__restrict__ keys, const int64_t *K0, const uint32_t *epoch0, const uint32_t *n_dev, uint32_t batch, uint32_t kpw,
-             uint32_t tiles_per_table, uint32_t n_tiles, uint32_t S0, uint32_t smask0, const QueryArgs) {
+query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const QueryArgs) {
+    const int64_t *__restrict__ const keys = global_at<const int64_t>(pointers.x);
+    const int64_t *const K0 = global_at<const int64_t>(pointers.y);
+    const uint32_t *const epoch0 = global_at<const uint32_t>(pointers.z);
+    const uint32_t *const n_dev = global_at<const uint32_t>(pointers.w);
+    const uint32_t batch = sizes.x, kpw = sizes.y, tiles_per_table = sizes.z, n_tiles = sizes.w, S0 = sets.x, smask0 = sets.y;
     __shared__ uint64_t s_src[WPB][KPW];                // (an odd number of rows is less than KPW: room for its copied last entry)
     __shared__ uint32_t s_dst[WPB][KPW];
     __shared__ int64_t  s_mkey[WPB][KPW];
@@ -1954,10 +1965,12 @@ template <int W, int U, int WPB, bool kCoherent, int kD>
 void launch_query_kernel(const QueryArgs &a, bool full, hipStream_t st) {
     const dim3 grid(a.n_tiles < kGridX ? a.n_tiles : kGridX, (a.n_tiles + kGridX - 1) / kGridX), block((WPB + 1) * kWave);
     const Table &t = a.tab[0];
+    const u64x4 pointers = {word_of(a.keys), word_of(t.K), word_of(t.epoch), word_of(a.n_dev)};
+    const u32x4 sizes = {a.B, a.kpw, a.tiles_per_table, a.n_tiles};
+    const u32x2 sets = {t.S, t.smask};
     if constexpr (WPB <= 8 || W <= 16) {           // query_shape gives no more than 8 workers to wider sets
 #define HPS_QUERY(full) \
-    hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, full>), grid, block, 0, st, a.keys, t.K, t.epoch, a.n_dev, a.B, a.kpw, \
-                       a.tiles_per_table, a.n_tiles, t.S, t.smask, a)
+    hipLaunchKernelGGL((query_kernel<W, kWave, U, WPB, kCoherent, kD, full>), grid, block, 0, st, pointers, sizes, sets, a)
         if (full) HPS_QUERY(true);
         else      HPS_QUERY(false);
 #undef HPS_QUERY
