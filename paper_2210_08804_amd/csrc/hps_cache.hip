@@ -164,16 +164,16 @@ struct alignas(64) Table {     // one cache as the kernels see it (one 64-byte l
 };
 static_assert(sizeof(Table) == 64, "one line of the kernel arguments per table");
 
-__device__ __forceinline__ uint32_t *seq_of(const Table &tb, uint32_t set) { return tb.sc + 2ull * set; }
+__device__ __forceinline__ uint32_t *seq_of(uint32_t *sc, uint32_t set) { return sc + 2ull * set; }
 
 // Writer epochs.  Every work-group of an insert or update kernel that has keys to handle counts
 // itself in before it stores a key or a row and out after its last key and row have landed, on the pair
-// blockIdx mod kEpochs.  A reader that finds started == finished in every pair, reads keys and rows,
+// (work-group's number) mod kEpochs.  A reader that finds started == finished in every pair, reads keys and rows,
 // and then finds every pair unchanged knows that no writer was at work in between, so it need not
 // look at the sequence words of its sets: a writer's count is at the memory side before its first
 // store is issued (writer_entered) and its stores are there before it counts itself
 // out, so a reader that saw any of those stores sees the pair changed or not yet even.
-__device__ __forceinline__ uint32_t *epoch_of(const Table &tb, uint32_t i) { return tb.epoch + (i % kEpochs) * kEpochStride; }
+__device__ __forceinline__ uint32_t *epoch_of(uint32_t *epoch, uint32_t i) { return epoch + (i % kEpochs) * kEpochStride; }
 
 // A wave's view of the pairs: lanes 0 .. kEpochs-1 hold {finished, started} of one pair each.
 __device__ __forceinline__ uint64_t read_epochs(const uint32_t *epoch) {
@@ -187,11 +187,11 @@ __device__ __forceinline__ uint64_t read_epochs(const uint32_t *epoch) {
 struct WriterGroup { uint32_t left, entered; };
 // Called by all threads of the work-group at the start, with a barrier of the work-group to follow.  Wave 0's count is
 // on its way when it returns.
-__device__ __forceinline__ void writer_enter(const Table &tb, WriterGroup *w) {
+__device__ __forceinline__ void writer_enter(uint32_t *pair, WriterGroup *w) {
     if (threadIdx.x == 0) {
         w->left = (uint32_t)kWavesPerWg;
         w->entered = 0u;
-        __hip_atomic_fetch_add(epoch_of(tb, blockIdx.x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(pair, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 // Wave 0, right after a wait for its outstanding memory operations, which covers the count: tells the
@@ -208,11 +208,11 @@ __device__ __forceinline__ void writer_entered(WriterGroup *w) {
     asm volatile("" ::: "memory");                          // no store of the wave moves up
 }
 // Called by each wave of the work-group when its own keys and rows have landed.
-__device__ __forceinline__ void writer_leave(const Table &tb, WriterGroup *w, bool told) {
+__device__ __forceinline__ void writer_leave(uint32_t *pair, WriterGroup *w, bool told) {
     if (!told) wait_vm0();                                  // (wave 0 had no key to look at)
     writer_tell(w, told);
     if (lane_id() == 0 && __hip_atomic_fetch_sub(&w->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 1u)
-        __hip_atomic_fetch_add(epoch_of(tb, blockIdx.x) + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(pair + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Division of a list of rows of C chunks into wave loads of 64 chunks.  Packed, so that a query's scalar
@@ -1211,14 +1211,19 @@ __global__ void __launch_bounds__((WPB + 1) * kWave) query_dedup_kernel(const Qu
 
 // ------------------------------------------------------------------ insert / update
 
+// What the writers need after their first loads; the rest they are given in registers, as query_kernel is.
 struct WriteArgs {
-    Table           tab;
-    const int64_t  *keys;
     const float    *vals;
-    const uint32_t *n_dev;      // optional device-side batch length
-    uint32_t        n;
+    float          *V;
+    uint32_t       *T;
+    uint32_t       *gdev;
+    uint32_t       *flags;
     RowGeom         g;
 };
+typedef const __attribute__((address_space(4))) WriteArgs *WriteArgsIn;
+constexpr uint32_t kWriteArgsAt = 56;          // behind 14 words
+static_assert(alignof(WriteArgs) == 8, "kWriteArgsAt");
+constexpr uint32_t kWriteGridX = 1u << 16;     // work-groups in a row of a writer's grid
 
 // Replace (Alg. 3).  The first KPW lanes of a wave own one key each; all 64 lanes copy rows.  A
 // pending lane takes its set's sequence word (the paper's slabset lock, Sec. 4.1) with one fetch-or
@@ -1244,37 +1249,39 @@ struct WriteArgs {
 // four, 505 with five; 64-way sets under LRU, where a search reads 768 bytes per key, 200,000 over 2^9 / 2^15 sets 3,750 / 150
 // with three, 6,750 / 179 with four.
 template <int W, int KPW, bool kLong, bool kLru>
-__global__ void __attribute__((amdgpu_waves_per_eu(1, (W == 64 && kLru ? 3 : 4)))) __launch_bounds__(kBlock) insert_kernel(const WriteArgs a) {
+__global__ void __attribute__((amdgpu_waves_per_eu(1, (W == 64 && kLru ? 3 : 4)))) __launch_bounds__(kBlock) insert_kernel(const u64x4 pointers, const u32x4 sizes, const uint64_t epochs, const WriteArgs) {
     constexpr bool kTight = kLong && kLru && W <= 8;
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
     __shared__ uint32_t s_srcrow[kWavesPerWg][kWave];
-    __shared__ uint32_t s_owner[kWavesPerWg][kWave * 2];
     __shared__ uint32_t s_first[kWavesPerWg * kWave];
     __shared__ int64_t  s_key[kWavesPerWg * KPW];
     __shared__ WriterGroup s_group;
 
+    const int64_t *__restrict__ const keys = global_at<const int64_t>(pointers.x);
+    const uint32_t *const n_dev = global_at<const uint32_t>(pointers.y);
+    int64_t *const K = global_at<int64_t>(pointers.z);
+    uint32_t *const sc = global_at<uint32_t>(pointers.w);
+    const uint32_t S = sizes.y, smask = sizes.z;
     const int lane = lane_id();
     const int wave = wave_id();
-    const RowGeom g = a.g;
-    const Table tb = a.tab;
-    // The table's fields and the batch are asked for at once: behind the test for an empty work-group they cost small batches 0.1 - 0.2 us.
-    asm volatile("" :: "s"(a.keys), "s"(tb.epoch), "s"(tb.gdev), "s"(tb.K), "s"(tb.sc), "s"(tb.S), "s"(tb.V));
-    uint32_t n = a.n;
-    if (a.n_dev) {
-        const uint32_t nd = *a.n_dev;
+    // One tile of KPW keys to a wave, no loop over tiles (see query_kernel).
+    const uint32_t wg = blockIdx.y * kWriteGridX + blockIdx.x, first = (wg * kWavesPerWg + (uint32_t)wave) * KPW, i = first + lane;
+    uint32_t n = sizes.x;
+    if (n_dev) {
+        const uint32_t nd = *n_dev;
         n = nd < n ? nd : n;
     }
-    const uint32_t n_tiles = (n + KPW - 1) / KPW;
-    const uint32_t wave_global = blockIdx.x * kWavesPerWg + wave;
-    const uint32_t n_waves = gridDim.x * kWavesPerWg;
-    const uint32_t g_now = kLru ? *tb.gdev : 0u;            // Alg. 3 stamps with the current iteration count
-    if (blockIdx.x * kWavesPerWg >= n_tiles) return;        // nothing for any wave of this work-group
-    auto key_of = [&](uint32_t tile) {
-        const uint32_t i = tile * KPW + lane;
-        return tile < n_tiles && lane < KPW && i < n ? a.keys[i] : kEmpty;
-    };
-    int64_t key = key_of(wave_global);
-    writer_enter(tb, &s_group);                             // its round trip runs beside that of the keys
+    if ((uint64_t)wg * kWavesPerWg * KPW >= n) return;      // nothing for any wave of this work-group
+    int64_t key = lane < KPW && i >= first && i < n ? keys[i] : kEmpty;
+    WriteArgsIn in = (WriteArgsIn)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + kWriteArgsAt);
+    asm volatile("" : "+s"(in));
+    const float *const vals = in->vals;
+    float *const V = in->V;
+    const RowGeom g = {in->g.d, in->g.C, in->g.LPR, in->g.lprShift, in->g.passes, {in->g.c16.C, in->g.c16.packed}, {in->g.c8.C, in->g.c8.packed}};
+    uint32_t *const pair = epoch_of(global_at<uint32_t>(epochs), wg);
+    uint32_t *const T = in->T;
+    const uint32_t g_now = kLru ? *in->gdev : 0u;           // Alg. 3 stamps with the current iteration count
+    writer_enter(pair, &s_group);                           // its round trip runs beside that of the keys
     // Copies of a key among the first keys of the work-group: all of them write their number into the key's hash slot,
     // the one whose number stays carries the key, the others drop out (Alg. 3 ignores a key that is already there,
     // so only one copy can ever take effect).  A slot shared by different keys thins nothing.  Attempts on one set go one
@@ -1293,103 +1300,87 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, (W == 64 && kLru ? 3 : 4))
         if (o != me && s_key[o] == key) key = kEmpty;
     }
     bool told = wave != 0;                                  // only wave 0 has something to tell
-    RowMover<(kLong ? 8 : 4), kLong> rows(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0]);
+    RowMover<(kLong ? 8 : 4), kLong> rows(g, vals, V, &s_srcrow[wave][0], &s_dst[wave][0]);
 
-    for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves, key = key_of(tile)) {
-        const uint32_t i = tile * KPW + lane;
-        const bool mine = lane < KPW && i < n;
-        bool pending = mine && !is_reserved(key);
-        const uint64_t h = mix64((uint64_t)key);
-        const uint32_t hs = (uint32_t)(h >> 32);
-        const uint32_t set = pending ? (tb.smask ? (hs & tb.smask) : (hs % tb.S)) : 0u;
+    bool pending = !is_reserved(key);
+    const uint32_t set = pending ? set_of(key, S, smask) : 0u;
 
-        // Further tiles, which the waves reach at different times, are thinned wave by wave.
-        if (tile != wave_global) {
-            if (pending) s_owner[wave][h & (kWave * 2 - 1)] = (uint32_t)lane;
-            wave_lds_fence();
-            const int o = pending ? (int)s_owner[wave][h & (kWave * 2 - 1)] : lane;
-            const int64_t ko = shfl64(key, o);
-            if (pending && o != lane && ko == key) pending = false;
-            wave_lds_fence();
+    // A search reads a set for every lane: the sets of those in m, for the others that of the first of them, which
+    // costs no request.  (Lanes that are done reading their own sets once more, which others write to, took 262,144 new keys over
+    // 2^14 sets from 130 to 148 us, over 2^16 from 88 to 97, and 70,000 under LRU of which a third are 64 keys from 38 to 58.)
+    auto set_in = [&](bool in, uint64_t m) { return in ? set : (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(m)); };
+    uint32_t rounds = 0;
+    while (const uint64_t pendmask = __ballot(pending)) {
+        if (++rounds > kMaxRounds) {                             // a set never came free: skip these keys
+            if (pending) __hip_atomic_fetch_or(in->flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+            break;
         }
-
-        // A search reads a set for every lane: the sets of those in m, for the others that of the first of them, which
-        // costs no request.  (Lanes that are done reading their own sets once more, which others write to, took 262,144 new keys over
-        // 2^14 sets from 130 to 148 us, over 2^16 from 88 to 97, and 70,000 under LRU of which a third are 64 keys from 38 to 58.)
-        auto set_in = [&](bool in, uint64_t m) { return in ? set : (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(m)); };
-        uint32_t rounds = 0;
-        while (const uint64_t pendmask = __ballot(pending)) {
-            if (++rounds > kMaxRounds) {                             // a set never came free: skip these keys
-                if (pending) __hip_atomic_fetch_or(tb.flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            // Look before owning: a key given many times (a miss list carries every occurrence) is found by
-            // all but the first without taking the word, instead of each occurrence owning the set in turn.
-            // On the first attempt the look travels beside the fetch-or, later in front of it.
-            int seen = -1;
-            int here = lane;
-            if constexpr (kTight) asm volatile("" : "+v"(here));     // the searches' lane arithmetic is done again, not kept in registers
-            if (rounds > 1) {
-                seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending, [] {}, KPW, here);
-                if (pending && seen >= 0) {
-                    if (kLru) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);    // Alg. 3: refresh
-                    pending = false;
-                }
-            }
-            // one 64-bit atomic on the set's {seq, ctr} word: takes the set and reads its counter
-            uint64_t word = 1ull;
-            if (pending)
-                word = __hip_atomic_fetch_or(reinterpret_cast<uint64_t *>(seq_of(tb, set)), 1ull, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-            if (rounds == 1) seen = probe_wave<W, KPW, true>(tb.K, key, set_in(pending, pendmask), pending, [] {}, KPW, here);
-            shared_acquire();                                        // the word is owned before the set is read
-            writer_tell(&s_group, told);
-            const uint32_t old = (uint32_t)word;
-            const uint32_t c = (uint32_t)(word >> 32);
-            bool own = pending && !(old & 1u);
+        // Look before owning: a key given many times (a miss list carries every occurrence) is found by
+        // all but the first without taking the word, instead of each occurrence owning the set in turn.
+        // On the first attempt the look travels beside the fetch-or, later in front of it.
+        int seen = -1;
+        int here = lane;
+        if constexpr (kTight) asm volatile("" : "+v"(here));     // the searches' lane arithmetic is done again, not kept in registers
+        if (rounds > 1) {
+            seen = probe_wave<W, KPW, true>(K, key, set_in(pending, pendmask), pending, [] {}, KPW, here);
             if (pending && seen >= 0) {
-                if (kLru) st_agent(tb.T + (uint64_t)set * W + (uint32_t)seen, g_now);
-                if (own) st_agent(reinterpret_cast<uint64_t *>(seq_of(tb, set)), word);
-                own = pending = false;
-            }
-            if (!__ballot(own)) {
-                if (__ballot(pending)) __builtin_amdgcn_s_sleep(8);
-                continue;
-            }
-            const uint64_t ownmask = __ballot(own);
-            const int r = rank_in(ownmask);
-            if (own) s_srcrow[wave][r] = i;
-            wave_lds_fence();
-            // the owners' rows are requested behind the sets' keys (LRU policy: and stamps) and travel while those are compared
-            auto rows_too = [&] { rows.start((uint32_t)__popcll(ownmask)); };
-            int victim = (int)(c & (W - 1));                         // victim counter
-            int way;
-            const uint32_t from = set_in(own, ownmask);
-            if constexpr (kLru) way = probe_lru_wave<W, KPW, (kTight ? 1 : 4)>(tb.K, tb.T, key, from, own, g_now, victim, here, rows_too);
-            else way = probe_wave<W, KPW, true>(tb.K, key, from, own, rows_too, KPW, here);
-            const bool fresh = own && way < 0;
-            if (fresh) way = victim;
-            if (kLru && own) st_agent(tb.T + (uint64_t)set * W + (uint32_t)way, g_now);
-            const uint64_t freshmask = __ballot(fresh);
-            if (freshmask) {
-                writer_entered(&s_group);
-                if (fresh) st_agent(tb.K + (uint64_t)set * W + (uint32_t)way, key);
-                if (own) s_dst[wave][r] = fresh ? (uint64_t)set * W + (uint32_t)way : kSkipRow;
-                wave_lds_fence();
-                rows.finish(freshmask == ownmask);
-            }
-            wave_lds_fence();
-            shared_release();                                        // rows and keys land before the words move on
-            if (own) {
-                // let go: a changed set gets seq + 2 and ctr + 1 in one store, an unchanged one its old word
-                st_agent(reinterpret_cast<uint64_t *>(seq_of(tb, set)),
-                         fresh ? (((uint64_t)(c + 1u) << 32) | (uint64_t)(old + 2u)) : word);
+                if (kLru) st_agent(T + (uint64_t)set * W + (uint32_t)seen, g_now);    // Alg. 3: refresh
                 pending = false;
             }
         }
+        // one 64-bit atomic on the set's {seq, ctr} word: takes the set and reads its counter
+        uint64_t word = 1ull;
+        if (pending)
+            word = __hip_atomic_fetch_or(reinterpret_cast<uint64_t *>(seq_of(sc, set)), 1ull, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+        if (rounds == 1) seen = probe_wave<W, KPW, true>(K, key, set_in(pending, pendmask), pending, [] {}, KPW, here);
+        shared_acquire();                                        // the word is owned before the set is read
+        writer_tell(&s_group, told);
+        const uint32_t old = (uint32_t)word;
+        const uint32_t c = (uint32_t)(word >> 32);
+        bool own = pending && !(old & 1u);
+        if (pending && seen >= 0) {
+            if (kLru) st_agent(T + (uint64_t)set * W + (uint32_t)seen, g_now);
+            if (own) st_agent(reinterpret_cast<uint64_t *>(seq_of(sc, set)), word);
+            own = pending = false;
+        }
+        if (!__ballot(own)) {
+            if (__ballot(pending)) __builtin_amdgcn_s_sleep(8);
+            continue;
+        }
+        const uint64_t ownmask = __ballot(own);
+        const int r = rank_in(ownmask);
+        if (own) s_srcrow[wave][r] = i;
+        wave_lds_fence();
+        // the owners' rows are requested behind the sets' keys (LRU policy: and stamps) and travel while those are compared
+        auto rows_too = [&] { rows.start((uint32_t)__popcll(ownmask)); };
+        int victim = (int)(c & (W - 1));                         // victim counter
+        int way;
+        const uint32_t from = set_in(own, ownmask);
+        if constexpr (kLru) way = probe_lru_wave<W, KPW, (kTight ? 1 : 4)>(K, T, key, from, own, g_now, victim, here, rows_too);
+        else way = probe_wave<W, KPW, true>(K, key, from, own, rows_too, KPW, here);
+        const bool fresh = own && way < 0;
+        if (fresh) way = victim;
+        if (kLru && own) st_agent(T + (uint64_t)set * W + (uint32_t)way, g_now);
+        const uint64_t freshmask = __ballot(fresh);
+        if (freshmask) {
+            writer_entered(&s_group);
+            if (fresh) st_agent(K + (uint64_t)set * W + (uint32_t)way, key);
+            if (own) s_dst[wave][r] = fresh ? (uint64_t)set * W + (uint32_t)way : kSkipRow;
+            wave_lds_fence();
+            rows.finish(freshmask == ownmask);
+        }
+        wave_lds_fence();
+        shared_release();                                        // rows and keys land before the words move on
+        if (own) {
+            // let go: a changed set gets seq + 2 and ctr + 1 in one store, an unchanged one its old word
+            st_agent(reinterpret_cast<uint64_t *>(seq_of(sc, set)),
+                     fresh ? (((uint64_t)(c + 1u) << 32) | (uint64_t)(old + 2u)) : word);
+            pending = false;
+        }
     }
-    writer_leave(tb, &s_group, told);                              // (every hold that stored a key or a row ended with shared_release: they have landed)
+    writer_leave(pair, &s_group, told);                              // (every hold that stored a key or a row ended with shared_release: they have landed)
 }
 
 // Update (Alg. 4) with one lock acquisition per run of lanes that share a set.  Key batches that
@@ -1405,128 +1396,128 @@ __global__ void __attribute__((amdgpu_waves_per_eu(1, (W == 64 && kLru ? 3 : 4))
 // twice as many wave loads in flight: 2 us more there, 3 us more on 2^18 scattered rows).  Long rows of 16 and 32 ways need the limit from
 // below too: with 129 registers 262,144 rows of 1,280 bytes, 32 ways, in a dump's order 145 us, 131 this way.
 template <int W, int KPW, bool kLong>
-__global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBlock) update_kernel(const WriteArgs a) {
+__global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBlock) update_kernel(const u64x4 pointers, const u32x4 sizes, const uint64_t epochs, const WriteArgs) {
     __shared__ uint64_t s_dst[kWavesPerWg][kWave];
     __shared__ uint32_t s_srcrow[kWavesPerWg][kWave];
     __shared__ WriterGroup s_group;
 
+    const int64_t *__restrict__ const keys = global_at<const int64_t>(pointers.x);
+    const uint32_t *const n_dev = global_at<const uint32_t>(pointers.y);
+    int64_t *const K = global_at<int64_t>(pointers.z);
+    uint32_t *const sc = global_at<uint32_t>(pointers.w);
+    const uint32_t S = sizes.y, smask = sizes.z;
     const int lane = lane_id();
     const int wave = wave_id();
-    const RowGeom g = a.g;
-    const Table tb = a.tab;
-    uint32_t n = a.n;
-    if (a.n_dev) {
-        const uint32_t nd = *a.n_dev;
+    // One tile of KPW keys to a wave, no loop over tiles (see query_kernel).
+    const uint32_t wg = blockIdx.y * kWriteGridX + blockIdx.x, first = (wg * kWavesPerWg + (uint32_t)wave) * KPW, i = first + lane;
+    uint32_t n = sizes.x;
+    if (n_dev) {
+        const uint32_t nd = *n_dev;
         n = nd < n ? nd : n;
     }
-    const uint32_t n_tiles = (n + KPW - 1) / KPW;
-    const uint32_t wave_global = blockIdx.x * kWavesPerWg + wave;
-    const uint32_t n_waves = gridDim.x * kWavesPerWg;
+    if ((uint64_t)wg * kWavesPerWg * KPW >= n) return;      // nothing for any wave of this work-group
+    int64_t key = lane < KPW && i >= first && i < n ? keys[i] : kEmpty;
+    WriteArgsIn in = (WriteArgsIn)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + kWriteArgsAt);
+    asm volatile("" : "+s"(in));
+    const float *const vals = in->vals;
+    float *const V = in->V;
+    const RowGeom g = {in->g.d, in->g.C, in->g.LPR, in->g.lprShift, in->g.passes, {in->g.c16.C, in->g.c16.packed}, {in->g.c8.C, in->g.c8.packed}};
+    uint32_t *const pair = epoch_of(global_at<uint32_t>(epochs), wg);
     const uint64_t le_lane = lane == 63 ? ~0ull : ((2ull << lane) - 1);     // bits 0..lane
-    if (blockIdx.x * kWavesPerWg >= n_tiles) return;        // nothing for any wave of this work-group
-    auto key_of = [&](uint32_t tile) {
-        const uint32_t i = tile * KPW + lane;
-        return tile < n_tiles && lane < KPW && i < n ? a.keys[i] : kEmpty;
-    };
-    int64_t key = key_of(wave_global);                      // requested before the work-group's barrier
-    writer_enter(tb, &s_group);
+    writer_enter(pair, &s_group);
     __syncthreads();
     bool told = wave != 0;                                  // only wave 0 has something to tell
 
-    for (uint32_t tile = wave_global; tile < n_tiles; tile += n_waves, key = key_of(tile)) {
-        const uint32_t i = tile * KPW + lane;
-        const bool mine = lane < KPW && i < n;
-        bool pending = mine && !is_reserved(key);
-        const uint32_t set = pending ? set_of(key, tb.S, tb.smask) : 0u;
+    bool pending = !is_reserved(key);
+    const uint32_t set = pending ? set_of(key, S, smask) : 0u;
 
-        uint32_t rounds = 0;
-        while (const uint64_t pendmask = __ballot(pending)) {
-            if (++rounds > kMaxRounds) {                             // a set never came free: skip these keys
-                if (pending) __hip_atomic_fetch_or(tb.flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            // groups: maximal runs of adjacent pending lanes with equal set
-            const uint32_t prev_set = (uint32_t)__shfl_up((int)set, 1, kWave);
-            const int prev_pend = __shfl_up((int)pending, 1, kWave);
-            const bool start = pending && (lane == 0 || !prev_pend || prev_set != set);
-            const uint64_t startmask = __ballot(start);
-            const int leader = pending ? 63 - __builtin_clzll(startmask & le_lane) : lane;
-            const uint64_t le_leader = leader == 63 ? ~0ull : ((2ull << leader) - 1);
-            const uint64_t above = startmask & ~le_leader;
-            const uint64_t lt_end = above ? ((1ull << __builtin_ctzll(above)) - 1) : ~0ull;
-            const uint64_t gmask = pendmask & lt_end & ~(le_leader >> 1);    // lanes leader .. end-1 that are pending
-            const bool is_leader = pending && lane == leader;
+    uint32_t rounds = 0;
+    while (const uint64_t pendmask = __ballot(pending)) {
+        if (++rounds > kMaxRounds) {                             // a set never came free: skip these keys
+            if (pending) __hip_atomic_fetch_or(in->flags, (uint32_t)HPS_FLAG_STUCK_SET, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+            break;
+        }
+        // groups: maximal runs of adjacent pending lanes with equal set
+        const uint32_t prev_set = (uint32_t)__shfl_up((int)set, 1, kWave);
+        const int prev_pend = __shfl_up((int)pending, 1, kWave);
+        const bool start = pending && (lane == 0 || !prev_pend || prev_set != set);
+        const uint64_t startmask = __ballot(start);
+        const int leader = pending ? 63 - __builtin_clzll(startmask & le_lane) : lane;
+        const uint64_t le_leader = leader == 63 ? ~0ull : ((2ull << leader) - 1);
+        const uint64_t above = startmask & ~le_leader;
+        const uint64_t lt_end = above ? ((1ull << __builtin_ctzll(above)) - 1) : ~0ull;
+        const uint64_t gmask = pendmask & lt_end & ~(le_leader >> 1);    // lanes leader .. end-1 that are pending
+        const bool is_leader = pending && lane == leader;
 
-            uint32_t v = is_leader ? ld_agent(seq_of(tb, set)) : 0u;
-            v = (uint32_t)__shfl((int)v, leader, kWave);
-            const bool busy = pending && (v & 1u);
-            shared_acquire();                                        // the word is read before the keys
-            writer_tell(&s_group, told);
-            // W lanes read a set's line, as in the other kernels; lanes without one to search read that of the first that has one, which
-            // is read anyway.  With 64 keys to a wave each lane reads its own set instead where that is less work: in a dump's order, where
-            // a run's lanes read the same line, and in wide sets when few lanes search, as behind a lost attempt.  (us, each lane its own / W lanes each /
-            // this way.  Rows of 512 bytes, random order, 8 ways: 262,144 95 / 85 / 85, absent 15.5 / 9.5 / 9.5; 100,000 rows, 16 ways 88 / 75 / 72,
-            // 64 ways 343 / 481 / 331, absent 37 / 21 / 22.  In a dump's order, 8 ways: 262,144 51.6 / 50.0 / 49.1; 100,000, 16 ways 29.0 / 29.1 / 27.1, 64 ways
-            // 39 / 62 / 39.  Both searches in the kernels of long rows and 8 ways cost 0.3-1 us in every order: 65,536 of 1,280 bytes in a dump's
-            // 34.7 / 34.9 / 35.1, random 53.6 / 53.5 / 54.4; fewer than four ways gain nothing.  With 16 keys to a wave W lanes each throughout.)
-            const bool search = pending && !busy;
-            const uint64_t smask = __ballot(search);
-            constexpr bool kBoth = KPW == kWave && W >= (kLong ? 16 : 4);
-            constexpr int kFew = W == 64 ? 32 : W >= 16 ? 8 : 0;
-            int way = -1;
-            if (kBoth && (2 * __popcll(startmask) <= __popcll(pendmask) || __popcll(smask) <= kFew)) {
-                if (search) {
-                    constexpr int F = W > 32 ? 32 : W;               // keys in flight together
+        uint32_t v = is_leader ? ld_agent(seq_of(sc, set)) : 0u;
+        v = (uint32_t)__shfl((int)v, leader, kWave);
+        const bool busy = pending && (v & 1u);
+        shared_acquire();                                        // the word is read before the keys
+        writer_tell(&s_group, told);
+        // W lanes read a set's line, as in the other kernels; lanes without one to search read that of the first that has one, which
+        // is read anyway.  With 64 keys to a wave each lane reads its own set instead where that is less work: in a dump's order, where
+        // a run's lanes read the same line, and in wide sets when few lanes search, as behind a lost attempt.  (us, each lane its own / W lanes each /
+        // this way.  Rows of 512 bytes, random order, 8 ways: 262,144 95 / 85 / 85, absent 15.5 / 9.5 / 9.5; 100,000 rows, 16 ways 88 / 75 / 72,
+        // 64 ways 343 / 481 / 331, absent 37 / 21 / 22.  In a dump's order, 8 ways: 262,144 51.6 / 50.0 / 49.1; 100,000, 16 ways 29.0 / 29.1 / 27.1, 64 ways
+        // 39 / 62 / 39.  Both searches in the kernels of long rows and 8 ways cost 0.3-1 us in every order: 65,536 of 1,280 bytes in a dump's
+        // 34.7 / 34.9 / 35.1, random 53.6 / 53.5 / 54.4; fewer than four ways gain nothing.  With 16 keys to a wave W lanes each throughout.)
+        const bool search = pending && !busy;
+        const uint64_t searchmask = __ballot(search);
+        constexpr bool kBoth = KPW == kWave && W >= (kLong ? 16 : 4);
+        constexpr int kFew = W == 64 ? 32 : W >= 16 ? 8 : 0;
+        int way = -1;
+        if (kBoth && (2 * __popcll(startmask) <= __popcll(pendmask) || __popcll(searchmask) <= kFew)) {
+            if (search) {
+                constexpr int F = W > 32 ? 32 : W;               // keys in flight together
 #pragma unroll 1
-                    for (int w0 = 0; w0 < W; w0 += F) {
-                        int64_t sk[F];
+                for (int w0 = 0; w0 < W; w0 += F) {
+                    int64_t sk[F];
 #pragma unroll
-                        for (int w = 0; w < F; ++w) sk[w] = ld_agent(tb.K + (uint64_t)set * W + w0 + w);
+                    for (int w = 0; w < F; ++w) sk[w] = ld_agent(K + (uint64_t)set * W + w0 + w);
 #pragma unroll
-                        for (int w = 0; w < F; ++w)
-                            if (sk[w] == key) way = w0 + w;
-                    }
+                    for (int w = 0; w < F; ++w)
+                        if (sk[w] == key) way = w0 + w;
                 }
-            } else if (smask) {
-                const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(smask));
-                way = probe_wave<W, KPW, true>(tb.K, key, search ? set : some, search);
             }
-            if (search && way < 0) pending = false;                  // not cached: ignored
-            bool winner = search && way >= 0;
+        } else if (searchmask) {
+            const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)set, __builtin_ctzll(searchmask));
+            way = probe_wave<W, KPW, true>(K, key, search ? set : some, search);
+        }
+        if (search && way < 0) pending = false;                  // not cached: ignored
+        bool winner = search && way >= 0;
 #pragma unroll
-            for (int w = 0; w < W; ++w) {                            // one lane per slot and round
-                const uint64_t m = __ballot(winner && way == w) & gmask;
-                if (winner && way == w && lane != __builtin_ctzll(m)) winner = false;
+        for (int w = 0; w < W; ++w) {                            // one lane per slot and round
+            const uint64_t m = __ballot(winner && way == w) & gmask;
+            if (winner && way == w && lane != __builtin_ctzll(m)) winner = false;
+        }
+        const bool group_needs = (__ballot(winner) & gmask) != 0;
+        bool won = false;
+        if (is_leader && !busy && group_needs) {
+            uint32_t expect = v;
+            won = __hip_atomic_compare_exchange_strong(seq_of(sc, set), &expect, v + 1u, __ATOMIC_RELAXED,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const bool gwon = __shfl((int)won, leader, kWave) != 0;
+        const bool act = winner && gwon;
+        const uint64_t actmask = __ballot(act);
+        if (actmask) {
+            shared_acquire();
+            writer_entered(&s_group);
+            if (act) {
+                const int r = rank_in(actmask);
+                s_dst[wave][r] = (uint64_t)set * W + (uint32_t)way;
+                s_srcrow[wave][r] = i;
             }
-            const bool group_needs = (__ballot(winner) & gmask) != 0;
-            bool won = false;
-            if (is_leader && !busy && group_needs) {
-                uint32_t expect = v;
-                won = __hip_atomic_compare_exchange_strong(seq_of(tb, set), &expect, v + 1u, __ATOMIC_RELAXED,
-                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            const bool gwon = __shfl((int)won, leader, kWave) != 0;
-            const bool act = winner && gwon;
-            const uint64_t actmask = __ballot(act);
-            if (actmask) {
-                shared_acquire();
-                writer_entered(&s_group);
-                if (act) {
-                    const int r = rank_in(actmask);
-                    s_dst[wave][r] = (uint64_t)set * W + (uint32_t)way;
-                    s_srcrow[wave][r] = i;
-                }
-                wave_lds_fence();
-                copy_rows_shared<(kLong ? 8 : 4), kLong>(g, a.vals, tb.V, &s_srcrow[wave][0], &s_dst[wave][0], (uint32_t)__popcll(actmask));
-                wave_lds_fence();
-                shared_release();                                    // rows land before the word moves on
-                if (won) st_agent(seq_of(tb, set), v + 2u);
-                if (act) pending = false;
-            }
+            wave_lds_fence();
+            copy_rows_shared<(kLong ? 8 : 4), kLong>(g, vals, V, &s_srcrow[wave][0], &s_dst[wave][0], (uint32_t)__popcll(actmask));
+            wave_lds_fence();
+            shared_release();                                    // rows land before the word moves on
+            if (won) st_agent(seq_of(sc, set), v + 2u);
+            if (act) pending = false;
         }
     }
-    writer_leave(tb, &s_group, told);
+    writer_leave(pair, &s_group, told);
 }
 
 // ------------------------------------------------------------------ small kernels
@@ -2055,13 +2046,10 @@ hps_status_t launch_query(uint32_t W, const QueryArgs &a, QueryShape q, bool coh
 template <bool kInsert>
 hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, size_t n,
                           const uint32_t *n_dev, hipStream_t st) {
-    WriteArgs a;
-    a.tab = table_of(c);
-    a.keys = keys;
-    a.vals = vals;
-    a.n_dev = n_dev;
-    a.n = (uint32_t)n;
-    a.g = make_geom(c->d);
+    const Table t = table_of(c);
+    const WriteArgs a{vals, t.V, t.T, t.gdev, t.flags, make_geom(c->d)};
+    const u64x4 pointers = {word_of(keys), word_of(n_dev), word_of(t.K), word_of(t.sc)};
+    const u32x4 sizes = {(uint32_t)n, t.S, t.smask, 0u};
     // Insert: 16 keys per wave, 8 while 4,096 waves (four per SIMD) hold the batch that way: 8,192 rows 12.1 -> 9.7 us,
     // 32,768 rows 16.8 -> 15.7; with 8 throughout the 425,984-key streaming step takes 166 instead of 149 us.
     // (32 and 64 are 3-45 % slower than 16 from 1 K to 1 M keys.)
@@ -2076,12 +2064,11 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
     const uint32_t least = c->W <= 4 ? 16 * c->W : c->W <= 16 ? 64u : c->W <= 32 ? 128u : ~0u;
     const uint32_t kpw = kInsert ? (n <= 32768 ? 8u : 16u) : (n < 32768 || (n <= 49152 && c->d >= least) ? 16u : (uint32_t)kWave);
     const uint64_t tiles = (n + kpw - 1) / kpw;
-    uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
-    if (blocks > (1u << 16)) blocks = 1u << 16;
-    const dim3 grid((uint32_t)blocks), block(kBlock);
+    const uint64_t blocks = (tiles + kWavesPerWg - 1) / kWavesPerWg;
+    const dim3 grid((uint32_t)(blocks < kWriteGridX ? blocks : kWriteGridX), (uint32_t)((blocks + kWriteGridX - 1) / kWriteGridX)), block(kBlock);
     const bool lng = c->d > 256;               // rows of more than one wave load
     switch (c->W) {
-#define HPS_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, 0, st, a)
+#define HPS_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, 0, st, pointers, sizes, word_of(t.epoch), a)
 #define HPS_INSERT(w, lru)                                                                  \
     do {                                                                                    \
         if (kpw == 8 && lng) HPS_LAUNCH(insert_kernel<w, 8, true, lru>);                    \
@@ -2092,7 +2079,7 @@ hps_status_t launch_write(hps_cache *c, const int64_t *keys, const float *vals, 
 #define HPS_CASE(w)                                                                         \
     case w:                                                                                 \
         if (kInsert) {                                                                      \
-            if (a.tab.T) HPS_INSERT(w, true);                                               \
+            if (t.T) HPS_INSERT(w, true);                                               \
             else HPS_INSERT(w, false);                                                      \
         } else if (kpw == 16) {                                                             \
             if (lng) HPS_LAUNCH(update_kernel<w, 16, true>);                                \
