@@ -37,8 +37,8 @@ extern "C" {
 typedef struct hps_dedup_session hps_dedup_t;
 
 /* Create a session for batches of up to max_n keys (0 < max_n <= 2^30) on the current device.
- * Allocates three hash tables of the next power of two >= 2 * max_n slots each (12 bytes per
- * slot): two that alternate between calls, one for calls captured into a HIP graph.
+ * Allocates three hash tables of the next power of two >= 2 * max_n slots each (4 * max_n up to 2^18
+ * keys, 8 * max_n from 513 to 2^15; 12 bytes per slot): two that alternate between calls, one for calls captured into a HIP graph.
  * Errors: HPS_ERR_INVALID_ARG, HPS_ERR_OOM, HPS_ERR_DEVICE; *out is NULL on failure. */
 hps_status_t hps_dedup_create(size_t max_n, hps_dedup_t **out);
 

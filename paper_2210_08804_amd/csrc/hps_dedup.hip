@@ -2,7 +2,7 @@
 // follows the lookup of Q*, for gfx950.
 //
 // dedup is a hash join of the batch with itself in one launch over an open-addressing table (one
-// 8-byte key word and one 4-byte number per slot, 2n..4n slots).  A session has two tables: a call works
+// 8-byte key word and one 4-byte number per slot, 2n..16n slots).  A session has two tables: a call works
 // on the clean one and wipes the part of the other one that the previous call used, so no call
 // waits for a clear.  A work-group takes 1024 (or 512) keys and
 //   elects one lane per distinct key of the tile in an LDS table (so a hot key reaches the global table
@@ -16,8 +16,9 @@
 // on the table.  One that does (a caller's mistake) can take a number away again: the wait is therefore bounded
 // and ends with a flag (kMaxRounds).
 // Bound by the chain of dependent round trips (key, swap, counter, number).  Two launches, the second
-// looking every position up again, took 17.7 us of kernel time for 106,496 keys (44 % distinct); this takes 12.1 us, 15.9
-// with a load of the slot in front of each compare-and-swap.
+// looking every position up again, took 17.7 us of kernel time for 106,496 keys (44 % distinct); this took 12.1 us, 15.9
+// with a load of the slot in front of each compare-and-swap, 38 with the line of the slot loaded beside it.  Per call, with the wipe on other
+// work-groups and tables that are emptier: 11.9 -> 10.4 us, 32,000 keys of which none is there twice 17.7 -> 7.1.
 // The order of unique_keys is the order in which tiles reach the counter: unspecified.
 #include <hip/hip_runtime.h>
 
@@ -92,139 +93,162 @@ __global__ void dedup_clear_kernel(int64_t *tkey, uint32_t *tuid, uint64_t n_slo
 
 __global__ void set_u32_kernel(uint32_t *p, uint32_t v) { *p = v; }
 
-// What hps_dedup_missed adds to a call.
-struct Missed {
+// A call's slots for n keys: a power of two, at least 2 * n; at least 4 * n up to 2^18 keys and 8 * n from 513 to 2^15, where wiping them is
+// little and the unluckiest lane's attempts, one round trip each, are what the call waits for (us, at least 2 / 4 / 8 n: 2,000 distinct keys
+// 11.0 / 7.0 / 5.9, 32,000 15.5 / 8.6 / 7.1, 106,496 17.7 / 12.8, of which 38,600 distinct 11.2 / 10.6; 65,000 4 / 8 n 10.8 / 10.9).  Up to 512
+// keys stay in 1,024 slots, which a test fills to the last one.
+__host__ __device__ __forceinline__ uint64_t slots_for(uint64_t n) {
+    const uint64_t least = n <= 512 ? 2 * n : n <= (1u << 15) ? 8 * n : n <= (1u << 18) ? 4 * n : 2 * n;
+    uint64_t p = 1024;
+    while (p < least) p <<= 1;
+    return p;
+}
+
+// Arguments that arrive in registers, in vectors (see hps_cache.hip), and the others.
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <typename T> __device__ __forceinline__ T *global_at(uint64_t word) { return (T *)(__attribute__((address_space(1))) T *)word; }
+inline uint64_t word_of(const void *p) { return (uint64_t)reinterpret_cast<uintptr_t>(p); }
+struct DedupArgs {
+    uint32_t *flags;
+    int64_t  *unique_keys;
+    uint32_t *inverse, *n_unique;
+    int64_t  *other_tkey;        // the table that the previous call worked on: its first other_dirty slots
+    uint32_t *other_tuid;
+    uint64_t  other_dirty;
+    uint32_t  groups;            // work-groups of the launch
+    // what hps_dedup_missed adds to a call
     const uint32_t *n_dev;       // the batch's length (<= n)
     uint32_t *n_host;            // it goes here too
     int64_t  *keys_host;         // and unique_keys here
 };
 
-// A call's slots for n keys: a power of two, at least 2 * n.
-__host__ __device__ __forceinline__ uint64_t slots_for(uint64_t n) {
-    uint64_t p = 1024;
-    while (p < 2 * n) p <<= 1;
-    return p;
-}
-
 // counter: low half = distinct keys so far, high half = tiles that have added theirs; zero between calls.
+// Work-groups 0 .. tiles - 1 take a tile of keys each; those from `wipers` on wipe the other table, a tile's behind its keys.
 template <int kTile, bool kMissed>                                   // keys (= threads) per work-group
-__global__ void __launch_bounds__(kTile) dedup_kernel(const int64_t *__restrict__ keys, uint32_t n, const Missed more,
-                                                      int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
-                                                      uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique,
-                                                      int64_t *other_tkey, uint32_t *other_tuid, uint64_t other_dirty) {
+__global__ void __launch_bounds__(kTile) dedup_kernel(const u64x4 pointers, const u32x4 sizes, const DedupArgs a) {
+    const int64_t *__restrict__ const keys = global_at<const int64_t>(pointers.x);
+    int64_t *const tkey = global_at<int64_t>(pointers.y);
+    uint32_t *const tuid = global_at<uint32_t>(pointers.z);
+    uint64_t *const counter = global_at<uint64_t>(pointers.w);
+    uint32_t n = sizes.x, mask = sizes.y;
+    const uint32_t tiles = sizes.z;                    // of the longest batch there may be
+    const uint32_t wipers = sizes.w;                   // the first work-group that wipes: tiles, or 0
     constexpr int kLds = 2 * kTile;                    // LDS table slots (load <= 0.5)
     __shared__ unsigned long long l_key[kLds];
     __shared__ uint32_t l_uid[kLds + 1];               // number of the key in that slot; the last one: of the marker
     __shared__ uint32_t l_marker_seen, l_cnt, l_base;
 
     const int lane = (int)(threadIdx.x & 63u);
+    const uint32_t tile = blockIdx.x;
+    auto wipe = [&] {
+        for (uint64_t i = (uint64_t)(tile - wipers) * kTile + threadIdx.x; i < a.other_dirty; i += (uint64_t)(a.groups - wipers) * kTile) {
+            a.other_tkey[i] = kEmpty;
+            a.other_tuid[i] = kNone;
+        }
+    };
+    if (tile >= tiles) return wipe();
+    const uint32_t i = tile * kTile + threadIdx.x;
+    const int64_t key = i < n ? keys[i] : 0;           // (of a length that is on the device: requested beside it)
     if (kMissed) {
-        const uint32_t nd = *more.n_dev;
+        const uint32_t nd = *a.n_dev;
         n = nd < n ? nd : n;
         mask = (uint32_t)(slots_for(n) - 1);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            *more.n_host = n;
-            if (n == 0) *n_unique = 0u;                // no tile does
+        if (tile == 0 && threadIdx.x == 0) {
+            *a.n_host = n;
+            if (n == 0) *a.n_unique = 0u;              // no tile does
+        }
+        if ((uint64_t)tile * kTile >= n) {
+            if (wipers == 0u) wipe();
+            return;
         }
     }
     const uint32_t n_tiles = (n + kTile - 1) / kTile;
-    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const uint32_t i = tile * kTile + threadIdx.x;
-        const bool live = i < n;
-        const int64_t key = live ? keys[i] : 0;
-        for (uint32_t j = threadIdx.x; j < (uint32_t)kLds; j += kTile) l_key[j] = (unsigned long long)kEmpty;
-        if (threadIdx.x == 0) {
-            l_marker_seen = 0u;
-            l_cnt = 0u;
-        }
-        __syncthreads();
+    const bool live = i < n;
+    for (uint32_t j = threadIdx.x; j < (uint32_t)kLds; j += kTile) l_key[j] = (unsigned long long)kEmpty;
+    if (threadIdx.x == 0) {
+        l_marker_seen = 0u;
+        l_cnt = 0u;
+    }
+    __syncthreads();
 
-        // one lane per distinct key of the tile goes on
-        const uint64_t h = mix64((uint64_t)key);
-        bool elected = false;
-        uint32_t ls = (uint32_t)kLds;
-        if (live) {
-            if (key == kEmpty) {
-                elected = atomicCAS(&l_marker_seen, 0u, 1u) == 0u;
-            } else {
-                ls = (uint32_t)(h >> 40) & (kLds - 1);
-                for (;;) {
-                    const unsigned long long old =
-                        atomicCAS(&l_key[ls], (unsigned long long)kEmpty, (unsigned long long)key);
-                    if (old == (unsigned long long)kEmpty) { elected = true; break; }
-                    if (old == (unsigned long long)key) break;
-                    ls = (ls + 1) & (kLds - 1);                // at most half of the slots are ever taken
-                }
+    // one lane per distinct key of the tile goes on
+    const uint64_t h = mix64((uint64_t)key);
+    bool elected = false;
+    uint32_t ls = (uint32_t)kLds;
+    if (live) {
+        if (key == kEmpty) {
+            elected = atomicCAS(&l_marker_seen, 0u, 1u) == 0u;
+        } else {
+            ls = (uint32_t)(h >> 40) & (kLds - 1);
+            for (;;) {
+                const unsigned long long old =
+                    atomicCAS(&l_key[ls], (unsigned long long)kEmpty, (unsigned long long)key);
+                if (old == (unsigned long long)kEmpty) { elected = true; break; }
+                if (old == (unsigned long long)key) break;
+                ls = (ls + 1) & (kLds - 1);                // at most half of the slots are ever taken
             }
         }
-        // the elected lane claims the key's slot of the global table, or finds that another tile has it
-        bool won = false, listed = false;              // listed: another tile has the key's slot, its number is there or on its way
-        uint32_t slot = 0u;
-        if (elected) {
-            if (key == kEmpty) {
-                slot = mask + 1u;
-                won = atomicCAS(reinterpret_cast<unsigned long long *>(tkey + slot),
-                                (unsigned long long)kEmpty, 0ull) == (unsigned long long)kEmpty;
-                listed = !won;
-            } else {
-                slot = (uint32_t)h & mask;
-                for (uint32_t probe = 0; probe <= mask; ++probe) {      // the table is at most half full
-                    const unsigned long long old =
-                        atomicCAS(reinterpret_cast<unsigned long long *>(tkey + slot),
-                                  (unsigned long long)kEmpty, (unsigned long long)key);
-                    won = old == (unsigned long long)kEmpty;
-                    listed = old == (unsigned long long)key;
-                    if (won || listed) break;
-                    slot = (slot + 1) & mask;
-                }
-            }
-        }
-        const uint64_t wonmask = __ballot(won);
-        uint32_t first = 0u;
-        if (lane == 0 && wonmask) first = atomicAdd(&l_cnt, (uint32_t)__popcll(wonmask));
-        const uint32_t rank = (uint32_t)__shfl((int)first, 0, 64) + bits_below(wonmask);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint64_t old = __hip_atomic_fetch_add(counter, (1ull << 32) | (uint64_t)l_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            l_base = (uint32_t)old;
-            if ((uint32_t)(old >> 32) + 1u == n_tiles) {
-                *n_unique = (uint32_t)old + l_cnt;
-                __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        __syncthreads();
-        if (won) {
-            const uint32_t uid = l_base + rank;
-            __hip_atomic_store(tuid + slot, uid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            unique_keys[uid] = key;
-            if (kMissed) more.keys_host[uid] = key;
-            l_uid[ls] = uid;
-        }
-        // Every number of this work-group is on its way: only now wait for the others'.  (The barrier also keeps the
-        // compiler from making the two conditions the two sides of one branch, the waiting side first.)
-        __syncthreads();
-        if (elected && !won) {
-            uint32_t uid = kNone;
-            for (uint32_t round = 0; listed && round < kMaxRounds; ++round) {
-                uid = __hip_atomic_load(tuid + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (uid != kNone) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-            if (uid == kNone) {                                       // no number came, or the table has no room: say so
-                __hip_atomic_fetch_or(flags, (uint32_t)HPS_DEDUP_FLAG_STUCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                uid = 0u;                                             // a place that an expansion may read
-            }
-            l_uid[ls] = uid;
-        }
-        __syncthreads();
-        if (live) inverse[i] = l_uid[ls];
-        __syncthreads();                                              // LDS is reused by the next tile
     }
-    // the slots the previous call used in the other table
-    for (uint64_t i = blockIdx.x * (uint64_t)kTile + threadIdx.x; i < other_dirty; i += (uint64_t)gridDim.x * kTile) {
-        other_tkey[i] = kEmpty;
-        other_tuid[i] = kNone;
+    // the elected lane claims the key's slot of the global table, or finds that another tile has it
+    bool won = false, listed = false;                  // listed: another tile has the key's slot, its number is there or on its way
+    uint32_t slot = 0u;
+    auto claim = [&](uint32_t at, int64_t with) {
+        const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long *>(tkey + at), (unsigned long long)kEmpty, (unsigned long long)with);
+        slot = at;
+        won = old == (unsigned long long)kEmpty;
+        listed = old == (unsigned long long)key;
+    };
+    if (elected && key == kEmpty) {
+        claim(mask + 1u, 0);
+        listed = !won;
+    } else if (elected) {
+        const uint32_t home = (uint32_t)h & mask;
+        for (uint32_t j = 0; j <= mask; ++j) {                    // the table is at most half full
+            claim((home + j) & mask, key);
+            if (won || listed) break;
+        }
     }
+    const uint64_t wonmask = __ballot(won);
+    uint32_t first = 0u;
+    if (lane == 0 && wonmask) first = atomicAdd(&l_cnt, (uint32_t)__popcll(wonmask));
+    const uint32_t rank = (uint32_t)__shfl((int)first, 0, 64) + bits_below(wonmask);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint64_t old = __hip_atomic_fetch_add(counter, (1ull << 32) | (uint64_t)l_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        l_base = (uint32_t)old;
+        if ((uint32_t)(old >> 32) + 1u == n_tiles) {
+            *a.n_unique = (uint32_t)old + l_cnt;
+            __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    if (won) {
+        const uint32_t uid = l_base + rank;
+        __hip_atomic_store(tuid + slot, uid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        a.unique_keys[uid] = key;
+        if (kMissed) a.keys_host[uid] = key;
+        l_uid[ls] = uid;
+    }
+    // Every number of this work-group is on its way: only now wait for the others'.  (The barrier also keeps the
+    // compiler from making the two conditions the two sides of one branch, the waiting side first.)
+    __syncthreads();
+    if (elected && !won) {
+        uint32_t uid = kNone;
+        for (uint32_t round = 0; listed && round < kMaxRounds; ++round) {
+            uid = __hip_atomic_load(tuid + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (uid != kNone) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        if (uid == kNone) {                                       // no number came, or the table has no room: say so
+            __hip_atomic_fetch_or(a.flags, (uint32_t)HPS_DEDUP_FLAG_STUCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uid = 0u;                                             // a place that an expansion may read
+        }
+        l_uid[ls] = uid;
+    }
+    __syncthreads();
+    if (live) a.inverse[i] = l_uid[ls];
+    if (wipers == 0u) wipe();
 }
 
 }  // namespace
@@ -233,7 +257,7 @@ struct hps_dedup_session {
     uint64_t  magic;
     int       device;
     size_t    max_n;
-    uint64_t  slots;        // power of two >= 2 * max_n (>= 1024); one more slot follows them
+    uint64_t  slots;        // slots_for(max_n); one more slot follows them
     int64_t  *tkey[3];      // [slots + 1] each; a call works on tkey[cur] (0 or 1), which is all free;
                             // table 2 serves calls that are being captured into a graph (see hps_dedup)
     uint32_t *tuid[3];      // [slots + 1] each
@@ -256,26 +280,25 @@ hps_status_t check_session(hps_dedup_session *s) {
 // Keys per work-group: 1024; 512 for batches that would leave most CUs without a work-group, whose lanes then share
 // LDS slots with half as many others (kernel times: 2,000 keys 7.7 -> 6.7 us, 16,000 9.1 -> 7.3, 32,000 9.3 -> 8.1, 65,000 equal).
 //
-// Work-groups: one per tile, and more if those would have to wipe more than kWipe slots of the other table per
-// thread; the further ones only wipe.  Two calls of one size leave at most four slots per key, so a loop over equal
-// batches launches none; a call of 300 keys behind one of 2^20 wipes 2^21 slots: 284 us by its one tile, 12 this way.
-constexpr uint32_t kWipe = 4;
+// Work-groups: one per tile.  What the previous call has used of the other table is wiped by further ones while the tiles leave CUs free
+// for them (up to kBeside keys), off the tiles' chain of round trips: 106,496 keys, 38,600 distinct, 11.9 -> 11.2 us.  Beyond, the tiles wipe when
+// they are done (425,984 keys, none twice, 38.5 us; further work-groups beside them 40.4), and more work-groups if those would have to wipe more than
+// kWipe slots per thread (300 keys behind a call of 2^20: 284 us by its one tile, 12 this way).
+constexpr uint32_t kWipe = 8, kWipeBehind = 4, kBeside = 1u << 18;
 
 template <bool kMissed = false>
-void launch_dedup(const int64_t *keys, uint32_t n, int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter,
-                  uint32_t *flags, int64_t *unique_keys, uint32_t *inverse, uint32_t *n_unique, int64_t *other_tkey, uint32_t *other_tuid,
-                  uint64_t other_dirty, uint32_t max_blocks, hipStream_t st, const Missed &more = Missed{nullptr, nullptr, nullptr}) {
+void launch_dedup(const int64_t *keys, uint32_t n, int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter, hipStream_t st, DedupArgs a) {
     const uint32_t tile = n <= kSmallBatch ? 512u : 1024u;
-    const uint64_t tiles = ((uint64_t)n + tile - 1) / tile;
-    const uint64_t wipers = other_dirty / (kWipe * tile);
-    const uint64_t blocks = tiles > wipers ? tiles : wipers;
-    const dim3 grid((uint32_t)(blocks < max_blocks ? blocks : max_blocks)), block(tile);
-    if (tile == 512u)
-        hipLaunchKernelGGL((dedup_kernel<512, kMissed>), grid, block, 0, st, keys, n, more, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
-                           other_tkey, other_tuid, other_dirty);
-    else
-        hipLaunchKernelGGL((dedup_kernel<1024, kMissed>), grid, block, 0, st, keys, n, more, tkey, tuid, mask, counter, flags, unique_keys, inverse, n_unique,
-                           other_tkey, other_tuid, other_dirty);
+    const uint32_t tiles = (n + tile - 1) / tile;
+    const bool beside = n <= kBeside;
+    const uint32_t per = (beside ? kWipe : kWipeBehind) * tile;
+    const uint32_t wiping = (uint32_t)((a.other_dirty + per - 1) / per);            // (at most 2^31 + 1 slots)
+    a.groups = beside ? tiles + wiping : tiles > wiping ? tiles : wiping;
+    const dim3 grid(a.groups), block(tile);
+    const u64x4 pointers = {word_of(keys), word_of(tkey), word_of(tuid), word_of(counter)};
+    const u32x4 sizes = {n, mask, tiles, beside ? tiles : 0u};
+    if (tile == 512u) hipLaunchKernelGGL((dedup_kernel<512, kMissed>), grid, block, 0, st, pointers, sizes, a);
+    else              hipLaunchKernelGGL((dedup_kernel<1024, kMissed>), grid, block, 0, st, pointers, sizes, a);
 }
 
 uint32_t *flags_behind(uint64_t *counter) { return reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(counter) + kFlagOffset); }
@@ -302,8 +325,8 @@ hps_status_t hps_dedup_missed(hps_dedup_session *s, const int64_t *keys, size_t 
     if (hps_status_t e = check_session(s)) return e;
     if (n_max == 0 || n_max > s->max_n) return fail(HPS_ERR_INVALID_ARG, "n_max must be in 1 .. the session's max_n");
     const int t = s->cur, o = 1 - t;
-    launch_dedup<true>(keys, (uint32_t)n_max, s->tkey[t], s->tuid[t], 0u, s->counter + t, flags_behind(s->counter), unique_keys, inverse, n_unique,
-                       s->tkey[o], s->tuid[o], s->dirty[o], (uint32_t)s->n_cus * 8u, st, Missed{n_dev, n_host, keys_host});
+    launch_dedup<true>(keys, (uint32_t)n_max, s->tkey[t], s->tuid[t], 0u, s->counter + t, st,
+                       DedupArgs{flags_behind(s->counter), unique_keys, inverse, n_unique, s->tkey[o], s->tuid[o], s->dirty[o], 0u, n_dev, n_host, keys_host});
     HIP_TRY(hipGetLastError());
     s->dirty[t] = slots_for(n_max) + 1;
     s->dirty[o] = 0;
@@ -320,7 +343,7 @@ const char *hps_dedup_last_error(void) { return g_err.c_str(); }
 hps_status_t hps_dedup_create(size_t max_n, hps_dedup_t **out) {
     if (!out) return fail(HPS_ERR_INVALID_ARG, "out must not be NULL");
     *out = nullptr;
-    // 2 * max_n slots must stay below 2^32: slot numbers, the mask and the extra slot behind the table are 32-bit
+    // slots_for(max_n) must stay below 2^32: slot numbers, the mask and the extra slot behind the table are 32-bit
     if (max_n == 0 || max_n > (1ull << 30)) return fail(HPS_ERR_INVALID_ARG, "max_n must be in 1 .. 2^30");
     hps_dedup_session *s = new (std::nothrow) hps_dedup_session();
     if (!s) return fail(HPS_ERR_OOM, "host allocation failed");
@@ -412,14 +435,14 @@ hps_status_t hps_dedup(hps_dedup_t *s, const int64_t *keys, size_t n, int64_t *u
         const uint64_t cb = (slots + 1 + kBlock - 1) / kBlock;
         hipLaunchKernelGGL(dedup_clear_kernel, dim3((uint32_t)(cb < cap ? cb : cap)), dim3(kBlock), 0, q,
                            s->tkey[2], s->tuid[2], slots + 1, s->counter + 2);
-        launch_dedup(keys, (uint32_t)n, s->tkey[2], s->tuid[2], mask, s->counter + 2, flags_behind(s->counter), unique_keys, inverse, n_unique,
-                     s->tkey[2], s->tuid[2], 0, cap, q);
+        launch_dedup(keys, (uint32_t)n, s->tkey[2], s->tuid[2], mask, s->counter + 2, q,
+                     DedupArgs{flags_behind(s->counter), unique_keys, inverse, n_unique, nullptr, nullptr, 0, 0u, nullptr, nullptr, nullptr});
         HIP_TRY(hipGetLastError());
         return HPS_OK;
     }
     const int t = s->cur, o = 1 - t;
-    launch_dedup(keys, (uint32_t)n, s->tkey[t], s->tuid[t], mask, s->counter + t, flags_behind(s->counter), unique_keys, inverse, n_unique,
-                 s->tkey[o], s->tuid[o], s->dirty[o], cap, q);
+    launch_dedup(keys, (uint32_t)n, s->tkey[t], s->tuid[t], mask, s->counter + t, q,
+                 DedupArgs{flags_behind(s->counter), unique_keys, inverse, n_unique, s->tkey[o], s->tuid[o], s->dirty[o], 0u, nullptr, nullptr, nullptr});
     HIP_TRY(hipGetLastError());
     s->dirty[t] = slots + 1;          // this call's slots, the extra one included
     s->dirty[o] = 0;
@@ -452,14 +475,15 @@ hps_status_t hps_dedup_noalloc(const int64_t *keys, size_t n, int64_t *unique_ke
     int n_cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (n_cus <= 0) n_cus = 256;
-    const uint64_t slots = slots_for(n);            // <= kNaSlots because n <= kNaMaxKeys
+    const uint64_t slots = slots_for(n) < kNaSlots ? slots_for(n) : kNaSlots;      // >= 2 n because n <= kNaMaxKeys
     const uint32_t mask = (uint32_t)(slots - 1);
     const uint32_t cap = (uint32_t)n_cus * 8u;
     // The array keeps what the last call left in it: the slots this call may touch and its counter
     // are cleared first (by a kernel, so that the call can be captured into a graph).
     const uint64_t cb = (slots + 1 + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(dedup_clear_kernel, dim3((uint32_t)(cb < cap ? cb : cap)), dim3(kBlock), 0, q, tkey, tuid, slots + 1, counter);
-    launch_dedup(keys, (uint32_t)n, tkey, tuid, mask, counter, flags_behind(counter), unique_keys, inverse, n_unique, tkey, tuid, 0, cap, q);
+    launch_dedup(keys, (uint32_t)n, tkey, tuid, mask, counter, q,
+                 DedupArgs{flags_behind(counter), unique_keys, inverse, n_unique, nullptr, nullptr, 0, 0u, nullptr, nullptr, nullptr});
     HIP_TRY(hipGetLastError());
     return HPS_OK;
 }
