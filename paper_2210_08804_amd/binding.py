@@ -43,6 +43,7 @@ EXPORTS = (
 FETCH_FN = C.CFUNCTYPE(None, C.c_void_p, C.POINTER(C.c_int64), C.c_size_t, C.POINTER(C.c_float))
 
 _lib = None
+_int32, _int64, _float32 = torch.int32, torch.int64, torch.float32
 
 
 class HpsError(RuntimeError):
@@ -133,6 +134,8 @@ def _check(status):
 def _ptr(t, dtype=None):
     if t is None:
         return None
+    if t.is_cuda and (t.dtype is dtype or dtype is None) and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise TypeError("device tensor expected")
     if dtype is not None and t.dtype != dtype:
@@ -142,13 +145,20 @@ def _ptr(t, dtype=None):
     return t.data_ptr()
 
 
+_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_initialized = False
+
+
 def _stream(stream):
     # The raw handle of the current stream, asked for at every call.  (torch.cuda.current_stream() makes a Stream object
     # first: 2.8 us of the 8.2 us that the host needs to issue a query, 0.3 us this way.)
+    global _initialized
     if stream is not None:
         return stream.cuda_stream
-    if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _initialized:
+        return _raw_stream(_device())
+    _initialized = torch.cuda.is_initialized()
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -196,9 +206,11 @@ def hps_cache_destroy(handle) -> None:
 
 
 def hps_cache_query(handle, keys, n, out, miss_idx, miss_keys, n_miss, stream=None) -> None:
-    _check(load_library().hps_cache_query(
-        handle, _ptr(keys, torch.int64), n, _ptr(out, torch.float32), _ptr(miss_idx, torch.int32),
-        _ptr(miss_keys, torch.int64), _ptr(n_miss, torch.int32), _stream(stream)))
+    status = (_lib or load_library()).hps_cache_query(
+        handle, _ptr(keys, _int64), n, _ptr(out, _float32), _ptr(miss_idx, _int32),
+        _ptr(miss_keys, _int64), _ptr(n_miss, _int32), _stream(stream))
+    if status:
+        _check(status)
 
 
 def hps_cache_query_dn(handle, keys, n_max, n_dev, out, miss_idx, miss_keys, n_miss, stream=None) -> None:
