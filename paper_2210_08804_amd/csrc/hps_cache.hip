@@ -1631,8 +1631,11 @@ __global__ void __launch_bounds__(kBlock) dump_kernel(const int64_t *__restrict_
 // once per lane and pass instead of once per element.  Bound by the 64-bit products of the mixes (four
 // per element before, two now) and by the rows written: 31.7 -> 20.7 us for the 90,000 missing rows of a
 // 425,984-key batch, written twice.  Few rows are spread over all waves (7,400 rows in 32s: 6.5 us, spread 4.1 us).
+// kPast: rows that go to both places.  The compact copy is what the caller reads next (an insert of the missing rows), the other
+// goes past the caches (streaming step of 425,984 keys 108.6 -> 106.0 us).
 constexpr uint32_t kBackingRows  = 32;
 constexpr uint32_t kBackingWaves = 8192;         // as many as 256 CUs hold
+template <bool kPast>
 __global__ void __launch_bounds__(kBlock) backing_kernel(const int64_t *__restrict__ keys, uint32_t n,
                                                          const uint32_t *__restrict__ n_dev, uint32_t version, const RowGeom g,
                                                          float *rows, const uint32_t *__restrict__ scatter_idx,
@@ -1671,7 +1674,9 @@ __global__ void __launch_bounds__(kBlock) backing_kernel(const int64_t *__restri
             if (r < cnt && c < g.C) {
                 const f32x4 v4 = {x[0], x[1], x[2], x[3]};
                 if (rows) *reinterpret_cast<f32x4 *>(rows + (i0 + r) * g.d + c * 4) = v4;
-                if (scatter_idx) *reinterpret_cast<f32x4 *>(scatter_out + (uint64_t)w * g.d + c * 4) = v4;
+                f32x4 *const to_out = reinterpret_cast<f32x4 *>(scatter_out + (uint64_t)w * g.d + c * 4);
+                if (kPast) __builtin_nontemporal_store(v4, to_out);
+                else if (scatter_idx) *to_out = v4;
             }
         }
     }
@@ -2464,21 +2469,17 @@ hps_status_t hps_membench_gather(const float *rows, const uint32_t *slot_of, siz
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (cus <= 0) cus = 256;
-    // the query kernel's shape for this batch size: 8 waves x up to 64 positions, trimmed to whole rounds over the CUs
-    constexpr int kWpb = 8;
-    const uint64_t full = (uint64_t)kWpb * kWave * (uint64_t)cus;
-    const uint64_t rounds = (n + full - 1) / full;
-    uint64_t kpw = (n + kWpb * (uint64_t)cus * rounds - 1) / (kWpb * (uint64_t)cus * rounds);
-    if (kpw < 16) kpw = 16;
-    if (kpw > (uint64_t)kWave) kpw = kWave;
+    // the worker waves and the keys per wave of a large query (query_shape)
+    constexpr int kWpb = 7;
+    const uint64_t kpw = query_shape(1, n, dim, (uint64_t)cus, false, false).kpw;
     const uint64_t tile = kpw * kWpb;
     const uint64_t blocks = (n + tile - 1) / tile;
     if (blocks >= (1ull << 31)) return fail(HPS_ERR_INVALID_ARG, "n too large");
     if (dim == 128)
-        hipLaunchKernelGGL((membench_gather_kernel<26, kWpb, 128>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
+        hipLaunchKernelGGL((membench_gather_kernel<32, kWpb, 128>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
                            static_cast<hipStream_t>(stream), rows, slot_of, (uint32_t)n, (uint32_t)kpw, make_geom(dim), out);
     else
-        hipLaunchKernelGGL((membench_gather_kernel<24, kWpb, 0>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
+        hipLaunchKernelGGL((membench_gather_kernel<32, kWpb, 0>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0,
                            static_cast<hipStream_t>(stream), rows, slot_of, (uint32_t)n, (uint32_t)kpw, make_geom(dim), out);
     HIP_TRY(hipGetLastError());
     return HPS_OK;
@@ -2494,21 +2495,17 @@ hps_status_t hps_membench_gather_half(const float *rows, const uint32_t *slot_of
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (cus <= 0) cus = 256;
-    constexpr int kWpb = 8;                     // the shape hps_membench_gather uses
-    const uint64_t full = (uint64_t)kWpb * kWave * (uint64_t)cus;
-    const uint64_t rounds = (n + full - 1) / full;
-    uint64_t kpw = (n + kWpb * (uint64_t)cus * rounds - 1) / (kWpb * (uint64_t)cus * rounds);
-    if (kpw < 16) kpw = 16;
-    if (kpw > (uint64_t)kWave) kpw = kWave;
+    constexpr int kWpb = 7;                     // the shape hps_membench_gather uses
+    const uint64_t kpw = query_shape(1, n, 128, (uint64_t)cus, false, false).kpw;
     const uint64_t tile = kpw * kWpb;
     const uint64_t blocks = (n + tile - 1) / tile;
     if (blocks >= (1ull << 31)) return fail(HPS_ERR_INVALID_ARG, "n too large");
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (reads)
-        hipLaunchKernelGGL((membench_half_kernel<26, kWpb, true>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0, st,
+        hipLaunchKernelGGL((membench_half_kernel<32, kWpb, true>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0, st,
                            rows, slot_of, (uint32_t)n, (uint32_t)kpw, out);
     else
-        hipLaunchKernelGGL((membench_half_kernel<26, kWpb, false>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0, st,
+        hipLaunchKernelGGL((membench_half_kernel<32, kWpb, false>), dim3((uint32_t)blocks), dim3(kWpb * kWave), 0, st,
                            rows, slot_of, (uint32_t)n, (uint32_t)kpw, out);
     HIP_TRY(hipGetLastError());
     return HPS_OK;
@@ -2547,8 +2544,12 @@ hps_status_t hps_backing_fetch(const int64_t *keys, size_t n, const uint32_t *n_
     const uint64_t per_block = (uint64_t)kWavesPerWg * ((uint32_t)kWave >> g.lprShift);
     uint64_t blocks = (n + per_block - 1) / per_block * g.passes;
     if (blocks > kBackingWaves / kWavesPerWg) blocks = kBackingWaves / kWavesPerWg;
-    hipLaunchKernelGGL(backing_kernel, dim3((uint32_t)blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream),
-                       keys, (uint32_t)n, n_dev, version, g, rows, scatter_idx, scatter_out);
+    if (rows && scatter_idx)
+        hipLaunchKernelGGL((backing_kernel<true>), dim3((uint32_t)blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream),
+                           keys, (uint32_t)n, n_dev, version, g, rows, scatter_idx, scatter_out);
+    else
+        hipLaunchKernelGGL((backing_kernel<false>), dim3((uint32_t)blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream),
+                           keys, (uint32_t)n, n_dev, version, g, rows, scatter_idx, scatter_out);
     HIP_TRY(hipGetLastError());
     return HPS_OK;
 }
