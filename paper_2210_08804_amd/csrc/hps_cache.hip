@@ -852,6 +852,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     // holds it to be no slower than the plain one there, which would gain as much; 50,000 of them dealt in
     // fours / sixteens 16.2 / 12.3, 47,000 of 106,496 9.3 / 8.9).
     const bool dealt = kFull && n_dev && kpw >= kDealt;
+    const uint32_t lanes = dealt ? (kpw + kDealt - 1) / kDealt * kDealt : kpw;      // that may have keys
     auto tiles_of = [&](uint32_t nd) {
         const uint32_t m = (nd + kDealt * WPB - 1) / (kDealt * WPB);
         return !kCoherent || !dealt ? n_tiles : m == 0 ? 1u : m < n_tiles ? m : n_tiles;
@@ -960,7 +961,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     };
 
     if constexpr (!kCoherent) {
-        const int  way = probe_wave<W, KPW, false>(K, key, set, want, kpw);
+        const int  way = probe_wave<W, KPW, false>(K, key, set, want, lanes);
         const bool hit = way >= 0;
         list_misses(live && !hit);
         const uint64_t hitmask = __ballot(hit);
@@ -985,7 +986,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
         // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not.)
         if (__ballot(want) && !__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {
             shared_acquire();                          // the epochs are read before any key or row
-            const int way = probe_wave<W, KPW, true>(K, key, set, want, kpw);
+            const int way = probe_wave<W, KPW, true>(K, key, set, want, lanes);
             const uint64_t fmask = __ballot(way >= 0);
             const int r = rank_in(fmask);
             const uint32_t nf = (uint32_t)__popcll(fmask);
@@ -1018,7 +1019,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
             const uint32_t v1 = pending ? ld_agent(sc + 2ull * set) : 0u;
             const bool busy = pending && (v1 & 1u);    // a writer holds the set: look again later
             shared_acquire();                          // the word is read before any key or row
-            const int w = probe_wave<W, KPW, true>(K, key, set, pending && !busy, [] {}, kpw, here);
+            const int w = probe_wave<W, KPW, true>(K, key, set, pending && !busy, [] {}, lanes, here);
             const bool found = w >= 0;
             const uint64_t fmask = __ballot(found);
             if (here < 2) s_retry[wave][here] = 0u;

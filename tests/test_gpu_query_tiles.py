@@ -12,11 +12,11 @@ from harness import DeviceCache, SENTINEL
 pytestmark = pytest.mark.gpu
 
 
-def filled(d, policy=0, ways=8):
-    """A cache and its oracle with 6,000 keys in 8,192 sets, none of which overflows; a batch over twice as many."""
+def filled(d, policy=0, ways=8, sets=8192):
+    """A cache and its oracle with 6,000 keys, which overflow no set; a batch over twice as many."""
     keys = np.arange(6000, dtype=np.int64)
     rows = inputs.backing_rows(keys, d)
-    gc, oc = DeviceCache(8192 * ways, ways, d, policy=policy), OracleCache(8192 * ways, ways, d)
+    gc, oc = DeviceCache(sets * ways, ways, d, policy=policy), OracleCache(sets * ways, ways, d)
     for k, r in zip(np.array_split(keys, 12), np.array_split(rows, 12)):
         B.hps_cache_insert(gc.h, torch.from_numpy(k).cuda(), torch.from_numpy(r).cuda(), len(k))
         torch.cuda.synchronize()
@@ -76,3 +76,39 @@ def test_batches_where_the_launch_shape_changes(d, n, checked):
         missed[wi] = True
         assert (out == want[inv]).all()
         assert (mi == np.flatnonzero(missed[inv])).all() and (mk == keys[missed[inv]]).all()
+
+
+@pytest.mark.parametrize("checked", [True, False])
+@pytest.mark.parametrize("n_max", [8000, 9000, 40000, 90000, 130000, 200000])
+@pytest.mark.parametrize("ways", [4, 32, 64])
+def test_dealt_keys_are_searched_in_sets_of_every_width(ways, n_max, checked):
+    """Keys per wave that are no multiple of sixteen: its last lanes get theirs by the deal alone.  (512-byte rows, 256 CUs, plain / default
+    mode: 20 / 21, 22 / 23, 32, 51 / 54, 37 / 39 and 56 / 59 keys per wave.)"""
+    d = 128
+    # No set gets more of the keys than it has ways, so which of them are cached does not hang on the order within an insert
+    # (4 ways over 8,192 sets: some do; over 2^17 sets, which would have 0.05 keys each, five in one are 2e-9 x 2^17 sets).
+    gc, oc = filled(d, ways=ways, sets=1 << 17 if ways < 32 else 1024)
+    assert np.bincount([oc.set_of(k) for k in range(6000)]).max() <= ways
+    with gc:
+        B.hps_cache_set_concurrent_writers(gc.h, checked)
+        keys = np.random.default_rng(n_max).integers(0, 12000, n_max)
+        dk = torch.from_numpy(keys).cuda()
+        uniq, inv = np.unique(keys, return_inverse=True)
+        rows, wi, _ = expected(oc, uniq, d)
+        missed = np.zeros(len(uniq), dtype=bool)
+        missed[wi] = True
+        rows, missed = torch.from_numpy(rows.view(np.int32))[torch.from_numpy(inv)].cuda(), missed[inv]
+        for m in (n_max, n_max - 1, n_max * 3 // 4, n_max // 3):
+            out = torch.full((n_max, d), 0, dtype=torch.int32, device="cuda")
+            out.fill_(SENTINEL)
+            mi = torch.full((n_max,), -1, dtype=torch.int32, device="cuda")
+            mk = torch.full((n_max,), -1, dtype=torch.int64, device="cuda")
+            nm = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+            nd = torch.tensor([m], dtype=torch.int32, device="cuda")
+            B.hps_cache_query_dn(gc.h, dk, n_max, nd, out.view(torch.float32), mi, mk, nm)
+            torch.cuda.synchronize()
+            want = np.flatnonzero(missed[:m])
+            assert int(nm.item()) == len(want), m
+            assert torch.equal(out[:m], rows[:m]) and bool((out[m:] == SENTINEL).all()), m
+            order = np.argsort(mi.cpu().numpy()[:len(want)])
+            assert (mi.cpu().numpy()[:len(want)][order] == want).all() and (mk.cpu().numpy()[:len(want)][order] == keys[want]).all(), m

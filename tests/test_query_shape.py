@@ -108,3 +108,55 @@ int main() {
     subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+DEALT = """
+constexpr uint32_t kDealt = %(dealt)s;
+uint32_t searched(uint32_t kpw, bool dealt) { return %(lanes)s; }
+int main() {
+    int partial = 0;
+    for (uint32_t ways : {32u, 64u})
+        for (bool checked : {false, true})
+            for (uint32_t d = 4; d <= 1024; d += d < 160 ? 4 : d / 8 / 4 * 4)
+                for (uint64_t batch = 1; batch < 1ull << 22; batch += batch / 37 + 1) {
+                    const QueryShape q = query_shape(1, batch, d, 256, checked, false, ways, true);
+                    const uint32_t kpw = q.kpw, WPB = (uint32_t)q.wpb, n_tiles = (uint32_t)((batch + kpw * WPB - 1) / (kpw * WPB));
+                    if (kpw < kDealt) continue;
+                    partial += kpw %% kDealt != 0;
+                    uint64_t keys = 0;
+                    for (uint32_t lane = 0; lane < 64; ++lane) {
+                        const uint32_t lt = 0, wave = 0, b = %(position)s;
+                        const uint32_t block = 8 * (64 / ways);           // lanes that probe_wave searches or leaves out together
+                        if (b < batch && lane / block * block >= searched(kpw, true)) {
+                            std::printf("ways %%u d %%u batch %%llu: %%u keys per wave, lane %%u has one and is not searched\\n", ways, d, (unsigned long long)batch, kpw, lane);
+                            return 1;
+                        }
+                        keys += n_tiles * WPB;
+                    }
+                    if (keys < batch) { std::printf("batch %%llu: %%llu lanes\\n", (unsigned long long)batch, (unsigned long long)keys); return 1; }
+                }
+    return partial ? 0 : 2;
+}
+"""
+
+
+def test_every_lane_that_is_dealt_a_key_is_searched(tmp_path):
+    """A batch whose length is read on the device is dealt to the waves in sixteens, up to more keys than kpw to a wave; in sets
+    of 32 ways and more the probe leaves out the lanes behind those it is told of.  Deal and count are taken from the source."""
+    with open(SRC) as f:
+        s = f.read()
+    rule = s[s.index("struct QueryShape {"):s.index("template <int W, int U, int WPB, bool kCoherent, int kD>\nvoid launch_query_kernel")]
+    kernel = s[s.index("\nquery_kernel(const u64x4"):s.index("query_dedup_kernel(")]
+    told = set(re.findall(r"probe_wave<W, KPW, \w+>\(K, key, set, [^;]*?(\w+)(?:, here)?\);", kernel))
+    assert len(re.findall(r"probe_wave<", kernel)) == 3 and len(told) == 1, told
+    told = told.pop()
+    lanes = re.search(r"const uint32_t %s\s*= (.*?);" % told, kernel)
+    src = tmp_path / "dealt.cpp"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <initializer_list>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
+                   + rule + DEALT % {"dealt": re.search(r"constexpr uint32_t kDealt = (\d+);", s)[1],
+                                     "lanes": lanes[1] if lanes else told,
+                                     "position": re.search(r"if \(dealt\) b = (.*?);", kernel)[1]})
+    exe = tmp_path / "dealt"
+    subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
