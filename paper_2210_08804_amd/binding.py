@@ -147,18 +147,16 @@ def _ptr(t, dtype=None):
 
 _device = getattr(torch._C, "_cuda_getDevice", None)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-_initialized = False
+_is_initialized = torch.cuda.is_initialized
 
 
 def _stream(stream):
     # The raw handle of the current stream, asked for at every call.  (torch.cuda.current_stream() makes a Stream object
     # first: 2.8 us of the 8.2 us that the host needs to issue a query, 0.3 us this way.)
-    global _initialized
     if stream is not None:
         return stream.cuda_stream
-    if _initialized:
+    if _is_initialized():                                # not in a forked child, which current_stream() refuses
         return _raw_stream(_device())
-    _initialized = torch.cuda.is_initialized()
     return torch.cuda.current_stream().cuda_stream
 
 
