@@ -45,6 +45,10 @@ __global__ void place_rows_kernel(float *out, const uint32_t *__restrict__ idx,
 // from the fetched rows to the end of a lookup, insert included).  Bound by the link.
 constexpr int kFetchedAhead = 4;                 // loads of a lane in flight (1 / 2 / 4: 57.1 / 53.0 / 52.7 us from this launch to the end of the lookup)
 constexpr uint64_t kMostShared = 128 << 10;      // bytes that rows of more than one entry may be read more than once
+// Bytes of rows up to which the kernel is the faster one: it saves the copy's start and end, but its rate over the link is the lower one (a
+// lookup of new keys only, rows of 512 bytes, copy / kernel: 2 MB 106 / 94 us, 8 MB 219 / 207, 12 MB 291 / 284, 14 MB 329 / 328, 16 MB
+// 367 / 372, 20 MB 440 / 461, 54 MB 1,102 / 1,321; rows of 64 and 2,048 bytes cross at 14 and 17 MB).
+constexpr uint64_t kMostPlaced = 12 << 20;
 __global__ void __launch_bounds__(256) place_fetched_kernel(float *out, const uint32_t *__restrict__ idx, const uint32_t *__restrict__ src,
                                                             const float *__restrict__ host, float *dev, uint32_t m, uint32_t d) {
     const uint32_t C = d / 4;
@@ -370,7 +374,8 @@ hps_status_t hps_lookup(hps_lookup_t *L, const int64_t *keys, size_t n, float *o
         const uint32_t u = *L->h_n_unique;
         L->fetch(L->user, L->h_ukeys, u, L->h_rows);
         // Entries that share a row each read it over the link: as long as that is less than what the runtime's copy takes to start and to end (4 us or so).
-        if ((uint64_t)(m - u) * L->dim * sizeof(float) <= kMostShared) {
+        const uint64_t row = L->dim * sizeof(float);
+        if ((uint64_t)(m - u) * row <= kMostShared && u * row <= kMostPlaced) {
             const uint64_t per = 256 * kFetchedAhead, blocks = ((uint64_t)m * (L->dim / 4) + per - 1) / per, most = 2048;
             hipLaunchKernelGGL(place_fetched_kernel, dim3((uint32_t)(blocks < most ? blocks : most)), dim3(256), 0, st, out, L->d_miss_idx, L->d_inv,
                                L->d_h_rows, L->d_rows, m, L->dim);

@@ -1,5 +1,8 @@
 """What a call costs beside another one: properties that results do not show.  Each test compares two times taken
 in turn on the same device, far enough apart that noise does not decide."""
+import time
+
+import numpy as np
 import pytest
 import torch
 
@@ -224,3 +227,36 @@ def test_few_long_rows_are_made_by_many_waves():
 
         times[d], = _median_us([calls], lambda: [busy.fill_(0.0) for _ in range(4)])
     assert times[4096] < 1.4 * times[256], f"us of 20 calls by row length: {times}"
+
+
+def test_many_fetched_rows_take_the_faster_way_to_the_device():
+    """A lookup of 53,248 new keys, rows of 1 KiB, with a fetch that does nothing: every key once against 6 % of them twice, which
+    has the rows copied.  (Once over twice: 1.0; 1.20 with the rows of the first read by the kernel that places them.)"""
+    u, d = 53248, 256
+    n = u + u // 16
+
+    @B.FETCH_FN
+    def fetch(user, keys, m, rows):
+        pass
+
+    out = torch.empty(n, d, device="cuda")
+    times = {}
+    for shared in (False, True):
+        h = B.hps_cache_create(1 << 18, 8, d)
+        lk = B.hps_lookup_create(h, n, 2.0, np.zeros(d, np.float32), fetch)
+        try:
+            took = []
+            for call in range(15):
+                keys = torch.arange(u, device="cuda") + (call << 20)
+                if shared:
+                    keys = torch.cat([keys, keys[:n - u]])
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                B.hps_lookup(lk, keys, len(keys), out)
+                took.append(time.perf_counter() - t)
+            times[shared] = sorted(took[3:])[6] * 1e6
+        finally:
+            torch.cuda.synchronize()
+            B.hps_lookup_destroy(lk)
+            B.hps_cache_destroy(h)
+    assert times[False] < 1.08 * times[True], f"us of a lookup by whether keys repeat: {times}"
