@@ -848,14 +848,13 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     if (threadIdx.x == 0) s_ready = 0u;
     // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, sixteen at a
     // time, so that a wave's keys can be requested beside it (50,000 of 106,496 keys: all in the first half of the waves 20.0 us, spread 14.6).
-    // At most kpw, rounded up to sixteens, fall to a wave.  In the default mode tiles to which none fall leave, and are not counted (3,000 of 300,000 keys 13.3 -> 6.8; a test
-    // holds it to be no slower than the plain one there, which would gain as much; 50,000 of them dealt in
-    // fours / sixteens 16.2 / 12.3, 47,000 of 106,496 9.3 / 8.9).
+    // At most kpw, rounded up to sixteens, fall to a wave.  Tiles to which none fall leave, and are not counted (4,000 of 200,000 keys plain 9.5 -> 5.2, 3,000 of 300,000 in the default mode 13.3 -> 6.8;
+    // 50,000 of them dealt in fours / sixteens 16.2 / 12.3, 47,000 of 106,496 9.3 / 8.9).
     const bool dealt = kFull && n_dev && kpw >= kDealt;
     const uint32_t lanes = dealt ? (kpw + kDealt - 1) / kDealt * kDealt : kpw;      // that may have keys
     auto tiles_of = [&](uint32_t nd) {
         const uint32_t m = (nd + kDealt * WPB - 1) / (kDealt * WPB);
-        return !kCoherent || !dealt ? n_tiles : m == 0 ? 1u : m < n_tiles ? m : n_tiles;
+        return !dealt ? n_tiles : m == 0 ? 1u : m < n_tiles ? m : n_tiles;
     };
 
     if (wave >= WPB) {
