@@ -851,7 +851,6 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     // At most kpw, rounded up to sixteens, fall to a wave.  Tiles to which none fall leave, and are not counted (4,000 of 200,000 keys plain 9.5 -> 5.2, 3,000 of 300,000 in the default mode 13.3 -> 6.8;
     // 50,000 of them dealt in fours / sixteens 16.2 / 12.3, 47,000 of 106,496 9.3 / 8.9).
     const bool dealt = kFull && n_dev && kpw >= kDealt;
-    const uint32_t lanes = dealt ? (kpw + kDealt - 1) / kDealt * kDealt : kpw;      // that may have keys
     auto tiles_of = [&](uint32_t nd) {
         const uint32_t m = (nd + kDealt * WPB - 1) / (kDealt * WPB);
         return !dealt ? n_tiles : m == 0 ? 1u : m < n_tiles ? m : n_tiles;
@@ -921,6 +920,9 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
         if (tile >= tiles_of(nd < batch ? nd : batch)) return;
         live = live && b < nd;
     }
+    // Lanes up to the last that has a key: a length on the device leaves a wave some of those that a full batch would fill (64 ways, rows
+    // of 512 bytes, 24,000 of 118,587 keys in the default mode 12.6 -> 9.5 without them).
+    const uint32_t lanes = dealt ? kWave - (uint32_t)__builtin_clzll(__ballot(live) | 1ull) : kpw;
     __syncthreads();                                   // s_ready is zero
     __builtin_amdgcn_sched_barrier(0);                 // (nobody waits here for keys)
     // All that is needed from here on, while the keys travel.

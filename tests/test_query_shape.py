@@ -112,6 +112,8 @@ int main() {
 
 DEALT = """
 constexpr uint32_t kDealt = %(dealt)s;
+uint64_t with_keys;                                                   // the lanes of the wave that have any
+#define __ballot(live) with_keys
 uint32_t searched(uint32_t kpw, bool dealt) { return %(lanes)s; }
 int main() {
     int partial = 0;
@@ -124,14 +126,21 @@ int main() {
                     if (kpw < kDealt) continue;
                     partial += kpw %% kDealt != 0;
                     uint64_t keys = 0;
-                    for (uint32_t lane = 0; lane < 64; ++lane) {
-                        const uint32_t lt = 0, wave = 0, b = %(position)s;
+                    for (uint64_t nd : {batch, batch / 3}) {
+                        with_keys = 0;
+                        keys = 0;
+                        for (uint32_t lane = 0; lane < 64; ++lane) {
+                            const uint32_t lt = 0, wave = 0, b = %(position)s;
+                            with_keys |= (uint64_t)(b < nd) << lane;
+                            keys += n_tiles * WPB;
+                        }
+                        const uint32_t last = with_keys ? 63 - (uint32_t)__builtin_clzll(with_keys) : 0, told = searched(kpw, true);
                         const uint32_t block = 8 * (64 / ways);           // lanes that probe_wave searches or leaves out together
-                        if (b < batch && lane / block * block >= searched(kpw, true)) {
-                            std::printf("ways %%u d %%u batch %%llu: %%u keys per wave, lane %%u has one and is not searched\\n", ways, d, (unsigned long long)batch, kpw, lane);
+                        if (last / block * block >= told || told > last + 1) {
+                            std::printf("ways %%u d %%u %%llu of %%llu keys: %%u keys per wave, lane %%u is the last that has one, %%u are searched\\n", ways, d,
+                                        (unsigned long long)nd, (unsigned long long)batch, kpw, last, told);
                             return 1;
                         }
-                        keys += n_tiles * WPB;
                     }
                     if (keys < batch) { std::printf("batch %%llu: %%llu lanes\\n", (unsigned long long)batch, (unsigned long long)keys); return 1; }
                 }
