@@ -756,6 +756,7 @@ struct QueryArgs {
     uint32_t       tiles_per_table;
     uint32_t       n_tiles;     // T * tiles_per_table (>= 1 even when B == 0)
     uint32_t       n_tables;    // T (<= HPS_MAX_TABLES <= 64: one helper lane per table finishes the call)
+    uint32_t       deal;        // keys that a wave takes at a time of a batch whose length is read on the device (a power of two), 0: its kpw
     RowGeom        g;
     Table          tab[HPS_MAX_TABLES];
 };
@@ -765,7 +766,6 @@ constexpr uint32_t kQueryArgsAt = 64;
 static_assert(alignof(QueryArgs) == 64, "kQueryArgsAt");
 typedef const __attribute__((address_space(4))) QueryArgs *QueryArgsIn;
 constexpr uint32_t kGridX = 1u << 20;          // work-groups in a row of a query's grid
-constexpr uint32_t kDealt = 16;                // neighbouring keys that a wave takes of a batch whose length is read on the device
 
 // Kernel arguments are read with scalar loads where they are first used, each followed by its own
 // wait; spread over several cache lines and basic blocks that put three to five dependent
@@ -823,7 +823,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     const int64_t *const K0 = global_at<const int64_t>(pointers.y);
     const uint32_t *const epoch0 = global_at<const uint32_t>(pointers.z);
     const uint32_t *const n_dev = global_at<const uint32_t>(pointers.w);
-    const uint32_t batch = sizes.x, kpw = sizes.y, tiles_per_table = sizes.z, n_tiles = sizes.w, S0 = sets.x, smask0 = sets.y;
+    const uint32_t batch = sizes.x, kpw = kFull ? sizes.y & 0xFFFFu : sizes.y, deal = kFull ? sizes.y >> 16 : 0u, tiles_per_table = sizes.z, n_tiles = sizes.w, S0 = sets.x, smask0 = sets.y;
     __shared__ uint64_t s_src[WPB][KPW];                // (an odd number of rows is less than KPW: room for its copied last entry)
     __shared__ uint32_t s_dst[WPB][KPW];
     __shared__ int64_t  s_mkey[WPB][KPW];
@@ -846,13 +846,14 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     }
     QueryArgsIn in = (QueryArgsIn)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + kQueryArgsAt);
     if (threadIdx.x == 0) s_ready = 0u;
-    // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, sixteen at a
+    // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, `deal` neighbours (deal_of) at a
     // time, so that a wave's keys can be requested beside it (50,000 of 106,496 keys: all in the first half of the waves 20.0 us, spread 14.6).
-    // At most kpw, rounded up to sixteens, fall to a wave.  Tiles to which none fall leave, and are not counted (4,000 of 200,000 keys plain 9.5 -> 5.2, 3,000 of 300,000 in the default mode 13.3 -> 6.8;
-    // 50,000 of them dealt in fours / sixteens 16.2 / 12.3, 47,000 of 106,496 9.3 / 8.9).
-    const bool dealt = kFull && n_dev && kpw >= kDealt;
+    // At most kpw, rounded up to whole deals, fall to a wave.  Tiles to which none fall leave, and are not counted (4,000 of 200,000 keys plain 9.5 -> 5.2,
+    // 3,000 of 300,000 in the default mode 13.3 -> 6.8).
+    const bool dealt = kFull && deal;
+    const uint32_t shift = dealt ? 31u - (uint32_t)__builtin_clz(deal) : 0u;
     auto tiles_of = [&](uint32_t nd) {
-        const uint32_t m = (nd + kDealt * WPB - 1) / (kDealt * WPB);
+        const uint32_t deals = (nd >> shift) + ((nd & (deal - 1)) != 0), m = deals / WPB + (deals % WPB != 0);
         return !dealt ? n_tiles : m == 0 ? 1u : m < n_tiles ? m : n_tiles;
     };
 
@@ -909,7 +910,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
         else           HPS_ARGS_NOW("s"(K), "s"(S), "s"(smask));
     }
     uint32_t b = (lt * WPB + wave) * kpw + lane;
-    if (dealt) b = ((uint32_t)lane / kDealt * (n_tiles * WPB) + lt * WPB + wave) * kDealt + (uint32_t)lane % kDealt;
+    if (dealt) b = ((((uint32_t)lane >> shift) * (n_tiles * WPB) + lt * WPB + wave) << shift) + ((uint32_t)lane & (deal - 1));
     bool          live = (lane < (int)kpw || dealt) && b < batch;
     const uint32_t pos = t * batch + b;                // position in keys/out (< 2^32 checked on host)
 
@@ -1917,7 +1918,18 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
 // hold, and its code, all of it executed, lines that a short launch has to fetch (13,312 keys of 512 bytes in groups of 16 / 32
 // 6.35 / 6.30, 5,000 keys in groups of 8 / 16 6.1 / 6.2; 425,984 keys in groups of 32 / 16 58 / 70).  11 workers with rows of 128 bytes: 16 / 8 43.1 / 44.2.
-struct QueryShape { uint32_t kpw; int u, wpb; };
+//
+// A length on the device: `deal` neighbouring keys go to a wave at a time, sixteen (a line of the batch; 50,000 of 106,496 keys in fours / sixteens 16.2 / 12.3,
+// 47,000 9.3 / 8.9) or as many as have 16 KiB of rows, since sixteen more or less are what one wave has more than another (sixteens / this way,
+// 33,000 of 41,033 keys of 4 KiB 38.1 / 33.1, of 2 KiB 21.2 / 19.3) or all that a wave has (820 of 4 KiB 12.7 / 6.0).  A wave's keys are whole deals, so that they
+// stay one group of rows (19,000 of 24,137 keys of 768 bytes plain, 21 keys to a wave 9.2, 16 7.6).  Over several rounds sixteens are the faster ones
+// again (24,000 of 118,587 keys of 1,280 bytes plain in eights / sixteens 12.6 / 9.8).
+struct QueryShape { uint32_t kpw; int u, wpb; uint32_t deal; };
+uint32_t deal_of(uint32_t d) {
+    uint32_t k = 16;
+    while (k > 1 && (uint64_t)k * d * 4 > 16384) k >>= 1;
+    return k;
+}
 
 // Most rows of d words that a wave moves with copy_rows, which counts their 16-byte chunks in 32 bits (fewer than 64
 // only for rows of 512 MiB and more).
@@ -1929,8 +1941,10 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
         const uint64_t k = bytes / row;
         return k < kMinKeysPerWave ? (uint64_t)kMinKeysPerWave : k < (uint64_t)kWave ? k : (uint64_t)kWave;
     };
+    uint64_t deal = !n_dev || dedup ? 1 : deal_of(d);
+    auto whole = [&](uint64_t k) { return (k + deal - 1) / deal * deal; };
     const uint64_t some = rows_of(16384), most = dedup || n_dev ? (uint64_t)kWave : rows_of(32768);
-    QueryShape q{(uint32_t)most, 0, 0};
+    QueryShape q{(uint32_t)most, 0, 0, 0};
     if (dedup) q.wpb = n < (1u << 14) ? 4 : 8;
     else if (n >= (n_dev ? 1u << 18 : 1u << 19) && d <= 64 && ways <= 16) q.wpb = d <= 8 && !coherent ? 15 : 11;
     else q.wpb = n <= 2 * some * cus ? 4 : 4 * n <= 15 * some * cus ? 5 : 7;      // up to cus / 2 and 3 / 4 cus tiles of that many keys per wave
@@ -1942,17 +1956,22 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
         if (rounds == 1) {
             uint64_t least = n < 4096 ? kMinKeysPerWave : 16;
             if (!dedup) least = (5 * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);    // 2 / 5 cus tiles
-            if (least > some) least = some;
+            if (least > some) least = some < 16 ? some : some - some % deal;
             if (least < kMinKeysPerWave) least = kMinKeysPerWave;
             if (k < least) k = least;
-        }
+            if (row > 512 && k > least) {
+                if (deal > 8 && whole(k) * row > 32768) deal = 8;
+                k = whole(k);
+            }
+        } else if (deal > 1) deal = 16;
         // a tile holds keys of one table: with several tables their last tiles are not full
         auto tiles = [&] { return n_tables * ((batch + q.wpb * k - 1) / (q.wpb * k)); };
         while (n_tables > 1 && k < (q.wpb < 7 ? some : most) && tiles() > rounds * cus) ++k;
         if (k < most) q.kpw = (uint32_t)k;
     }
     if (!dedup && q.kpw > most_rows(d)) q.kpw = (uint32_t)most_rows(d);
-    const uint64_t bytes = q.kpw * row;                        // a wave's rows
+    if (deal > 1 && (q.kpw >= 16 || q.kpw % deal == 0)) q.deal = (uint32_t)deal;
+    const uint64_t bytes = (q.deal ? whole(q.kpw) : q.kpw) * row;      // a wave's rows
     if (d == 128 && q.wpb == 4 && q.kpw <= 8) q.u = 4;
     else if (q.wpb == 11) q.u = d <= 16 ? 8 : 16;
     else q.u = bytes <= 8192 && (d != 128 || q.wpb == 4) ? 8 : bytes <= 16384 ? 16 : 32;
@@ -1964,7 +1983,7 @@ void launch_query_kernel(const QueryArgs &a, bool full, hipStream_t st) {
     const dim3 grid(a.n_tiles < kGridX ? a.n_tiles : kGridX, (a.n_tiles + kGridX - 1) / kGridX), block((WPB + 1) * kWave);
     const Table &t = a.tab[0];
     const u64x4 pointers = {word_of(a.keys), word_of(t.K), word_of(t.epoch), word_of(a.n_dev)};
-    const u32x4 sizes = {a.B, a.kpw, a.tiles_per_table, a.n_tiles};
+    const u32x4 sizes = {a.B, a.kpw | a.deal << 16, a.tiles_per_table, a.n_tiles};
     const u32x2 sets = {t.S, t.smask};
     if constexpr (WPB <= 8 || W <= 16) {           // query_shape gives no more than 8 workers to wider sets
 #define HPS_QUERY(full) \
@@ -2343,6 +2362,7 @@ static hps_status_t query_call(hps_cache_t *const *caches, uint32_t n_tables, co
     const QueryShape shape = query_shape(n_tables, batch, caches[0]->d, (uint64_t)caches[0]->n_cus, coherent, dedup, caches[0]->W, n_dev != nullptr);
     const uint32_t kpw = shape.kpw;
     a.kpw = kpw;
+    a.deal = shape.deal;
     const uint32_t tile = kpw * (uint32_t)shape.wpb;
     a.tiles_per_table = (uint32_t)((batch + tile - 1) / tile);
     if (a.tiles_per_table == 0) a.tiles_per_table = 1;          // an empty batch still publishes n_miss = 0

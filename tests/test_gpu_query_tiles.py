@@ -32,7 +32,9 @@ def expected(oc, keys, d):
 
 @pytest.mark.parametrize("checked", [True, False])
 @pytest.mark.parametrize("policy", [0, 1])
-@pytest.mark.parametrize("d,n_max", [(128, 26624), (128, 5000), (32, 7000), (320, 9000)])
+@pytest.mark.parametrize("d,n_max", [(128, 26624), (32, 7000),      # dealt in sixteens, 32 and 18 keys to a wave
+                                     (192, 9000), (320, 30000), (1024, 3000), (512, 20000),   # in 16s, 8s, 4s and 8s, whole ones
+                                     (128, 5000), (320, 9000)])      # not dealt: 13 and 12 neighbouring keys to a wave
 def test_length_on_the_device_at_the_edges_of_the_deal(d, n_max, policy, checked):
     gc, oc = filled(d, policy)
     with gc:
@@ -40,7 +42,7 @@ def test_length_on_the_device_at_the_edges_of_the_deal(d, n_max, policy, checked
         keys = np.random.default_rng(5).integers(0, 12000, n_max)
         dk = torch.from_numpy(keys).cuda()
         # one deal, one wave's and one tile's worth of keys with 4, 5 and 7 workers, and the whole batch; each with its neighbours
-        for m in sorted({max(0, min(n_max, e + o)) for e in (0, 16, 32, 64, 80, 112, 128, 1024, n_max) for o in (-1, 0, 1)}):
+        for m in sorted({max(0, min(n_max, e + o)) for e in (0, 4, 16, 28, 32, 56, 64, 80, 112, 128, 1024, n_max) for o in (-1, 0, 1)}):
             out = torch.full((n_max, d), 0, dtype=torch.int32, device="cuda")
             out.fill_(SENTINEL)
             mi = torch.full((n_max,), -1, dtype=torch.int32, device="cuda")

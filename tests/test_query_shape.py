@@ -111,7 +111,6 @@ int main() {
 
 
 DEALT = """
-constexpr uint32_t kDealt = %(dealt)s;
 uint64_t with_keys;                                                   // the lanes of the wave that have any
 #define __ballot(live) with_keys
 uint32_t searched(uint32_t kpw, bool dealt) { return %(lanes)s; }
@@ -123,8 +122,10 @@ int main() {
                 for (uint64_t batch = 1; batch < 1ull << 22; batch += batch / 37 + 1) {
                     const QueryShape q = query_shape(1, batch, d, 256, checked, false, ways, true);
                     const uint32_t kpw = q.kpw, WPB = (uint32_t)q.wpb, n_tiles = (uint32_t)((batch + kpw * WPB - 1) / (kpw * WPB));
-                    if (kpw < kDealt) continue;
-                    partial += kpw %% kDealt != 0;
+                    const uint32_t deal = q.deal;
+                    if (deal == 0) continue;
+                    const uint32_t shift = 31u - (uint32_t)__builtin_clz(deal);
+                    partial += kpw %% deal != 0;
                     uint64_t keys = 0;
                     for (uint64_t nd : {batch, batch / 3}) {
                         with_keys = 0;
@@ -150,7 +151,7 @@ int main() {
 
 
 def test_every_lane_that_is_dealt_a_key_is_searched(tmp_path):
-    """A batch whose length is read on the device is dealt to the waves in sixteens, up to more keys than kpw to a wave; in sets
+    """A batch whose length is read on the device is dealt to the waves in sixteens (long rows: in fewer), up to more keys than kpw to a wave; in sets
     of 32 ways and more the probe leaves out the lanes behind those it is told of.  Deal and count are taken from the source."""
     with open(SRC) as f:
         s = f.read()
@@ -162,10 +163,45 @@ def test_every_lane_that_is_dealt_a_key_is_searched(tmp_path):
     lanes = re.search(r"const uint32_t %s\s*= (.*?);" % told, kernel)
     src = tmp_path / "dealt.cpp"
     src.write_text("#include <cstdint>\n#include <cstdio>\n#include <initializer_list>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
-                   + rule + DEALT % {"dealt": re.search(r"constexpr uint32_t kDealt = (\d+);", s)[1],
-                                     "lanes": lanes[1] if lanes else told,
+                   + rule + DEALT % {"lanes": lanes[1] if lanes else told,
                                      "position": re.search(r"if \(dealt\) b = (.*?);", kernel)[1]})
     exe = tmp_path / "dealt"
+    subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+WHOLE_DEALS = """
+int main() {
+    int dealt = 0;
+    for (bool checked : {false, true})
+        for (uint32_t d = 4; d <= 1024; d += 4)
+            for (uint64_t batch = 1; batch <= 7 * 64 * 256; batch += batch / 37 + 1) {     // batches of one round
+                const QueryShape q = query_shape(1, batch, d, 256, checked, false, 8, true);
+                if (q.deal == 0) continue;
+                ++dealt;
+                const uint64_t row = (uint64_t)d * 4, rows = (q.kpw + q.deal - 1) / q.deal * q.deal;
+                const bool power = (q.deal & (q.deal - 1)) == 0 && rows <= 64;
+                if (!power || q.deal * row > 16384 || (q.kpw * row <= 30000 && rows * row > (uint64_t)q.u * 1024)) {
+                    std::printf("d %u batch %llu: %u keys per wave in deals of %u, %d wave loads\\n", d, (unsigned long long)batch, q.kpw, q.deal, q.u);
+                    return 1;
+                }
+            }
+    return dealt ? 0 : 2;
+}
+"""
+
+
+def test_dealt_rows_are_one_group(tmp_path):
+    """Keys of a batch whose length is read on the device go to the waves in deals of up to 16 KiB of rows, and a wave's deals stay
+    within one group of wave loads where its keys do with room for a deal that is not full."""
+    with open(SRC) as f:
+        s = f.read()
+    rule = s[s.index("struct QueryShape {"):s.index("template <int W, int U, int WPB, bool kCoherent, int kD>\nvoid launch_query_kernel")]
+    src = tmp_path / "whole.cpp"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <initializer_list>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
+                   + rule + WHOLE_DEALS)
+    exe = tmp_path / "whole"
     subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
