@@ -1904,7 +1904,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // Keys per wave: 16 KiB of rows (64 rows of up to 256 bytes) while the batch fits the CUs that way, else up to 32 KiB, which is the
 // longest group.  Fewer and larger waves than would fill the chip: every tile adds to one counter word, ~11 ns each
 // one after the other (26,624 keys of 512 bytes 15 / 32 keys to a wave 8.4 / 7.5, of 256 bytes 15 / 64 8.1 / 6.9; 106,496 keys 60 / 64
-// 16.1 / 15.6).  Small batches are bound by the chain of round trips of a wave, to which its own rows add, and go down to 8 keys, for about 100 tiles.
+// 16.1 / 15.6).  Small batches are bound by the chain of round trips of a wave, to which its own rows add, and go down to 8 keys (16 from 4,096 keys on), for about
+// 100 tiles (4,907 keys plain 12 / 16 keys to a wave, of 512 bytes 4.8 / 4.6, of 128 bytes 4.6 / 4.4).
 // Beyond one round of tiles over the CUs the waves are trimmed such that the last round is full (106,496 keys of 1 KiB 64 / 32 to a wave 34.8 / 30);
 // with several tables the keys per wave go up as long as the tables' last, partly empty tiles would start another round (26 x 1,024 keys checked
 // 16.1 -> 11.2, 26 x 4,096 plain 20.9 -> 18.9).
@@ -1954,8 +1955,8 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
         if (coherent) k += k / 15;                             // (a few CUs without a tile are less than the tiles more; 425,984 keys plain 60 / 64 56.1 / 57.4)
         if (rounds == 1) {
-            uint64_t least = n < 4096 ? kMinKeysPerWave : 16;
-            if (!dedup) least = (5 * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);    // 2 / 5 cus tiles
+            uint64_t least = dedup ? kMinKeysPerWave : (5 * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);      // 2 / 5 cus tiles
+            if (n >= 4096 && (dedup || least < 16)) least = 16;
             if (least > some) least = some < 16 ? some : some - some % deal;
             if (least < kMinKeysPerWave) least = kMinKeysPerWave;
             if (k < least) k = least;

@@ -205,3 +205,33 @@ def test_dealt_rows_are_one_group(tmp_path):
     subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def run_rule(tmp_path, body):
+    """Compiles the rule of the launch shapes with a main of its own and runs it."""
+    with open(SRC) as f:
+        s = f.read()
+    rule = s[s.index("struct QueryShape {"):s.index("template <int W, int U, int WPB, bool kCoherent, int kD>\nvoid launch_query_kernel")]
+    src = tmp_path / "rule.cpp"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <initializer_list>\nconstexpr int kWave = 64;\nconstexpr uint32_t kMinKeysPerWave = 8;\n"
+                   + rule + body)
+    exe = tmp_path / "rule"
+    subprocess.run(["g++", "-O2", "-std=c++17", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def test_batches_of_4096_keys_and_more_have_16_to_a_wave(tmp_path):
+    """Every work-group adds to one counter word: with fewer keys to a wave there are more of them."""
+    run_rule(tmp_path, """
+int main() {
+    for (uint32_t ways : {1u, 8u, 64u})
+        for (uint32_t d = 4; d <= 256; d += 4)
+            for (uint64_t n = 4096; n < 30000; n += 97)
+                for (bool checked : {false, true}) {
+                    const uint32_t k = query_shape(1, n, d, 256, checked, false, ways).kpw;
+                    if (k < 16) { std::printf("ways %u d %u batch %llu: %u keys per wave\\n", ways, d, (unsigned long long)n, k); return 1; }
+                }
+    return 0;
+}
+""")
