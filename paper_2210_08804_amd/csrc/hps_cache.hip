@@ -1908,7 +1908,7 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // 100 tiles (4,907 keys plain 12 / 16 keys to a wave, of 512 bytes 4.8 / 4.6, of 128 bytes 4.6 / 4.4).
 // Beyond one round of tiles over the CUs the waves are trimmed such that the last round is full (106,496 keys of 1 KiB 64 / 32 to a wave 34.8 / 30);
 // with several tables the keys per wave go up as long as the tables' last, partly empty tiles would start another round (26 x 1,024 keys checked
-// 16.1 -> 11.2, 26 x 4,096 plain 20.9 -> 18.9).
+// 16.1 -> 11.2), and where they would with full waves too, the waves are trimmed for one round more (26 x 4,096 plain 18.5 -> 15.5, 7 x 16,384 18.5 -> 15.6; rows of more than 256 bytes: of shorter ones a CU holds several work-groups).
 //
 // Workers.  4 while that makes few tiles, 5 up to three quarters of the CUs, then 7 (5 / 7 / 8, 26,624 keys of 512 bytes 7.5 / 7.8 / 7.9;
 // 7 / 8, 106,496 keys 15.6 / 15.8, 425,984 keys 58.2 / 60.2, 106,496 of 1 KiB 29.9 / 30.7).  From 2^19 rows of up to 256 bytes on 11, one work-group per CU
@@ -1950,7 +1950,10 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     else if (n >= (n_dev ? 1u << 18 : 1u << 19) && d <= 64 && ways <= 16) q.wpb = d <= 8 && !coherent ? 15 : 11;
     else q.wpb = n <= 2 * some * cus ? 4 : 4 * n <= 15 * some * cus ? 5 : 7;      // up to cus / 2 and 3 / 4 cus tiles of that many keys per wave
     const uint64_t full = (uint64_t)q.wpb * most * cus;        // keys per round
-    const uint64_t rounds = n ? (n + full - 1) / full : 1;
+    uint64_t rounds = n ? (n + full - 1) / full : 1;
+    // a tile holds keys of one table: with several tables their last tiles are not full
+    auto tiles_of = [&](uint64_t keys) { return n_tables * ((batch + keys - 1) / keys); };
+    if (!dedup && d > 64 && q.wpb == 7 && rounds < 8 && tiles_of(7 * most) > rounds * cus) ++rounds;
     if (rounds <= 8) {
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
         if (coherent) k += k / 15;                             // (a few CUs without a tile are less than the tiles more; 425,984 keys plain 60 / 64 56.1 / 57.4)
@@ -1965,9 +1968,7 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
                 k = whole(k);
             }
         } else if (deal > 1) deal = 16;
-        // a tile holds keys of one table: with several tables their last tiles are not full
-        auto tiles = [&] { return n_tables * ((batch + q.wpb * k - 1) / (q.wpb * k)); };
-        while (n_tables > 1 && k < (q.wpb < 7 ? some : most) && tiles() > rounds * cus) ++k;
+        while (n_tables > 1 && k < (q.wpb < 7 ? some : most) && tiles_of(q.wpb * k) > rounds * cus) ++k;
         if (k < most) q.kpw = (uint32_t)k;
     }
     if (!dedup && q.kpw > most_rows(d)) q.kpw = (uint32_t)most_rows(d);

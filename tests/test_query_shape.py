@@ -235,3 +235,25 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_the_last_tiles_of_several_tables_do_not_start_a_round(tmp_path):
+    """Rows of more than 256 bytes: full tiles of several tables, the last of each not full, do not leave a few work-groups
+    to a round of their own."""
+    run_rule(tmp_path, """
+int main() {
+    for (uint32_t tables = 2; tables <= 32; ++tables)
+        for (uint32_t d : {68u, 128u, 320u, 512u})
+            for (uint64_t batch = 512; batch < 60000; batch += batch / 50)
+                for (bool checked : {false, true}) {
+                    const QueryShape q = query_shape(tables, batch, d, 256, checked, false);
+                    const uint64_t tiles = tables * ((batch + q.kpw * q.wpb - 1) / (q.kpw * q.wpb));
+                    const uint64_t most = 32768 / (d * 4) > 64 ? 64 : 32768 / (d * 4);
+                    if (tiles < 3 * 256 && tiles > 256 && tiles % 256 > 0 && tiles % 256 < 16 && q.kpw == most) {
+                        std::printf("%u tables d %u batch %llu: %llu tiles\\n", tables, d, (unsigned long long)batch, (unsigned long long)tiles);
+                        return 1;
+                    }
+                }
+    return 0;
+}
+""")
