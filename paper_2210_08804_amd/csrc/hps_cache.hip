@@ -1913,7 +1913,10 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // Workers.  4 while that makes few tiles, 5 up to three quarters of the CUs, then 7 (5 / 7 / 8, 26,624 keys of 512 bytes 7.5 / 7.8 / 7.9;
 // 7 / 8, 106,496 keys 15.6 / 15.8, 425,984 keys 58.2 / 60.2, 106,496 of 1 KiB 29.9 / 30.7).  From 2^19 rows of up to 256 bytes on 11, one work-group per CU
 // (7 / 11, checked: 851,968 rows of 256 bytes 72 / 67.5, of 128 bytes 44.5 / 43.1, of 64 bytes 32.8 / 32.2; at 425,984 rows of 128 bytes 23.3 / 23.5), plain of up to 32
-// bytes 15 (11 / 15, 3,407,872 of 16 bytes 74.6 / 68.0); sets of more than 16 ways not, whose keys spill there.
+// bytes 15 (11 / 15, 3,407,872 of 16 bytes 74.6 / 68.0); sets of more than 16 ways not, whose keys spill there.  Plain, short rows from where tiles of 7 x 64 keys
+// are more than the CUs: of up to 128 bytes 15 or 11, whichever takes fewer rounds, with 64 keys to a wave, since two or three work-groups fit a CU (7 trimmed / this way, 118,205 keys
+// of 128 bytes 11.3 / 8.3, 261,863 15.4 / 12.2, 475,504 22.5 / 19.1; of 64 bytes 389,757 18.7 / 13.6; 2 tables x 59,029 11.2 / 8.4), of up to 256 bytes 11 for one round (118,205 keys
+// 12.0 / 10.1).  A length on the device, rows of 512 bytes plain: 8 where that is one round and 7 are two (59,000 of 118,587 keys 12.4 / 9.6).
 //
 // Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
 // first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
@@ -1938,6 +1941,9 @@ uint64_t most_rows(uint32_t d) { return (1ull << 31) / (d / 4); }
 
 QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t cus, bool coherent, bool dedup, uint32_t ways = 8, bool n_dev = false) {
     const uint64_t n = n_tables * batch, row = (uint64_t)d * 4;
+    // a tile holds keys of one table: with several tables their last tiles are not full
+    auto tiles_of = [&](uint64_t keys) { return n_tables * ((batch + keys - 1) / keys); };
+    auto rounds_of = [&](uint64_t workers) { return (tiles_of(workers * kWave) + cus - 1) / cus; };     // with 64 keys to a wave
     auto rows_of = [&](uint64_t bytes) {                       // rows of a wave
         const uint64_t k = bytes / row;
         return k < kMinKeysPerWave ? (uint64_t)kMinKeysPerWave : k < (uint64_t)kWave ? k : (uint64_t)kWave;
@@ -1946,15 +1952,17 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     auto whole = [&](uint64_t k) { return (k + deal - 1) / deal * deal; };
     const uint64_t some = rows_of(16384), most = dedup || n_dev ? (uint64_t)kWave : rows_of(32768);
     QueryShape q{(uint32_t)most, 0, 0, 0};
+    const bool small = !dedup && d <= 64 && ways <= 16, many = small && n >= (n_dev ? 1u << 18 : 1u << 19);
+    const bool between = small && !many && !coherent && rounds_of(7) > 1 && (d <= 32 || rounds_of(11) == 1);
     if (dedup) q.wpb = n < (1u << 14) ? 4 : 8;
-    else if (n >= (n_dev ? 1u << 18 : 1u << 19) && d <= 64 && ways <= 16) q.wpb = d <= 8 && !coherent ? 15 : 11;
+    else if (many) q.wpb = d <= 8 && !coherent ? 15 : 11;
+    else if (between) q.wpb = d <= 32 && rounds_of(15) < rounds_of(11) ? 15 : 11;
+    else if (n_dev && !coherent && d == 128 && rounds_of(7) == 2 && rounds_of(8) == 1) q.wpb = 8;
     else q.wpb = n <= 2 * some * cus ? 4 : 4 * n <= 15 * some * cus ? 5 : 7;      // up to cus / 2 and 3 / 4 cus tiles of that many keys per wave
     const uint64_t full = (uint64_t)q.wpb * most * cus;        // keys per round
     uint64_t rounds = n ? (n + full - 1) / full : 1;
-    // a tile holds keys of one table: with several tables their last tiles are not full
-    auto tiles_of = [&](uint64_t keys) { return n_tables * ((batch + keys - 1) / keys); };
     if (!dedup && d > 64 && q.wpb == 7 && rounds < 8 && tiles_of(7 * most) > rounds * cus) ++rounds;
-    if (rounds <= 8) {
+    if (rounds <= 8 && !between) {
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
         if (coherent) k += k / 15;                             // (a few CUs without a tile are less than the tiles more; 425,984 keys plain 60 / 64 56.1 / 57.4)
         if (rounds == 1) {
@@ -1975,7 +1983,8 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     if (deal > 1 && (q.kpw >= 16 || q.kpw % deal == 0)) q.deal = (uint32_t)deal;
     const uint64_t bytes = (q.deal ? whole(q.kpw) : q.kpw) * row;      // a wave's rows
     if (d == 128 && q.wpb == 4 && q.kpw <= 8) q.u = 4;
-    else if (q.wpb == 11) q.u = d <= 16 ? 8 : 16;
+    else if (q.wpb == 11) q.u = d <= (between ? 32u : 16u) ? 8 : 16;
+    else if (q.wpb == 8 && !dedup) q.u = 32;
     else q.u = bytes <= 8192 && (d != 128 || q.wpb == 4) ? 8 : bytes <= 16384 ? 16 : 32;
     return q;
 }
@@ -2038,6 +2047,7 @@ hps_status_t launch_query_w(const QueryArgs &a, QueryShape q, bool coherent, boo
             case 11605: launch_query_kernel<W, 16, 5, false, 128>(a, full, st); break;
             case 11607: launch_query_kernel<W, 16, 7, false, 128>(a, full, st); break;
             case 13207: launch_query_kernel<W, 32, 7, false, 128>(a, full, st); break;
+            case 13208: launch_query_kernel<W, 32, 8, false, 128>(a, full, st); break;
             case 804: launch_query_kernel<W, 8, 4, false, 0>(a, full, st); break;
             case 1604: launch_query_kernel<W, 16, 4, false, 0>(a, full, st); break;
             case 3204: launch_query_kernel<W, 32, 4, false, 0>(a, full, st); break;

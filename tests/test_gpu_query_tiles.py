@@ -64,7 +64,8 @@ def test_length_on_the_device_at_the_edges_of_the_deal(d, n_max, policy, checked
 @pytest.mark.parametrize("d,n", [
     (128, 1), (128, 3264), (128, 3265), (128, 16384), (128, 16385), (128, 30720), (128, 30721), (128, 57344), (128, 57345),
     (512, 4096), (512, 4097), (512, 7681), (512, 28673), (4, 1 << 19), (16, (1 << 19) - 1), (16, (1 << 19) + 705), (32, (1 << 19) + 1), (64, 1 << 19),
-    (68, 1 << 19), (1024, 2049)])
+    (68, 1 << 19), (1024, 2049),
+    (32, 114689), (32, 180225), (16, 245761), (32, 360449), (32, 491521), (64, 114689), (64, 180225)])
 def test_batches_where_the_launch_shape_changes(d, n, checked):
     gc, oc = filled(d)
     with gc:
@@ -81,11 +82,11 @@ def test_batches_where_the_launch_shape_changes(d, n, checked):
 
 
 @pytest.mark.parametrize("checked", [True, False])
-@pytest.mark.parametrize("n_max", [8000, 9000, 40000, 90000, 130000, 200000])
+@pytest.mark.parametrize("n_max", [8000, 9000, 40000, 90000, 120000, 130000, 200000])
 @pytest.mark.parametrize("ways", [4, 32, 64])
 def test_dealt_keys_are_searched_in_sets_of_every_width(ways, n_max, checked):
     """Keys per wave that are no multiple of sixteen: its last lanes get theirs by the deal alone.  (512-byte rows, 256 CUs, plain / default
-    mode: 20 / 21, 22 / 23, 32, 51 / 54, 37 / 39 and 56 / 59 keys per wave.)"""
+    mode: 20 / 21, 22 / 23, 32, 51 / 54, 59 (8 workers) / 36, 37 / 39 and 56 / 59 keys per wave.)"""
     d = 128
     # No set gets more of the keys than it has ways, so which of them are cached does not hang on the order within an insert
     # (4 ways over 8,192 sets: some do; over 2^17 sets, which would have 0.05 keys each, five in one are 2e-9 x 2^17 sets).

@@ -11,13 +11,15 @@ MAIN = """
 int main() {
     for (uint64_t cus : {256ull, 128ull, 38ull, 32ull, 1ull})
         for (uint32_t t : {1u, 3u, 26u, 32u})
-            for (int mode = 0; mode < 3; ++mode)                       // plain, checked, in-tile dedup
+            for (int form = 0; form < 9; ++form)
                 for (uint32_t d = 4; d <= 2048; d += d < 160 ? 4 : d / 8 / 4 * 4)
-                    for (double x = 0; x < 32; x += 0.1)
+                    for (double x = 0; x < 32; x += 0.15)
                         for (int o = -1; o < 2; ++o) {
                             const uint64_t batch = (uint64_t)(__builtin_exp2(x) / t) + 1 + o;
-                            if (batch * t >= (1ull << 32) || (mode == 1 && d > 1024)) continue;
-                            const QueryShape q = query_shape(t, batch, d, cus, mode == 1, mode == 2);
+                            const int mode = form % 3;                             // plain, checked, in-tile dedup
+                            const bool n_dev = form >= 6;
+                            if (batch * t >= (1ull << 32) || (mode == 1 && d > 1024) || (n_dev && t > 1)) continue;
+                            const QueryShape q = query_shape(t, batch, d, cus, mode == 1, mode == 2, form / 3 == 1 ? 32 : 8, n_dev);
                             const int id = (d == 128 ? 10000 : 0) + q.u * 100 + q.wpb;
                             if (q.kpw < 1 || q.kpw > 64) { std::printf("kpw %u\\n", q.kpw); return 1; }
                             if (mode == 2 ? (q.wpb != 4 && q.wpb != 8) : !kShapes[mode].count(id)) {
@@ -254,6 +256,29 @@ int main() {
                         return 1;
                     }
                 }
+    return 0;
+}
+""")
+
+
+def test_short_rows_are_not_spread_over_more_work_groups_than_they_fill(tmp_path):
+    """Plain, rows of up to 128 bytes from where work-groups of 7 x 64 keys are more than the CUs: no more of them than full ones of 8
+    workers would be; of up to 256 bytes: one round while 8 workers need no more."""
+    run_rule(tmp_path, """
+int main() {
+    for (uint32_t ways : {1u, 8u, 16u})
+        for (uint32_t tables : {1u, 2u, 13u, 26u})
+            for (uint32_t d = 4; d <= 64; d += 4)
+                for (bool n_dev : {false, true})
+                    for (uint64_t batch = 114689 / tables + 1; batch * tables < (n_dev ? 1u << 18 : 1u << 19); batch += batch / 61 + 1) {
+                        if (n_dev && tables > 1) continue;
+                        const QueryShape q = query_shape(tables, batch, d, 256, false, false, ways, n_dev);
+                        const uint64_t tiles = tables * ((batch + q.kpw * q.wpb - 1) / (q.kpw * q.wpb)), of8 = tables * ((batch + 511) / 512);
+                        if (d <= 32 ? tiles > of8 : of8 <= 256 && tiles > 256) {
+                            std::printf("ways %u tables %u d %u batch %llu: %llu work-groups\\n", ways, tables, d, (unsigned long long)batch, (unsigned long long)tiles);
+                            return 1;
+                        }
+                    }
     return 0;
 }
 """)
