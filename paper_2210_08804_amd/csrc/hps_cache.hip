@@ -1918,6 +1918,9 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // of 128 bytes 11.3 / 8.3, 261,863 15.4 / 12.2, 475,504 22.5 / 19.1; of 64 bytes 389,757 18.7 / 13.6; 2 tables x 59,029 11.2 / 8.4), of up to 256 bytes 11 for one round (118,205 keys
 // 12.0 / 10.1).  A length on the device, rows of 512 bytes plain: 8 where that is one round and 7 are two (59,000 of 118,587 keys 12.4 / 9.6).
 //
+// Sets of 32 and 64 ways: a wave reads them for 16 or 8 lanes at a time, a wave load for two keys or one, so its keys are whole 16s or 8s while the batch fits the CUs, of 64 ways
+// 24 at most, and half the CUs get a tile (20,214 keys of 128 bytes plain, 32 ways 49 / 32 keys to a wave 7.3 / 6.4, 64 ways 49 / 24 9.6 / 7.5; 8,192 of 512 bytes, 32 ways 20 / 16 6.0 / 5.6).
+//
 // Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
 // first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
 // hold, and its code, all of it executed, lines that a short launch has to fetch (13,312 keys of 512 bytes in groups of 16 / 32
@@ -1950,13 +1953,16 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     };
     uint64_t deal = !n_dev || dedup ? 1 : deal_of(d);
     auto whole = [&](uint64_t k) { return (k + deal - 1) / deal * deal; };
-    const uint64_t some = rows_of(16384), most = dedup || n_dev ? (uint64_t)kWave : rows_of(32768);
+    const uint64_t block = ways > 16 && !dedup ? 512 / ways : 1;       // lanes that the probe searches or leaves out together
+    uint64_t some = rows_of(16384);
+    if (block == 8 && some > 24) some = 24;
+    const uint64_t most = dedup || n_dev ? (uint64_t)kWave : rows_of(32768);
     QueryShape q{(uint32_t)most, 0, 0, 0};
-    const bool small = !dedup && d <= 64 && ways <= 16, many = small && n >= (n_dev ? 1u << 18 : 1u << 19);
-    const bool between = small && !many && !coherent && rounds_of(7) > 1 && (d <= 32 || rounds_of(11) == 1);
+    const bool small = !dedup && d <= 64, many = small && ways <= 16 && n >= (n_dev ? 1u << 18 : 1u << 19);
+    const bool between = small && !many && !coherent && rounds_of(7) > 1 && (ways > 16 ? ways == 32 && rounds_of(7) == 2 : d <= 32 || rounds_of(11) == 1);
     if (dedup) q.wpb = n < (1u << 14) ? 4 : 8;
     else if (many) q.wpb = d <= 8 && !coherent ? 15 : 11;
-    else if (between) q.wpb = d <= 32 && rounds_of(15) < rounds_of(11) ? 15 : 11;
+    else if (between) q.wpb = ways > 16 ? 7 : d <= 32 && rounds_of(15) < rounds_of(11) ? 15 : 11;
     else if (n_dev && !coherent && d == 128 && rounds_of(7) == 2 && rounds_of(8) == 1) q.wpb = 8;
     else q.wpb = n <= 2 * some * cus ? 4 : 4 * n <= 15 * some * cus ? 5 : 7;      // up to cus / 2 and 3 / 4 cus tiles of that many keys per wave
     const uint64_t full = (uint64_t)q.wpb * most * cus;        // keys per round
@@ -1966,11 +1972,13 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
         if (coherent) k += k / 15;                             // (a few CUs without a tile are less than the tiles more; 425,984 keys plain 60 / 64 56.1 / 57.4)
         if (rounds == 1) {
-            uint64_t least = dedup ? kMinKeysPerWave : (5 * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);      // 2 / 5 cus tiles
+            uint64_t least = dedup ? kMinKeysPerWave : ((block > 1 ? 4 : 5) * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);      // 1 / 2 or 2 / 5 cus tiles
             if (n >= 4096 && (dedup || least < 16)) least = 16;
             if (least > some) least = some < 16 ? some : some - some % deal;
             if (least < kMinKeysPerWave) least = kMinKeysPerWave;
+            if (least > block) least = (least + block / 2) / block * block;
             if (k < least) k = least;
+            if (block == 8) k = (k + 7) / 8 * 8;
             if (row > 512 && k > least) {
                 if (deal > 8 && whole(k) * row > 32768) deal = 8;
                 k = whole(k);

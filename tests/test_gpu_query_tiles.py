@@ -86,7 +86,8 @@ def test_batches_where_the_launch_shape_changes(d, n, checked):
 @pytest.mark.parametrize("ways", [4, 32, 64])
 def test_dealt_keys_are_searched_in_sets_of_every_width(ways, n_max, checked):
     """Keys per wave that are no multiple of sixteen: its last lanes get theirs by the deal alone.  (512-byte rows, 256 CUs, plain / default
-    mode: 20 / 21, 22 / 23, 32, 51 / 54, 59 (8 workers) / 36, 37 / 39 and 56 / 59 keys per wave.)"""
+    mode: 20, 22, 32, 51 / 54, 59 (8 workers) / 36, 37 / 39 and 56 / 59 keys per wave;
+    of 64 ways 16, 16, 24, 56, 59 / 36, 37 / 39 and 56 / 59.)"""
     d = 128
     # No set gets more of the keys than it has ways, so which of them are cached does not hang on the order within an insert
     # (4 ways over 8,192 sets: some do; over 2^17 sets, which would have 0.05 keys each, five in one are 2e-9 x 2^17 sets).

@@ -282,3 +282,21 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_waves_do_not_search_wide_sets_for_nobody(tmp_path):
+    """Sets of 32 and 64 ways are searched for 16 and 8 lanes at a time: while a batch fits the CUs that way, its waves have whole
+    16s and whole 8s of keys, of 64 ways no more than 24."""
+    run_rule(tmp_path, """
+int main() {
+    for (uint32_t ways : {32u, 64u})
+        for (uint32_t d = 4; d <= 128; d += 4)
+            for (uint64_t n = 4096; n <= (ways == 32 ? 16 * 7 * 256 : 24 * 7 * 256); n += 113)
+                for (bool checked : {false, true}) {
+                    const uint32_t k = query_shape(1, n, d, 256, checked, false, ways).kpw;
+                    if (k % (ways == 32 ? 16 : 8) && !(checked && ways == 32 && n > 15 * 7 * 256)) { std::printf("ways %u d %u batch %llu: %u keys per wave\\n", ways, d, (unsigned long long)n, k); return 1; }
+                    if (ways == 64 && k > (checked ? 32 : 24)) { std::printf("64 ways d %u batch %llu: %u keys per wave\\n", d, (unsigned long long)n, k); return 1; }
+                }
+    return 0;
+}
+""")
