@@ -1429,7 +1429,6 @@ __global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBl
     float *const V = in->V;
     const RowGeom g = {in->g.d, in->g.C, in->g.LPR, in->g.lprShift, in->g.passes, {in->g.c16.C, in->g.c16.packed}, {in->g.c8.C, in->g.c8.packed}};
     uint32_t *const pair = epoch_of(global_at<uint32_t>(epochs), wg);
-    const uint64_t le_lane = lane == 63 ? ~0ull : ((2ull << lane) - 1);     // bits 0..lane
     writer_enter(pair, &s_group);
     __syncthreads();
     bool told = wave != 0;                                  // only wave 0 has something to tell
@@ -1449,6 +1448,9 @@ __global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBl
         const int prev_pend = __shfl_up((int)pending, 1, kWave);
         const bool start = pending && (lane == 0 || !prev_pend || prev_set != set);
         const uint64_t startmask = __ballot(start);
+        int here = lane;
+        asm volatile("" : "+v"(here));                           // made here, not kept in registers beside the rows
+        const uint64_t le_lane = ~0ull >> (63 - here);           // bits 0..lane
         const int leader = pending ? 63 - __builtin_clzll(startmask & le_lane) : lane;
         const uint64_t le_leader = leader == 63 ? ~0ull : ((2ull << leader) - 1);
         const uint64_t above = startmask & ~le_leader;
@@ -1512,8 +1514,10 @@ __global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBl
             writer_entered(&s_group);
             if (act) {
                 const int r = rank_in(actmask);
+                uint32_t at = first;
+                asm volatile("" : "+s"(at));                     // i, made again for the same reason
                 s_dst[wave][r] = (uint64_t)set * W + (uint32_t)way;
-                s_srcrow[wave][r] = i;
+                s_srcrow[wave][r] = at + (uint32_t)lane;
             }
             wave_lds_fence();
             copy_rows_shared<(kLong ? 8 : 4), kLong>(g, vals, V, &s_srcrow[wave][0], &s_dst[wave][0], (uint32_t)__popcll(actmask));
