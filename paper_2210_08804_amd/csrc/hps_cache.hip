@@ -1431,6 +1431,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(4, 4))) __launch_bounds__(kBl
     uint32_t *const pair = epoch_of(global_at<uint32_t>(epochs), wg);
     writer_enter(pair, &s_group);
     __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);                      // (nobody waits in front of it for keys, with wave 0 also for its count)
     bool told = wave != 0;                                  // only wave 0 has something to tell
 
     bool pending = !is_reserved(key);

@@ -64,3 +64,18 @@ def test_updates_keep_their_registers_out_of_memory(metadata, W, kpw, lng):
     assert len(mine) == 1
     assert re.search(r"\.vgpr_spill_count:\s*(\d+)", mine[0])[1] == "0"
     assert re.search(r"\.private_segment_fixed_size:\s*(\d+)", mine[0])[1] == "0"
+
+
+@pytest.mark.parametrize("lng", [0, 1])
+@pytest.mark.parametrize("kpw", [16, 64])
+@pytest.mark.parametrize("W", [2, 8, 64])
+def test_updates_do_not_wait_for_keys_in_front_of_their_barrier(metadata, objects, W, kpw, lng):
+    """A wait for the keys there is for wave 0 also one for its count of the work-group, and the others wait for wave 0.  (What the
+    kernels do in front of the barrier is the same for all sets; three widths are looked at.)"""
+    name, = [k for k in metadata if f"update_kernelILi{W}ELi{kpw}ELb{lng}E" in k and not k.endswith(".kd")]
+    for f in objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", f"--disassemble-symbols={name}", f], check=True, capture_output=True, text=True).stdout
+        if "s_barrier" in text:
+            assert "vmcnt" not in text[:text.index("s_barrier")]
+            return
+    raise AssertionError(f"no object has {name}")
