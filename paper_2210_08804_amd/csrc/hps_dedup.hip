@@ -280,11 +280,12 @@ hps_status_t check_session(hps_dedup_session *s) {
 // Keys per work-group: 1024; 512 for batches that would leave most CUs without a work-group, whose lanes then share
 // LDS slots with half as many others (kernel times: 2,000 keys 7.7 -> 6.7 us, 16,000 9.1 -> 7.3, 32,000 9.3 -> 8.1, 65,000 equal).
 //
-// Work-groups: one per tile.  What the previous call has used of the other table is wiped by further ones while the tiles leave CUs free
-// for them (up to kBeside keys), off the tiles' chain of round trips: 106,496 keys, 38,600 distinct, 11.9 -> 11.2 us.  Beyond, the tiles wipe when
-// they are done (425,984 keys, none twice, 38.5 us; further work-groups beside them 40.4), and more work-groups if those would have to wipe more than
-// kWipe slots per thread (300 keys behind a call of 2^20: 284 us by its one tile, 12 this way).
-constexpr uint32_t kWipe = 8, kWipeBehind = 4, kBeside = 1u << 18;
+// Work-groups: one per tile.  What the previous call has used of the other table is wiped by further ones while the tiles leave an eighth of the CUs
+// free for them (up to kBeside keys), off the tiles' chain of round trips: 106,496 keys, 38,600 distinct, 11.9 -> 11.2 us.  Beyond, the tiles wipe when
+// they are done (425,984 keys, none twice, 38.5 us; further work-groups beside them 40.4; 240,000 to 262,000 keys, a tenth distinct, 20.9 / 23.7, 44 % distinct 23.2 / 25.2, none
+// twice 21.6 / 21.1, but 44 % of 200,000 to 229,000 19.7 / 18.4), and more work-groups if those would have to wipe more than
+// kWipeBehind slots per thread (300 keys behind a call of 2^20: 284 us by its one tile, 12 this way).
+constexpr uint32_t kWipe = 8, kWipeBehind = 4, kBeside = 7u << 15;
 
 template <bool kMissed = false>
 void launch_dedup(const int64_t *keys, uint32_t n, int64_t *tkey, uint32_t *tuid, uint32_t mask, uint64_t *counter, hipStream_t st, DedupArgs a) {
