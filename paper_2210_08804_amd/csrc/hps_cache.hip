@@ -1936,13 +1936,14 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 //
 // A length on the device: `deal` neighbouring keys go to a wave at a time, sixteen (a line of the batch; 50,000 of 106,496 keys in fours / sixteens 16.2 / 12.3,
 // 47,000 9.3 / 8.9) or as many as have 16 KiB of rows, since sixteen more or less are what one wave has more than another (sixteens / this way,
-// 33,000 of 41,033 keys of 4 KiB 38.1 / 33.1, of 2 KiB 21.2 / 19.3) or all that a wave has (820 of 4 KiB 12.7 / 6.0).  A wave's keys are whole deals, so that they
+// 33,000 of 41,033 keys of 4 KiB 38.1 / 33.1, of 2 KiB 21.2 / 19.3) or all that a wave has (820 of 4 KiB 12.7 / 6.0).  Of rows of 2 KiB and more a deal has 8 KiB: a wave with two of
+// 16 KiB beside one with three waits for it (16 / 8 KiB, 22,937 of 32,768 keys of 2 KiB 18.7 / 16.4, 11,468 of 16,384 of 4 KiB 18.4 / 16.2; a fifth of them 8.0 / 8.8).  A wave's keys are whole deals, so that they
 // stay one group of rows (19,000 of 24,137 keys of 768 bytes plain, 21 keys to a wave 9.2, 16 7.6).  Over several rounds sixteens are the faster ones
 // again (24,000 of 118,587 keys of 1,280 bytes plain in eights / sixteens 12.6 / 9.8).
 struct QueryShape { uint32_t kpw; int u, wpb; uint32_t deal; };
 uint32_t deal_of(uint32_t d) {
     uint32_t k = 16;
-    while (k > 1 && (uint64_t)k * d * 4 > 16384) k >>= 1;
+    while (k > 1 && (uint64_t)k * d * 4 > (d < 512 || k == 2 ? 16384 : 8192)) k >>= 1;
     return k;
 }
 

@@ -33,7 +33,7 @@ def expected(oc, keys, d):
 @pytest.mark.parametrize("checked", [True, False])
 @pytest.mark.parametrize("policy", [0, 1])
 @pytest.mark.parametrize("d,n_max", [(128, 26624), (32, 7000),      # dealt in sixteens, 32 and 18 keys to a wave
-                                     (192, 9000), (320, 30000), (1024, 3000), (512, 20000),   # in 16s, 8s, 4s and 8s, whole ones
+                                     (192, 9000), (320, 30000), (1024, 3000), (512, 20000),   # in 16s, 8s, 2s and 4s, whole ones
                                      (128, 5000), (320, 9000)])      # not dealt: 13 and 12 neighbouring keys to a wave
 def test_length_on_the_device_at_the_edges_of_the_deal(d, n_max, policy, checked):
     gc, oc = filled(d, policy)
