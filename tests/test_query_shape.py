@@ -13,7 +13,7 @@ int main() {
         for (uint32_t t : {1u, 3u, 26u, 32u})
             for (int form = 0; form < 9; ++form)
                 for (uint32_t d = 4; d <= 2048; d += d < 160 ? 4 : d / 8 / 4 * 4)
-                    for (double x = 0; x < 32; x += 0.15)
+                    for (double x = 0; x < 32; x += 0.1)
                         for (int o = -1; o < 2; ++o) {
                             const uint64_t batch = (uint64_t)(__builtin_exp2(x) / t) + 1 + o;
                             const int mode = form % 3;                             // plain, checked, in-tile dedup
