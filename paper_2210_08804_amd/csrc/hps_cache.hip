@@ -801,8 +801,9 @@ __device__ __forceinline__ void finish_call(uint32_t *n_miss, uint64_t *slot, ui
 // address, one after the other, and hold up what else goes to that channel, which a wave waits for while it reads rows and
 // nobody does while they are written (told as soon as the misses were known: 39,999 keys of 1,280 bytes plain 18.6 us, this way 15.7; 106,496 of
 // 512 bytes 17.3, 16.3; 26 tables 214, 208).  Where a wave has little to read, or few tiles meet, nothing waits for the atomics but the end of the call: plain waves of up to
-// 8 KiB of rows (16 KiB in up to 192 tiles of 512-byte rows) tell at once.  (Behind the loads / at once, us: 2 tables x 858 keys of 128 bytes 4.1 / 3.8, 4,907 keys of 512 bytes 4.6 / 4.2,
-// 118,205 keys of 128 bytes 8.3 / 7.3; but 64 keys of 256 bytes to a wave, 30,926 keys of 1 KiB 1.17 times as long.)
+// 8 KiB of rows (12 KiB in up to 192 tiles of 512-byte rows) tell at once.  (Behind the loads / at once, us: 2 tables x 858 keys of 128 bytes 4.1 / 3.8, 4,907 keys of 512 bytes 4.6 / 4.2,
+// 118,205 keys of 128 bytes 8.3 / 7.3; but 64 keys of 256 bytes to a wave, 30,926 keys of 1 KiB 1.17 times as long.  Rows that come from 8 GiB of memory, 512 bytes: 6,656 keys, 17 to a wave, 6.0 / 5.5,
+// 9,620, 24 to a wave, 6.3 / 6.3, 13,312, 32 to a wave, 6.8 / 7.2, 26,624 7.8 / 8.7, 39,936 8.8 / 10.4.)
 // One tile to a work-group, and no loop over tiles around it: what a loop keeps in registers from one tile to the next took up to 100 more of
 // them, and as long before the first load (registers plain / checked, 512-byte rows in groups of 32: 221 / 237 with the loop, 138 / 151 without,
 // 128-byte rows checked 103, 62).  The first 14 words of the arguments arrive in registers (-amdgpu-kernarg-preload-count), so that a
@@ -981,7 +982,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
         }
         stamp(hit, way);
         wave_lds_fence();
-        const bool early = n_tiles <= 192 ? U <= (kD ? 16 : 8) : U <= 8 && W <= 16;
+        const bool early = n_tiles <= 192 ? U <= 8 || (kD && U <= 16 && kpw <= 24) : U <= 8 && W <= 16;
         if (early || !nh) tell();
         if (nh) copy_rows<U, kD>(g, V, out, &s_src[wave][0], &s_dst[wave][0], nh, [&] { if (!early) tell(); });
     } else {
