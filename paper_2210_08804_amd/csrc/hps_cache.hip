@@ -1925,7 +1925,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // bytes 15 (11 / 15, 3,407,872 of 16 bytes 74.6 / 68.0); sets of more than 16 ways not, whose keys spill there.  Plain, short rows from where tiles of 7 x 64 keys
 // are more than the CUs: of up to 128 bytes 15 or 11, whichever takes fewer rounds, with 64 keys to a wave, since two or three work-groups fit a CU (7 trimmed / this way, 118,205 keys
 // of 128 bytes 11.3 / 8.3, 261,863 15.4 / 12.2, 475,504 22.5 / 19.1; of 64 bytes 389,757 18.7 / 13.6; 2 tables x 59,029 11.2 / 8.4), of up to 256 bytes 11 for one round (118,205 keys
-// 12.0 / 10.1).  A length on the device, rows of 512 bytes plain: 8 where that is one round and 7 are two (59,000 of 118,587 keys 12.4 / 9.6).
+// 12.0 / 10.1).  Over several rounds their waves are trimmed as well, to 48 keys at least (64 / trimmed, rows of 128 bytes that come from 2 GiB of memory: 286,000 keys 17.2 / 16.3, 364,000 21.5 / 19.3, 425,984 22.8 / 21.7,
+// from the caches 370,000 20.2 / 20.0).  A length on the device, rows of 512 bytes plain: 8 where that is one round and 7 are two (59,000 of 118,587 keys 12.4 / 9.6).
 //
 // Sets of 32 and 64 ways: a wave reads them for 16 or 8 lanes at a time, a wave load for two keys or one, so its keys are whole 16s or 8s while the batch fits the CUs, of 64 ways
 // 24 at most, and half the CUs get a tile (20,214 keys of 128 bytes plain, 32 ways 49 / 32 keys to a wave 7.3 / 6.4, 64 ways 49 / 24 9.6 / 7.5; 8,192 of 512 bytes, 32 ways 20 / 16 6.0 / 5.6).
@@ -1978,8 +1979,9 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     const uint64_t full = (uint64_t)q.wpb * most * cus;        // keys per round
     uint64_t rounds = n ? (n + full - 1) / full : 1;
     if (!dedup && d > 64 && q.wpb == 7 && rounds < 8 && tiles_of(7 * most) > rounds * cus) ++rounds;
-    if (rounds <= 8 && !between) {
+    if (rounds <= 8 && (!between || (rounds > 1 && ways <= 16))) {
         uint64_t k = (n + q.wpb * cus * rounds - 1) / (q.wpb * cus * rounds);
+        if (between && k < 48) k = 48;
         if (coherent) k += k / 15;                             // (a few CUs without a tile are less than the tiles more; 425,984 keys plain 60 / 64 56.1 / 57.4)
         if (rounds == 1) {
             uint64_t least = dedup ? kMinKeysPerWave : ((block > 1 ? 4 : 5) * n + 2 * q.wpb * cus - 1) / (2 * q.wpb * cus);      // 1 / 2 or 2 / 5 cus tiles

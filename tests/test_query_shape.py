@@ -322,3 +322,26 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_short_rows_fill_their_last_round(tmp_path):
+    """Plain, rows of up to 128 bytes, 11 or 15 workers: where full waves would leave the last of several rounds less than two thirds full, the waves
+    are trimmed to fill three quarters of it."""
+    run_rule(tmp_path, """
+int main() {
+    int trimmed = 0;
+    for (uint32_t ways : {1u, 8u, 16u})
+        for (uint32_t d = 4; d <= 32; d += 4)
+            for (uint64_t n = 114689; n < 1u << 19; n += 997) {
+                const QueryShape q = query_shape(1, n, d, 256, false, false, ways);
+                const uint64_t full = (n + 64 * q.wpb - 1) / (64 * q.wpb), tiles = (n + q.kpw * q.wpb - 1) / (q.kpw * q.wpb);
+                if (full <= 256 || full % 256 == 0 || full % 256 > 170) continue;
+                ++trimmed;
+                if (tiles % 256 && tiles % 256 < 192) {
+                    std::printf("ways %u d %u batch %llu: %llu work-groups, %llu with full waves\\n", ways, d, (unsigned long long)n, (unsigned long long)tiles, (unsigned long long)full);
+                    return 1;
+                }
+            }
+    return trimmed ? 0 : 2;
+}
+""")
