@@ -193,7 +193,7 @@ def test_waves_without_keys_look_for_nothing():
 
 
 def test_a_wide_set_is_read_for_the_keys_of_a_wave_only():
-    """40,000 keys, 23 to a wave, default mode.  (64 ways over 8: 1.25; 2.15 with the loads of lanes
+    """40,000 keys, 24 to a wave, default mode.  (64 ways over 8: 1.25; 1.9 with the loads of lanes
     without keys.)"""
     n, d, times = 40000, 128, {}
     keys = torch.randint(0, 1 << 16, (n,), device="cuda")
@@ -354,3 +354,29 @@ def test_rows_from_a_large_cache_are_not_held_up_by_the_count():
         torch.cuda.synchronize()
         B.hps_cache_destroy(h)
     assert plain < 1.10 * default, f"us of 40 calls: plain {plain:.1f}, default {default:.1f}"
+
+
+@pytest.mark.parametrize("n", [20000, 40000])
+def test_a_wide_set_is_read_for_no_more_lanes_than_have_keys(n):
+    """24 keys to a wave, default mode, 8 ways against 64.  (64 ways over 8: 1.28 and 1.25; 1.67 and 1.75-1.9 with the loads of
+    lanes without keys.)"""
+    d, times = 128, {}
+    keys = torch.randint(0, 1 << 16, (n,), device="cuda")
+    out = torch.empty(n, d, device="cuda")
+    mi, mk = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int64, device="cuda")
+    nm = torch.zeros(1, dtype=torch.int32, device="cuda")
+    busy = torch.empty(1 << 26, device="cuda")
+    for W in (8, 64):
+        h = B.hps_cache_create(1 << 17, W, d)
+
+        def calls():
+            for _ in range(20):
+                B.hps_cache_query(h, keys, n, out, mi, mk, nm)
+
+        try:
+            B.hps_cache_insert(h, torch.arange(1 << 16, device="cuda"), torch.zeros(1 << 16, d, device="cuda"), 1 << 16)
+            times[W], = _median_us([calls], lambda: [busy.fill_(0.0) for _ in range(4)])
+        finally:
+            torch.cuda.synchronize()
+            B.hps_cache_destroy(h)
+    assert times[64] < 1.45 * times[8], f"us of 20 calls by ways: {times}"
