@@ -1929,7 +1929,8 @@ uint64_t *counter_word(hps_cache *c, void *stream) {
 // from the caches 370,000 20.2 / 20.0).  A length on the device, rows of 512 bytes plain: 8 where that is one round and 7 are two (59,000 of 118,587 keys 12.4 / 9.6).
 //
 // Sets of 32 and 64 ways: a wave reads them for 16 or 8 lanes at a time, a wave load for two keys or one, so its keys are whole 16s or 8s while the batch fits the CUs, of 64 ways
-// 24 at most, and half the CUs get a tile (20,214 keys of 128 bytes plain, 32 ways 49 / 32 keys to a wave 7.3 / 6.4, 64 ways 49 / 24 9.6 / 7.5; 8,192 of 512 bytes, 32 ways 20 / 16 6.0 / 5.6).
+// 24 at most, and half the CUs get a tile (20,214 keys of 128 bytes plain, 32 ways 49 / 32 keys to a wave 7.3 / 6.4, 64 ways 49 / 24 9.6 / 7.5; 8,192 of 512 bytes, 32 ways 20 / 16 6.0 / 5.6).  Not more than 16 KiB of rows
+// for it (6 tables x 4,481 keys of 400 bytes, 32 ways 48 / 32 11.3 / 9.8), and rows of more than 1 KiB as in other sets (16,282 keys of 2 KiB, 64 ways 16 / 10 15.5 / 13.2).
 //
 // Group size: a wave's whole share of rows in one group (a second group waits, with its own loads, for the
 // first group's stores), and not much more: the registers of a larger group are waves that the CU cannot
@@ -1964,7 +1965,7 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
     };
     uint64_t deal = !n_dev || dedup ? 1 : deal_of(d);
     auto whole = [&](uint64_t k) { return (k + deal - 1) / deal * deal; };
-    const uint64_t block = ways > 16 && !dedup ? 512 / ways : 1;       // lanes that the probe searches or leaves out together
+    const uint64_t block = ways > 16 && !dedup && d <= 256 ? 512 / ways : 1;       // lanes that the probe searches or leaves out together
     uint64_t some = rows_of(16384);
     if (block == 8 && some > 24) some = 24;
     const uint64_t most = dedup || n_dev ? (uint64_t)kWave : rows_of(32768);
@@ -1988,7 +1989,10 @@ QueryShape query_shape(uint32_t n_tables, uint64_t batch, uint32_t d, uint64_t c
             if (n >= 4096 && (dedup || least < 16)) least = 16;
             if (least > some) least = some < 16 ? some : some - some % deal;
             if (least < kMinKeysPerWave) least = kMinKeysPerWave;
-            if (least > block) least = (least + block / 2) / block * block;
+            if (least > block) {
+                least = (least + block / 2) / block * block;
+                if (least > some && some >= block) least = some - some % block;
+            }
             if (k < least) k = least;
             if (block == 8) k = (k + 7) / 8 * 8;
             if (row > 512 && k > least) {

@@ -345,3 +345,23 @@ int main() {
     return trimmed ? 0 : 2;
 }
 """)
+
+
+def test_wide_sets_do_not_make_waves_of_long_rows_longer(tmp_path):
+    """Whole blocks of keys take a wave no further than 16 KiB of rows, and rows of more than 1 KiB are moved as in other sets."""
+    run_rule(tmp_path, """
+int main() {
+    for (uint32_t ways : {32u, 64u})
+        for (uint32_t d = 64; d <= 1024; d += 4)
+            for (bool checked : {false, true})
+                for (uint64_t n = 4096; n < 60000; n += 331) {
+                    const uint32_t k = query_shape(1, n, d, 256, checked, false, ways).kpw, other = query_shape(1, n, d, 256, checked, false, 8).kpw;
+                    const uint64_t some = 16384 / (d * 4);
+                    if (d > 256 ? k != other : n < 2 * some * 256 && some >= 512 / ways && k > some) {
+                        std::printf("%u ways d %u batch %llu: %u keys per wave, 8 ways %u\\n", ways, d, (unsigned long long)n, k, other);
+                        return 1;
+                    }
+                }
+    return 0;
+}
+""")
