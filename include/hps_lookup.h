@@ -55,7 +55,9 @@ hps_status_t hps_lookup_create(hps_cache_t *cache, size_t max_batch, float hit_t
  * precision (a deliberate reading of the hit-rate step of Alg. 1, whose divisor is declared as the
  * capacity of the cache).  On return every row of out is either its key's cached row, its fetched
  * row (synchronous mode) or the default row (asynchronous mode), in stream order: the call
- * synchronises the host with `stream` once, to read the miss count, as Alg. 1 needs it.
+ * synchronises the host with `stream` to read the miss count, as Alg. 1 needs it; where that leads to
+ * synchronous insertion, also for the distinct keys, if they did not come with the count, and at the
+ * end, because the next call uses the same workspace.
  * *hit_rate [host] and *was_synchronous [host] may be NULL.  A stream that is being captured into a graph is refused
  * (DEVICE): the wait cannot be captured.
  */

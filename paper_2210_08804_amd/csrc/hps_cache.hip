@@ -639,7 +639,7 @@ __device__ __forceinline__ void copy_rows_shared(const RowGeom &g, const float *
 // ballot over the equality test gives every key its way.  Returns the way or -1.  between() runs after
 // the loads of the (last) round have been issued: it may issue further loads behind them.  Only the first `lanes`
 // lanes have keys; with sets of 32 ways and more a wave load covers two keys or one, and those of the other lanes are left out
-// (40,000 keys of 512 bytes in 64-way sets, 23 keys per wave, checked: 19.8 us with them, all on the line of set 0, 10.2 without).
+// (40,000 keys of 512 bytes in 64-way sets, 24 keys per wave, checked: 16.1 us with them, all on the line of set 0, 11.3 without).
 // A lane that wants nothing seeks a value that no slot holds: its key travels alone, one shuffle in four less than with its `want` beside it.
 template <int W, int KPW, bool kShared = false, typename Between>
 __device__ __forceinline__ int probe_wave(const int64_t *__restrict__ K, int64_t key,
@@ -852,7 +852,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
     // A length that is read on the device: its keys are dealt to all the waves launched for the longest one, `deal` neighbours (deal_of) at a
     // time, so that a wave's keys can be requested beside it (50,000 of 106,496 keys: all in the first half of the waves 20.0 us, spread 14.6).
     // At most kpw, rounded up to whole deals, fall to a wave.  Tiles to which none fall leave, and are not counted (4,000 of 200,000 keys plain 9.5 -> 5.2,
-    // 3,000 of 300,000 in the default mode 13.3 -> 6.8).
+    // 3,000 of 300,000 plain 14.0 -> 5.6, in the default mode 13.5 -> 5.9).
     const bool dealt = kFull && deal;
     const uint32_t shift = dealt ? 31u - (uint32_t)__builtin_clz(deal) : 0u;
     auto tiles_of = [&](uint32_t nd) {
@@ -989,7 +989,7 @@ query_kernel(const u64x4 pointers, const u32x4 sizes, const u32x2 sets, const Qu
         bool pending = want;
         list_misses(live && !want);
         // No writer at work.  (A wave without keys, of which a length on the device can leave most, has nothing to
-        // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not.)
+        // look for: 3,000 of 300,000 keys 14.5 us if it does, 12.9 if not, while work-groups without keys stayed.)
         if (__ballot(want) && !__ballot((uint32_t)e1 != (uint32_t)(e1 >> 32))) {
             shared_acquire();                          // the epochs are read before any key or row
             const int way = probe_wave<W, KPW, true>(K, key, set, want, lanes);
@@ -2180,7 +2180,7 @@ hps_status_t write_call(hps_cache *c, const int64_t *keys, const float *vals, si
 
 hipError_t hps_launch_expand_rows(const float *rows, const uint32_t *inverse, uint32_t n, uint32_t dim, float *out,
                                   uint32_t cus, hipStream_t st) {
-    // 8 waves per work-group; keys per wave and group sizes as for the query (query_shape).  A launch has fewer than 2^32
+    // 8 waves per work-group, keys per wave for full rounds of them, a wave's rows in one group of wave loads.  A launch has fewer than 2^32
     // work-items, and there is one for each position or more: at most 2^30 positions go in one (a quarter of what a call may have).
     constexpr uint32_t kWpb = 8, kMost = 1u << 30;
     const RowGeom g = make_geom(dim);
